@@ -555,11 +555,10 @@ def summarize_traffic(args) -> int:
         fb = info.fwd_bytes
         bb = info.bwd_accum_bytes if acc else info.bwd_bytes
         res = {}
-        # the kernels are template instances: forward <lane type, NREP, ...>, backward <dtype, elements,
-        # accumulate, NREP, ...>, NREP = destination copies when that is 1, 2, 4 or 8 and 0 otherwise
+        # the kernels are template instances: forward <NREP, ...>, backward <dtype, accumulate, NREP, ...>, NREP = destination copies when that is 1, 2, 4 or 8 and 0 otherwise
         nrep = info.dst_copies if info.dst_copies in (1, 2, 4, 8) else 0
-        pats = {0: re.compile(r"hp_forward_kernel<[^,]+, %d, " % nrep),
-                1: re.compile(r"hp_backward_kernel<\d+, \d+, %s, %d, " % ("true" if acc else "false", nrep))}
+        pats = {0: re.compile(r"hp_forward_kernel<%d, " % nrep),
+                1: re.compile(r"hp_backward_kernel<\d+, %s, %d, " % ("true" if acc else "false", nrep))}
         if info.boundary_bytes < (1 << 20):
             log(f"{label}: {info.boundary_bytes} B boundary - too small for a per-launch traffic figure, skipped")
             continue

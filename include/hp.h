@@ -259,8 +259,8 @@ int hp_plan_segments(const hp_plan_t *plan, hp_segment_t *out, int32_t cap);
  *             the text rows of dst_bufs) on another stream must have finished,
  *             or the caller makes `stream` wait for it first.  The same holds
  *             for every call below that takes a stream.
- * Pointers must be aligned to the element size; 16-byte alignment (with a row
- * size that is a multiple of 16) selects the vector path.  Returns after
+ * Pointers must be aligned to the element size; rows of any length and pointers
+ * of any such alignment move in 16-byte lanes.  Returns after
  * enqueueing. */
 int hp_forward(const hp_plan_t *plan, const void *const *src_bufs,
                void *const *dst_bufs, void *stream);
@@ -303,8 +303,7 @@ int hp_zero_image_rows(const hp_plan_t *plan, void *const *dst_bufs, void *strea
  * dtype) and the sum s is applied as acc = acc + s to every source TP copy.
  *   dst_grad_bufs:  as for hp_backward (bf16 or f32 per the plan's dtype).
  *   src_accum_bufs: HOST array of n_src_bufs DEVICE pointers to binary32 arrays
- *                   [rows_i, hidden], read and written; 4-byte aligned (16-byte
- *                   alignment and hidden % 4 == 0 select the vector path).
+ *                   [rows_i, hidden], read and written; 4-byte aligned.
  * Has its own launch shape (direction 2). */
 int hp_backward_accumulate(const hp_plan_t *plan, const void *const *dst_grad_bufs,
                            void *const *src_accum_bufs, void *stream);

@@ -47,17 +47,50 @@ struct BufTable {
 };
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-template <typename V, bool NT>
-__device__ __forceinline__ V ld(const V *p) {
-    if constexpr (NT) return __builtin_nontemporal_load(p);
-    else return *p;
+// A lane chunk of N bytes as a register type, and the same type as it lies in
+// memory: element-aligned only.  gfx950 loads and stores of any width take any
+// address, so rows of every length and buffers of every alignment go through
+// 16-byte lanes; an aligned address costs the same as with an aligned type.
+// Lanes of one element instead (2 bytes) spent the time on instructions, not on
+// memory: hidden 2305 in bf16 to four copies, 284 MB a launch, forward 91 ->
+// 42 us, backward 72 -> 49 us.
+template <int N> struct Bytes {
+    typedef uint32_t type __attribute__((ext_vector_type(N / 4)));
+    typedef uint32_t mem __attribute__((ext_vector_type(N / 4), aligned(2)));
+};
+template <> struct Bytes<4> { typedef uint32_t type; typedef uint32_t mem __attribute__((aligned(2))); };
+template <> struct Bytes<2> { typedef uint16_t type; typedef uint16_t mem; };
+
+template <int N, bool NT>
+__device__ __forceinline__ typename Bytes<N>::type ld(const char *p) {
+    typedef typename Bytes<N>::mem M;
+    if constexpr (NT) return __builtin_nontemporal_load((const M *)p);
+    else return *(const M *)p;
 }
-template <typename V, bool NT>
-__device__ __forceinline__ void st(V *p, V v) {
-    if constexpr (NT) __builtin_nontemporal_store(v, p);
-    else *p = v;
+template <int N, bool NT>
+__device__ __forceinline__ void st(char *p, typename Bytes<N>::type v) {
+    typedef typename Bytes<N>::mem M;
+    if constexpr (NT) __builtin_nontemporal_store((M)v, (M *)p);
+    else *(M *)p = (M)v;
+}
+
+// What the tiles of a launch look like.  Three kernels, because the start of a
+// workgroup is what a launch of short-lived ones waits for: testing for ragged
+// rows in the kernel of whole lines cost 3 % there (110 MB forward to two copies:
+// 25.5 -> 26.4 us).
+enum Tiles {
+    kLines,     // dense on both sides, and every row is whole 128-byte lines
+    kRagged,    // dense on both sides, rows of any length
+    kStrided,   // groups of whole row-strided rows ([S,B,H] order with several samples per rank, rows shorter than a tile)
+};
+
+// The tile of this workgroup.  Ragged: its ends on lines of the first destination copy.
+template <Tiles TILES>
+__device__ __forceinline__ TileView my_tile(const KParams &k, const BufTable &bufs) {
+    TileView t = locate_tile(k, blockIdx.x);
+    if (TILES == kRagged) hp::align_tile(t, (uint64_t)(uintptr_t)bufs.p[k.dst_base + t.dst_buf0]);
+    return t;
 }
 
 // ---------------------------------------------------------------------------
@@ -67,86 +100,87 @@ __device__ __forceinline__ void st(V *p, V v) {
 // are issued before the first store.  With GUARD the group is the ragged end of
 // a tile: lanes past the end re-read the tile's last chunk and skip the stores,
 // so there is still no branch around a load.
-template <typename V, int NREP, int U, bool GUARD, bool NTL, bool NTS>
+template <int NREP, int U, Tiles TILES, bool GUARD, bool NTL, bool NTS>
 __device__ __forceinline__ void forward_group(const BufTable &bufs, const KParams &k, const TileView &t,
                                               const char *src, uint32_t nrep, uint32_t done, uint32_t n) {
-    V v[U];
+    u32x4 v[U];
     uint32_t i[U];
+    hp::ChunkView c[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         i[u] = done + u * blockDim.x + threadIdx.x;
-        v[u] = ld<V, NTL>((const V *)src + (GUARD ? min(i[u], n - 1) : i[u]));
+        c[u] = hp::chunk_at<16, TILES != kStrided, GUARD && TILES == kRagged>(k, t, GUARD ? min(i[u], n - 1) : i[u]);
+        v[u] = ld<16, NTL>(src + c[u].src);
     }
 #pragma unroll 4
     for (uint32_t r = 0; r < nrep; ++r) {
         char *dst = (char *)bufs.p[k.dst_base + t.dst_buf0 + r] + t.dst_off;
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            if (!GUARD || i[u] < n) st<V, NTS>((V *)dst + i[u], v[u]);
+            if (!GUARD || i[u] < n) st<16, NTS>(dst + (TILES != kStrided ? c[u].src : c[u].dst), v[u]);
     }
 }
 
-template <typename V, int NREP, bool NTL, bool NTS>
+template <int NREP, Tiles TILES, bool NTL, bool NTS>
+__device__ __forceinline__ void forward_tile(const BufTable &bufs, const KParams &k, const TileView &t, uint32_t nrep) {
+    const char *src = (const char *)bufs.p[t.src_buf] + t.src_off;
+    uint32_t n, whole;
+    hp::count_chunks<16, TILES != kStrided>(k, t, n, whole);
+    const uint32_t step = blockDim.x;
+    uint32_t done = 0;                                       // uniform
+    if (TILES != kLines && __builtin_expect(n == 0, 0)) {                       // shorter than a chunk
+        for (uint32_t i = threadIdx.x; i < t.nbytes / 2; i += step) {
+            const hp::ChunkView c = hp::element_at<2>(k, t, i);
+            const uint16_t v = ld<2, NTL>(src + c.src);
+            for (uint32_t r = 0; r < nrep; ++r)
+                st<2, NTS>((char *)bufs.p[k.dst_base + t.dst_buf0 + r] + t.dst_off + c.dst, v);
+        }
+        return;
+    }
+    for (; whole - done >= 4 * step; done += 4 * step)
+        forward_group<NREP, 4, TILES, false, NTL, NTS>(bufs, k, t, src, nrep, done, n);
+    if (whole - done >= 2 * step) {
+        forward_group<NREP, 2, TILES, false, NTL, NTS>(bufs, k, t, src, nrep, done, n);
+        done += 2 * step;
+    }
+    if (whole - done >= step) {
+        forward_group<NREP, 1, TILES, false, NTL, NTS>(bufs, k, t, src, nrep, done, n);
+        done += step;
+    }
+    if (n - done > 0) forward_group<NREP, 1, TILES, true, NTL, NTS>(bufs, k, t, src, nrep, done, n);
+}
+
+template <int NREP, Tiles TILES, bool NTL, bool NTS>
 __global__ void __launch_bounds__(1024)
 hp_forward_kernel(const KParams k, const BufTable bufs) {
-    const TileView t = locate_tile(k, blockIdx.x);
-    const uint32_t nrep = NREP > 0 ? (uint32_t)NREP : k.dst_copies;
-    const char *src = (const char *)bufs.p[t.src_buf] + t.src_off;
-    const uint32_t n = t.nbytes / (uint32_t)sizeof(V);      // lane chunks in this tile, >= 1
-    const uint32_t step = blockDim.x;
-
-    if (t.pitch_rows == 1) {
-        uint32_t done = 0;                                   // uniform
-        for (; n - done >= 4 * step; done += 4 * step)
-            forward_group<V, NREP, 4, false, NTL, NTS>(bufs, k, t, src, nrep, done, n);
-        if (n - done >= 2 * step) {
-            forward_group<V, NREP, 2, false, NTL, NTS>(bufs, k, t, src, nrep, done, n);
-            done += 2 * step;
-        }
-        if (n - done >= step) {
-            forward_group<V, NREP, 1, false, NTL, NTS>(bufs, k, t, src, nrep, done, n);
-            done += step;
-        }
-        if (n - done > 0) forward_group<V, NREP, 1, true, NTL, NTS>(bufs, k, t, src, nrep, done, n);
-    } else {
-        // row-strided destination ([S,B,H] order with several samples per rank)
-        const uint64_t pitch = (uint64_t)t.pitch_rows * k.row_bytes;
-        for (uint32_t i = threadIdx.x; i < n; i += step) {
-            const uint32_t byte = i * (uint32_t)sizeof(V);
-            const uint32_t row = byte / k.row_bytes;
-            const uint32_t col = byte - row * k.row_bytes;
-            const V v = ld<V, NTL>((const V *)(src + byte));
-            for (uint32_t r = 0; r < nrep; ++r) {
-                char *dst = (char *)bufs.p[k.dst_base + t.dst_buf0 + r] + t.dst_off;
-                st<V, NTS>((V *)(dst + row * pitch + col), v);
-            }
-        }
-    }
+    const TileView t = my_tile<TILES>(k, bufs);
+    forward_tile<NREP, TILES, NTL, NTS>(bufs, k, t, NREP > 0 ? (uint32_t)NREP : k.dst_copies);
 }
 
 // ---------------------------------------------------------------------------
 // zero rows: the forward's store pattern with nothing read - every image-token
 // row of every destination copy is set to zero
 // ---------------------------------------------------------------------------
-template <typename V, bool NTS>
-__global__ void __launch_bounds__(1024)
-hp_zero_rows_kernel(const KParams k, const BufTable bufs) {
-    const TileView t = locate_tile(k, blockIdx.x);
-    const uint32_t n = t.nbytes / (uint32_t)sizeof(V);
-    const V zero = {};
+template <Tiles TILES, bool NTS>
+__device__ __forceinline__ void zero_tile(const BufTable &bufs, const KParams &k, const TileView &t) {
+    uint32_t n, whole;
+    hp::count_chunks<16, TILES != kStrided>(k, t, n, whole);
     for (uint32_t r = 0; r < k.dst_copies; ++r) {
         char *dst = (char *)bufs.p[k.dst_base + t.dst_buf0 + r] + t.dst_off;
-        if (t.pitch_rows == 1) {
-            for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) st<V, NTS>((V *)dst + i, zero);
+        if (TILES != kLines && n == 0) {
+            for (uint32_t i = threadIdx.x; i < t.nbytes / 2; i += blockDim.x)
+                st<2, NTS>(dst + hp::element_at<2>(k, t, i).dst, 0);
         } else {
-            const uint64_t pitch = (uint64_t)t.pitch_rows * k.row_bytes;
-            for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) {
-                const uint32_t byte = i * (uint32_t)sizeof(V);
-                const uint32_t row = byte / k.row_bytes;
-                st<V, NTS>((V *)(dst + row * pitch + (byte - row * k.row_bytes)), zero);
-            }
+            for (uint32_t i = threadIdx.x; i < n; i += blockDim.x)
+                st<16, NTS>(dst + hp::chunk_at<16, TILES != kStrided, TILES == kRagged>(k, t, i).dst, (u32x4)0u);
         }
     }
+}
+
+template <Tiles TILES, bool NTS>
+__global__ void __launch_bounds__(1024)
+hp_zero_rows_kernel(const KParams k, const BufTable bufs) {
+    zero_tile<TILES, NTS>(bufs, k, my_tile<TILES>(k, bufs));
 }
 
 // ---------------------------------------------------------------------------
@@ -165,10 +199,6 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
 
-// A lane chunk of N bytes (16, 8, 4 or 2) as a register type.
-template <int N> struct Bytes { typedef uint32_t type __attribute__((ext_vector_type(N / 4))); };
-template <> struct Bytes<4> { typedef uint32_t type; };
-template <> struct Bytes<2> { typedef uint16_t type; };
 template <int N>
 __device__ __forceinline__ uint32_t get_word(const typename Bytes<N>::type &v, int j) {
     if constexpr (N >= 8) return v[j];
@@ -214,38 +244,48 @@ struct Elems {
     }
 };
 
+// Elements per lane chunk.  Overwriting: 16 bytes of gradients.  Accumulating:
+// four elements, one 16-byte chunk of binary32 accumulators per lane, so that
+// every accumulator load and store instruction of a wave covers 1 KiB without
+// gaps (bf16 gradients then come in 8-byte pieces).  Eight bf16 elements per lane
+// would pair a 16-byte gradient load with 32 bytes of accumulators per lane, i.e.
+// two half-covered store instructions per line: measured 6 % more HBM write
+// traffic and 3-6 % less throughput.
+template <int DT, bool ACC>
+constexpr int kLaneElems = ACC || DT == HP_F32 ? 4 : 8;
+
 // U chunks of E elements per lane starting at chunk `done`, straight-line: the
 // loads of all replicas (groups of four when the replica count is only known at
-// run time) are issued before the first add.  GUARD as in forward_group.
+// run time) are issued before the first add.  GUARD as in forward_group; ELEMENT:
+// E = 1 and the walk goes element by element.
 // ACC = false: the folded sum is rounded to the gradients' dtype and overwrites
 // the source-gradient rows.  ACC = true: the source side holds binary32
-// accumulators; the folded sum is added to them (one more binary32 add).
-template <int DT, int E, bool ACC, int NREP, int U, bool GUARD, bool NTL, bool NTS>
+// accumulators; the folded sum is added to them (one more binary32 add).  A chunk
+// that was moved back to end with its run computes some elements that the chunk
+// before it computes too: an overwriting store repeats the same values, an
+// accumulating one leaves them out.
+template <int DT, int E, bool ACC, int NREP, int U, Tiles TILES, bool GUARD, bool NTL, bool NTS>
 __device__ __forceinline__ void backward_group(const BufTable &bufs, const KParams &k, const TileView &t,
                                                uint32_t nrep, uint32_t done, uint32_t n) {
     typedef Elems<DT, E> In;
     typedef Elems<ACC ? HP_F32 : DT, E> Out;
     typedef typename In::V VI;
     typedef typename Out::V VO;
+    constexpr bool ELEMENT = E == 1;
     constexpr int G = NREP > 0 ? NREP : 4;
     constexpr uint32_t kElemBytes = DT == HP_F32 ? 4 : 2;
-    const bool dense = t.pitch_rows == 1;
-    const uint64_t pitch = (uint64_t)t.pitch_rows * k.row_bytes;
-    uint32_t i[U], ic[U];
-    uint64_t goff[U];
+    constexpr uint32_t kWiden = ACC ? 4 / kElemBytes : 1;      // accumulator bytes per gradient byte
+    uint32_t i[U];
+    hp::ChunkView c[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         i[u] = done + u * blockDim.x + threadIdx.x;
-        ic[u] = GUARD ? min(i[u], n - 1) : i[u];
-        const uint32_t byte = ic[u] * (uint32_t)In::kBytes;
-        if (dense) goff[u] = byte;
-        else {
-            const uint32_t row = byte / k.row_bytes;
-            goff[u] = row * pitch + (byte - row * k.row_bytes);
-        }
+        const uint32_t ic = GUARD ? min(i[u], n - 1) : i[u];
+        if constexpr (ELEMENT) c[u] = hp::element_at<kElemBytes>(k, t, ic);
+        else c[u] = hp::chunk_at<In::kBytes, TILES != kStrided, GUARD && TILES == kRagged>(k, t, ic);
     }
     // source-side offset of this tile in the output dtype
-    const uint64_t out_off = ACC ? t.src_off / kElemBytes * 4 : t.src_off;
+    const uint64_t out_off = t.src_off * kWiden;
     float acc[U][E];
     for (uint32_t r0 = 0; r0 < nrep; r0 += G) {
         VI v[G][U];
@@ -255,7 +295,7 @@ __device__ __forceinline__ void backward_group(const BufTable &bufs, const KPara
             const uint32_t r = NREP > 0 ? r0 + g : min(r0 + g, nrep - 1);
             const char *gp = (const char *)bufs.p[k.dst_base + t.dst_buf0 + r] + t.dst_off;
 #pragma unroll
-            for (int u = 0; u < U; ++u) v[g][u] = ld<VI, NTL>((const VI *)(gp + goff[u]));
+            for (int u = 0; u < U; ++u) v[g][u] = ld<In::kBytes, NTL>(gp + (TILES != kStrided && !ELEMENT ? c[u].src : c[u].dst));
         }
         // ascending tp: copy 0 starts the accumulator, copies 1.. are added in order
 #pragma unroll
@@ -279,41 +319,61 @@ __device__ __forceinline__ void backward_group(const BufTable &bufs, const KPara
             char *out = (char *)bufs.p[t.src_buf + s] + out_off;
 #pragma unroll
             for (int u = 0; u < U; ++u)
-                if (!GUARD || i[u] < n) st<VO, NTS>((VO *)out + i[u], res[u]);
+                if (!GUARD || i[u] < n) st<Out::kBytes, NTS>(out + c[u].src, res[u]);
         }
     } else {
         for (uint32_t s = 0; s < t.src_copies; ++s) {
             char *out = (char *)bufs.p[t.src_buf + s] + out_off;
             VO old[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) old[u] = ld<VO, NTL>((const VO *)out + ic[u]);
+            for (int u = 0; u < U; ++u) old[u] = ld<Out::kBytes, NTL>(out + c[u].src * kWiden);
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 float x[E];
                 Out::unpack(old[u], x);
 #pragma unroll
                 for (int e = 0; e < E; ++e) x[e] = x[e] + acc[u][e];
-                if (!GUARD || i[u] < n) st<VO, NTS>((VO *)out + i[u], Out::pack(x));
+                if (GUARD && i[u] >= n) continue;
+                if (ELEMENT || TILES == kLines || (TILES == kRagged && !GUARD) || c[u].over == 0) {
+                    st<Out::kBytes, NTS>(out + c[u].src * kWiden, Out::pack(x));
+                } else {
+#pragma unroll
+                    for (int e = 0; e < E; ++e)
+                        if (e * kElemBytes >= c[u].over)
+                            st<4, NTS>(out + c[u].src * kWiden + e * 4, __float_as_uint(x[e]));
+                }
             }
         }
     }
 }
 
-template <int DT, int E, bool ACC, int NREP, bool NTL, bool NTS>
-__global__ void __launch_bounds__(1024)
-hp_backward_kernel(const KParams k, const BufTable bufs) {
-    const TileView t = locate_tile(k, blockIdx.x);
-    const uint32_t nrep = NREP > 0 ? (uint32_t)NREP : k.dst_copies;
-    const uint32_t n = t.nbytes / (uint32_t)Elems<DT, E>::kBytes;   // lane chunks in this tile, >= 1
+template <int DT, bool ACC, int NREP, Tiles TILES, bool NTL, bool NTS>
+__device__ __forceinline__ void backward_tile(const BufTable &bufs, const KParams &k, const TileView &t, uint32_t nrep) {
+    constexpr int E = kLaneElems<DT, ACC>;
+    constexpr uint32_t kElemBytes = DT == HP_F32 ? 4 : 2;
+    uint32_t n, whole;
+    hp::count_chunks<Elems<DT, E>::kBytes, TILES != kStrided>(k, t, n, whole);
     const uint32_t step = blockDim.x;
     uint32_t done = 0;                                               // uniform
-    for (; n - done >= 2 * step; done += 2 * step)
-        backward_group<DT, E, ACC, NREP, 2, false, NTL, NTS>(bufs, k, t, nrep, done, n);
-    if (n - done >= step) {
-        backward_group<DT, E, ACC, NREP, 1, false, NTL, NTS>(bufs, k, t, nrep, done, n);
+    if (TILES != kLines && __builtin_expect(n == 0, 0)) {                               // shorter than a chunk
+        for (n = t.nbytes / kElemBytes; done < n; done += step)
+            backward_group<DT, 1, ACC, 0, 1, TILES, true, NTL, NTS>(bufs, k, t, nrep, done, n);
+        return;
+    }
+    for (; whole - done >= 2 * step; done += 2 * step)
+        backward_group<DT, E, ACC, NREP, 2, TILES, false, NTL, NTS>(bufs, k, t, nrep, done, n);
+    if (whole - done >= step) {
+        backward_group<DT, E, ACC, NREP, 1, TILES, false, NTL, NTS>(bufs, k, t, nrep, done, n);
         done += step;
     }
-    if (n - done > 0) backward_group<DT, E, ACC, NREP, 1, true, NTL, NTS>(bufs, k, t, nrep, done, n);
+    if (n - done > 0) backward_group<DT, E, ACC, NREP, 1, TILES, true, NTL, NTS>(bufs, k, t, nrep, done, n);
+}
+
+template <int DT, bool ACC, int NREP, Tiles TILES, bool NTL, bool NTS>
+__global__ void __launch_bounds__(1024)
+hp_backward_kernel(const KParams k, const BufTable bufs) {
+    const TileView t = my_tile<TILES>(k, bufs);
+    backward_tile<DT, ACC, NREP, TILES, NTL, NTS>(bufs, k, t, NREP > 0 ? (uint32_t)NREP : k.dst_copies);
 }
 
 // ---------------------------------------------------------------------------
@@ -353,7 +413,7 @@ __device__ __forceinline__ void probe_group(const ProbeArgs &a, uint64_t base, u
             if (r0 + g < a.n_read) {
                 const u32x4 *p = a.rd[r0 + g] + base;
 #pragma unroll
-                for (int u = 0; u < U; ++u) v[g][u] = ld<u32x4, NTL>(p + (GUARD ? min(i[u], n - 1) : i[u]));
+                for (int u = 0; u < U; ++u) v[g][u] = ld<16, NTL>((const char *)(p + (GUARD ? min(i[u], n - 1) : i[u])));
             }
 #pragma unroll
         for (int g = 0; g < 4; ++g)
@@ -365,7 +425,7 @@ __device__ __forceinline__ void probe_group(const ProbeArgs &a, uint64_t base, u
     for (uint32_t w = 0; w < a.n_write; ++w) {
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            if (!GUARD || i[u] < n) st<u32x4, NTS>(a.wr[w] + base + i[u], acc[u]);
+            if (!GUARD || i[u] < n) st<16, NTS>((char *)(a.wr[w] + base + i[u]), acc[u]);
     }
     if (a.n_write == 0) {
         // read-only pattern: keep the loads alive with a store that the data never triggers
@@ -384,11 +444,11 @@ __device__ __forceinline__ void probe_deep(const ProbeArgs &a, uint64_t base) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         v[u] = (u32x4){1u, 2u, 3u, 4u};
-        if (a.n_read) v[u] = ld<u32x4, NTL>(a.rd[0] + base + u * blockDim.x + threadIdx.x);
+        if (a.n_read) v[u] = ld<16, NTL>((const char *)(a.rd[0] + base + u * blockDim.x + threadIdx.x));
     }
     for (uint32_t w = 0; w < a.n_write; ++w) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) st<u32x4, NTS>(a.wr[w] + base + u * blockDim.x + threadIdx.x, v[u]);
+        for (int u = 0; u < U; ++u) st<16, NTS>((char *)(a.wr[w] + base + u * blockDim.x + threadIdx.x), v[u]);
     }
 }
 
@@ -526,76 +586,64 @@ unsigned lds_for_cap(int block, int waves_per_cu) {
     return (unsigned)std::min(lds, 64 * 1024);
 }
 
-template <typename V, bool NTL, bool NTS>
-void launch_forward_nrep(int copies, const LaunchCfg &c, const BufTable &bt, const KParams &k) {
+template <Tiles TILES, bool NTL, bool NTS>
+void launch_forward(int copies, const LaunchCfg &c, const BufTable &bt, const KParams &k) {
     switch (copies) {
-        case 1: HP_LAUNCH((hp_forward_kernel<V, 1, NTL, NTS>), c, k, bt); break;
-        case 2: HP_LAUNCH((hp_forward_kernel<V, 2, NTL, NTS>), c, k, bt); break;
-        case 4: HP_LAUNCH((hp_forward_kernel<V, 4, NTL, NTS>), c, k, bt); break;
-        case 8: HP_LAUNCH((hp_forward_kernel<V, 8, NTL, NTS>), c, k, bt); break;
-        default: HP_LAUNCH((hp_forward_kernel<V, 0, NTL, NTS>), c, k, bt); break;
+        case 1: HP_LAUNCH((hp_forward_kernel<1, TILES, NTL, NTS>), c, k, bt); break;
+        case 2: HP_LAUNCH((hp_forward_kernel<2, TILES, NTL, NTS>), c, k, bt); break;
+        case 4: HP_LAUNCH((hp_forward_kernel<4, TILES, NTL, NTS>), c, k, bt); break;
+        case 8: HP_LAUNCH((hp_forward_kernel<8, TILES, NTL, NTS>), c, k, bt); break;
+        default: HP_LAUNCH((hp_forward_kernel<0, TILES, NTL, NTS>), c, k, bt); break;
     }
 }
 
-template <bool NTL, bool NTS>
-void launch_forward_width(int width, int copies, const LaunchCfg &c, const BufTable &bt, const KParams &k) {
-    switch (width) {
-        case 16: launch_forward_nrep<u32x4, NTL, NTS>(copies, c, bt, k); break;
-        case 4: launch_forward_nrep<uint32_t, NTL, NTS>(copies, c, bt, k); break;
-        default: launch_forward_nrep<uint16_t, NTL, NTS>(copies, c, bt, k); break;
-    }
-}
-
-template <int DT, int E, bool ACC, bool NTL, bool NTS>
+template <int DT, bool ACC, Tiles TILES, bool NTL, bool NTS>
 void launch_backward_nrep(int copies, const LaunchCfg &c, const BufTable &bt, const KParams &k) {
     switch (copies) {
-        case 1: HP_LAUNCH((hp_backward_kernel<DT, E, ACC, 1, NTL, NTS>), c, k, bt); break;
-        case 2: HP_LAUNCH((hp_backward_kernel<DT, E, ACC, 2, NTL, NTS>), c, k, bt); break;
-        case 4: HP_LAUNCH((hp_backward_kernel<DT, E, ACC, 4, NTL, NTS>), c, k, bt); break;
-        case 8: HP_LAUNCH((hp_backward_kernel<DT, E, ACC, 8, NTL, NTS>), c, k, bt); break;
-        default: HP_LAUNCH((hp_backward_kernel<DT, E, ACC, 0, NTL, NTS>), c, k, bt); break;
+        case 1: HP_LAUNCH((hp_backward_kernel<DT, ACC, 1, TILES, NTL, NTS>), c, k, bt); break;
+        case 2: HP_LAUNCH((hp_backward_kernel<DT, ACC, 2, TILES, NTL, NTS>), c, k, bt); break;
+        case 4: HP_LAUNCH((hp_backward_kernel<DT, ACC, 4, TILES, NTL, NTS>), c, k, bt); break;
+        case 8: HP_LAUNCH((hp_backward_kernel<DT, ACC, 8, TILES, NTL, NTS>), c, k, bt); break;
+        default: HP_LAUNCH((hp_backward_kernel<DT, ACC, 0, TILES, NTL, NTS>), c, k, bt); break;
     }
 }
 
-// `elems` = elements per lane chunk, chosen by backward_elems().
-template <bool NTL, bool NTS>
-void launch_backward_shape(int dtype, bool acc, int elems, int copies, const LaunchCfg &c, const BufTable &bt,
-                           const KParams &k) {
+template <Tiles TILES, bool NTL, bool NTS>
+void launch_backward(int dtype, bool acc, int copies, const LaunchCfg &c, const BufTable &bt, const KParams &k) {
     if (dtype == HP_F32) {
-        if (elems == 4) {
-            if (acc) launch_backward_nrep<HP_F32, 4, true, NTL, NTS>(copies, c, bt, k);
-            else launch_backward_nrep<HP_F32, 4, false, NTL, NTS>(copies, c, bt, k);
-        } else {
-            if (acc) launch_backward_nrep<HP_F32, 1, true, NTL, NTS>(copies, c, bt, k);
-            else launch_backward_nrep<HP_F32, 1, false, NTL, NTS>(copies, c, bt, k);
-        }
-    } else if (acc) {
-        if (elems == 4) launch_backward_nrep<HP_BF16, 4, true, NTL, NTS>(copies, c, bt, k);
-        else launch_backward_nrep<HP_BF16, 1, true, NTL, NTS>(copies, c, bt, k);
+        if (acc) launch_backward_nrep<HP_F32, true, TILES, NTL, NTS>(copies, c, bt, k);
+        else launch_backward_nrep<HP_F32, false, TILES, NTL, NTS>(copies, c, bt, k);
     } else {
-        if (elems == 8) launch_backward_nrep<HP_BF16, 8, false, NTL, NTS>(copies, c, bt, k);
-        else if (elems == 2) launch_backward_nrep<HP_BF16, 2, false, NTL, NTS>(copies, c, bt, k);
-        else launch_backward_nrep<HP_BF16, 1, false, NTL, NTS>(copies, c, bt, k);
+        if (acc) launch_backward_nrep<HP_BF16, true, TILES, NTL, NTS>(copies, c, bt, k);
+        else launch_backward_nrep<HP_BF16, false, TILES, NTL, NTS>(copies, c, bt, k);
     }
 }
 
 enum Direction { kForward = 0, kBackward = 1, kBackwardAcc = 2, kZeroRows = 3 };   // kZeroRows: forward's launch shape
 
-// Enqueues one kernel for direction `dir` with launch shape `L`.  `lane` is the
-// lane chunk chosen by prepare(): bytes for forward, elements for backward.
-int enqueue_params(const hp_plan *p, Direction dir, const hp::Launch &L, const BufTable &bt, int lane,
-                   hipStream_t stream, EventPair ev, const KParams &k);
+template <Tiles TILES>
+void launch_other(const hp_plan *p, Direction dir, const LaunchCfg &c, const BufTable &bt, const KParams &k) {
+    if (dir == kZeroRows) HP_LAUNCH((hp_zero_rows_kernel<TILES, true>), c, k, bt);
+    else if (dir == kForward) launch_forward<TILES, false, true>(p->dst_copies, c, bt, k);
+    else launch_backward<TILES, true, true>(p->dtype, dir == kBackwardAcc, p->dst_copies, c, bt, k);
+}
 
-int enqueue(const hp_plan *p, Direction dir, const hp::Launch &L, const BufTable &bt, int lane,
-            hipStream_t stream, EventPair ev) {
-    const int rc = enqueue_params(p, dir, L, bt, lane, stream, ev,
+// Enqueues one kernel for direction `dir` with launch shape `L`.
+int enqueue_params(const hp_plan *p, Direction dir, const hp::Launch &L, const BufTable &bt, hipStream_t stream,
+                   EventPair ev, const KParams &k);
+
+int enqueue(const hp_plan *p, Direction dir, const hp::Launch &L, const BufTable &bt, hipStream_t stream,
+            EventPair ev) {
+    const int rc = enqueue_params(p, dir, L, bt, stream, ev,
                                   hp::kernel_params(*p, L.tile_variant, p->d_segs, p->d_tree));
     if (rc == HP_OK) p->note_stream((void *)stream);
     return rc;
 }
 
-int enqueue_params(const hp_plan *p, Direction dir, const hp::Launch &L, const BufTable &bt, int lane,
-                   hipStream_t stream, EventPair ev, const KParams &k) {
+int enqueue_params(const hp_plan *p, Direction dir, const hp::Launch &L, const BufTable &bt, hipStream_t stream,
+                   EventPair ev, const KParams &params) {
+    KParams k = params;
+    if (dir == kBackwardAcc) hp::set_row_chunks(k, 4u * (uint32_t)p->elem_bytes);
     LaunchCfg c;
     c.grid = dim3(p->n_tiles(L.tile_variant));
     c.block = dim3((unsigned)L.block);
@@ -603,25 +651,28 @@ int enqueue_params(const hp_plan *p, Direction dir, const hp::Launch &L, const B
     c.stream = stream;
     c.ev = ev;
     const int nt = L.nontemporal & 3, copies = p->dst_copies;
-    if (dir == kZeroRows) {
-        const bool nts = (nt & 2) != 0;
-        if (lane == 16) { if (nts) HP_LAUNCH((hp_zero_rows_kernel<u32x4, true>), c, k, bt); else HP_LAUNCH((hp_zero_rows_kernel<u32x4, false>), c, k, bt); }
-        else if (lane == 4) { if (nts) HP_LAUNCH((hp_zero_rows_kernel<uint32_t, true>), c, k, bt); else HP_LAUNCH((hp_zero_rows_kernel<uint32_t, false>), c, k, bt); }
-        else { if (nts) HP_LAUNCH((hp_zero_rows_kernel<uint16_t, true>), c, k, bt); else HP_LAUNCH((hp_zero_rows_kernel<uint16_t, false>), c, k, bt); }
+    const bool acc = dir == kBackwardAcc;
+    const bool strided = p->strided && k.parts_per_row == 0;
+    if (strided || k.row_bytes % hp::kLineBytes) {
+        // the cache policy that the kernels of whole lines start from, whatever the shape asks for
+        if (strided) launch_other<kStrided>(p, dir, c, bt, k);
+        else launch_other<kRagged>(p, dir, c, bt, k);
+    } else if (dir == kZeroRows) {
+        if (nt & 2) HP_LAUNCH((hp_zero_rows_kernel<kLines, true>), c, k, bt);
+        else HP_LAUNCH((hp_zero_rows_kernel<kLines, false>), c, k, bt);
     } else if (dir == kForward) {
         switch (nt) {
-            case 0: launch_forward_width<false, false>(lane, copies, c, bt, k); break;
-            case 1: launch_forward_width<true, false>(lane, copies, c, bt, k); break;
-            case 2: launch_forward_width<false, true>(lane, copies, c, bt, k); break;
-            default: launch_forward_width<true, true>(lane, copies, c, bt, k); break;
+            case 0: launch_forward<kLines, false, false>(copies, c, bt, k); break;
+            case 1: launch_forward<kLines, true, false>(copies, c, bt, k); break;
+            case 2: launch_forward<kLines, false, true>(copies, c, bt, k); break;
+            default: launch_forward<kLines, true, true>(copies, c, bt, k); break;
         }
     } else {
-        const bool acc = dir == kBackwardAcc;
         switch (nt) {
-            case 0: launch_backward_shape<false, false>(p->dtype, acc, lane, copies, c, bt, k); break;
-            case 1: launch_backward_shape<true, false>(p->dtype, acc, lane, copies, c, bt, k); break;
-            case 2: launch_backward_shape<false, true>(p->dtype, acc, lane, copies, c, bt, k); break;
-            default: launch_backward_shape<true, true>(p->dtype, acc, lane, copies, c, bt, k); break;
+            case 0: launch_backward<kLines, false, false>(p->dtype, acc, copies, c, bt, k); break;
+            case 1: launch_backward<kLines, true, false>(p->dtype, acc, copies, c, bt, k); break;
+            case 2: launch_backward<kLines, false, true>(p->dtype, acc, copies, c, bt, k); break;
+            default: launch_backward<kLines, true, true>(p->dtype, acc, copies, c, bt, k); break;
         }
     }
     if (hip_failed(hipGetLastError())) return HP_EHIP;
@@ -631,12 +682,9 @@ int enqueue_params(const hp_plan *p, Direction dir, const hp::Launch &L, const B
 // Fills the pointer table and checks what the kernels assume: every buffer a
 // segment touches is present, and the plan's tables live on the current device.
 // Forward reads only copy tp = 0 of a source rank; the backward directions
-// write every copy.  *lane receives the widest lane chunk that the row size and
-// every pointer allow: bytes (16, 4 or the element size) for forward, elements
-// for backward (the binary32 accumulators of kBackwardAcc are addressed in
-// 16-byte or 4-byte chunks).
-int prepare(const hp_plan *p, Direction dir, const void *const *src, const void *const *dst,
-            BufTable *bt, int *lane, bool plan_tables = true) {
+// write every copy.  Pointers have to be aligned to their element size.
+int prepare(const hp_plan *p, Direction dir, const void *const *src, const void *const *dst, BufTable *bt,
+            bool plan_tables = true) {
     if (!p || (!src && dir != kZeroRows) || !dst) return HP_EINVAL;
     if (p->segments.empty()) return HP_OK;
     if (plan_tables) {                                      // the launch will read the plan's own device tables
@@ -647,7 +695,7 @@ int prepare(const hp_plan *p, Direction dir, const void *const *src, const void 
     }
     std::memset(bt, 0, sizeof(*bt));
     int n = 0;
-    uint64_t src_bits = 0, dst_bits = (uint64_t)p->row_bytes;
+    uint64_t src_bits = 0, dst_bits = 0;
     for (int i = 0; i < p->n_src_bufs; ++i) {
         const bool needed = dir != kZeroRows && p->src_rows[i] > 0 && (dir != kForward || p->src_leader[i]);
         if (needed && !src[i]) return HP_EINVAL;
@@ -660,25 +708,8 @@ int prepare(const hp_plan *p, Direction dir, const void *const *src, const void 
         dst_bits |= (uint64_t)(uintptr_t)dst[j];
     }
     const uint64_t eb = (uint64_t)p->elem_bytes;
-    if (dir == kBackwardAcc) {
-        // Four elements per lane: one 16-byte chunk of binary32 accumulators per lane, so that every
-        // accumulator load and store instruction of a wave covers 1 KiB without gaps (bf16 gradients
-        // then come in 8-byte pieces).  Eight bf16 elements per lane would pair a 16-byte gradient load
-        // with 32 bytes of accumulators per lane, i.e. two half-covered store instructions per line:
-        // measured 6 % more HBM write traffic and 3-6 % less throughput.
-        if (((dst_bits & (4 * eb - 1)) | (src_bits & 15)) == 0) *lane = 4;
-        else if (((dst_bits & (eb - 1)) | (src_bits & 3)) == 0) *lane = 1;
-        else return HP_EALIGN;
-    } else {
-        const uint64_t bits = src_bits | dst_bits;
-        int width;
-        if ((bits & 15) == 0) width = 16;
-        else if ((bits & 3) == 0) width = 4;
-        else if ((bits & (eb - 1)) == 0) width = (int)eb;
-        else return HP_EALIGN;
-        *lane = (dir == kForward || dir == kZeroRows) ? width : width / (int)eb;
-    }
-    return HP_OK;
+    const uint64_t src_elem = dir == kBackwardAcc ? 4 : eb;
+    return ((dst_bits & (eb - 1)) | (src_bits & (src_elem - 1))) == 0 ? HP_OK : HP_EALIGN;
 }
 
 bool launch_ok(const hp::Launch &L) {
@@ -911,7 +942,6 @@ struct Companion {
     Direction dir;
     hp::Launch L;
     const BufTable *bt;
-    int lane;
 };
 
 // Steady-state cost of one launch of a candidate (plus its companion, if any):
@@ -922,21 +952,21 @@ struct Companion {
 // kernel ends): that work is paid by whatever runs next, so it has to land
 // inside the measured span.  Returns the median over `bursts` bursts in
 // milliseconds, or a negative value on a HIP error.
-float time_candidate(const hp_plan *p, Direction dir, const hp::Launch &L, const BufTable &bt, int lane,
+float time_candidate(const hp_plan *p, Direction dir, const hp::Launch &L, const BufTable &bt,
                      hipStream_t stream, const BurstEvents &ev, int bursts, int burst, const Companion *co) {
     float t[8];
     if (bursts > 8) bursts = 8;
     if (burst < 2) burst = 2;
-    if (enqueue(p, dir, L, bt, lane, stream, EventPair{}) != HP_OK) return -1.f;      // warm-up
-    if (co && enqueue(p, co->dir, co->L, *co->bt, co->lane, stream, EventPair{}) != HP_OK) return -1.f;
+    if (enqueue(p, dir, L, bt, stream, EventPair{}) != HP_OK) return -1.f;      // warm-up
+    if (co && enqueue(p, co->dir, co->L, *co->bt, stream, EventPair{}) != HP_OK) return -1.f;
     for (int b = 0; b < bursts; ++b) {
         for (int i = 0; i < burst; ++i) {
             const bool last = i == burst - 1;
             EventPair pair;
             if (i == 0) pair = EventPair{ev.e[0], ev.e[1]};
             else if (last && !co) pair = EventPair{ev.e[2], ev.e[3]};
-            if (enqueue(p, dir, L, bt, lane, stream, pair) != HP_OK) return -1.f;
-            if (co && enqueue(p, co->dir, co->L, *co->bt, co->lane, stream,
+            if (enqueue(p, dir, L, bt, stream, pair) != HP_OK) return -1.f;
+            if (co && enqueue(p, co->dir, co->L, *co->bt, stream,
                               last ? EventPair{ev.e[2], ev.e[3]} : EventPair{}) != HP_OK)
                 return -1.f;
         }
@@ -956,7 +986,7 @@ float time_candidate(const hp_plan *p, Direction dir, const hp::Launch &L, const
 // caps of the best two and the current shape are then re-timed by the median of
 // three bursts of four, because the top of the ranking is flat and single
 // timings are noisy.
-int tune_direction(hp_plan *p, Direction dir, const BufTable &bt, int lane, hipStream_t stream,
+int tune_direction(hp_plan *p, Direction dir, const BufTable &bt, hipStream_t stream,
                    const Companion *co) {
     BurstEvents ev;
     if (!ev.create()) return HP_EHIP;
@@ -973,7 +1003,7 @@ int tune_direction(hp_plan *p, Direction dir, const BufTable &bt, int lane, hipS
             for (int cap : caps) {
                 if (cap && cap < 2 * (b / 64)) continue;                // cap below two workgroups
                 const hp::Launch L{v, b, cap, cur.nontemporal};
-                const float ms = time_candidate(p, dir, L, bt, lane, stream, ev, 1, 3, co);
+                const float ms = time_candidate(p, dir, L, bt, stream, ev, 1, 3, co);
                 if (ms < 0) { rc = HP_EHIP; break; }
                 cands.push_back(Cand{ms, L});
             }
@@ -1001,7 +1031,7 @@ int tune_direction(hp_plan *p, Direction dir, const BufTable &bt, int lane, hipS
         hp::Launch best = cur;
         float best_ms = 1e30f;
         for (const Cand &c : cands) {
-            const float ms = time_candidate(p, dir, c.L, bt, lane, stream, ev, 3, 4, co);
+            const float ms = time_candidate(p, dir, c.L, bt, stream, ev, 3, 4, co);
             if (ms < 0) { rc = HP_EHIP; break; }
             if (ms < best_ms) { best_ms = ms; best = c.L; }
         }
@@ -1197,42 +1227,37 @@ int hp_plan_set_launch(hp_plan_t *p, int32_t direction, const hp_launch_t *in) {
 
 int hp_forward(const hp_plan_t *p, const void *const *src_bufs, void *const *dst_bufs, void *stream) {
     BufTable bt;
-    int width = 0;
-    int rc = prepare(p, kForward, src_bufs, (const void *const *)dst_bufs, &bt, &width);
+    int rc = prepare(p, kForward, src_bufs, (const void *const *)dst_bufs, &bt);
     if (rc != HP_OK || p->segments.empty()) return rc;
-    return enqueue(p, kForward, p->fwd, bt, width, (hipStream_t)stream, next_event_pair(0));
+    return enqueue(p, kForward, p->fwd, bt, (hipStream_t)stream, next_event_pair(0));
 }
 
 int hp_zero_image_rows(const hp_plan_t *p, void *const *dst_bufs, void *stream) {
     BufTable bt;
-    int width = 0;
-    int rc = prepare(p, kZeroRows, nullptr, (const void *const *)dst_bufs, &bt, &width);
+    int rc = prepare(p, kZeroRows, nullptr, (const void *const *)dst_bufs, &bt);
     if (rc != HP_OK || p->segments.empty()) return rc;
-    return enqueue(p, kZeroRows, p->fwd, bt, width, (hipStream_t)stream, EventPair{});
+    return enqueue(p, kZeroRows, p->fwd, bt, (hipStream_t)stream, EventPair{});
 }
 
 int hp_backward(const hp_plan_t *p, const void *const *dst_grad_bufs, void *const *src_grad_bufs,
                 void *stream) {
     BufTable bt;
-    int width = 0;
-    int rc = prepare(p, kBackward, (const void *const *)src_grad_bufs, dst_grad_bufs, &bt, &width);
+    int rc = prepare(p, kBackward, (const void *const *)src_grad_bufs, dst_grad_bufs, &bt);
     if (rc != HP_OK || p->segments.empty()) return rc;
-    return enqueue(p, kBackward, p->bwd, bt, width, (hipStream_t)stream, next_event_pair(1));
+    return enqueue(p, kBackward, p->bwd, bt, (hipStream_t)stream, next_event_pair(1));
 }
 
 int hp_backward_accumulate(const hp_plan_t *p, const void *const *dst_grad_bufs, void *const *src_accum_bufs,
                            void *stream) {
     BufTable bt;
-    int lane = 0;
-    int rc = prepare(p, kBackwardAcc, (const void *const *)src_accum_bufs, dst_grad_bufs, &bt, &lane);
+    int rc = prepare(p, kBackwardAcc, (const void *const *)src_accum_bufs, dst_grad_bufs, &bt);
     if (rc != HP_OK || p->segments.empty()) return rc;
-    return enqueue(p, kBackwardAcc, p->acc, bt, lane, (hipStream_t)stream, next_event_pair(2));
+    return enqueue(p, kBackwardAcc, p->acc, bt, (hipStream_t)stream, next_event_pair(2));
 }
 
 int hp_forward_static(const hp_plan_t *p, const void *const *src_bufs, void *const *dst_bufs, void *stream) {
     BufTable bt;
-    int width = 0;
-    int rc = prepare(p, kForward, src_bufs, (const void *const *)dst_bufs, &bt, &width, /*plan_tables=*/false);
+    int rc = prepare(p, kForward, src_bufs, (const void *const *)dst_bufs, &bt, /*plan_tables=*/false);
     if (rc != HP_OK || p->segments.empty()) return rc;
     // what this launch reads: the segment descriptors and the search tree of its tile size only
     const hp::Launch &L = p->fwd;
@@ -1251,7 +1276,7 @@ int hp_forward_static(const hp_plan_t *p, const void *const *src_bufs, void *con
     if (rc != HP_OK) return rc;
     KParams k = hp::kernel_params(*p, L.tile_variant, (const hp::Seg *)tables, (const uint32_t *)(tables + seg_bytes));
     for (uint32_t l = 0; l < k.n_levels; ++l) k.level_off[l] -= tree_begin;               // offsets inside the copied tree
-    return enqueue_params(p, kForward, L, bt, width, st, EventPair{}, k);
+    return enqueue_params(p, kForward, L, bt, st, EventPair{}, k);
 }
 
 int hp_plan_tune(hp_plan_t *p, const void *const *src_bufs, void *const *dst_bufs,
@@ -1261,30 +1286,30 @@ int hp_plan_tune(hp_plan_t *p, const void *const *src_bufs, void *const *dst_buf
     if ((dst_grad_bufs == nullptr) != (src_grad_bufs == nullptr)) return HP_EINVAL;
     if (p->segments.empty()) return HP_OK;
     BufTable bt_f, bt_b;
-    int lane_f = 0, lane_b = 0, rc = HP_OK;
-    if (src_bufs) rc = prepare(p, kForward, src_bufs, (const void *const *)dst_bufs, &bt_f, &lane_f);
+    int rc = HP_OK;
+    if (src_bufs) rc = prepare(p, kForward, src_bufs, (const void *const *)dst_bufs, &bt_f);
     if (rc == HP_OK && dst_grad_bufs)
-        rc = prepare(p, kBackward, (const void *const *)src_grad_bufs, dst_grad_bufs, &bt_b, &lane_b);
+        rc = prepare(p, kBackward, (const void *const *)src_grad_bufs, dst_grad_bufs, &bt_b);
     const bool both = src_bufs && dst_grad_bufs;
     // A timing loop over a small plan runs out of the 256 MB memory-side cache and
     // ranks shapes by a behaviour that a training step's fresh buffers do not
     // show: such plans keep their shapes and get one plain launch per direction.
     const int64_t boundary = p->n_rows * p->row_bytes;
     if (rc == HP_OK && (1 + (int64_t)p->dst_copies) * boundary < kMinTunedBytes) {
-        if (src_bufs) rc = enqueue(p, kForward, p->fwd, bt_f, lane_f, (hipStream_t)stream, EventPair{});
+        if (src_bufs) rc = enqueue(p, kForward, p->fwd, bt_f, (hipStream_t)stream, EventPair{});
         if (rc == HP_OK && dst_grad_bufs)
-            rc = enqueue(p, kBackward, p->bwd, bt_b, lane_b, (hipStream_t)stream, EventPair{});
+            rc = enqueue(p, kBackward, p->bwd, bt_b, (hipStream_t)stream, EventPair{});
         if (rc == HP_OK && hip_failed(hipStreamSynchronize((hipStream_t)stream))) rc = HP_EHIP;
         return rc;
     }
     if (rc == HP_OK && src_bufs) {
-        const Companion co{kBackward, p->bwd, &bt_b, lane_b};
-        rc = tune_direction(p, kForward, bt_f, lane_f, (hipStream_t)stream, both ? &co : nullptr);
+        const Companion co{kBackward, p->bwd, &bt_b};
+        rc = tune_direction(p, kForward, bt_f, (hipStream_t)stream, both ? &co : nullptr);
         if (rc == HP_OK) g_shapes.remember(p, true, false);
     }
     if (rc == HP_OK && dst_grad_bufs) {
-        const Companion co{kForward, p->fwd, &bt_f, lane_f};
-        rc = tune_direction(p, kBackward, bt_b, lane_b, (hipStream_t)stream, both ? &co : nullptr);
+        const Companion co{kForward, p->fwd, &bt_f};
+        rc = tune_direction(p, kBackward, bt_b, (hipStream_t)stream, both ? &co : nullptr);
         if (rc == HP_OK) g_shapes.remember(p, false, true);
     }
     return rc;
@@ -1405,14 +1430,13 @@ int hp_plan_tune_accumulate(hp_plan_t *p, const void *const *dst_grad_bufs, void
     if (!p || !dst_grad_bufs || !src_accum_bufs) return HP_EINVAL;
     if (p->segments.empty()) return HP_OK;
     BufTable bt;
-    int lane = 0;
-    int rc = prepare(p, kBackwardAcc, (const void *const *)src_accum_bufs, dst_grad_bufs, &bt, &lane);
+    int rc = prepare(p, kBackwardAcc, (const void *const *)src_accum_bufs, dst_grad_bufs, &bt);
     if (rc == HP_OK && p->bwd_accum_bytes < kMinTunedBytes) {              // as in hp_plan_tune: no search
-        rc = enqueue(p, kBackwardAcc, p->acc, bt, lane, (hipStream_t)stream, EventPair{});
+        rc = enqueue(p, kBackwardAcc, p->acc, bt, (hipStream_t)stream, EventPair{});
         if (rc == HP_OK && hip_failed(hipStreamSynchronize((hipStream_t)stream))) rc = HP_EHIP;
         return rc;
     }
-    if (rc == HP_OK) rc = tune_direction(p, kBackwardAcc, bt, lane, (hipStream_t)stream, nullptr);
+    if (rc == HP_OK) rc = tune_direction(p, kBackwardAcc, bt, (hipStream_t)stream, nullptr);
     if (rc == HP_OK) g_shapes.remember(p, false, false, true);
     return rc;
 }

@@ -301,6 +301,7 @@ int build_host_plan(const hp_layout_t *srcs, int32_t n_edges, const hp_layout_t 
     p->dst_rows_per_buf = b_loc * walk.piece;
     const bool sbh = dst->row_order == HP_ROW_SBH;
     const int64_t stride = (sbh && b_loc > 1) ? b_loc : 1;
+    p->strided = stride != 1;
 
     p->n_rows = 0;
     p->bwd_bytes = p->bwd_accum_bytes = 0;

@@ -79,6 +79,7 @@ struct hp_plan {
     int32_t src_copies = 1, dst_copies = 1;   // src_copies: of the first edge (edges may differ, see seg_copies)
     int64_t bwd_bytes = 0, bwd_accum_bytes = 0;   // algorithmic bytes of the two backward flavours
     int64_t dst_rows_per_buf = 0;
+    bool strided = false;                 // every segment is row-strided on the destination side (else none is)
     std::vector<int64_t> src_rows;        // per source buffer
     std::vector<uint8_t> src_leader;      // per source buffer: 1 = copy tp 0 of its rank (the one forward reads)
     std::vector<int32_t> seg_copies;      // per segment: TP copies of its source rank

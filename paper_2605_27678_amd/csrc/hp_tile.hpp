@@ -27,6 +27,8 @@ struct KParams {
     uint32_t row_bytes;
     uint32_t rows_per_tile;     // row-strided segments, rows shorter than a tile: tile_bytes / row_bytes
     uint32_t parts_per_row;     // row-strided segments, rows of at least a tile: ceil(row_bytes / tile_bytes); else 0
+    uint32_t row_chunks;        // row-strided tiles of whole rows: lane chunks of one row (see set_row_chunks)
+    uint32_t row_magic, row_one;
     uint32_t dst_base;          // index of the first destination pointer in BufTable
     uint32_t dst_copies;        // replicas of each row on the destination side
 };
@@ -38,6 +40,8 @@ struct TileView {
     uint32_t pitch_rows;        // 1 = dense destination
     uint32_t src_buf, dst_buf0;
     uint32_t src_copies;        // identical TP copies of the source rank
+    uint32_t first;             // dense: 1 = the tile starts its run (the segment, or one row of a row-strided one)
+    uint64_t left;              // dense: bytes from the tile's start to the end of its run
 };
 
 // One node of the search tree: 16 ascending keys (padding = UINT32_MAX) fetched
@@ -76,12 +80,14 @@ HP_HD TileView locate_tile(const KParams &k, uint32_t tile) {
     v.src_buf = s.src_buf;
     v.dst_buf0 = s.dst_buf0;
     v.src_copies = s.src_copies;
+    v.first = t == 0;
     if (s.pitch_rows == 1) {
         const uint64_t off = (uint64_t)t * k.tile_bytes;
         const uint64_t left = (uint64_t)s.n_rows * k.row_bytes - off;
         v.src_off = s.src_off + off;
         v.dst_off = s.dst_off + off;
         v.nbytes = left < k.tile_bytes ? (uint32_t)left : k.tile_bytes;
+        v.left = left;
     } else if (k.parts_per_row) {
         // a piece of one row: dense on both sides, handled like a dense tile
         const uint32_t row = t / k.parts_per_row;
@@ -91,6 +97,8 @@ HP_HD TileView locate_tile(const KParams &k, uint32_t tile) {
         v.src_off = s.src_off + (uint64_t)row * k.row_bytes + off;
         v.dst_off = s.dst_off + (uint64_t)row * s.pitch_rows * k.row_bytes + off;
         v.nbytes = left < k.tile_bytes ? left : k.tile_bytes;
+        v.first = off == 0;
+        v.left = left;
     } else {
         const uint64_t row0 = (uint64_t)t * k.rows_per_tile;
         const uint64_t rows_left = s.n_rows - row0;
@@ -98,10 +106,92 @@ HP_HD TileView locate_tile(const KParams &k, uint32_t tile) {
         v.src_off = s.src_off + row0 * k.row_bytes;
         v.dst_off = s.dst_off + row0 * s.pitch_rows * k.row_bytes;
         v.nbytes = rows * k.row_bytes;
+        v.left = v.nbytes;
     }
     return v;
 }
 
+// Moves both ends of a dense tile up to the next 128-byte line of its first
+// destination copy (`dst_base` = that buffer's address), except where its run
+// begins and ends: the tiles of a run still partition it, but where rows are no
+// multiple of a line, two tiles - two workgroups, on two XCDs with an L2 each -
+// no longer share one.  A tile of fewer than 128 bytes may become empty.
+constexpr uint32_t kLineBytes = 128;
+HP_HD void align_tile(TileView &v, uint64_t dst_base) {
+    if (v.pitch_rows != 1) return;
+    const uint32_t up = (uint32_t)(0 - (dst_base + v.dst_off)) & (kLineBytes - 1);
+    const uint32_t end = v.left < v.nbytes + up ? (uint32_t)v.left : v.nbytes + up;
+    const uint32_t begin = v.first ? 0u : up < end ? up : end;
+    v.src_off += begin;
+    v.dst_off += begin;
+    v.nbytes = end - begin;
+}
+
+// Row-strided tiles of whole rows: chunk i of the tile is chunk i % row_chunks of
+// row i / row_chunks, in chunks of `unit` bytes.  row_magic = ceil(2^32 / row_chunks)
+// divides exactly while i * row_chunks < 2^32 (here i < 2^16 and row_chunks <= 2^13:
+// such rows are shorter than the largest tile of 64 KiB); for a single chunk, whose
+// magic would not fit, row_one passes i through.
+inline void set_row_chunks(KParams &k, uint32_t unit) {
+    k.row_chunks = (k.row_bytes + unit - 1) / unit;
+    k.row_one = k.row_chunks == 1 ? ~0u : 0u;
+    k.row_magic = k.row_one ? 0u : (uint32_t)((((uint64_t)1 << 32) + k.row_chunks - 1) / k.row_chunks);
+}
+
+// Where a lane's chunk lies: bytes from the tile's start on the dense (source)
+// side and on the destination side, and how many of its bytes the chunk before
+// it covers as well (the last chunk of a run whose length is no multiple of
+// the chunk is moved back so that it ends with the run).
+struct ChunkView {
+    uint64_t dst;
+    uint32_t src, over;
+};
+template <uint32_t UNIT, bool DENSE, bool GUARD>
+HP_HD ChunkView chunk_at(const KParams &k, const TileView &t, uint32_t i) {
+    ChunkView c;
+    if (DENSE) {
+        const uint32_t at = i * UNIT, last = t.nbytes - UNIT;
+        c.src = GUARD && at > last ? last : at;
+        c.over = at - c.src;
+        c.dst = c.src;
+    } else {
+        const uint32_t row = (uint32_t)(((uint64_t)i * k.row_magic) >> 32) + (i & k.row_one);
+        const uint32_t at = (i - row * k.row_chunks) * UNIT, last = k.row_bytes - UNIT;
+        const uint32_t col = at > last ? last : at;
+        c.src = row * k.row_bytes + col;
+        c.over = at - col;
+        c.dst = (uint64_t)row * t.pitch_rows * k.row_bytes + col;
+    }
+    return c;
+}
+
+// How many chunks of UNIT bytes a tile has, and how many of them lie in their
+// run as they are (those before the moved one).  0 chunks: the run is shorter
+// than a chunk and is walked element by element.
+template <uint32_t UNIT, bool DENSE>
+HP_HD void count_chunks(const KParams &k, const TileView &t, uint32_t &all, uint32_t &whole) {
+    if (DENSE) {
+        all = t.nbytes >= UNIT ? (t.nbytes + UNIT - 1) / UNIT : 0u;
+        whole = all ? t.nbytes / UNIT : 0u;
+    } else {
+        all = whole = k.row_bytes >= UNIT ? t.nbytes / k.row_bytes * k.row_chunks : 0u;
+    }
+}
+
+// The walk one element at a time (ELEM bytes): element i of the tile.
+template <uint32_t ELEM>
+HP_HD ChunkView element_at(const KParams &k, const TileView &t, uint32_t i) {
+    ChunkView c;
+    const uint32_t at = i * ELEM;
+    c.src = at;
+    c.over = 0;
+    if (t.pitch_rows == 1) c.dst = at;
+    else {
+        const uint32_t row = at / k.row_bytes;
+        c.dst = (uint64_t)row * t.pitch_rows * k.row_bytes + (at - row * k.row_bytes);
+    }
+    return c;
+}
 
 // The kernel parameters of a launch with tiles of 1 KiB << variant; segs and
 // tree point at the plan's tables wherever the caller keeps them (device memory
@@ -116,6 +206,7 @@ inline KParams kernel_params(const hp_plan &p, int variant, const Seg *segs, con
     k.row_bytes = (uint32_t)p.row_bytes;
     k.rows_per_tile = std::max<uint32_t>(1u, k.tile_bytes / k.row_bytes);
     k.parts_per_row = k.row_bytes >= k.tile_bytes ? (k.row_bytes + k.tile_bytes - 1) / k.tile_bytes : 0u;
+    set_row_chunks(k, 16u);
     k.dst_base = (uint32_t)p.n_src_bufs;
     k.dst_copies = (uint32_t)p.dst_copies;
     return k;

@@ -1,0 +1,85 @@
+"""Rows and buffers that no vector width divides: the ragged and the row-strided kernels at the sizes where a chunk,
+a line or a tile ends inside a row.  Bit for bit against the oracle, with guards around every buffer."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2605_27678_amd as hp
+from oracle import oracle
+from paper_2605_27678_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+GUARD = 192                  # elements before and after every buffer
+
+
+class Padded:
+    """A [rows, hidden] buffer inside a larger one, `off` elements after a 256-byte boundary."""
+
+    def __init__(self, values, off):
+        flat = values.reshape(-1)
+        self.n, self.at = flat.size, GUARD + off
+        self.whole = np.full(self.at + self.n + GUARD, 0x5A, flat.dtype)
+        self.whole[self.at:self.at + self.n] = flat
+        signed = self.whole.view({2: np.int16, 4: np.int32}[flat.itemsize])
+        self.dev = torch.from_numpy(signed).cuda()
+        kind = torch.bfloat16 if flat.dtype == np.uint16 else torch.float32
+        self.t = self.dev[self.at:self.at + self.n].view(kind).view(values.shape)
+
+    def check(self, want, what):
+        got = self.dev.cpu().numpy().view(self.whole.dtype)
+        assert np.array_equal(got[:self.at], self.whole[:self.at]), (what, "bytes before the buffer")
+        assert np.array_equal(got[self.at + self.n:], self.whole[self.at + self.n:]), (what, "bytes after the buffer")
+        assert np.array_equal(got[self.at:self.at + self.n].view(np.uint8), want.reshape(-1).view(np.uint8)), what
+
+
+# hidden: below a chunk (1, 3, 7), a chunk and its neighbours, around a line, around tiles of 1 and 2 KiB
+@pytest.mark.parametrize("f32", [False, True])
+@pytest.mark.parametrize("hidden,tp,sbh,off", [(1, 2, True, 0), (3, 3, False, 1), (7, 4, True, 3), (8, 8, True, 1),
+                                               (9, 1, False, 5), (63, 4, False, 0), (65, 2, True, 1), (511, 5, True, 0),
+                                               (513, 4, False, 7), (1001, 16, False, 1), (1025, 2, True, 2),
+                                               (64, 4, False, 1)])
+def test_ragged_rows_and_buffers(hidden, tp, sbh, off, f32):
+    rng = np.random.default_rng(hidden * 31 + tp)
+    src = wl.Grid(tp=2, dp=3)
+    dst = wl.Grid(tp=tp, cp=2, dp=1, cp_split=wl.CP_ZIGZAG, row_order=wl.ROW_SBH if sbh else wl.ROW_BSH)
+    tm = wl.token_map_from_lens(rng, 2, 48, hidden, [[1, 9, 17, 2], [30, 5]])
+    tm.dtype = wl.DT_F32 if f32 else wl.DT_BF16
+    plan, prob = hp.hp_plan_create(src, dst, tm), oracle.Problem(src, dst, tm)
+    rows, drows = prob.src_rows(), prob.dst_rows()
+
+    def values(r):
+        x = torch.from_numpy(rng.standard_normal((r, hidden), dtype=np.float32))
+        return x.numpy() if f32 else x.to(torch.bfloat16).view(torch.int16).numpy().view(np.uint16)
+
+    # every buffer at an alignment of its own
+    at = iter(range(off, 10 ** 6, max(1, off)))
+    x = [Padded(values(r), next(at) % 64) for r in rows]
+    d = [Padded(values(drows), next(at) % 64) for _ in range(prob.n_dst)]
+    g = [Padded(values(drows), next(at) % 64) for _ in range(prob.n_dst)]
+    y = [Padded(values(r), next(at) % 64) for r in rows]
+    a = [Padded(rng.standard_normal((r, hidden), dtype=np.float32), next(at) % 64) for r in rows]
+    cut = lambda b: b.whole[b.at:b.at + b.n].copy().reshape(b.t.shape)                # noqa: E731
+    T = lambda bs: [b.t for b in bs]                                                  # noqa: E731
+
+    want_d, want_y, want_a = [cut(b) for b in d], [cut(b) for b in y], [cut(b) for b in a]
+    prob.forward([cut(b) for b in x], want_d)
+    (prob.backward_f32 if f32 else prob.backward_bf16)([cut(b) for b in g], want_y)
+    prob.backward_accumulate([cut(b) for b in g], want_a)
+    hp.hp_forward(plan, T(x), T(d))
+    hp.hp_backward(plan, T(g), T(y))
+    hp.hp_backward_accumulate(plan, T(g), T(a))
+    torch.cuda.synchronize()
+    for kind, bufs, want in (("forward", d, want_d), ("backward", y, want_y), ("accumulate", a, want_a)):
+        for i, (b, w) in enumerate(zip(bufs, want)):
+            b.check(w, (kind, i))
+    for b, w in zip(d, want_d):
+        b.whole[b.at:b.at + b.n] = w.reshape(-1)
+    prob_zero = [w.view(np.uint32 if f32 else np.uint16).copy() for w in want_d]
+    for j, z in enumerate(prob_zero):
+        sb, _ = prob.forward_map(j)
+        z[sb >= 0] = 0
+    hp.hp_zero_image_rows(plan, T(d))
+    torch.cuda.synchronize()
+    for j, (b, z) in enumerate(zip(d, prob_zero)):
+        b.check(z, ("zero", j))
+    plan.close()
