@@ -168,8 +168,10 @@ typedef struct hp_segment {
  * (Colocated communicator, second paragraph; the non-colocated communicator
  * builds the same fixed routing on both sides): validates the two grids and the token map,
  * builds the segment table (runs of rows contiguous on both sides) and the
- * search trees that map a workgroup to its segment on the host, and uploads
- * them to the CURRENT HIP device (a few KB; one synchronous copy into a device
+ * search trees that map a workgroup to its segment on the host, and ties the
+ * plan to the CURRENT HIP device.  Tables that leave room for the buffer pointers
+ * in a launch's 4 KiB of arguments (up to about a hundred segments) travel there
+ * with every launch; larger ones are uploaded (one synchronous copy into a device
  * block that is recycled from earlier plans when one is free).
  * src, dst, map: host structs, read only during the call.
  * *out receives an owned plan; release it with hp_plan_destroy. */
@@ -313,21 +315,22 @@ int hp_backward_accumulate(const hp_plan_t *plan, const void *const *dst_grad_bu
  * harnesses that forbid hipMalloc.  hp_forward reads its plan's tables from a
  * device block that hp_plan_create allocated; this call instead takes ANY plan
  * (normally a host-only one from hp_plan_create_host or the host_only variants,
- * whose creation makes no HIP call), writes the tables this launch needs - the
- * segment descriptors and the search tree of the plan's forward tile size -
- * into a fixed array that the library holds in each GPU's memory from load to
- * process end (HP_STATIC_MAX_TABLE_BYTES, 64 KiB: about 1700 segments), and
- * launches the same kernel on them.  The table bytes travel as arguments of
- * small copy kernels on `stream` ahead of the transform kernel, so no host
- * buffer has to outlive the call.  It calls no hipMalloc / hipFree / hipMemcpy
+ * whose creation makes no HIP call) and launches the same kernel.  Small plans
+ * carry their tables in the launch's arguments anyway (see hp_plan_create); of a
+ * larger one this call writes what the launch needs - the segment descriptors and
+ * the search tree of the plan's forward tile size - into a fixed array that the
+ * library holds in each GPU's memory from load to process end
+ * (HP_STATIC_MAX_TABLE_BYTES, 64 KiB: about 1700 segments).  The table bytes then
+ * travel as arguments of small copy kernels on `stream` ahead of the transform
+ * kernel, so no host buffer has to outlive the call.  It calls no hipMalloc / hipFree / hipMemcpy
  * and no other allocating routine.  The first call on a device looks up the
  * array's address (hipGetSymbolAddress); make that call outside graph capture.
  *   plan, src_bufs, dst_bufs, stream: as for hp_forward; the result is the same.
  * Returns HP_ELAYOUT when the tables exceed HP_STATIC_MAX_TABLE_BYTES (use
  * hp_forward with a device plan then), otherwise hp_forward's codes; HP_ESTATE
  * is not returned for host-only plans here.
- * All calls on one GPU share that GPU's array and it keeps the last call's
- * tables: calls on the SAME stream are ordered by the stream, calls that overlap
+ * All calls of larger plans on one GPU share that GPU's array and it keeps the
+ * last call's tables: calls on the SAME stream are ordered by the stream, calls that overlap
  * on different streams (or threads using different streams) of one GPU race on
  * it and must be serialised by the caller.  No timing events are attached. */
 #define HP_STATIC_MAX_TABLE_BYTES 65536

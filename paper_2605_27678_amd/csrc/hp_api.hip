@@ -46,6 +46,16 @@ struct BufTable {
     void *p[HP_MAX_BUFFERS];
 };
 
+// The arguments of a transform kernel.  The tables of a plan that leaves the
+// room travel behind its buffer pointers (inline_tables), so that a plan of up to
+// about a hundred segments needs no device memory, no upload and, in the
+// kernel, no load from memory that the launch itself has not just written.
+struct Args {
+    KParams k;
+    BufTable b;
+};
+static_assert(sizeof(Args) <= 4096, "kernel arguments");
+
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // A lane chunk of N bytes as a register type, and the same type as it lies in
@@ -87,9 +97,13 @@ enum Tiles {
 
 // The tile of this workgroup.  Ragged: its ends on lines of the first destination copy.
 template <Tiles TILES>
-__device__ __forceinline__ TileView my_tile(const KParams &k, const BufTable &bufs) {
-    TileView t = locate_tile(k, blockIdx.x);
-    if (TILES == kRagged) hp::align_tile(t, (uint64_t)(uintptr_t)bufs.p[k.dst_base + t.dst_buf0]);
+__device__ __forceinline__ TileView my_tile(const Args &a) {
+    // the kernel's arguments are one Args and begin with it
+    const uintptr_t args = (uintptr_t)__builtin_amdgcn_kernarg_segment_ptr();
+    const uintptr_t segs = a.k.seg_at ? args + a.k.seg_at : (uintptr_t)a.k.segs;
+    const uintptr_t tree = a.k.seg_at ? args + a.k.tree_at : (uintptr_t)a.k.tree;
+    TileView t = locate_tile(a.k, (const HP_TABLE hp::Seg *)segs, (const HP_TABLE uint32_t *)tree, blockIdx.x);
+    if (TILES == kRagged) hp::align_tile(t, (uint64_t)(uintptr_t)a.b.p[a.k.dst_base + t.dst_buf0]);
     return t;
 }
 
@@ -152,9 +166,9 @@ __device__ __forceinline__ void forward_tile(const BufTable &bufs, const KParams
 
 template <int NREP, Tiles TILES, bool NTL, bool NTS>
 __global__ void __launch_bounds__(1024)
-hp_forward_kernel(const KParams k, const BufTable bufs) {
-    const TileView t = my_tile<TILES>(k, bufs);
-    forward_tile<NREP, TILES, NTL, NTS>(bufs, k, t, NREP > 0 ? (uint32_t)NREP : k.dst_copies);
+hp_forward_kernel(const Args a) {
+    const TileView t = my_tile<TILES>(a);
+    forward_tile<NREP, TILES, NTL, NTS>(a.b, a.k, t, NREP > 0 ? (uint32_t)NREP : a.k.dst_copies);
 }
 
 // ---------------------------------------------------------------------------
@@ -179,8 +193,8 @@ __device__ __forceinline__ void zero_tile(const BufTable &bufs, const KParams &k
 
 template <Tiles TILES, bool NTS>
 __global__ void __launch_bounds__(1024)
-hp_zero_rows_kernel(const KParams k, const BufTable bufs) {
-    zero_tile<TILES, NTS>(bufs, k, my_tile<TILES>(k, bufs));
+hp_zero_rows_kernel(const Args a) {
+    zero_tile<TILES, NTS>(a.b, a.k, my_tile<TILES>(a));
 }
 
 // ---------------------------------------------------------------------------
@@ -371,9 +385,9 @@ __device__ __forceinline__ void backward_tile(const BufTable &bufs, const KParam
 
 template <int DT, bool ACC, int NREP, Tiles TILES, bool NTL, bool NTS>
 __global__ void __launch_bounds__(1024)
-hp_backward_kernel(const KParams k, const BufTable bufs) {
-    const TileView t = my_tile<TILES>(k, bufs);
-    backward_tile<DT, ACC, NREP, TILES, NTL, NTS>(bufs, k, t, NREP > 0 ? (uint32_t)NREP : k.dst_copies);
+hp_backward_kernel(const Args a) {
+    const TileView t = my_tile<TILES>(a);
+    backward_tile<DT, ACC, NREP, TILES, NTL, NTS>(a.b, a.k, t, NREP > 0 ? (uint32_t)NREP : a.k.dst_copies);
 }
 
 // ---------------------------------------------------------------------------
@@ -587,45 +601,72 @@ unsigned lds_for_cap(int block, int waves_per_cu) {
 }
 
 template <Tiles TILES, bool NTL, bool NTS>
-void launch_forward(int copies, const LaunchCfg &c, const BufTable &bt, const KParams &k) {
+void launch_forward(int copies, const LaunchCfg &c, const Args &a) {
     switch (copies) {
-        case 1: HP_LAUNCH((hp_forward_kernel<1, TILES, NTL, NTS>), c, k, bt); break;
-        case 2: HP_LAUNCH((hp_forward_kernel<2, TILES, NTL, NTS>), c, k, bt); break;
-        case 4: HP_LAUNCH((hp_forward_kernel<4, TILES, NTL, NTS>), c, k, bt); break;
-        case 8: HP_LAUNCH((hp_forward_kernel<8, TILES, NTL, NTS>), c, k, bt); break;
-        default: HP_LAUNCH((hp_forward_kernel<0, TILES, NTL, NTS>), c, k, bt); break;
+        case 1: HP_LAUNCH((hp_forward_kernel<1, TILES, NTL, NTS>), c, a); break;
+        case 2: HP_LAUNCH((hp_forward_kernel<2, TILES, NTL, NTS>), c, a); break;
+        case 4: HP_LAUNCH((hp_forward_kernel<4, TILES, NTL, NTS>), c, a); break;
+        case 8: HP_LAUNCH((hp_forward_kernel<8, TILES, NTL, NTS>), c, a); break;
+        default: HP_LAUNCH((hp_forward_kernel<0, TILES, NTL, NTS>), c, a); break;
     }
 }
 
 template <int DT, bool ACC, Tiles TILES, bool NTL, bool NTS>
-void launch_backward_nrep(int copies, const LaunchCfg &c, const BufTable &bt, const KParams &k) {
+void launch_backward_nrep(int copies, const LaunchCfg &c, const Args &a) {
     switch (copies) {
-        case 1: HP_LAUNCH((hp_backward_kernel<DT, ACC, 1, TILES, NTL, NTS>), c, k, bt); break;
-        case 2: HP_LAUNCH((hp_backward_kernel<DT, ACC, 2, TILES, NTL, NTS>), c, k, bt); break;
-        case 4: HP_LAUNCH((hp_backward_kernel<DT, ACC, 4, TILES, NTL, NTS>), c, k, bt); break;
-        case 8: HP_LAUNCH((hp_backward_kernel<DT, ACC, 8, TILES, NTL, NTS>), c, k, bt); break;
-        default: HP_LAUNCH((hp_backward_kernel<DT, ACC, 0, TILES, NTL, NTS>), c, k, bt); break;
+        case 1: HP_LAUNCH((hp_backward_kernel<DT, ACC, 1, TILES, NTL, NTS>), c, a); break;
+        case 2: HP_LAUNCH((hp_backward_kernel<DT, ACC, 2, TILES, NTL, NTS>), c, a); break;
+        case 4: HP_LAUNCH((hp_backward_kernel<DT, ACC, 4, TILES, NTL, NTS>), c, a); break;
+        case 8: HP_LAUNCH((hp_backward_kernel<DT, ACC, 8, TILES, NTL, NTS>), c, a); break;
+        default: HP_LAUNCH((hp_backward_kernel<DT, ACC, 0, TILES, NTL, NTS>), c, a); break;
     }
 }
 
 template <Tiles TILES, bool NTL, bool NTS>
-void launch_backward(int dtype, bool acc, int copies, const LaunchCfg &c, const BufTable &bt, const KParams &k) {
+void launch_backward(int dtype, bool acc, int copies, const LaunchCfg &c, const Args &a) {
     if (dtype == HP_F32) {
-        if (acc) launch_backward_nrep<HP_F32, true, TILES, NTL, NTS>(copies, c, bt, k);
-        else launch_backward_nrep<HP_F32, false, TILES, NTL, NTS>(copies, c, bt, k);
+        if (acc) launch_backward_nrep<HP_F32, true, TILES, NTL, NTS>(copies, c, a);
+        else launch_backward_nrep<HP_F32, false, TILES, NTL, NTS>(copies, c, a);
     } else {
-        if (acc) launch_backward_nrep<HP_BF16, true, TILES, NTL, NTS>(copies, c, bt, k);
-        else launch_backward_nrep<HP_BF16, false, TILES, NTL, NTS>(copies, c, bt, k);
+        if (acc) launch_backward_nrep<HP_BF16, true, TILES, NTL, NTS>(copies, c, a);
+        else launch_backward_nrep<HP_BF16, false, TILES, NTL, NTS>(copies, c, a);
     }
 }
 
 enum Direction { kForward = 0, kBackward = 1, kBackwardAcc = 2, kZeroRows = 3 };   // kZeroRows: forward's launch shape
 
 template <Tiles TILES>
-void launch_other(const hp_plan *p, Direction dir, const LaunchCfg &c, const BufTable &bt, const KParams &k) {
-    if (dir == kZeroRows) HP_LAUNCH((hp_zero_rows_kernel<TILES, true>), c, k, bt);
-    else if (dir == kForward) launch_forward<TILES, false, true>(p->dst_copies, c, bt, k);
-    else launch_backward<TILES, true, true>(p->dtype, dir == kBackwardAcc, p->dst_copies, c, bt, k);
+void launch_other(const hp_plan *p, Direction dir, const LaunchCfg &c, const Args &a) {
+    if (dir == kZeroRows) HP_LAUNCH((hp_zero_rows_kernel<TILES, true>), c, a);
+    else if (dir == kForward) launch_forward<TILES, false, true>(p->dst_copies, c, a);
+    else launch_backward<TILES, true, true>(p->dtype, dir == kBackwardAcc, p->dst_copies, c, a);
+}
+
+// Whether a launch's tables fit behind the buffer pointers: the descriptors and
+// the level below the root (there are no more for so few segments).  The same
+// for every tile size, because every tree has as many keys.
+size_t inline_seg_at(const hp_plan *p) {
+    return (offsetof(Args, b) + (size_t)(p->n_src_bufs + p->n_dst_bufs) * sizeof(void *) + 63) / 64 * 64;
+}
+bool inline_tables(const hp_plan *p) {
+    const size_t n = p->segments.size();
+    const size_t leaves = n > (size_t)hp::kTreeFanout ? (n + hp::kTreeFanout - 1) / hp::kTreeFanout * 64 : 0;
+    return inline_seg_at(p) + (n * sizeof(hp::Seg) + 63) / 64 * 64 + leaves <= sizeof(Args);
+}
+
+// Puts the tables of a launch with tiles of 1 KiB << variant behind the buffer
+// pointers.
+void put_tables(const hp_plan *p, int variant, Args &a) {
+    const size_t seg_at = inline_seg_at(p), n = p->dsegs.size();
+    const size_t tree_at = seg_at + (n * sizeof(hp::Seg) + 63) / 64 * 64;
+    a.k.seg_at = (uint32_t)seg_at;
+    a.k.tree_at = (uint32_t)tree_at;
+    std::memcpy((char *)&a + seg_at, p->dsegs.data(), n * sizeof(hp::Seg));
+    if (a.k.n_levels > 1) {
+        const size_t keys = (n + hp::kTreeFanout - 1) / hp::kTreeFanout * hp::kTreeFanout;
+        std::memcpy((char *)&a + tree_at, p->tree.data() + a.k.level_off[0], keys * sizeof(uint32_t));
+        a.k.level_off[0] = 0;
+    }
 }
 
 // Enqueues one kernel for direction `dir` with launch shape `L`.
@@ -636,14 +677,18 @@ int enqueue(const hp_plan *p, Direction dir, const hp::Launch &L, const BufTable
             EventPair ev) {
     const int rc = enqueue_params(p, dir, L, bt, stream, ev,
                                   hp::kernel_params(*p, L.tile_variant, p->d_segs, p->d_tree));
-    if (rc == HP_OK) p->note_stream((void *)stream);
+    if (rc == HP_OK && p->d_segs) p->note_stream((void *)stream);
     return rc;
 }
 
 int enqueue_params(const hp_plan *p, Direction dir, const hp::Launch &L, const BufTable &bt, hipStream_t stream,
                    EventPair ev, const KParams &params) {
-    KParams k = params;
-    if (dir == kBackwardAcc) hp::set_row_chunks(k, 4u * (uint32_t)p->elem_bytes);
+    Args a;
+    a.k = params;
+    std::memcpy(a.b.p, bt.p, (size_t)(p->n_src_bufs + p->n_dst_bufs) * sizeof(void *));
+    if (dir == kBackwardAcc) hp::set_row_chunks(a.k, 4u * (uint32_t)p->elem_bytes);
+    if (!a.k.segs) put_tables(p, L.tile_variant, a);
+    const KParams &k = a.k;
     LaunchCfg c;
     c.grid = dim3(p->n_tiles(L.tile_variant));
     c.block = dim3((unsigned)L.block);
@@ -655,24 +700,24 @@ int enqueue_params(const hp_plan *p, Direction dir, const hp::Launch &L, const B
     const bool strided = p->strided && k.parts_per_row == 0;
     if (strided || k.row_bytes % hp::kLineBytes) {
         // the cache policy that the kernels of whole lines start from, whatever the shape asks for
-        if (strided) launch_other<kStrided>(p, dir, c, bt, k);
-        else launch_other<kRagged>(p, dir, c, bt, k);
+        if (strided) launch_other<kStrided>(p, dir, c, a);
+        else launch_other<kRagged>(p, dir, c, a);
     } else if (dir == kZeroRows) {
-        if (nt & 2) HP_LAUNCH((hp_zero_rows_kernel<kLines, true>), c, k, bt);
-        else HP_LAUNCH((hp_zero_rows_kernel<kLines, false>), c, k, bt);
+        if (nt & 2) HP_LAUNCH((hp_zero_rows_kernel<kLines, true>), c, a);
+        else HP_LAUNCH((hp_zero_rows_kernel<kLines, false>), c, a);
     } else if (dir == kForward) {
         switch (nt) {
-            case 0: launch_forward<kLines, false, false>(copies, c, bt, k); break;
-            case 1: launch_forward<kLines, true, false>(copies, c, bt, k); break;
-            case 2: launch_forward<kLines, false, true>(copies, c, bt, k); break;
-            default: launch_forward<kLines, true, true>(copies, c, bt, k); break;
+            case 0: launch_forward<kLines, false, false>(copies, c, a); break;
+            case 1: launch_forward<kLines, true, false>(copies, c, a); break;
+            case 2: launch_forward<kLines, false, true>(copies, c, a); break;
+            default: launch_forward<kLines, true, true>(copies, c, a); break;
         }
     } else {
         switch (nt) {
-            case 0: launch_backward<kLines, false, false>(p->dtype, acc, copies, c, bt, k); break;
-            case 1: launch_backward<kLines, true, false>(p->dtype, acc, copies, c, bt, k); break;
-            case 2: launch_backward<kLines, false, true>(p->dtype, acc, copies, c, bt, k); break;
-            default: launch_backward<kLines, true, true>(p->dtype, acc, copies, c, bt, k); break;
+            case 0: launch_backward<kLines, false, false>(p->dtype, acc, copies, c, a); break;
+            case 1: launch_backward<kLines, true, false>(p->dtype, acc, copies, c, a); break;
+            case 2: launch_backward<kLines, false, true>(p->dtype, acc, copies, c, a); break;
+            default: launch_backward<kLines, true, true>(p->dtype, acc, copies, c, a); break;
         }
     }
     if (hip_failed(hipGetLastError())) return HP_EHIP;
@@ -688,12 +733,11 @@ int prepare(const hp_plan *p, Direction dir, const void *const *src, const void 
     if (!p || (!src && dir != kZeroRows) || !dst) return HP_EINVAL;
     if (p->segments.empty()) return HP_OK;
     if (plan_tables) {                                      // the launch will read the plan's own device tables
-        if (!p->d_segs) return HP_ESTATE;
+        if (p->device < 0) return HP_ESTATE;
         int dev = -1;
         if (hip_failed(hipGetDevice(&dev))) return HP_EHIP;
         if (dev != p->device) return HP_ESTATE;
     }
-    std::memset(bt, 0, sizeof(*bt));
     int n = 0;
     uint64_t src_bits = 0, dst_bits = 0;
     for (int i = 0; i < p->n_src_bufs; ++i) {
@@ -870,7 +914,7 @@ int create_common(const hp_layout_t *srcs, int32_t n_edges, const hp_layout_t *d
     if (rc == HP_OK && upload) {
         if (hip_failed(hipGetDevice(&p->device))) rc = HP_EHIP;
         if (rc == HP_OK) g_shapes.apply(p);
-        if (rc == HP_OK && !p->segments.empty()) {
+        if (rc == HP_OK && !p->segments.empty() && !inline_tables(p)) {
             // descriptors and prefix arrays go up in one copy
             const size_t seg_bytes = (p->dsegs.size() * sizeof(hp::Seg) + 63) / 64 * 64;   // keep tree nodes 64-byte aligned
             const size_t first_bytes = p->tree.size() * sizeof(uint32_t);
@@ -1184,7 +1228,7 @@ int hp_plan_query(const hp_plan_t *p, hp_plan_info_t *info) {
     o.bwd_bytes = p->bwd_bytes;
     o.n_segments = (int32_t)p->segments.size();
     o.n_tiles = (int32_t)p->n_tiles(p->fwd.tile_variant);
-    o.on_device = (p->d_segs != nullptr || (p->device >= 0 && p->segments.empty())) ? 1 : 0;
+    o.on_device = p->device >= 0 ? 1 : 0;
     o.device = p->device;
     o.n_maps = p->n_maps;
     o.elem_bytes = p->elem_bytes;
@@ -1259,8 +1303,11 @@ int hp_forward_static(const hp_plan_t *p, const void *const *src_bufs, void *con
     BufTable bt;
     int rc = prepare(p, kForward, src_bufs, (const void *const *)dst_bufs, &bt, /*plan_tables=*/false);
     if (rc != HP_OK || p->segments.empty()) return rc;
-    // what this launch reads: the segment descriptors and the search tree of its tile size only
     const hp::Launch &L = p->fwd;
+    if (inline_tables(p))
+        return enqueue_params(p, kForward, L, bt, (hipStream_t)stream, EventPair{},
+                              hp::kernel_params(*p, L.tile_variant, nullptr, nullptr));
+    // what this launch reads: the segment descriptors and the search tree of its tile size only
     const hp::TreeInfo &ti = p->tree_info[L.tile_variant];
     const size_t seg_bytes = (p->dsegs.size() * sizeof(hp::Seg) + 63) / 64 * 64;          // tree nodes stay 64-byte aligned
     const uint32_t tree_begin = ti.level_off[0];

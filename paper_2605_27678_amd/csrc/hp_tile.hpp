@@ -19,8 +19,10 @@ namespace hp {
 
 // Everything else a kernel needs, also by value.
 struct KParams {
+    uint32_t root[kTreeFanout]; // the top node of this launch's tree: read with the arguments, no load of its own
     const Seg *segs;            // segment descriptors
     const uint32_t *tree;       // search trees (64-byte aligned nodes of 16 keys)
+    uint32_t seg_at, tree_at;   // if not 0: the tables travel with the arguments, this many bytes from their start
     uint32_t n_levels;          // levels of this launch's tree
     uint32_t level_off[kMaxTreeLevels];   // start of each level, in keys; level 0 = leaves
     uint32_t tile_bytes;
@@ -44,15 +46,26 @@ struct TileView {
     uint64_t left;              // dense: bytes from the tile's start to the end of its run
 };
 
-// One node of the search tree: 16 ascending keys (padding = UINT32_MAX) fetched
-// with one 64-byte scalar load (the tree must sit at a 64-byte aligned address).  Returns how many keys are <= tile, and the
-// largest of them.
-HP_HD void search_node(const uint32_t *node, uint32_t tile, uint32_t &count, uint32_t &key) {
-    const uint32_t *p = (const uint32_t *)__builtin_assume_aligned(node, 64);
+// Tables are read through the scalar cache wherever they lie.
+#if defined(__HIP_DEVICE_COMPILE__)
+#define HP_TABLE __attribute__((address_space(4)))
+#else
+#define HP_TABLE
+#endif
+
+// One node of the search tree: 16 ascending keys (padding = UINT32_MAX), fetched
+// with one 64-byte scalar load.  Returns how many keys are <= tile, and the
+// largest of them.  About a hundred instructions a node, and that is as well:
+// the scalar unit then hands a compute unit's workgroups to memory at an even
+// pace.  The same search in three instructions a key (48 in all) made the
+// memory-bound launches slower at every resident-wave cap (2.06 GB backward
+// from four copies: 304 -> 320 us).
+template <typename Node>
+HP_HD void search_node(Node node, uint32_t tile, uint32_t &count, uint32_t &key) {
     uint32_t c = 0, best = 0;
 #pragma unroll
     for (int j = 0; j < kTreeFanout; ++j) {
-        const uint32_t v = p[j];
+        const uint32_t v = node[j];
         const bool le = v <= tile;
         c += le ? 1u : 0u;
         best = le ? v : best;
@@ -62,18 +75,21 @@ HP_HD void search_node(const uint32_t *node, uint32_t tile, uint32_t &count, uin
 }
 
 // Scalar code: every value here is uniform over the workgroup.  One dependent
-// scalar load per tree level, then the descriptor, then the buffer pointers.
-HP_HD TileView locate_tile(const KParams &k, uint32_t tile) {
-    uint32_t lo = 0, first = 0;
+// scalar load per tree level below the root, then the descriptor, then the buffer
+// pointers.  segs and tree point at k's tables (k.segs and k.tree, or behind the
+// arguments).
+HP_HD TileView locate_tile(const KParams &k, const HP_TABLE Seg *segs, const HP_TABLE uint32_t *tree, uint32_t tile) {
+    uint32_t lo, first, count;
+    search_node(k.root, tile, count, first);
+    lo = count - 1;
 #pragma unroll
-    for (int l = kMaxTreeLevels - 1; l >= 0; --l) {
-        if ((uint32_t)l < k.n_levels) {
-            uint32_t count;
-            search_node(k.tree + k.level_off[l] + (size_t)lo * kTreeFanout, tile, count, first);
+    for (int l = kMaxTreeLevels - 2; l >= 0; --l) {
+        if ((uint32_t)l + 1 < k.n_levels) {
+            search_node(tree + k.level_off[l] + (size_t)lo * kTreeFanout, tile, count, first);
             lo = lo * kTreeFanout + count - 1;
         }
     }
-    const Seg s = k.segs[lo];
+    const HP_TABLE Seg &s = segs[lo];
     const uint32_t t = tile - first;
     TileView v;
     v.pitch_rows = s.pitch_rows;
@@ -110,6 +126,10 @@ HP_HD TileView locate_tile(const KParams &k, uint32_t tile) {
     }
     return v;
 }
+
+#if !defined(__HIP_DEVICE_COMPILE__)
+inline TileView locate_tile(const KParams &k, uint32_t tile) { return locate_tile(k, k.segs, k.tree, tile); }
+#endif
 
 // Moves both ends of a dense tile up to the next 128-byte line of its first
 // destination copy (`dst_base` = that buffer's address), except where its run
@@ -198,10 +218,14 @@ HP_HD ChunkView element_at(const KParams &k, const TileView &t, uint32_t i) {
 // for a launch, the plan's host vectors for the host-side walk).
 inline KParams kernel_params(const hp_plan &p, int variant, const Seg *segs, const uint32_t *tree) {
     KParams k;
+    const TreeInfo &ti = p.tree_info[variant];
+    for (int j = 0; j < kTreeFanout; ++j)
+        k.root[j] = ti.n_levels ? p.tree[ti.level_off[ti.n_levels - 1] + j] : UINT32_MAX;
     k.segs = segs;
     k.tree = tree;
-    k.n_levels = p.tree_info[variant].n_levels;
-    for (int l = 0; l < kMaxTreeLevels; ++l) k.level_off[l] = p.tree_info[variant].level_off[l];
+    k.seg_at = k.tree_at = 0;
+    k.n_levels = ti.n_levels;
+    for (int l = 0; l < kMaxTreeLevels; ++l) k.level_off[l] = ti.level_off[l];
     k.tile_bytes = tile_bytes_of(variant);
     k.row_bytes = (uint32_t)p.row_bytes;
     k.rows_per_tile = std::max<uint32_t>(1u, k.tile_bytes / k.row_bytes);

@@ -83,3 +83,37 @@ def test_ragged_rows_and_buffers(hidden, tp, sbh, off, f32):
     for j, (b, z) in enumerate(zip(d, prob_zero)):
         b.check(z, ("zero", j))
     plan.close()
+
+
+# where a plan's tables go: with a launch's arguments or into device memory (the tree's levels and the last segments
+# that fit: 1 level up to 16 segments, arguments full a little above 100)
+@pytest.mark.parametrize("n_seg", [1, 16, 17, 32, 100, 104, 105, 106, 107, 108, 109, 110, 112, 130, 257])
+def test_tables_in_the_arguments_and_in_device_memory(n_seg):
+    rng = np.random.default_rng(n_seg)
+    src, dst = wl.Grid(dp=1), wl.Grid(tp=2)
+    seq, hidden = 4 * n_seg + 3, 72
+    start = (4 * np.arange(n_seg)).astype(np.int32)
+    tm = wl.TokenMap(1, seq, hidden, np.zeros(n_seg, np.int32), start, rng.integers(1, 4, n_seg).astype(np.int32))
+    plan, prob = hp.hp_plan_create(src, dst, tm), oracle.Problem(src, dst, tm)
+    assert plan.info.n_segments == n_seg and plan.info.on_device == 1
+    bits = lambda n, s: wl.bf16_bits(wl.random_bf16((n, hidden), s))                  # noqa: E731
+    rows, drows = prob.src_rows(), prob.dst_rows()
+    x, d, g = [bits(r, 1) for r in rows], [bits(drows, 2 + j) for j in range(2)], [bits(drows, 4 + j) for j in range(2)]
+    dev = lambda a: torch.from_numpy(a.view(np.int16)).cuda().view(torch.bfloat16)     # noqa: E731
+    back = lambda t: t.view(torch.int16).cpu().numpy().view(np.uint16)                # noqa: E731
+    X, D, E, G = [dev(a) for a in x], [dev(a) for a in d], [dev(a) for a in d], [dev(a) for a in g]
+    Y = [torch.zeros_like(t) for t in X]
+    host = hp.hp_plan_create_host(src, dst, tm)
+    hp.hp_forward(plan, X, D)
+    hp.hp_forward_static(host, X, E)
+    hp.hp_backward(plan, G, Y)
+    plan.close()                                            # with its launches still queued
+    torch.cuda.synchronize()
+    y = [np.zeros_like(a) for a in x]
+    prob.forward(x, d)
+    prob.backward_bf16(g, y)
+    for j in range(2):
+        assert np.array_equal(back(D[j]), d[j]) and np.array_equal(back(E[j]), d[j])
+    assert np.array_equal(back(Y[0]), y[0])
+    with pytest.raises(hp.HpError):
+        hp.hp_forward(host, X, D)                           # a host-only plan is refused, however small
