@@ -296,6 +296,19 @@ int hp_backward(const hp_plan_t *plan, const void *const *dst_grad_bufs,
  * Uses hp_forward's launch shape; allocates nothing; returns after enqueueing. */
 int hp_zero_image_rows(const hp_plan_t *plan, void *const *dst_bufs, void *stream);
 
+/* hp_text_grads - the gradient of the fused sequence with respect to the text
+ * embeddings that hp_forward overwrote at the image positions: text_grad_bufs
+ * receive a copy of dst_grad_bufs in which the image-token rows are zero.  What
+ * hp_zero_image_rows gives on a copy, without reading those rows or writing them
+ * twice, and for every buffer in one launch or a few.
+ *   dst_grad_bufs, text_grad_bufs: HOST arrays of n_dst_bufs DEVICE pointers,
+ *             shapes as for hp_forward's dst_bufs; no buffer may overlap another.
+ *             Every row of every text_grad_bufs buffer is written.
+ * The first call on a plan works out its runs of text and image rows on the host;
+ * nothing is allocated on the device.  Returns after enqueueing. */
+int hp_text_grads(const hp_plan_t *plan, const void *const *dst_grad_bufs,
+                  void *const *text_grad_bufs, void *stream);
+
 /* hp_backward_accumulate - as hp_backward, but the source side holds binary32
  * gradient ACCUMULATORS that are added to instead of overwritten: the gradients
  * that accumulate on the packed boundary tensor over the microbatches of a

@@ -5,7 +5,7 @@ materialises the source module's activation in the destination layout and its
 backward applies the reverse transform (Method, paragraph on boundary edges).
 This module only strings the library's calls together for torch.autograd -
 every tensor element is still moved by the HIP kernels behind hp_forward,
-hp_backward and hp_zero_image_rows:
+hp_backward and hp_text_grads:
 
     outs = boundary_transform(plan, src_bufs, text_bufs)
 
@@ -17,7 +17,7 @@ buffer, the incoming gradient with the image-token rows set to zero.
 """
 from __future__ import annotations
 
-from typing import List, Sequence
+from typing import List, Optional, Sequence
 
 import torch
 
@@ -39,12 +39,19 @@ class _BoundaryTransform(torch.autograd.Function):
     def backward(ctx, *grad_dst):
         plan, stream = ctx.plan, torch.cuda.current_stream()
         grads = [g.contiguous() for g in grad_dst]
-        src_grads: List[torch.Tensor] = [torch.empty(shape, dtype=dtype, device=device)
-                                         for shape, dtype, device in ctx.src_meta]
-        plan.backward(grads, src_grads, stream)
+        src_grads: List[Optional[torch.Tensor]] = [None] * ctx.n_src
+        if any(ctx.needs_input_grad[2:2 + ctx.n_src]):
+            src_grads = [torch.empty(shape, dtype=dtype, device=device) for shape, dtype, device in ctx.src_meta]
+            plan.backward(grads, src_grads, stream)
         # gradient with respect to the text embeddings: the rows forward replaced carry none
-        text_grads = [g.clone() for g in grads]
-        plan.zero_image_rows(text_grads, stream)
+        text_grads: List[Optional[torch.Tensor]] = [None] * len(grads)
+        if any(ctx.needs_input_grad[2 + ctx.n_src:]):
+            if torch.is_grad_enabled():                     # create_graph: the copy is part of the graph
+                text_grads = [g.clone() for g in grads]
+                plan.zero_image_rows(text_grads, stream)
+            else:
+                text_grads = [torch.empty_like(g) for g in grads]
+                plan.text_grads(grads, text_grads, stream)
         return (None, None, *src_grads, *text_grads)
 
 

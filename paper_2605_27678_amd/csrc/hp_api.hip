@@ -198,6 +198,56 @@ hp_zero_rows_kernel(const Args a) {
 }
 
 // ---------------------------------------------------------------------------
+// text gradients: a copy of the destination gradients with the image-token rows
+// set to zero, which are not read
+// ---------------------------------------------------------------------------
+// One tile of one buffer per workgroup: blockIdx.x = tile of the runs (text or
+// image rows of a buffer, see dst_runs), blockIdx.y = copy.  The pointers are the
+// gradients' and, from dst_base on, the results'.  Bound by memory: the rows
+// outside the images are read once and every row is written once, against a
+// copy of everything and a second pass of stores over the image rows: four
+// buffers of 268 MB in [S,B,H] order, half of them image rows, 491 -> 281 us.
+template <Tiles TILES>
+__global__ void __launch_bounds__(1024)
+hp_text_grads_kernel(const Args a) {
+    const KParams &k = a.k;
+    const TileView t = my_tile<TILES>(a);
+    // a run lies at the same place in both buffers
+    const char *src = (const char *)a.b.p[t.src_buf + blockIdx.y] + t.dst_off;
+    char *dst = (char *)a.b.p[k.dst_base + t.dst_buf0 + blockIdx.y] + t.dst_off;
+    uint32_t n, whole;
+    hp::count_chunks<16, TILES != kStrided>(k, t, n, whole);
+    const uint32_t step = blockDim.x;
+    if (TILES != kLines && __builtin_expect(n == 0, 0)) {             // shorter than a chunk
+        for (uint32_t i = threadIdx.x; i < t.nbytes / 2; i += step) {
+            const uint64_t at = hp::element_at<2>(k, t, i).dst;
+            uint16_t v = 0;
+            if (!t.src_copies) v = ld<2, true>(src + at);
+            st<2, true>(dst + at, v);
+        }
+        return;
+    }
+    constexpr int U = 4;
+    for (uint32_t done = 0; done < n; done += U * step) {
+        u32x4 v[U];
+        uint64_t at[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t i = done + u * step + threadIdx.x;
+            at[u] = hp::chunk_at<16, TILES != kStrided, TILES == kRagged>(k, t, min(i, n - 1)).dst;
+            v[u] = (u32x4)0u;
+        }
+        if (!t.src_copies) {                                          // uniform: text
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = ld<16, true>(src + at[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (done + u * step + threadIdx.x < n) st<16, true>(dst + at[u], v[u]);
+    }
+}
+
+// ---------------------------------------------------------------------------
 // backward: NREP destination-gradient copies -> fp32 fold -> source copies
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
@@ -697,7 +747,7 @@ int enqueue_params(const hp_plan *p, Direction dir, const hp::Launch &L, const B
     c.ev = ev;
     const int nt = L.nontemporal & 3, copies = p->dst_copies;
     const bool acc = dir == kBackwardAcc;
-    const bool strided = p->strided && k.parts_per_row == 0;
+    const bool strided = p->dst_stride != 1 && k.parts_per_row == 0;
     if (strided || k.row_bytes % hp::kLineBytes) {
         // the cache policy that the kernels of whole lines start from, whatever the shape asks for
         if (strided) launch_other<kStrided>(p, dir, c, a);
@@ -722,6 +772,84 @@ int enqueue_params(const hp_plan *p, Direction dir, const hp::Launch &L, const B
     }
     if (hip_failed(hipGetLastError())) return HP_EHIP;
     return HP_OK;
+}
+
+// One launch of the text-gradient kernel: `n` of the runs from `runs` on, whose
+// buffers are the `bufs` from `buf0` on; its tables always travel with the
+// arguments.
+struct RunGroup {
+    size_t first, n;
+    int32_t buf0, bufs;
+};
+size_t run_bytes(size_t n, int32_t bufs) {
+    const size_t ptrs = (offsetof(Args, b) + (size_t)bufs * 2 * sizeof(void *) + 63) / 64 * 64;
+    const size_t leaves = n > (size_t)hp::kTreeFanout ? (n + hp::kTreeFanout - 1) / hp::kTreeFanout * 64 : 0;
+    return ptrs + (n * sizeof(hp::Seg) + 63) / 64 * 64 + leaves;
+}
+// As many runs a launch as the arguments hold.
+std::vector<RunGroup> group_runs(const std::vector<hp::Seg> &runs, int32_t copies) {
+    std::vector<RunGroup> groups;
+    for (size_t i = 0; i < runs.size(); ++i) {
+        const int32_t buf0 = runs[i].dst_buf0;
+        if (!groups.empty()) {
+            RunGroup &g = groups.back();
+            const int32_t bufs = buf0 + copies - g.buf0;
+            if (run_bytes(g.n + 1, bufs) <= sizeof(Args)) {
+                ++g.n;
+                g.bufs = bufs;
+                continue;
+            }
+        }
+        groups.push_back(RunGroup{i, 1, buf0, copies});
+    }
+    return groups;
+}
+
+// 4 KiB tiles, four chunks a lane, 16 waves a compute unit: over tiles of 1 to 16 KiB,
+// 64 to 256 lanes and caps of 4 to 32, the best or within 3 % of it for dense,
+// row-strided and ragged rows (1.6 GB in [B,S,H] order: 254 us, 6.35 TB/s; the
+// forward's 4 KiB x 128 lanes x 20 waves: 287; loads that stay cached: 2-4 % slower).
+const hp::Launch kTextLaunch{2, 64, 16, 3};
+
+int enqueue_runs(const hp_plan *p, const std::vector<hp::Seg> &runs, const RunGroup &g, const void *const *grad,
+                 void *const *out, hipStream_t stream) {
+    const int variant = kTextLaunch.tile_variant;
+    Args a;
+    a.k = hp::kernel_params(*p, variant, nullptr, nullptr);
+    for (int32_t i = 0; i < g.bufs; ++i) {
+        a.b.p[i] = const_cast<void *>(grad[g.buf0 + i]);
+        a.b.p[g.bufs + i] = out[g.buf0 + i];
+    }
+    a.k.dst_base = (uint32_t)g.bufs;
+    const size_t seg_at = (offsetof(Args, b) + (size_t)g.bufs * 2 * sizeof(void *) + 63) / 64 * 64;
+    const size_t tree_at = seg_at + (g.n * sizeof(hp::Seg) + 63) / 64 * 64;
+    const size_t nodes = (g.n + hp::kTreeFanout - 1) / hp::kTreeFanout;
+    a.k.seg_at = (uint32_t)seg_at;
+    a.k.tree_at = (uint32_t)tree_at;
+    a.k.n_levels = nodes > 1 ? 2 : 1;
+    a.k.level_off[0] = 0;
+    hp::Seg *segs = (hp::Seg *)((char *)&a + seg_at);
+    uint32_t *keys = nodes > 1 ? (uint32_t *)((char *)&a + tree_at) : a.k.root;
+    uint64_t tiles = 0;
+    for (int j = 0; j < hp::kTreeFanout; ++j) a.k.root[j] = UINT32_MAX;
+    for (size_t i = 0; i < nodes * hp::kTreeFanout; ++i) {
+        keys[i] = i < g.n ? (uint32_t)tiles : UINT32_MAX;
+        if (nodes > 1 && i % hp::kTreeFanout == 0) a.k.root[i / hp::kTreeFanout] = keys[i];
+        if (i >= g.n) continue;
+        segs[i] = runs[g.first + i];
+        segs[i].src_buf = segs[i].dst_buf0 = (uint16_t)(segs[i].dst_buf0 - g.buf0);
+        tiles += hp::tiles_of(segs[i].n_rows, segs[i].pitch_rows, p->row_bytes, a.k.tile_bytes);
+        if (tiles > 0x7fffffffull) return HP_ELAYOUT;
+    }
+    LaunchCfg c;
+    c.grid = dim3((unsigned)tiles, (unsigned)p->dst_copies);
+    c.block = dim3((unsigned)kTextLaunch.block);
+    c.lds_bytes = lds_for_cap(kTextLaunch.block, kTextLaunch.waves_per_cu);
+    c.stream = stream;
+    if (p->dst_stride != 1 && a.k.parts_per_row == 0) HP_LAUNCH((hp_text_grads_kernel<kStrided>), c, a);
+    else if (a.k.row_bytes % hp::kLineBytes) HP_LAUNCH((hp_text_grads_kernel<kRagged>), c, a);
+    else HP_LAUNCH((hp_text_grads_kernel<kLines>), c, a);
+    return hip_failed(hipGetLastError()) ? HP_EHIP : HP_OK;
 }
 
 // Fills the pointer table and checks what the kernels assume: every buffer a
@@ -1281,6 +1409,46 @@ int hp_zero_image_rows(const hp_plan_t *p, void *const *dst_bufs, void *stream) 
     int rc = prepare(p, kZeroRows, nullptr, (const void *const *)dst_bufs, &bt);
     if (rc != HP_OK || p->segments.empty()) return rc;
     return enqueue(p, kZeroRows, p->fwd, bt, (hipStream_t)stream, EventPair{});
+}
+
+int hp_text_grads(const hp_plan_t *p, const void *const *dst_grad_bufs, void *const *text_grad_bufs, void *stream) {
+    if (!p || !dst_grad_bufs || !text_grad_bufs) return HP_EINVAL;
+    if (!p->segments.empty()) {                             // as for every call: a plan without rows is tied to no device
+        int dev = -1;
+        if (p->device < 0) return HP_ESTATE;
+        if (hip_failed(hipGetDevice(&dev))) return HP_EHIP;
+        if (dev != p->device) return HP_ESTATE;
+    }
+    uint64_t bits = 0;
+    for (int j = 0; j < p->n_dst_bufs; ++j) {
+        if (!dst_grad_bufs[j] || !text_grad_bufs[j]) return HP_EINVAL;
+        bits |= (uint64_t)(uintptr_t)dst_grad_bufs[j] | (uint64_t)(uintptr_t)text_grad_bufs[j];
+    }
+    if (bits & (uint64_t)(p->elem_bytes - 1)) return HP_EALIGN;
+    try {
+        std::call_once(p->runs_once, [&] { p->runs = hp::dst_runs(*p, false); });
+        std::vector<hp::Seg> whole;
+        const std::vector<hp::Seg> *runs = &p->runs;
+        std::vector<RunGroup> groups = group_runs(*runs, p->dst_copies);
+        // Many short runs take many launches.  Each costs about 3.5 us, the time of some 20 MB; what they save is
+        // reading and storing the image rows twice.
+        const uint64_t saved = 2 * (uint64_t)p->n_rows * (uint64_t)p->row_bytes * (uint64_t)p->dst_copies;
+        const bool copy = groups.size() > 2 + saved / 20000000;
+        if (copy) {
+            whole = hp::dst_runs(*p, true);
+            runs = &whole;
+            groups = group_runs(whole, p->dst_copies);
+        }
+        for (const RunGroup &g : groups) {
+            const int rc = enqueue_runs(p, *runs, g, dst_grad_bufs, text_grad_bufs, (hipStream_t)stream);
+            if (rc != HP_OK) return rc;
+        }
+        return copy ? hp_zero_image_rows(p, text_grad_bufs, stream) : HP_OK;
+    } catch (const std::bad_alloc &) {
+        return HP_ENOMEM;
+    } catch (...) {
+        return HP_EINVAL;
+    }
 }
 
 int hp_backward(const hp_plan_t *p, const void *const *dst_grad_bufs, void *const *src_grad_bufs,

@@ -15,6 +15,7 @@
 #include <limits>
 #include <new>
 #include <numeric>
+#include <tuple>
 
 namespace hp {
 
@@ -32,6 +33,56 @@ int tile_variant_of(int64_t tile_bytes) {
     for (int v = 0; v < kTileVariants; ++v)
         if (tile_bytes == (int64_t)tile_bytes_of(v)) return v;
     return -1;
+}
+
+// Dense runs are cut by bytes.  Row-strided ones are cut row by row: a row at
+// least one tile long is cut into ceil(row / tile) dense pieces, shorter rows are
+// grouped tile / row to a tile.  The kernels use the same formulas.
+uint64_t tiles_of(uint64_t n_rows, uint64_t pitch_rows, int64_t row_bytes, uint32_t tile) {
+    if (pitch_rows == 1) return (n_rows * row_bytes + tile - 1) / tile;
+    if ((uint64_t)row_bytes >= tile) return n_rows * (((uint64_t)row_bytes + tile - 1) / tile);
+    const uint64_t rows_per = tile / (uint64_t)row_bytes;
+    return (n_rows + rows_per - 1) / rows_per;
+}
+
+std::vector<Seg> dst_runs(const hp_plan &p, bool whole) {
+    const int64_t stride = p.dst_stride;
+    std::vector<size_t> order(whole ? 0 : p.segments.size());
+    std::iota(order.begin(), order.end(), (size_t)0);
+    auto place = [&](size_t i) {                           // buffer, column, position in the column
+        const hp_segment_t &s = p.segments[i];
+        return std::make_tuple((int64_t)s.dst_buf0, s.dst_row0 % stride, s.dst_row0 / stride);
+    };
+    std::sort(order.begin(), order.end(), [&](size_t a, size_t b) { return place(a) < place(b); });
+    std::vector<Seg> runs;
+    const int64_t column = p.dst_rows_per_buf / stride;
+    size_t at = 0;
+    for (int64_t buf = 0; buf < p.n_dst_bufs; buf += p.dst_copies)
+        for (int64_t col = 0; col < stride; ++col) {
+            int64_t done = 0;                              // rows of this column that have a run
+            auto add = [&](int64_t rows, uint32_t image) {
+                if (rows <= 0) return;
+                if (done > 0 && runs.back().src_copies == image && runs.back().n_rows + rows <= (int64_t)kMaxSegRows) {
+                    runs.back().n_rows += (uint32_t)rows;
+                    done += rows;
+                }
+                else while (rows > 0) {
+                    const int64_t n = std::min<int64_t>(rows, kMaxSegRows);
+                    const uint64_t off = (uint64_t)(done * stride + col) * (uint64_t)p.row_bytes;
+                    runs.push_back(Seg{off, off, (uint32_t)n, (uint32_t)stride, (uint16_t)buf, (uint16_t)buf, image});
+                    done += n;
+                    rows -= n;
+                }
+            };
+            for (; at < order.size(); ++at) {
+                const hp_segment_t &s = p.segments[order[at]];
+                if (s.dst_buf0 != buf || s.dst_row0 % stride != col) break;
+                add(s.dst_row0 / stride - done, 0);
+                add(s.n_rows, 1);
+            }
+            add(column - done, 0);
+        }
+    return runs;
 }
 
 namespace {
@@ -137,17 +188,6 @@ int validate(const hp_layout_t *src, const hp_layout_t *dst, const hp_token_map_
     return HP_OK;
 }
 
-// Tiles of `tile` bytes needed by a segment: dense segments are cut by bytes.
-// Row-strided ones are cut row by row: a row at least one tile long is cut into
-// ceil(row / tile) dense pieces, shorter rows are grouped tile / row to a tile.
-// The kernels use the same formulas.
-uint64_t tiles_of(const hp_segment_t &s, int64_t row_bytes, uint32_t tile) {
-    if (s.dst_row_stride == 1) return ((uint64_t)s.n_rows * row_bytes + tile - 1) / tile;
-    if ((uint64_t)row_bytes >= tile) return (uint64_t)s.n_rows * (((uint64_t)row_bytes + tile - 1) / tile);
-    const uint64_t rows_per = tile / (uint64_t)row_bytes;
-    return ((uint64_t)s.n_rows + rows_per - 1) / rows_per;
-}
-
 int make_tables(hp_plan *p) {
     const size_t n = p->segments.size();
     p->dsegs.resize(n);
@@ -171,7 +211,7 @@ int make_tables(hp_plan *p) {
         uint32_t *row = p->first_tile.data() + (size_t)v * (n + 1);
         for (size_t i = 0; i < n; ++i) {
             row[i] = (uint32_t)acc;
-            acc += tiles_of(p->segments[i], p->row_bytes, tile_bytes_of(v));
+            acc += tiles_of((uint64_t)p->segments[i].n_rows, (uint64_t)p->segments[i].dst_row_stride, p->row_bytes, tile_bytes_of(v));
             if (acc > 0x7fffffffull) return HP_ELAYOUT;        // grid size limit
         }
         row[n] = (uint32_t)acc;
@@ -301,7 +341,7 @@ int build_host_plan(const hp_layout_t *srcs, int32_t n_edges, const hp_layout_t 
     p->dst_rows_per_buf = b_loc * walk.piece;
     const bool sbh = dst->row_order == HP_ROW_SBH;
     const int64_t stride = (sbh && b_loc > 1) ? b_loc : 1;
-    p->strided = stride != 1;
+    p->dst_stride = stride;
 
     p->n_rows = 0;
     p->bwd_bytes = p->bwd_accum_bytes = 0;

@@ -79,7 +79,7 @@ struct hp_plan {
     int32_t src_copies = 1, dst_copies = 1;   // src_copies: of the first edge (edges may differ, see seg_copies)
     int64_t bwd_bytes = 0, bwd_accum_bytes = 0;   // algorithmic bytes of the two backward flavours
     int64_t dst_rows_per_buf = 0;
-    bool strided = false;                 // every segment is row-strided on the destination side (else none is)
+    int64_t dst_stride = 1;               // destination row stride of every segment ([S,B,H]: samples per rank)
     std::vector<int64_t> src_rows;        // per source buffer
     std::vector<uint8_t> src_leader;      // per source buffer: 1 = copy tp 0 of its rank (the one forward reads)
     std::vector<int32_t> seg_copies;      // per segment: TP copies of its source rank
@@ -106,6 +106,11 @@ struct hp_plan {
         used_streams.push_back(stream);
     }
 
+    // Every row of the destination buffers as runs of text and of image rows, for
+    // hp_text_grads: made by its first call (dst_runs).
+    mutable std::once_flag runs_once;
+    mutable std::vector<hp::Seg> runs;
+
     uint32_t n_tiles(int variant) const {
         const size_t n = segments.size();
         return n ? first_tile[(size_t)variant * (n + 1) + n] : 0u;
@@ -122,4 +127,14 @@ namespace hp {
 // edges.  Returns HP_OK or a negative error; *plan is only meaningful on HP_OK.
 int build_host_plan(const hp_layout_t *srcs, int32_t n_edges, const hp_layout_t *dst,
                     const hp_token_map_t *maps, int32_t n_maps, hp_plan *plan);
+
+// Tiles of `tile` bytes that a run of n_rows rows is cut into.
+uint64_t tiles_of(uint64_t n_rows, uint64_t pitch_rows, int64_t row_bytes, uint32_t tile);
+
+// The rows of every first copy of the destination buffers as runs that partition
+// them, by buffer and position: src_copies = 0 for text rows and 1 for image rows,
+// both offsets those of the run in its buffer, both buffer indices its first copy's
+// (among the destination buffers).  whole: one run of text a buffer (and, row-
+// strided plans, a column of it), whatever lies there.
+std::vector<Seg> dst_runs(const hp_plan &p, bool whole);
 }  // namespace hp

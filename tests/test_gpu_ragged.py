@@ -79,9 +79,44 @@ def test_ragged_rows_and_buffers(hidden, tp, sbh, off, f32):
         sb, _ = prob.forward_map(j)
         z[sb >= 0] = 0
     hp.hp_zero_image_rows(plan, T(d))
+    text = [Padded(values(drows), next(at) % 64) for _ in range(prob.n_dst)]
+    hp.hp_text_grads(plan, T(g), T(text))
     torch.cuda.synchronize()
     for j, (b, z) in enumerate(zip(d, prob_zero)):
         b.check(z, ("zero", j))
+    for j, (b, t) in enumerate(zip(g, text)):
+        want = cut(b)
+        want[prob.forward_map(j)[0] >= 0] = 0
+        t.check(want, ("text", j))
+        b.check(cut(b), ("gradient", j))
+    plan.close()
+
+
+# hp_text_grads: one launch of runs, several, or (many short runs: more launches than the bytes are worth) a copy and
+# a pass of zeros; no image at all; row-strided columns
+@pytest.mark.parametrize("n_img,hidden,f32,sbh", [(0, 96, False, False), (0, 96, False, True), (3, 4096, False, True),
+                                                  (257, 72, False, False), (257, 16384, True, False),
+                                                  (300, 200, False, True)])
+def test_text_gradients(n_img, hidden, f32, sbh):
+    rng = np.random.default_rng(n_img)
+    dst = wl.Grid(tp=2, row_order=wl.ROW_SBH if sbh else wl.ROW_BSH)
+    samp = np.sort(rng.integers(0, 2, n_img)).astype(np.int32)
+    start = np.concatenate([4 * np.arange(int((samp == b).sum())) for b in range(2)]).astype(np.int32)
+    seq = 4 * max(1, n_img) + 2
+    tm = wl.TokenMap(2, seq, hidden, samp, start, rng.integers(1, 4, n_img).astype(np.int32), None, int(f32))
+    plan = hp.hp_plan_create(wl.Grid(), dst, tm)
+    dt = torch.float32 if f32 else torch.bfloat16
+    g = [torch.randn(2 * seq, hidden, device="cuda").to(dt) for _ in range(2)]
+    out = [torch.full_like(t, 7.0) for t in g]
+    keep = [t.clone() for t in g]
+    for _ in range(2):                                      # the first call and one that finds the runs
+        hp.hp_text_grads(plan, g, out)
+    image = torch.zeros(2, seq, dtype=torch.bool)
+    for b, s, n in zip(tm.img_sample, tm.img_start, tm.img_len):
+        image[int(b), int(s):int(s) + int(n)] = True
+    image = (image.t() if sbh else image).reshape(-1).cuda()
+    for t, o, k in zip(g, out, keep):
+        assert torch.equal(o, torch.where(image[:, None], torch.zeros_like(t), t)) and torch.equal(t, k)
     plan.close()
 
 
@@ -117,3 +152,28 @@ def test_tables_in_the_arguments_and_in_device_memory(n_seg):
     assert np.array_equal(back(Y[0]), y[0])
     with pytest.raises(hp.HpError):
         hp.hp_forward(host, X, D)                           # a host-only plan is refused, however small
+
+
+@pytest.mark.parametrize("src_grad,text_grad,graph", [(True, False, False), (False, True, False), (True, True, True)])
+def test_autograd_gives_only_the_gradients_that_are_wanted(src_grad, text_grad, graph):
+    """Frozen text embeddings, a frozen encoder, and create_graph: the same values as with everything trained."""
+    rng = np.random.default_rng(9)
+    dst = wl.Grid(tp=2, cp=2)
+    tm = wl.token_map_from_lens(rng, 2, 24, 40, [[5, 7], [9]])
+    plan = hp.hp_plan_create(wl.Grid(dp=2), dst, tm)
+    drows = plan.info.dst_rows_per_buf
+    new = lambda r, s: wl.random_bf16((r, 40), s, "cuda")                             # noqa: E731
+
+    def grads(src_on, text_on, create):
+        x = [new(r, i).requires_grad_(src_on) for i, r in enumerate(plan.src_rows())]
+        t = [new(drows, 10 + j).requires_grad_(text_on) for j in range(4)]
+        w = [new(drows, 20 + j) for j in range(4)]
+        outs = hp.boundary_transform(plan, x, [a.clone() for a in t])
+        g = torch.autograd.grad(outs, x * src_on + t * text_on, w, create_graph=create)
+        return list(g[:len(x)]) if src_on else [], list(g[len(x):]) if src_on else list(g)
+
+    want_x, want_t = grads(True, True, False)
+    got_x, got_t = grads(src_grad, text_grad, graph)
+    assert len(got_x) == len(want_x) * src_grad and len(got_t) == len(want_t) * text_grad
+    assert all(torch.equal(a, b) for a, b in zip(got_x, want_x)) and all(torch.equal(a, b) for a, b in zip(got_t, want_t))
+    plan.close()

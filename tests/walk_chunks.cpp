@@ -84,6 +84,32 @@ static bool walk_plan(const hp_plan &p, const uint32_t *tree, uint64_t dst_base)
     return true;
 }
 
+// The runs of hp_text_grads: a partition of every buffer's rows in which exactly
+// the segments' rows are image rows.
+static bool check_runs(const hp_plan &p) {
+    v = -1; tile = 0;
+    for (int whole = 0; whole < 2; ++whole) {
+        std::vector<std::vector<int>> rows((size_t)p.n_dst_bufs, std::vector<int>((size_t)p.dst_rows_per_buf, -1));
+        for (const hp::Seg &r : hp::dst_runs(p, whole != 0)) {
+            CHECK(r.n_rows > 0 && r.src_off == r.dst_off && r.src_buf == r.dst_buf0 && r.pitch_rows == p.dst_stride);
+            for (uint32_t i = 0; i < r.n_rows; ++i) {
+                int &cell = rows[r.dst_buf0][r.dst_off / (uint64_t)p.row_bytes + (uint64_t)i * r.pitch_rows];
+                CHECK(cell == -1);
+                cell = (int)r.src_copies;
+            }
+        }
+        for (const hp_segment_t &s : p.segments)
+            for (int64_t i = 0; i < s.n_rows; ++i) {
+                int &cell = rows[s.dst_buf0][s.dst_row0 + i * s.dst_row_stride];
+                CHECK(cell == (whole ? 0 : 1));
+                cell = 0;
+            }
+        for (int b = 0; b < p.n_dst_bufs; ++b)
+            for (int x : rows[b]) CHECK(x == (b % p.dst_copies ? -1 : 0));
+    }
+    return true;
+}
+
 int main(int argc, char **argv) {
     std::setvbuf(stdout, nullptr, _IONBF, 0);
     std::mt19937_64 rng(argc > 1 ? std::atoll(argv[1]) : 1);
@@ -107,6 +133,7 @@ int main(int argc, char **argv) {
         hp_plan p;
         if (hp::build_host_plan(&src, 1, &dst, &m, 1, &p) != HP_OK || p.segments.empty()) continue;
         ++done;
+        if (!check_runs(p)) return 1;
         uint32_t *tree = (uint32_t *)std::aligned_alloc(64, (p.tree.size() * 4 + 63) / 64 * 64 + 64);
         std::copy(p.tree.begin(), p.tree.end(), tree);
         const uint64_t e = (uint64_t)p.elem_bytes, bases[] = {0, e, 16, 126 / e * e};
