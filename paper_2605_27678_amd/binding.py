@@ -1,4 +1,6 @@
-"""ctypes binding of libhp.so - argument marshalling only.
+"""ctypes binding of libhp.so - argument marshalling only.  The calls of a step
+(forward, backward, ...) go through hp_marshal.so, a small CPython extension
+that checks the tensors and makes the call in one go.
 
 Function names mirror the C ABI in include/hp.h (hp_plan_create, hp_forward,
 hp_backward, ...).  Every step of the transform runs in the library's HIP
@@ -9,6 +11,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import sys
 from typing import List, Optional, Sequence
 
 import numpy as np
@@ -74,6 +77,31 @@ EXPORTS = ["hp_plan_create", "hp_plan_create_host", "hp_plan_create_batched", "h
            "hp_strerror", "hp_last_hip_error", "hp_version"]
 
 _handle = None
+_marshal = None                 # hp_marshal's call(), once loaded
+_ADDR = {}                      # addresses of the calls that go through it
+SRC, DST, ACCUM = 0, 1, 2       # what a list of buffers is: source, destination, binary32 accumulators
+
+
+class _Desc(C.Structure):
+    """What hp_marshal needs to know of a plan (the same layout there)."""
+    _fields_ = [("n_src", C.c_int64), ("n_dst", C.c_int64), ("dst_rows", C.c_int64), ("hidden", C.c_int64),
+                ("elem_bytes", C.c_int64), ("src_rows", C.POINTER(C.c_int64))]
+
+
+def _load_marshal():
+    """Loads hp_marshal.so once.  Only called when torch is there (it needs its libraries)."""
+    global _marshal
+    from importlib.machinery import ExtensionFileLoader
+    from importlib.util import module_from_spec, spec_from_file_location
+    path = os.path.join(_PKG, "hp_marshal.so")
+    if not os.path.exists(path):
+        raise RuntimeError(f"{path} is missing: build it first (python -m paper_2605_27678_amd.build)")
+    loader = ExtensionFileLoader("hp_marshal", path)
+    module = module_from_spec(spec_from_file_location("hp_marshal", path, loader=loader))
+    loader.exec_module(module)
+    for name in ("hp_forward", "hp_forward_static", "hp_backward", "hp_backward_accumulate", "hp_text_grads"):
+        _ADDR[name] = C.cast(getattr(_lib(), name), C.c_void_p).value
+    _marshal = module.call
 
 
 def _lib():
@@ -262,6 +290,11 @@ class Plan:
         self.info = hp_plan_info_t()
         _check(L.hp_plan_query(self._h, C.byref(self.info)), "hp_plan_query")
         self.elem_bytes = self.info.elem_bytes
+        n = self.info.n_src_bufs
+        self._rows = (C.c_int64 * n)()
+        _check(L.hp_plan_src_rows(self._h, self._rows, n), "hp_plan_src_rows")
+        self._desc = _Desc(n, self.info.n_dst_bufs, self.info.dst_rows_per_buf, self.hidden, self.elem_bytes, self._rows)
+        self._desc_at = C.addressof(self._desc)
 
     def get_launch(self, direction: int) -> dict:
         out = hp_launch_t()
@@ -287,10 +320,7 @@ class Plan:
 
     # -- introspection ------------------------------------------------------
     def src_rows(self) -> List[int]:
-        n = self.info.n_src_bufs
-        buf = (C.c_int64 * n)()
-        _check(_lib().hp_plan_src_rows(self._h, buf, n), "hp_plan_src_rows")
-        return list(buf)
+        return list(self._rows)
 
     def segments(self) -> List[hp_segment_t]:
         n = self.info.n_segments
@@ -299,6 +329,19 @@ class Plan:
         return [arr[i] for i in range(n)]
 
     # -- marshalling --------------------------------------------------------
+    def _call(self, name: str, kind_a: int, a, kind_b: int, b, stream) -> bool:
+        """The call through hp_marshal.  False if the arguments need a closer look than it takes."""
+        if _marshal is None:
+            if "torch" not in sys.modules:
+                return False
+            _load_marshal()
+        rc = _marshal(_ADDR[name], self._h.value or 0, self._desc_at, kind_a, a, kind_b, b, stream)
+        if rc is None:
+            return False
+        if rc < 0:
+            raise HpError(rc, name)
+        return True
+
     def _pointers(self, tensors: Sequence, rows: Sequence[int], what: str, esize: Optional[int] = None):
         esize = esize or self.elem_bytes
         P = (C.c_void_p * len(tensors))()
@@ -326,12 +369,16 @@ class Plan:
         _check(_lib().hp_plan_tune_accumulate(self._h, pd, ps, _stream_handle(stream)), "hp_plan_tune_accumulate")
 
     def forward(self, src_bufs: Sequence, dst_bufs: Sequence, stream=None) -> None:
+        if self._call("hp_forward", SRC, src_bufs, DST, dst_bufs, stream):
+            return
         ps, pd = self._src_dst(src_bufs, dst_bufs)
         _check(_lib().hp_forward(self._h, ps, pd, _stream_handle(stream)), "hp_forward")
 
     def forward_static(self, src_bufs: Sequence, dst_bufs: Sequence, stream=None) -> None:
         """hp_forward through the library's fixed table array: works on host-only
         plans and allocates nothing."""
+        if self._call("hp_forward_static", SRC, src_bufs, DST, dst_bufs, stream):
+            return
         ps, pd = self._src_dst(src_bufs, dst_bufs)
         _check(_lib().hp_forward_static(self._h, ps, pd, _stream_handle(stream)), "hp_forward_static")
 
@@ -344,6 +391,8 @@ class Plan:
 
     def text_grads(self, dst_grad_bufs: Sequence, text_grad_bufs: Sequence, stream=None) -> None:
         """text_grad_bufs = dst_grad_bufs with the image-token rows zero."""
+        if self._call("hp_text_grads", DST, dst_grad_bufs, DST, text_grad_bufs, stream):
+            return
         if len(dst_grad_bufs) != self.info.n_dst_bufs or len(text_grad_bufs) != self.info.n_dst_bufs:
             raise ValueError("wrong number of buffers for this plan")
         rows = [self.info.dst_rows_per_buf] * len(dst_grad_bufs)
@@ -351,11 +400,15 @@ class Plan:
         _check(_lib().hp_text_grads(self._h, pg, pt, _stream_handle(stream)), "hp_text_grads")
 
     def backward(self, dst_grad_bufs: Sequence, src_grad_bufs: Sequence, stream=None) -> None:
+        if self._call("hp_backward", DST, dst_grad_bufs, SRC, src_grad_bufs, stream):
+            return
         ps, pd = self._src_dst(src_grad_bufs, dst_grad_bufs)
         _check(_lib().hp_backward(self._h, pd, ps, _stream_handle(stream)), "hp_backward")
 
     def backward_accumulate(self, dst_grad_bufs: Sequence, src_accum_bufs: Sequence, stream=None) -> None:
         """src_accum_bufs: float32 accumulators [rows_i, hidden], added to in place."""
+        if self._call("hp_backward_accumulate", DST, dst_grad_bufs, ACCUM, src_accum_bufs, stream):
+            return
         ps, pd = self._src_dst(src_accum_bufs, dst_grad_bufs, src_esize=4)
         _check(_lib().hp_backward_accumulate(self._h, pd, ps, _stream_handle(stream)),
                "hp_backward_accumulate")

@@ -1,5 +1,6 @@
 """Builds libhp.so (the C-ABI library: host plan builder + gfx950 kernels) with
-hipcc, in-tree, next to the sources' package."""
+hipcc and hp_marshal.so (the binding's tensor marshalling) with g++, in-tree,
+next to the sources' package."""
 from __future__ import annotations
 
 import os
@@ -11,6 +12,7 @@ _ROOT = os.path.dirname(_PKG)
 CSRC = os.path.join(_PKG, "csrc")
 LIB_PATH = os.path.join(_PKG, "libhp.so")
 SOURCES = ["hp_api.hip", "hp_plan.cpp"]
+MARSHAL_PATH = os.path.join(_PKG, "hp_marshal.so")
 
 HIPCC_FLAGS = [
     "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -30,8 +32,29 @@ def hipcc_path() -> str:
     raise RuntimeError("hipcc not found: the HIP library cannot be built on this machine")
 
 
+def build_marshal(verbose: bool = False) -> str:
+    """Compile the CPython extension that takes torch tensors to the C ABI."""
+    import sysconfig
+    import torch
+    t = os.path.dirname(torch.__file__)
+    cmd = ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-Wextra", "-Wno-unused-parameter",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I", os.path.join(_ROOT, "include"), "-isystem", sysconfig.get_paths()["include"],
+           "-isystem", os.path.join(t, "include"), "-isystem", os.path.join(t, "include", "torch", "csrc", "api", "include"),
+           "-o", MARSHAL_PATH, os.path.join(CSRC, "hp_marshal.cpp"),
+           "-L" + os.path.join(t, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("g++ failed:\n" + res.stdout + res.stderr)
+    return MARSHAL_PATH
+
+
 def build_library(verbose: bool = False, extra_flags=()) -> str:
-    """Compile every source for gfx950 into paper_2605_27678_amd/libhp.so."""
+    """Compile every source for gfx950 into paper_2605_27678_amd/libhp.so, and
+    the marshalling extension beside it."""
+    build_marshal(verbose)
     cmd = [hipcc_path(), *HIPCC_FLAGS, *extra_flags,
            "-I", os.path.join(_ROOT, "include"), "-I", CSRC,
            "-o", LIB_PATH, *[os.path.join(CSRC, s) for s in SOURCES]]
