@@ -241,13 +241,64 @@ int make_tables(hp_plan *p) {
     return HP_OK;
 }
 
+// The shapes of launches whose size calls for others than the replica counts
+// alone.  Measured over tiles of 1 to 8 KiB, 64 to 256 lanes and caps of 4 to 32 at
+// 8 MB to 2 GB of traffic for 1 to 16 copies, in both element types, ragged and
+// row-strided rows among them; a line stands where a shape is at least 2 % faster
+// over the whole range that it is given.  Launches of up to about 400 MB find part
+// of their buffers in the 256 MB memory-side cache and want more waves; replica
+// counts without a kernel of their own (all but 1, 2, 4 and 8) wait for their
+// groups of four loads and want more of them in flight.
+void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
+    constexpr int K1 = 0, K4 = 2, K8 = 3;                    // tiles of 1, 4 and 8 KiB
+    const int c = p->dst_copies, s = p->src_copies;
+    const bool generic = c != 1 && c != 2 && c != 4 && c != 8;
+    constexpr double MB = 1e6;
+    auto set = [](Launch &L, int tile, int block, int cap) { L = Launch{tile, block, cap, L.nontemporal}; };
+
+    const double fwd = (1.0 + c) * (double)p->n_rows * (double)p->row_bytes;
+    if (c == 1 && fwd >= 200 * MB) set(f, K4, 128, 24);                         // 820 MB: 134 -> 129 us
+    else if (c == 2 && fwd >= 16 * MB && fwd < 300 * MB) set(f, K8, 256, 16);   // 283 MB: 46.2 -> 44.1
+    else if (c == 3 && fwd >= 450 * MB) set(f, K1, 64, 28);                     // 2 GB: 326 -> 319
+    else if (c == 4 && fwd >= 100 * MB && fwd < 450 * MB) set(f, K1, 64, 12);   // 150 MB: 22.4 -> 22.2, 280 MB: 1.03
+    else if (c >= 5 && c <= 7 && fwd >= 16 * MB && fwd < 450 * MB) set(f, K1, 64, 10);   // 40 and 150 MB: 1.07-1.08
+    else if (c == 8 && fwd >= 30 * MB && fwd < 450 * MB) set(f, K1, 64, 6);     // 40 MB: 7.3 -> 6.9, 280 MB: 1.07
+    else if (c > 8 && fwd >= 100 * MB && fwd < 450 * MB) set(f, K1, 64, 5);     // 280 MB, 16 copies: 1.15
+
+    const double bwd = (double)p->bwd_bytes;
+    if (bwd >= 16 * MB) {
+        if (c == 1 && s == 1) bwd < 200 * MB ? set(b, K1, 64, 28) : set(b, K4, 128, 24);   // 150 MB: 25.4 -> 24.2, 820 MB: 128 -> 125
+        else if (c == 2 && s == 1 && bwd < 300 * MB) set(b, K8, 256, 24);       // 150 MB: 25.9 -> 25.1
+        else if (c == 2 && s > 1) set(b, K1, 64, 20);                           // 2.7 GB: 434 -> 401
+        else if (c == 4 && s == 1 && bwd < 450 * MB) set(b, K1, 64, 24);        // 150 MB: 27.4 -> 25.5, 280 MB: 1.04
+        else if (generic && c < 8) set(b, K1, 64, c <= 5 && s == 1 ? 28 : 24);  // 3 copies, 2 GB: 376 -> 301
+        else if (c > 8 && bwd >= 100 * MB && bwd < 250 * MB) set(b, K4, 128, 24);   // 16 copies, 150 MB: 30.0 -> 26.4
+    }
+
+    const double acc = (double)p->bwd_accum_bytes;
+    if (acc < 1 * MB) return;                                                   // a few tiles: nothing to choose
+    if (s > 1) {
+        if (acc < 200 * MB || generic) set(a, K1, 64, 16);                      // two source copies, 83 MB: 1.07-1.15
+    } else if (p->elem_bytes == 4) {
+        set(a, K1, 64, 24);                                                     // binary32: 1.06-1.26 for 2 and 4 copies
+    } else if (acc < 400 * MB) {
+        if (c <= 5) set(a, K4, 256, 24);                                        // 3 copies, 260 MB: 49.8 -> 41.2
+        else if (c < 8) set(a, K1, 64, 24);
+        else if (c == 8) set(a, K4, 256, 16);                                   // 200 MB: 36.1 -> 34.9
+        else set(a, K1, 64, 20);                                                // 16 copies, 180 MB: 43.0 -> 30.5
+    } else if (c == 1 || generic) {
+        set(a, K1, 64, c <= 8 ? 20 : 16);                                       // 3 copies, 3.5 GB: 605 -> 523; 16: 475 -> 368
+    }
+}
+
 // Launch shapes for a new plan.  Both kernels are fastest when roughly 100 KB
 // of traffic per compute unit is in flight, so the resident-wave cap that suits
 // a plan falls as the number of buffers a row's traffic spreads over rises:
 // 1 + dst_copies for forward, dst_copies + src_copies for backward.  The table
 // is what the measured search (hp_plan_tune) picks most often per replica count
-// on the five workloads and their sequence-sharded variants; an option that is
-// not HP_AUTO overrides its field.
+// on the five workloads and their sequence-sharded variants; by_size puts others
+// in their place where the launch's size calls for it; an option that is not
+// HP_AUTO overrides its field.
 void default_launches(hp_plan *p) {
     Options o;
     {
@@ -262,6 +313,7 @@ void default_launches(hp_plan *p) {
     // caps as the measured search finds them for 6, 8 and 16 streams (configs 4, 3 and 5)
     const int acc_streams = c + s * 8 / p->elem_bytes;
     Launch a{1, 64, acc_streams <= 4 ? 16 : acc_streams <= 6 ? 13 : acc_streams <= 8 ? 11 : acc_streams <= 12 ? 9 : 7, 3};
+    by_size(p, f, b, a);
     auto apply = [](Launch &L, int64_t tile, int64_t block, int64_t waves, int64_t nt) {
         if (tile > 0) L.tile_variant = tile_variant_of(tile);
         if (block > 0) L.block = (int32_t)block;
