@@ -896,12 +896,25 @@ bool launch_ok(const hp::Launch &L) {
 // size classes; a destroyed plan's block waits here for the next plan on the
 // same device.  A block may still be read by kernels that were enqueued before
 // its plan was destroyed: it carries one event per stream the plan was used on,
-// recorded at destroy time, and is not overwritten before they have completed.
+// recorded at destroy time, and is not overwritten before they have completed.  A
+// plan made while the last one's kernels still run takes another block - up to
+// kMaxPending of a kind, after that it waits for the oldest - so that a step that
+// makes its plan does not wait for the step before.
 struct TablePool {
     struct Block { void *p; size_t bytes; int device; std::vector<hipEvent_t> pending; };
     std::mutex mu;
     std::vector<Block> free_blocks;
     static constexpr size_t kMaxCached = 64;
+    static constexpr size_t kMaxPending = 4;
+
+    static bool done(const Block &b) {
+        for (hipEvent_t e : b.pending)
+            if (hipEventQuery(e) != hipSuccess) {
+                (void)hipGetLastError();                    // not ready is no error
+                return false;
+            }
+        return true;
+    }
 
     static void wait_and_drop(std::vector<hipEvent_t> &events) {
         for (hipEvent_t e : events) {
@@ -916,11 +929,18 @@ struct TablePool {
         Block b{nullptr, 0, -1, {}};
         {
             std::lock_guard<std::mutex> lk(mu);
-            size_t best = free_blocks.size();               // smallest that fits; the oldest among equals
-            for (size_t i = 0; i < free_blocks.size(); ++i)
-                if (free_blocks[i].device == device && free_blocks[i].bytes >= need &&
-                    (best == free_blocks.size() || free_blocks[i].bytes < free_blocks[best].bytes))
+            // the smallest that fits and whose work is done, the oldest among equals; else the oldest that fits,
+            // if there are enough of them
+            size_t best = free_blocks.size(), waiting = best, n_waiting = 0;
+            for (size_t i = 0; i < free_blocks.size(); ++i) {
+                if (free_blocks[i].device != device || free_blocks[i].bytes < need) continue;
+                if (!done(free_blocks[i])) {
+                    if (n_waiting++ == 0) waiting = i;
+                } else if (best == free_blocks.size() || free_blocks[i].bytes < free_blocks[best].bytes) {
                     best = i;
+                }
+            }
+            if (best == free_blocks.size() && n_waiting >= kMaxPending) best = waiting;
             if (best != free_blocks.size()) {
                 b = std::move(free_blocks[best]);
                 free_blocks.erase(free_blocks.begin() + best);
@@ -983,6 +1003,22 @@ struct TablePool {
         }
     }
 } g_pool;
+
+// A stream of the library's own on each device, for the uploads of plan tables: a
+// copy on the default stream would wait for whatever runs there.  Created on first
+// use, ordered against no other stream, held until the process ends.
+hipStream_t upload_stream(int device, int *rc) {
+    constexpr int kMaxDevices = 64;
+    static std::mutex mu;
+    static hipStream_t streams[kMaxDevices] = {nullptr};
+    if (device < 0 || device >= kMaxDevices) { *rc = HP_ESTATE; return nullptr; }
+    std::lock_guard<std::mutex> lk(mu);
+    if (!streams[device] && hip_failed(hipStreamCreateWithFlags(&streams[device], hipStreamNonBlocking))) {
+        streams[device] = nullptr;
+        *rc = HP_EHIP;
+    }
+    return streams[device];
+}
 
 // Launch shapes found by hp_plan_tune are remembered per problem class (dtype,
 // row size, replica counts, device) and seed later plans of the same class, so a
@@ -1053,7 +1089,10 @@ int create_common(const hp_layout_t *srcs, int32_t n_edges, const hp_layout_t *d
                 p->d_segs = (hp::Seg *)g_pool.get(staging.size(), p->device, &p->d_bytes, &rc);
                 if (rc == HP_OK) {
                     p->d_tree = (uint32_t *)((char *)p->d_segs + seg_bytes);
-                    if (hip_failed(hipMemcpy(p->d_segs, staging.data(), staging.size(), hipMemcpyHostToDevice)))
+                    hipStream_t up = upload_stream(p->device, &rc);
+                    if (rc == HP_OK &&
+                        (hip_failed(hipMemcpyAsync(p->d_segs, staging.data(), staging.size(), hipMemcpyHostToDevice, up)) ||
+                         hip_failed(hipStreamSynchronize(up))))
                         rc = HP_EHIP;
                 }
             } catch (const std::bad_alloc &) {

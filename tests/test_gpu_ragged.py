@@ -177,3 +177,34 @@ def test_autograd_gives_only_the_gradients_that_are_wanted(src_grad, text_grad, 
     assert len(got_x) == len(want_x) * src_grad and len(got_t) == len(want_t) * text_grad
     assert all(torch.equal(a, b) for a, b in zip(got_x, want_x)) and all(torch.equal(a, b) for a, b in zip(got_t, want_t))
     plan.close()
+
+
+def test_plans_made_while_the_last_ones_still_run():
+    """Plans with tables in device memory, each used on one of two busy streams and dropped at once: every launch reads
+    its own plan's tables."""
+    dst, hidden, n_seg = wl.Grid(tp=2), 72, 300
+    seq = 4 * n_seg
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    busy = torch.randn(4096, 4096, device="cuda")
+    x = wl.random_bf16((2 * seq, hidden), 3, "cuda")
+    outs, maps = [], []
+    torch.cuda.synchronize()
+    for i in range(24):
+        rng = np.random.default_rng(i)
+        start = np.sort(rng.choice(np.arange(0, seq, 4), n_seg - i, replace=False)).astype(np.int32)
+        tm = wl.TokenMap(1, seq, hidden, np.zeros(n_seg - i, np.int32), start, rng.integers(1, 4, n_seg - i).astype(np.int32))
+        st = streams[i % 2]
+        with torch.cuda.stream(st):
+            busy @ busy
+            out = [torch.zeros(seq, hidden, dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+            plan = hp.hp_plan_create(wl.Grid(), dst, tm)
+            hp.hp_forward(plan, [x], out, st)
+            plan.close()
+        outs.append(out)
+        maps.append(tm)
+    torch.cuda.synchronize()
+    for out, tm in zip(outs, maps):
+        pos = np.concatenate([np.arange(s, s + n) for s, n in zip(tm.img_start, tm.img_len)])
+        want = torch.zeros(seq, hidden, dtype=torch.bfloat16, device="cuda")
+        want[torch.from_numpy(pos).cuda()] = x[:len(pos)]
+        assert torch.equal(out[0], want) and torch.equal(out[1], want)
