@@ -170,8 +170,9 @@ typedef struct hp_segment {
  * builds the segment table (runs of rows contiguous on both sides) and the
  * search trees that map a workgroup to its segment on the host, and ties the
  * plan to the CURRENT HIP device.  Tables that leave room for the buffer pointers
- * in a launch's 4 KiB of arguments (up to about a hundred segments) travel there
- * with every launch; larger ones are uploaded (one synchronous copy into a device
+ * in a launch's 4 KiB of arguments (up to about a hundred segments, launches of
+ * less than 1 GiB) travel there with every launch; others are uploaded (one
+ * synchronous copy, which waits for no stream of the caller's, into a device
  * block that is recycled from earlier plans when one is free).
  * src, dst, map: host structs, read only during the call.
  * *out receives an owned plan; release it with hp_plan_destroy. */
@@ -222,8 +223,8 @@ int hp_plan_create_joined(const hp_layout_t *srcs, int32_t n_edges, const hp_lay
  * hipMalloc / hipFree pair each time.  NULL is allowed.  The call may follow the
  * last hp_forward / hp_backward that uses the plan at once, without any
  * synchronisation: the block is not overwritten before the streams those calls
- * were enqueued on have passed them (an event per stream is recorded here and
- * waited for when the block is next handed out).  Call it with the plan's
+ * were enqueued on have passed them (an event per stream is recorded here; the
+ * block is next handed out when they have completed).  Call it with the plan's
  * device current.  Every stream the plan was used on must still exist when this
  * is called (destroy the plan before the stream, not after: the handle is
  * queried and an event is recorded on it here).  A plan whose calls were

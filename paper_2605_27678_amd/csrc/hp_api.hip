@@ -47,8 +47,8 @@ struct BufTable {
 };
 
 // The arguments of a transform kernel.  The tables of a plan that leaves the
-// room travel behind its buffer pointers (inline_tables), so that a plan of up to
-// about a hundred segments needs no device memory, no upload and, in the
+// room travel behind its buffer pointers (inline_tables), so that an ordinary plan
+// of up to about a hundred segments needs no device memory, no upload and, in the
 // kernel, no load from memory that the launch itself has not just written.
 struct Args {
     KParams k;
@@ -692,16 +692,22 @@ void launch_other(const hp_plan *p, Direction dir, const LaunchCfg &c, const Arg
     else launch_backward<TILES, true, true>(p->dtype, dir == kBackwardAcc, p->dst_copies, c, a);
 }
 
-// Whether a launch's tables fit behind the buffer pointers: the descriptors and
-// the level below the root (there are no more for so few segments).  The same
-// for every tile size, because every tree has as many keys.
+// Whether a plan's tables travel with its launches: they fit behind the buffer
+// pointers - the descriptors and the level below the root, there are no more for
+// so few segments; the same for every tile size, because every tree has as many
+// keys - and a launch moves less than 1 GiB.  From there on the upload is lost in
+// the launch (170 us and more), and tables in device memory are the faster ones to
+// walk (2.06 GB backward from four copies: 311 us with them in the arguments, 308
+// in device memory; below, 330 MB made, used and dropped: 53 against 79 us).
+constexpr int64_t kMaxInlineBytes = (int64_t)1 << 30;
 size_t inline_seg_at(const hp_plan *p) {
     return (offsetof(Args, b) + (size_t)(p->n_src_bufs + p->n_dst_bufs) * sizeof(void *) + 63) / 64 * 64;
 }
 bool inline_tables(const hp_plan *p) {
     const size_t n = p->segments.size();
     const size_t leaves = n > (size_t)hp::kTreeFanout ? (n + hp::kTreeFanout - 1) / hp::kTreeFanout * 64 : 0;
-    return inline_seg_at(p) + (n * sizeof(hp::Seg) + 63) / 64 * 64 + leaves <= sizeof(Args);
+    return inline_seg_at(p) + (n * sizeof(hp::Seg) + 63) / 64 * 64 + leaves <= sizeof(Args) &&
+           (1 + (int64_t)p->dst_copies) * p->n_rows * p->row_bytes < kMaxInlineBytes;
 }
 
 // Puts the tables of a launch with tiles of 1 KiB << variant behind the buffer

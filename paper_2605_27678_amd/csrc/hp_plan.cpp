@@ -260,7 +260,6 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
     if (c == 1 && fwd >= 200 * MB) set(f, K4, 128, 24);                         // 820 MB: 134 -> 129 us
     else if (c == 2 && fwd >= 16 * MB && fwd < 300 * MB) set(f, K8, 256, 16);   // 283 MB: 46.2 -> 44.1
     else if (c == 3 && fwd >= 450 * MB) set(f, K1, 64, 28);                     // 2 GB: 326 -> 319
-    else if (c == 4 && fwd >= 100 * MB && fwd < 450 * MB) set(f, K1, 64, 12);   // 150 MB: 22.4 -> 22.2, 280 MB: 1.03
     else if (c >= 5 && c <= 7 && fwd >= 16 * MB && fwd < 450 * MB) set(f, K1, 64, 10);   // 40 and 150 MB: 1.07-1.08
     else if (c == 8 && fwd >= 30 * MB && fwd < 450 * MB) set(f, K1, 64, 6);     // 40 MB: 7.3 -> 6.9, 280 MB: 1.07
     else if (c > 8 && fwd >= 100 * MB && fwd < 450 * MB) set(f, K1, 64, 5);     // 280 MB, 16 copies: 1.15
