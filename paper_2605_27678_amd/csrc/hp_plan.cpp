@@ -252,9 +252,10 @@ int make_tables(hp_plan *p) {
 void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
     constexpr int K1 = 0, K4 = 2, K8 = 3;                    // tiles of 1, 4 and 8 KiB
     const int c = p->dst_copies, s = p->src_copies;
-    const bool generic = c != 1 && c != 2 && c != 4 && c != 8;
+    const bool generic = c != 1 && c != 2 && c != 4 && c != 8, f32 = p->elem_bytes == 4, dense = p->dst_stride == 1;
     constexpr double MB = 1e6;
     auto set = [](Launch &L, int tile, int block, int cap) { L = Launch{tile, block, cap, L.nontemporal}; };
+    auto in = [](double bytes, double from, double to) { return bytes >= from * MB && bytes < to * MB; };
 
     const double fwd = (1.0 + c) * (double)p->n_rows * (double)p->row_bytes;
     if (c == 1 && fwd >= 200 * MB) set(f, K4, 128, 24);                         // 820 MB: 134 -> 129 us
@@ -276,17 +277,23 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
 
     const double acc = (double)p->bwd_accum_bytes;
     if (acc < 1 * MB) return;                                                   // a few tiles: nothing to choose
-    if (s > 1) {
-        if (acc < 200 * MB || generic) set(a, K1, 64, 16);                      // two source copies, 83 MB: 1.07-1.15
-    } else if (p->elem_bytes == 4) {
-        set(a, K1, 64, 24);                                                     // binary32: 1.06-1.26 for 2 and 4 copies
+    if (f32) {
+        // More waves make these launches faster and the forward after them slower by as much: only the middle sizes gain,
+        // and none with several source copies (0.77-1.05).
+        const bool gains = c <= 5 ? in(acc, 90, 200)                            // 0.99-1.11; 48 MB: 0.93-1.02, 400 MB: 0.74-1.04
+                           : c < 8 ? acc < 350 * MB                             // 1.01-1.48; 680 MB: 0.81-0.97
+                           : c == 8 ? dense && in(acc, 150, 400)                // 1.00-1.05; 670 MB: 0.84-0.89
+                                    : acc < 300 * MB;                           // 1.02-1.30; 1.6 GB: 0.87-0.97
+        if (s == 1 && gains) set(a, K1, 64, 24);
+    } else if (s > 1) {
+        if (acc < 200 * MB || generic) set(a, K1, 64, 16);                      // 1.04-1.44
     } else if (acc < 400 * MB) {
-        if (c <= 5) set(a, K4, 256, 24);                                        // 3 copies, 260 MB: 49.8 -> 41.2
-        else if (c < 8) set(a, K1, 64, 24);
-        else if (c == 8) set(a, K4, 256, 16);                                   // 200 MB: 36.1 -> 34.9
-        else set(a, K1, 64, 20);                                                // 16 copies, 180 MB: 43.0 -> 30.5
+        if (c == 2 ? acc < 280 * MB : c <= 5) set(a, K4, 256, 24);              // 0.97-1.48; two copies, 300 MB: 0.99-1.02
+        else if (c >= 5 && c < 8) set(a, K1, 64, 24);                           // 1.10-1.63
+        else if (c == 8 && dense && in(acc, 50, 350)) set(a, K4, 256, 16);      // 1.01-1.11; 27 MB 0.96, 400 MB 0.99, [S,B,H] 0.96-1.07
+        else if (c > 8) set(a, K1, 64, 20);                                     // 1.21-1.71
     } else if (c == 1 || generic) {
-        set(a, K1, 64, c <= 8 ? 20 : 16);                                       // 3 copies, 3.5 GB: 605 -> 523; 16: 475 -> 368
+        set(a, K1, 64, c <= 8 ? 20 : 16);                                       // 1.02-1.26, more than 8 copies 1.20-1.37
     }
 }
 

@@ -486,3 +486,31 @@ def test_plans_from_several_threads():
         t.join()
     hp.hp_set_option("tile_bytes_fwd", -1)
     assert not errors, errors
+
+
+def _shape_of(direction, tp, mbytes, f32=False, tp_src=1, images=1, row_bytes=8192):
+    """Tile, workgroup and cap of a plan whose launch of this direction moves about `mbytes` MB."""
+    e = 4 if f32 else 2
+    per_row = (1 + tp, tp + tp_src, tp + 8 * tp_src / e)[direction] * row_bytes
+    n = max(1, round(mbytes * 1e6 / per_row / images))
+    start = [i * (n + 1) for i in range(images)]
+    tm = wl.TokenMap(1, images * (n + 1), row_bytes // e, [0] * images, start, [n] * images, None, int(f32))
+    p = hp.hp_plan_create_host(wl.Grid(tp=tp_src), wl.Grid(tp=tp), tm)
+    assert p.info.n_segments == images
+    L = p.get_launch(direction)
+    p.close()
+    return L["tile_bytes"], L["block_threads"], L["waves_per_cu"]
+
+
+@pytest.mark.parametrize("tp,tp_src,mbytes,cap", [
+    (1, 1, 450, 16), (1, 1, 120, 24), (2, 1, 53, 16), (2, 1, 120, 24), (2, 1, 400, 16), (4, 1, 48, 13), (4, 1, 120, 24),
+    (4, 1, 360, 13), (4, 1, 2400, 13), (5, 1, 1400, 11), (6, 1, 300, 24), (7, 1, 670, 9), (8, 1, 45, 9), (8, 1, 200, 24),
+    (8, 1, 1300, 9), (12, 1, 160, 24), (16, 1, 2100, 7), (2, 2, 80, 13), (3, 2, 70, 11), (8, 2, 50, 9)])
+def test_binary32_accumulation_leaves_its_starting_shape_only_where_another_is_faster(tp, tp_src, mbytes, cap):
+    assert _shape_of(2, tp, mbytes, True, tp_src) == ((1024, 64, 24) if cap == 24 else (2048, 64, cap))
+
+
+@pytest.mark.parametrize("direction,tp,tp_src,mbytes,f32,images,want", [
+    (2, 2, 1, 300, False, 1, (2048, 64, 13)), (2, 8, 1, 27, False, 1, (2048, 64, 9)), (2, 8, 1, 200, False, 1, (4096, 256, 16))])
+def test_shapes_by_size_hold_where_they_were_measured_to_be_faster(direction, tp, tp_src, mbytes, f32, images, want):
+    assert _shape_of(direction, tp, mbytes, f32, tp_src, images) == want
