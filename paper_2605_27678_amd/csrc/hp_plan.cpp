@@ -253,6 +253,7 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
     constexpr int K1 = 0, K4 = 2, K8 = 3;                    // tiles of 1, 4 and 8 KiB
     const int c = p->dst_copies, s = p->src_copies;
     const bool generic = c != 1 && c != 2 && c != 4 && c != 8, f32 = p->elem_bytes == 4, dense = p->dst_stride == 1;
+    const size_t segs = p->segments.size();
     constexpr double MB = 1e6;
     auto set = [](Launch &L, int tile, int block, int cap) { L = Launch{tile, block, cap, L.nontemporal}; };
     auto in = [](double bytes, double from, double to) { return bytes >= from * MB && bytes < to * MB; };
@@ -265,15 +266,24 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
     else if (c == 8 && fwd >= 30 * MB && fwd < 450 * MB) set(f, K1, 64, 6);     // 40 MB: 7.3 -> 6.9, 280 MB: 1.07
     else if (c > 8 && fwd >= 100 * MB && fwd < 450 * MB) set(f, K1, 64, 5);     // 280 MB, 16 copies: 1.15
 
+    // With one and two copies a workgroup moves little for each search, and the depth of the tree (16 segments a level)
+    // decides.
     const double bwd = (double)p->bwd_bytes;
-    if (bwd >= 16 * MB) {
-        if (c == 1 && s == 1) bwd < 200 * MB ? set(b, K1, 64, 28) : set(b, K4, 128, 24);   // 150 MB: 25.4 -> 24.2, 820 MB: 128 -> 125
-        else if (c == 2 && s == 1 && bwd < 300 * MB) set(b, K8, 256, 24);       // 150 MB: 25.9 -> 25.1
-        else if (c == 2 && s > 1) set(b, K1, 64, 20);                           // 2.7 GB: 434 -> 401
-        else if (c == 4 && s == 1 && bwd < 450 * MB) set(b, K1, 64, 24);        // 150 MB: 27.4 -> 25.5, 280 MB: 1.04
-        else if (generic && c < 8) set(b, K1, 64, c <= 5 && s == 1 ? 28 : 24);  // 3 copies, 2 GB: 376 -> 301
-        else if (c > 8 && bwd >= 100 * MB && bwd < 250 * MB) set(b, K4, 128, 24);   // 16 copies, 150 MB: 30.0 -> 26.4
+    if (c == 1 && s == 1 && in(bwd, 25, 200)) {
+        if (segs <= 16) set(b, K1, 64, 28);                                     // 1.01-1.09; more segments 0.73-0.86
     }
+    else if (c == 1 && s == 1 && bwd >= 200 * MB) {
+        if (segs <= 256) set(b, K4, 128, 24);                                   // 0.99-1.04; more segments 0.95-1.00
+    }
+    else if (c == 2 && s == 1 && in(bwd, 80, 250)) {
+        if (segs <= 16) set(b, K8, 256, 24);                                    // 0.99-1.06; more segments 0.96-1.02, 40 MB 0.97-1.05
+    }
+    else if (c == 2 && s > 1 && bwd >= 40 * MB) set(b, K1, 64, 20);             // 1.05-1.09; 27 MB: 0.95-1.02
+    else if (c == 4 && s == 1 && in(bwd, 35, 260)) set(b, K1, 64, 24);          // 1.01-1.14; 300 MB: 0.97-1.04, 400 MB: 0.96
+    else if (generic && c < 8 && bwd >= (c <= 5 ? 16 : 30) * MB &&              // 3 copies 1.03-1.35, 5 to 7 0.98-1.28
+             !(f32 && (s > 1 ? bwd >= 600 * MB : c == 7 && bwd >= 500 * MB)))   // there 0.97-1.02 and 0.95-1.02
+        set(b, K1, 64, c <= 5 && s == 1 ? 28 : 24);
+    else if (c > 8 && !f32 && in(bwd, 100, 250)) set(b, K4, 128, 24);           // 0.98-1.14; binary32: 0.97-1.00, 300 MB: 0.94-1.01
 
     const double acc = (double)p->bwd_accum_bytes;
     if (acc < 1 * MB) return;                                                   // a few tiles: nothing to choose
