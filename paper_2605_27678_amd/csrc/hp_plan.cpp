@@ -242,11 +242,16 @@ int make_tables(hp_plan *p) {
 }
 
 // The shapes of launches whose size calls for others than the replica counts
-// alone.  Measured over tiles of 1 to 8 KiB, 64 to 256 lanes and caps of 4 to 32 at
-// 8 MB to 2 GB of traffic for 1 to 16 copies, in both element types, ragged and
-// row-strided rows among them; a line stands where a shape is at least 2 % faster
-// over the whole range that it is given.  Launches of up to about 400 MB find part
-// of their buffers in the 256 MB memory-side cache and want more waves; replica
+// alone.  Each line was measured against the shape that it replaces in the
+// sequence a program runs (forward, backward, forward, ...; forward, accumulate,
+// ... - a shape that leaves dirty lines behind is paid for by the next launch,
+// and ranks wrongly when it is timed alone), in both element types, with rows of
+// 1 to 24 KiB, images of 16 to 1024 rows, both row orders and launches of 8 MB to
+// 2 GB (accumulating ones to 5 GB); the figures are the direction's gain over that
+// range, and after the semicolon what it would be where the line has ended.  Copy
+// counts measured: 1 to 14 and 16 with one source copy; 1 to 8 and 12 with two.
+// Launches of up to about 400 MB find part of
+// their buffers in the 256 MB memory-side cache and want more waves; replica
 // counts without a kernel of their own (all but 1, 2, 4 and 8) wait for their
 // groups of four loads and want more of them in flight.
 void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
@@ -259,12 +264,13 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
     auto in = [](double bytes, double from, double to) { return bytes >= from * MB && bytes < to * MB; };
 
     const double fwd = (1.0 + c) * (double)p->n_rows * (double)p->row_bytes;
-    if (c == 1 && fwd >= 200 * MB) set(f, K4, 128, 24);                         // 820 MB: 134 -> 129 us
-    else if (c == 2 && fwd >= 16 * MB && fwd < 300 * MB) set(f, K8, 256, 16);   // 283 MB: 46.2 -> 44.1
-    else if (c == 3 && fwd >= 450 * MB) set(f, K1, 64, 28);                     // 2 GB: 326 -> 319
-    else if (c >= 5 && c <= 7 && fwd >= 16 * MB && fwd < 450 * MB) set(f, K1, 64, 10);   // 40 and 150 MB: 1.07-1.08
-    else if (c == 8 && fwd >= 30 * MB && fwd < 450 * MB) set(f, K1, 64, 6);     // 40 MB: 7.3 -> 6.9, 280 MB: 1.07
-    else if (c > 8 && fwd >= 100 * MB && fwd < 450 * MB) set(f, K1, 64, 5);     // 280 MB, 16 copies: 1.15
+    if (c == 1 && fwd >= 200 * MB && segs <= 256) set(f, K4, 128, 24);          // 0.99-1.03; more segments 0.98-1.03
+    else if (c == 2 && in(fwd, 40, 290)) set(f, K8, 256, 16);                   // 0.98-1.13; 300 MB: 0.96-1.00
+    else if (c >= 5 && c <= 7 && in(fwd, 40, 450)) {
+        if (c > 5 || segs <= 16) set(f, K1, 64, 10);                            // 0.96-1.20; 20 MB 0.89-1.06, five copies and more segments 0.87-1.03
+    }
+    else if (c == 8 && dense && in(fwd, 40, 450)) set(f, K1, 64, 6);            // 0.99-1.25; [S,B,H] order 0.93-1.02
+    else if (c >= 10 && dense && in(fwd, 100, 450)) set(f, K1, 64, 5);          // 0.96-1.28; 9 copies 0.91-1.09, [S,B,H] 0.86-1.05
 
     // With one and two copies a workgroup moves little for each search, and the depth of the tree (16 segments a level)
     // decides.
