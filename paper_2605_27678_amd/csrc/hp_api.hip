@@ -207,7 +207,7 @@ hp_zero_rows_kernel(const Args a) {
 // outside the images are read once and every row is written once, against a
 // copy of everything and a second pass of stores over the image rows: four
 // buffers of 268 MB in [S,B,H] order, half of them image rows, 491 -> 281 us.
-template <Tiles TILES>
+template <Tiles TILES, bool NTL>
 __global__ void __launch_bounds__(1024)
 hp_text_grads_kernel(const Args a) {
     const KParams &k = a.k;
@@ -222,7 +222,7 @@ hp_text_grads_kernel(const Args a) {
         for (uint32_t i = threadIdx.x; i < t.nbytes / 2; i += step) {
             const uint64_t at = hp::element_at<2>(k, t, i).dst;
             uint16_t v = 0;
-            if (!t.src_copies) v = ld<2, true>(src + at);
+            if (!t.src_copies) v = ld<2, NTL>(src + at);
             st<2, true>(dst + at, v);
         }
         return;
@@ -239,7 +239,7 @@ hp_text_grads_kernel(const Args a) {
         }
         if (!t.src_copies) {                                          // uniform: text
 #pragma unroll
-            for (int u = 0; u < U; ++u) v[u] = ld<16, true>(src + at[u]);
+            for (int u = 0; u < U; ++u) v[u] = ld<16, NTL>(src + at[u]);
         }
 #pragma unroll
         for (int u = 0; u < U; ++u)
@@ -811,14 +811,47 @@ std::vector<RunGroup> group_runs(const std::vector<hp::Seg> &runs, int32_t copie
     return groups;
 }
 
+// The runs that hp_text_grads launches for a plan: of text and of image rows, or
+// (*whole) whole buffers to copy, whose image rows are then zeroed.  Runs save the
+// image rows one reading and one writing, about 1 us for 6 MB, and take a launch
+// for every hundred or so, about 4 us each after the first; a copy is two launches.
+// Two buffers of 67 MB, half of them image rows: 512 runs 56 us, 800 runs 67, copied
+// 53; 1000 images in two buffers of 34 MB: 99 against 30; two of 524 MB: 4096 runs
+// 441 us, 5120 row-strided ones 589, copied 476 and 481.
+std::vector<hp::Seg> text_runs(const hp_plan *p, bool *whole) {
+    const double saved = 2.0 * (double)p->n_rows * (double)p->row_bytes * p->dst_copies;
+    const double most = 1.75 + saved / 25e6;                             // launches
+    // About as many runs as there will be at least (segments in another order than their rows count as apart): where
+    // they are too many they are not even made.
+    int64_t images = 0;
+    for (size_t i = 0; i < p->segments.size(); ++i) {
+        const hp_segment_t &b = p->segments[i], &a = p->segments[i ? i - 1 : 0];
+        images += !i || a.dst_buf0 != b.dst_buf0 || a.dst_row0 + a.n_rows * a.dst_row_stride != b.dst_row0;
+    }
+    const int64_t columns = p->n_dst_bufs / p->dst_copies * p->dst_stride;
+    const double runs = (double)std::max(columns, std::max(images, 2 * images - columns));
+    *whole = images == 0 || runs * sizeof(hp::Seg) > most * sizeof(Args);
+    if (!*whole) {
+        std::vector<hp::Seg> r = hp::dst_runs(*p, false);
+        *whole = (double)group_runs(r, p->dst_copies).size() > most;
+        if (!*whole) return r;
+    }
+    return hp::dst_runs(*p, true);
+}
+
 // 4 KiB tiles, four chunks a lane, 16 waves a compute unit: over tiles of 1 to 16 KiB,
 // 64 to 256 lanes and caps of 4 to 32, the best or within 3 % of it for dense,
 // row-strided and ragged rows (1.6 GB in [B,S,H] order: 254 us, 6.35 TB/s; the
 // forward's 4 KiB x 128 lanes x 20 waves: 287; loads that stay cached: 2-4 % slower).
 const hp::Launch kTextLaunch{2, 64, 16, 3};
+// Copies of whole buffers that find the gradients in the 256 MB memory-side cache
+// read them from there: 67 MB 31.8 -> 30.0 us, 134 MB 46.4 -> 39.9 (torch's clones:
+// 34.0 and 41.8); from there on streaming loads are the faster ones (1.07 GB 473
+// against 485).
+constexpr int64_t kCachedCopyBytes = (int64_t)1 << 28;
 
-int enqueue_runs(const hp_plan *p, const std::vector<hp::Seg> &runs, const RunGroup &g, const void *const *grad,
-                 void *const *out, hipStream_t stream) {
+int enqueue_runs(const hp_plan *p, const std::vector<hp::Seg> &runs, const RunGroup &g, bool cached,
+                 const void *const *grad, void *const *out, hipStream_t stream) {
     const int variant = kTextLaunch.tile_variant;
     Args a;
     a.k = hp::kernel_params(*p, variant, nullptr, nullptr);
@@ -852,9 +885,12 @@ int enqueue_runs(const hp_plan *p, const std::vector<hp::Seg> &runs, const RunGr
     c.block = dim3((unsigned)kTextLaunch.block);
     c.lds_bytes = lds_for_cap(kTextLaunch.block, kTextLaunch.waves_per_cu);
     c.stream = stream;
-    if (p->dst_stride != 1 && a.k.parts_per_row == 0) HP_LAUNCH((hp_text_grads_kernel<kStrided>), c, a);
-    else if (a.k.row_bytes % hp::kLineBytes) HP_LAUNCH((hp_text_grads_kernel<kRagged>), c, a);
-    else HP_LAUNCH((hp_text_grads_kernel<kLines>), c, a);
+    const bool lines = a.k.row_bytes % hp::kLineBytes == 0;
+    if (runs[g.first].pitch_rows != 1 && a.k.parts_per_row == 0) HP_LAUNCH((hp_text_grads_kernel<kStrided, true>), c, a);
+    else if (cached && lines) HP_LAUNCH((hp_text_grads_kernel<kLines, false>), c, a);
+    else if (cached) HP_LAUNCH((hp_text_grads_kernel<kRagged, false>), c, a);
+    else if (lines) HP_LAUNCH((hp_text_grads_kernel<kLines, true>), c, a);
+    else HP_LAUNCH((hp_text_grads_kernel<kRagged, true>), c, a);
     return hip_failed(hipGetLastError()) ? HP_EHIP : HP_OK;
 }
 
@@ -1471,24 +1507,14 @@ int hp_text_grads(const hp_plan_t *p, const void *const *dst_grad_bufs, void *co
     }
     if (bits & (uint64_t)(p->elem_bytes - 1)) return HP_EALIGN;
     try {
-        std::call_once(p->runs_once, [&] { p->runs = hp::dst_runs(*p, false); });
-        std::vector<hp::Seg> whole;
-        const std::vector<hp::Seg> *runs = &p->runs;
-        std::vector<RunGroup> groups = group_runs(*runs, p->dst_copies);
-        // Many short runs take many launches.  Each costs about 3.5 us, the time of some 20 MB; what they save is
-        // reading and storing the image rows twice.
-        const uint64_t saved = 2 * (uint64_t)p->n_rows * (uint64_t)p->row_bytes * (uint64_t)p->dst_copies;
-        const bool copy = groups.size() > 2 + saved / 20000000;
-        if (copy) {
-            whole = hp::dst_runs(*p, true);
-            runs = &whole;
-            groups = group_runs(whole, p->dst_copies);
-        }
-        for (const RunGroup &g : groups) {
-            const int rc = enqueue_runs(p, *runs, g, dst_grad_bufs, text_grad_bufs, (hipStream_t)stream);
+        std::call_once(p->runs_once, [&] { p->runs = text_runs(p, &p->runs_whole); });
+        const bool cached =
+            p->runs_whole && p->dst_rows_per_buf * p->row_bytes * (int64_t)p->n_dst_bufs < kCachedCopyBytes;
+        for (const RunGroup &g : group_runs(p->runs, p->dst_copies)) {
+            const int rc = enqueue_runs(p, p->runs, g, cached, dst_grad_bufs, text_grad_bufs, (hipStream_t)stream);
             if (rc != HP_OK) return rc;
         }
-        return copy ? hp_zero_image_rows(p, text_grad_bufs, stream) : HP_OK;
+        return p->runs_whole ? hp_zero_image_rows(p, text_grad_bufs, stream) : HP_OK;
     } catch (const std::bad_alloc &) {
         return HP_ENOMEM;
     } catch (...) {

@@ -46,15 +46,24 @@ uint64_t tiles_of(uint64_t n_rows, uint64_t pitch_rows, int64_t row_bytes, uint3
 }
 
 std::vector<Seg> dst_runs(const hp_plan &p, bool whole) {
+    std::vector<Seg> runs;
+    if (whole) {                                           // dense, whatever the row order
+        for (int64_t buf = 0; buf < p.n_dst_bufs; buf += p.dst_copies)
+            for (int64_t row = 0; row < p.dst_rows_per_buf; row += kMaxSegRows) {
+                const uint64_t off = (uint64_t)row * (uint64_t)p.row_bytes;
+                const int64_t n = std::min<int64_t>(p.dst_rows_per_buf - row, kMaxSegRows);
+                runs.push_back(Seg{off, off, (uint32_t)n, 1, (uint16_t)buf, (uint16_t)buf, 0});
+            }
+        return runs;
+    }
     const int64_t stride = p.dst_stride;
-    std::vector<size_t> order(whole ? 0 : p.segments.size());
+    std::vector<size_t> order(p.segments.size());
     std::iota(order.begin(), order.end(), (size_t)0);
     auto place = [&](size_t i) {                           // buffer, column, position in the column
         const hp_segment_t &s = p.segments[i];
         return std::make_tuple((int64_t)s.dst_buf0, s.dst_row0 % stride, s.dst_row0 / stride);
     };
     std::sort(order.begin(), order.end(), [&](size_t a, size_t b) { return place(a) < place(b); });
-    std::vector<Seg> runs;
     const int64_t column = p.dst_rows_per_buf / stride;
     size_t at = 0;
     for (int64_t buf = 0; buf < p.n_dst_bufs; buf += p.dst_copies)

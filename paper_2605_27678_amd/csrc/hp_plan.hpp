@@ -106,9 +106,9 @@ struct hp_plan {
         used_streams.push_back(stream);
     }
 
-    // Every row of the destination buffers as runs of text and of image rows, for
-    // hp_text_grads: made by its first call (dst_runs).
+    // The runs that hp_text_grads launches (dst_runs), made by its first call.
     mutable std::once_flag runs_once;
+    mutable bool runs_whole = false;
     mutable std::vector<hp::Seg> runs;
 
     uint32_t n_tiles(int variant) const {
@@ -134,7 +134,7 @@ uint64_t tiles_of(uint64_t n_rows, uint64_t pitch_rows, int64_t row_bytes, uint3
 // The rows of every first copy of the destination buffers as runs that partition
 // them, by buffer and position: src_copies = 0 for text rows and 1 for image rows,
 // both offsets those of the run in its buffer, both buffer indices its first copy's
-// (among the destination buffers).  whole: one run of text a buffer (and, row-
-// strided plans, a column of it), whatever lies there.
+// (among the destination buffers).  whole: one dense run of text a buffer,
+// whatever lies there and in whichever row order.
 std::vector<Seg> dst_runs(const hp_plan &p, bool whole);
 }  // namespace hp

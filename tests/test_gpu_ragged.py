@@ -120,6 +120,30 @@ def test_text_gradients(n_img, hidden, f32, sbh):
     plan.close()
 
 
+# many short runs: whole buffers are copied, whatever the row order, and their image rows zeroed; small ones through the
+# memory-side cache, large ones (the last two) past it
+@pytest.mark.parametrize("batch,seq,hidden,tp,f32,sbh", [(300, 20, 72, 2, False, True), (300, 20, 67, 3, True, True),
+                                                         (513, 9, 64, 1, False, False), (1, 1500, 1001, 2, False, False),
+                                                         (2, 33000, 2112, 1, False, True), (1, 66000, 2111, 1, False, False)])
+def test_text_gradients_of_many_short_images(batch, seq, hidden, tp, f32, sbh):
+    per = max(1, 600 // batch)
+    samp = np.repeat(np.arange(batch), per).astype(np.int32)
+    start = np.tile(np.arange(per) * (seq // per) + 1, batch).astype(np.int32)
+    tm = wl.TokenMap(batch, seq, hidden, samp, start, np.full(len(samp), 1, np.int32), None, int(f32))
+    plan = hp.hp_plan_create(wl.Grid(dp=2), wl.Grid(tp=tp, row_order=wl.ROW_SBH if sbh else wl.ROW_BSH), tm)
+    dt = torch.float32 if f32 else torch.bfloat16
+    g = [torch.randn(batch * seq, hidden, device="cuda").to(dt) for _ in range(tp)]
+    out = [torch.full_like(t, 7.0) for t in g]
+    keep = [t.clone() for t in g]
+    hp.hp_text_grads(plan, g, out)
+    image = torch.zeros(batch, seq, dtype=torch.bool)
+    image[torch.from_numpy(samp).long(), torch.from_numpy(start).long()] = True
+    image = (image.t() if sbh else image).reshape(-1).cuda()
+    for t, o, k in zip(g, out, keep):
+        assert torch.equal(o, torch.where(image[:, None], torch.zeros_like(t), t)) and torch.equal(t, k)
+    plan.close()
+
+
 # where a plan's tables go: with a launch's arguments or into device memory (the tree's levels and the last segments
 # that fit: 1 level up to 16 segments, arguments full a little above 100)
 @pytest.mark.parametrize("n_seg", [1, 16, 17, 32, 100, 104, 105, 106, 107, 108, 109, 110, 112, 130, 257])

@@ -85,13 +85,16 @@ static bool walk_plan(const hp_plan &p, const uint32_t *tree, uint64_t dst_base)
 }
 
 // The runs of hp_text_grads: a partition of every buffer's rows in which exactly
-// the segments' rows are image rows.
+// the segments' rows are image rows; whole: one dense run for each first copy.
 static bool check_runs(const hp_plan &p) {
     v = -1; tile = 0;
     for (int whole = 0; whole < 2; ++whole) {
         std::vector<std::vector<int>> rows((size_t)p.n_dst_bufs, std::vector<int>((size_t)p.dst_rows_per_buf, -1));
-        for (const hp::Seg &r : hp::dst_runs(p, whole != 0)) {
-            CHECK(r.n_rows > 0 && r.src_off == r.dst_off && r.src_buf == r.dst_buf0 && r.pitch_rows == p.dst_stride);
+        const std::vector<hp::Seg> runs = hp::dst_runs(p, whole != 0);
+        if (whole) CHECK(runs.size() == (size_t)(p.n_dst_bufs / p.dst_copies));
+        for (const hp::Seg &r : runs) {
+            CHECK(r.n_rows > 0 && r.src_off == r.dst_off && r.src_buf == r.dst_buf0);
+            CHECK(r.pitch_rows == (whole ? 1 : p.dst_stride));
             for (uint32_t i = 0; i < r.n_rows; ++i) {
                 int &cell = rows[r.dst_buf0][r.dst_off / (uint64_t)p.row_bytes + (uint64_t)i * r.pitch_rows];
                 CHECK(cell == -1);
