@@ -685,11 +685,22 @@ void launch_backward(int dtype, bool acc, int copies, const LaunchCfg &c, const 
 
 enum Direction { kForward = 0, kBackward = 1, kBackwardAcc = 2, kZeroRows = 3 };   // kZeroRows: forward's launch shape
 
+// The kernel of one tile kind, in the shape's cache policy.
+template <Tiles TILES, bool NTL, bool NTS>
+void launch_nt(const hp_plan *p, Direction dir, const LaunchCfg &c, const Args &a) {
+    if (dir == kZeroRows) HP_LAUNCH((hp_zero_rows_kernel<TILES, NTS>), c, a);
+    else if (dir == kForward) launch_forward<TILES, NTL, NTS>(p->dst_copies, c, a);
+    else launch_backward<TILES, NTL, NTS>(p->dtype, dir == kBackwardAcc, p->dst_copies, c, a);
+}
+
 template <Tiles TILES>
-void launch_other(const hp_plan *p, Direction dir, const LaunchCfg &c, const Args &a) {
-    if (dir == kZeroRows) HP_LAUNCH((hp_zero_rows_kernel<TILES, true>), c, a);
-    else if (dir == kForward) launch_forward<TILES, false, true>(p->dst_copies, c, a);
-    else launch_backward<TILES, true, true>(p->dtype, dir == kBackwardAcc, p->dst_copies, c, a);
+void launch_tiles(const hp_plan *p, Direction dir, int nontemporal, const LaunchCfg &c, const Args &a) {
+    switch (nontemporal & 3) {
+        case 0: launch_nt<TILES, false, false>(p, dir, c, a); break;
+        case 1: launch_nt<TILES, true, false>(p, dir, c, a); break;
+        case 2: launch_nt<TILES, false, true>(p, dir, c, a); break;
+        default: launch_nt<TILES, true, true>(p, dir, c, a); break;
+    }
 }
 
 // Whether a plan's tables travel with its launches: they fit behind the buffer
@@ -751,31 +762,9 @@ int enqueue_params(const hp_plan *p, Direction dir, const hp::Launch &L, const B
     c.lds_bytes = lds_for_cap(L.block, L.waves_per_cu);
     c.stream = stream;
     c.ev = ev;
-    const int nt = L.nontemporal & 3, copies = p->dst_copies;
-    const bool acc = dir == kBackwardAcc;
-    const bool strided = p->dst_stride != 1 && k.parts_per_row == 0;
-    if (strided || k.row_bytes % hp::kLineBytes) {
-        // the cache policy that the kernels of whole lines start from, whatever the shape asks for
-        if (strided) launch_other<kStrided>(p, dir, c, a);
-        else launch_other<kRagged>(p, dir, c, a);
-    } else if (dir == kZeroRows) {
-        if (nt & 2) HP_LAUNCH((hp_zero_rows_kernel<kLines, true>), c, a);
-        else HP_LAUNCH((hp_zero_rows_kernel<kLines, false>), c, a);
-    } else if (dir == kForward) {
-        switch (nt) {
-            case 0: launch_forward<kLines, false, false>(copies, c, a); break;
-            case 1: launch_forward<kLines, true, false>(copies, c, a); break;
-            case 2: launch_forward<kLines, false, true>(copies, c, a); break;
-            default: launch_forward<kLines, true, true>(copies, c, a); break;
-        }
-    } else {
-        switch (nt) {
-            case 0: launch_backward<kLines, false, false>(p->dtype, acc, copies, c, a); break;
-            case 1: launch_backward<kLines, true, false>(p->dtype, acc, copies, c, a); break;
-            case 2: launch_backward<kLines, false, true>(p->dtype, acc, copies, c, a); break;
-            default: launch_backward<kLines, true, true>(p->dtype, acc, copies, c, a); break;
-        }
-    }
+    if (p->dst_stride != 1 && k.parts_per_row == 0) launch_tiles<kStrided>(p, dir, L.nontemporal, c, a);
+    else if (k.row_bytes % hp::kLineBytes) launch_tiles<kRagged>(p, dir, L.nontemporal, c, a);
+    else launch_tiles<kLines>(p, dir, L.nontemporal, c, a);
     if (hip_failed(hipGetLastError())) return HP_EHIP;
     return HP_OK;
 }

@@ -2,6 +2,7 @@
 GPU, and the binding's refusal to work without the built library (there is no
 CPU or PyTorch path to fall back to)."""
 import os
+import re
 import subprocess
 import sys
 
@@ -108,3 +109,21 @@ def test_plain_c_client_links_against_the_library(tmp_path):
     assert r.returncode == 0, r.stderr
     r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and "abi client ok" in r.stdout, r.stdout + r.stderr
+
+
+def test_every_cache_policy_has_its_kernel_for_every_kind_of_row():
+    """hp_launch_t.nontemporal applies to whole-line, ragged and row-strided rows alike: each of the four policies is a
+    kernel of its own in each kind, direction and element type."""
+    from paper_2605_27678_amd import binding
+    r = subprocess.run(["nm", "-C", binding.LIB_PATH], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stderr
+    names = set(re.findall(r"(hp_\w+_kernel<[^>]*>)", r.stdout.replace("(anonymous namespace)::", "")))
+    for tiles in ("0", "1", "2"):
+        for nts in ("false", "true"):
+            assert f"hp_zero_rows_kernel<(Tiles){tiles}, {nts}>" in names
+            for ntl in ("false", "true"):
+                for copies in (0, 1, 2, 4, 8):
+                    assert f"hp_forward_kernel<{copies}, (Tiles){tiles}, {ntl}, {nts}>" in names
+                    for dtype in (0, 1):
+                        for acc in ("false", "true"):
+                            assert f"hp_backward_kernel<{dtype}, {acc}, {copies}, (Tiles){tiles}, {ntl}, {nts}>" in names

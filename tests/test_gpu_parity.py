@@ -105,6 +105,37 @@ def test_launch_shapes(tile, block, nt, waves):
     check_case(w.src, w.dst, w.maps[0], seed=tile % 97)
 
 
+@pytest.mark.parametrize("hidden,sbh", [(320, False), (100, False), (64, True), (100, True)])
+@pytest.mark.parametrize("tile,block,nt,waves,tp", [(1024, 64, 1, 0, 2), (1024, 128, 0, 4, 4), (32768, 256, 2, 8, 1),
+                                                    (65536, 512, 3, 16, 3), (16384, 1024, 1, 32, 8), (65536, 64, 0, 12, 4),
+                                                    (8192, 192, 3, 6, 2), (2048, 64, 1, 1, 1)])
+def test_launch_shapes_of_every_kind_of_row(tile, block, nt, waves, tp, hidden, sbh):
+    """Large tiles, workgroups of several waves and all four cache policies on whole-line, ragged and row-strided rows, in
+    every direction and both element types."""
+    bwd = dict(tile_bytes=(1 << 26) // tile, block_threads=64 * (16 // (block // 64)), waves_per_cu=32 - waves,
+               nontemporal=3 - nt)
+    for k, v in dict(tile_bytes=tile, block_threads=block, waves_per_cu=waves, nontemporal=nt).items():
+        hp.hp_set_option(k + "_fwd", v)
+        hp.hp_set_option(k + "_bwd", bwd[k])
+    rng = np.random.default_rng(tile + hidden)
+    src = wl.Grid(tp=1 + tp % 2, dp=2)
+    dst = wl.Grid(tp=tp, cp=2, cp_split=wl.CP_ZIGZAG, row_order=wl.ROW_SBH if sbh else wl.ROW_BSH)
+    tm = wl.token_map_from_lens(rng, 3, 320, hidden, [[151, 97], [300], [5, 64, 130]])
+    check_case(src, dst, tm, seed=tile % 97)
+    for dtype in (wl.DT_BF16, wl.DT_F32):
+        check_case_extended(src, dst, replace(tm, dtype=dtype), seed=hidden, acc_launch=dict(bwd, nontemporal=nt))
+    plan, prob = hp.hp_plan_create(src, dst, tm), oracle.Problem(src, dst, tm)
+    assert plan.get_launch(0)["nontemporal"] == nt and plan.get_launch(1) == bwd
+    d = [wl.random_bf16((prob.dst_rows(), hidden), j) for j in range(prob.n_dst)]
+    got = [t.cuda() for t in d]
+    hp.hp_zero_image_rows(plan, got)
+    for j, (t, g) in enumerate(zip(d, got)):
+        want = _to_host_bits(t).copy()
+        want[prob.forward_map(j)[0] >= 0] = 0
+        assert np.array_equal(_to_host_bits(g), want)
+    plan.close()
+
+
 @pytest.mark.parametrize("tp", [1, 2, 3, 4, 5, 8, 16])
 def test_replica_counts(tp):
     rng = np.random.default_rng(tp)
