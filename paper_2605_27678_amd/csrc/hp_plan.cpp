@@ -322,6 +322,20 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
     }
 }
 
+// HIP refuses a grid of 2^32 work-items or more: 64 GiB in tiles of 1 KiB, one
+// wave each.  Such a launch takes the next larger tiles.
+void keep_grid(const hp_plan *p, Launch &L) {
+    constexpr uint64_t kItems = (uint64_t)1 << 32;
+    const uint64_t most = std::max<uint64_t>((uint64_t)(p->n_rows * p->row_bytes) >> 10, (uint64_t)p->n_rows);
+    if ((most + p->segments.size()) * (uint64_t)L.block < kItems) return;
+    for (; L.tile_variant + 1 < kTileVariants; ++L.tile_variant) {
+        uint64_t tiles = 0;
+        for (const hp_segment_t &s : p->segments)
+            tiles += tiles_of((uint64_t)s.n_rows, (uint64_t)s.dst_row_stride, p->row_bytes, tile_bytes_of(L.tile_variant));
+        if (tiles * (uint64_t)L.block < kItems) return;
+    }
+}
+
 // Launch shapes for a new plan.  Both kernels are fastest when roughly 100 KB
 // of traffic per compute unit is in flight, so the resident-wave cap that suits
 // a plan falls as the number of buffers a row's traffic spreads over rises:
@@ -345,6 +359,7 @@ void default_launches(hp_plan *p) {
     const int acc_streams = c + s * 8 / p->elem_bytes;
     Launch a{1, 64, acc_streams <= 4 ? 16 : acc_streams <= 6 ? 13 : acc_streams <= 8 ? 11 : acc_streams <= 12 ? 9 : 7, 3};
     by_size(p, f, b, a);
+    for (Launch *L : {&f, &b, &a}) keep_grid(p, *L);
     auto apply = [](Launch &L, int64_t tile, int64_t block, int64_t waves, int64_t nt) {
         if (tile > 0) L.tile_variant = tile_variant_of(tile);
         if (block > 0) L.block = (int32_t)block;

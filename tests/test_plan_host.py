@@ -527,3 +527,18 @@ def test_binary32_accumulation_leaves_its_starting_shape_only_where_another_is_f
     (2, 2, 1, 300, False, 1, (2048, 64, 13)), (2, 8, 1, 27, False, 1, (2048, 64, 9)), (2, 8, 1, 200, False, 1, (4096, 256, 16))])
 def test_shapes_by_size_hold_where_they_were_measured_to_be_faster(direction, tp, tp_src, mbytes, f32, images, want):
     assert _shape_of(direction, tp, mbytes, f32, tp_src, images) == want
+
+
+@pytest.mark.parametrize("tp,tp_src,gib,hidden,sbh", [(1, 1, 66, 12288, False), (1, 1, 120, 12288, False), (2, 1, 70, 8192, False),
+                                                      (3, 1, 65, 8192, False), (3, 2, 66, 8192, False), (1, 1, 40, 260, True)])
+def test_grids_of_the_largest_launches_stay_below_2_to_the_32_work_items(tp, tp_src, gib, hidden, sbh):
+    """HIP refuses a grid of 2^32 work-items or more; such a launch fits the card's memory."""
+    rows = (gib << 30) // (2 * hidden)
+    batch = 2 if sbh else 1
+    tm = wl.TokenMap(batch, rows // batch, hidden, list(range(batch)), [0] * batch, [rows // batch] * batch)
+    p = hp.hp_plan_create_host(wl.Grid(tp=tp_src), wl.Grid(tp=tp, row_order=wl.ROW_SBH if sbh else wl.ROW_BSH), tm)
+    for d in (0, 1, 2):
+        L = p.get_launch(d)
+        p.set_launch(0, **L)                                # n_tiles is the forward shape's
+        assert p.info.n_tiles * L["block_threads"] < 2 ** 32, (d, L)
+    p.close()
