@@ -386,11 +386,13 @@ int hp_plan_set_launch(hp_plan_t *plan, int32_t direction, const hp_launch_t *in
  * SYNCHRONOUS: waits on `stream` repeatedly, takes tens to hundreds of
  * milliseconds, creates and destroys four HIP events, and must not run
  * concurrently with other calls that use the same plan.
- * The winning shapes are also remembered per problem class (dtype, row size,
- * TP_dst copies, TP_src copies, device): plans of the same class created later
+ * The winning shapes are also remembered per problem class (dtype, row size, row
+ * order, TP_dst copies, TP_src copies, device): plans of the same class created later
  * by hp_plan_create / hp_plan_create_batched / hp_plan_create_joined start from them instead of the
- * process-wide defaults, so a caller that rebuilds its plan every step tunes
- * once.  hp_forget_tuned_shapes drops what was remembered. */
+ * process-wide defaults in every direction in which a launch moves 128 MiB or more,
+ * so a caller that rebuilds its plan every step tunes once.  Smaller launches
+ * keep their defaults, which depend on their size.  hp_forget_tuned_shapes drops
+ * what was remembered. */
 int hp_plan_tune(hp_plan_t *plan, const void *const *src_bufs, void *const *dst_bufs,
                  const void *const *dst_grad_bufs, void *const *src_grad_bufs, void *stream);
 void hp_forget_tuned_shapes(void);

@@ -1051,18 +1051,26 @@ hipStream_t upload_stream(int device, int *rc) {
     return streams[device];
 }
 
+// hp_plan_tune searches only plans whose forward launch moves at least this much.
+constexpr int64_t kMinTunedBytes = (int64_t)1 << 30;
+
 // Launch shapes found by hp_plan_tune are remembered per problem class (dtype,
-// row size, replica counts, device) and seed later plans of the same class, so a
-// caller that rebuilds its plan every step tunes once.
+// row size, row order, replica counts, device) and seed later plans of the same
+// class, so a caller that rebuilds its plan every step tunes once.  Only launches
+// that are not far smaller than what is searched take them: an eighth of it.
+// Below, buffers lie in the memory-side cache and a plan's own starting shape
+// is the better one (40 to 100 MB, the best shape at 2 GB against it: forward
+// 0.96-1.12 of its time, backward 1.00-1.16, accumulating 0.99-1.15).
+constexpr int64_t kMinSeededBytes = kMinTunedBytes / 8;
 struct ShapeCache {
-    struct Entry { int dtype; int64_t row_bytes; int dst_copies, src_copies, device; hp::Launch fwd, bwd, acc; bool has_fwd, has_bwd, has_acc; };
+    struct Entry { int dtype; int64_t row_bytes; bool sbh; int dst_copies, src_copies, device; hp::Launch fwd, bwd, acc; bool has_fwd, has_bwd, has_acc; };
     std::mutex mu;
     std::vector<Entry> entries;
 
     Entry *find(const hp_plan *p) {
         for (Entry &e : entries)
-            if (e.dtype == p->dtype && e.row_bytes == p->row_bytes && e.dst_copies == p->dst_copies &&
-                e.src_copies == p->src_copies && e.device == p->device)
+            if (e.dtype == p->dtype && e.row_bytes == p->row_bytes && e.sbh == (p->dst_stride != 1) &&
+                e.dst_copies == p->dst_copies && e.src_copies == p->src_copies && e.device == p->device)
                 return &e;
         return nullptr;
     }
@@ -1071,8 +1079,8 @@ struct ShapeCache {
         Entry *e = find(p);
         if (!e) {
             if (entries.size() >= 256) entries.erase(entries.begin());
-            entries.push_back(Entry{p->dtype, p->row_bytes, p->dst_copies, p->src_copies, p->device, p->fwd, p->bwd,
-                                    p->acc, false, false, false});
+            entries.push_back(Entry{p->dtype, p->row_bytes, p->dst_stride != 1, p->dst_copies, p->src_copies, p->device,
+                                    p->fwd, p->bwd, p->acc, false, false, false});
             e = &entries.back();
         }
         if (fwd) { e->fwd = p->fwd; e->has_fwd = true; }
@@ -1082,9 +1090,9 @@ struct ShapeCache {
     void apply(hp_plan *p) {
         std::lock_guard<std::mutex> lk(mu);
         if (const Entry *e = find(p)) {
-            if (e->has_fwd) p->fwd = e->fwd;
-            if (e->has_bwd) p->bwd = e->bwd;
-            if (e->has_acc) p->acc = e->acc;
+            if (e->has_fwd && (1 + (int64_t)p->dst_copies) * p->n_rows * p->row_bytes >= kMinSeededBytes) p->fwd = e->fwd;
+            if (e->has_bwd && p->bwd_bytes >= kMinSeededBytes) p->bwd = e->bwd;
+            if (e->has_acc && p->bwd_accum_bytes >= kMinSeededBytes) p->acc = e->acc;
         }
     }
     void clear() {
@@ -1171,9 +1179,6 @@ struct BurstEvents {
             if (x) (void)hipEventDestroy(x);
     }
 };
-
-// hp_plan_tune searches only plans whose forward launch moves at least this much.
-constexpr int64_t kMinTunedBytes = (int64_t)1 << 30;
 
 // What runs right after every candidate launch while it is being timed: the
 // plan's other direction with its current launch shape, when the caller gave

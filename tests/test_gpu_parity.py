@@ -646,6 +646,33 @@ def test_tune_accumulate_picks_a_valid_shape_and_keeps_the_sum_exact():
     assert small.get_launch(2) == before
 
 
+def test_tuned_shapes_seed_neither_small_launches_nor_the_other_row_order():
+    """A shape that was found on a launch of 1 GiB suits no launch out of the memory-side cache, and none of other kernels."""
+    H, src, dst = 4096, wl.Grid(), wl.Grid(tp=2)
+
+    def plan(rows, order=wl.ROW_BSH, batch=1):
+        tm = wl.TokenMap(batch, rows + 1, H, list(range(batch)), [0] * batch, [rows] * batch)
+        return hp.hp_plan_create(src, replace(dst, row_order=order), tm)
+
+    big = plan(44000)                                       # 1.08 GB a forward launch
+    bufs = [[torch.zeros((r, H), dtype=torch.bfloat16, device="cuda") for r in rows]
+            for rows in (big.src_rows(), [big.info.dst_rows_per_buf] * 2, [big.info.dst_rows_per_buf] * 2, big.src_rows())]
+    for d in (0, 1):
+        big.set_launch(d, nontemporal=1)                    # the search keeps it, and no default has it
+    hp.hp_plan_tune(big, *bufs)
+    for d in (0, 1):
+        assert plan(22000).get_launch(d) == big.get_launch(d) and big.get_launch(d)["nontemporal"] == 1
+    sizes = {rows: plan(rows) for rows in (1000, 4000, 5600)}           # 25, 98 and 138 MB
+    hp.hp_forget_tuned_shapes()
+    for rows, p in sizes.items():
+        if rows < 5600:
+            assert [p.get_launch(d) for d in (0, 1, 2)] == [plan(rows).get_launch(d) for d in (0, 1, 2)]
+    hp.hp_plan_tune(big, *bufs)
+    before = plan(11000, wl.ROW_SBH, 4)
+    hp.hp_forget_tuned_shapes()
+    assert [before.get_launch(d) for d in (0, 1, 2)] == [plan(11000, wl.ROW_SBH, 4).get_launch(d) for d in (0, 1, 2)]
+
+
 def test_tune_leaves_small_plans_alone():
     """Less than 1 GiB per forward launch: no search (it would be timed out of
     the memory-side cache); the buffers still end up as after one call."""
