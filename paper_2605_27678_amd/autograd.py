@@ -13,11 +13,12 @@ hp_backward and hp_text_grads:
 they are modified in place (the image-token rows are overwritten) and returned.
 Backward gives, for every source buffer, the TP-summed gradient of its rows (all
 TP copies of a source rank receive the same gradient) and, for every text
-buffer, the incoming gradient with the image-token rows set to zero.
+buffer, the incoming gradient with the image-token rows set to zero.  With
+create_graph these are differentiable in turn, to any order.
 """
 from __future__ import annotations
 
-from typing import List, Optional, Sequence
+from typing import List, Sequence
 
 import torch
 
@@ -37,22 +38,60 @@ class _BoundaryTransform(torch.autograd.Function):
 
     @staticmethod
     def backward(ctx, *grad_dst):
-        plan, stream = ctx.plan, torch.cuda.current_stream()
-        grads = [g.contiguous() for g in grad_dst]
-        src_grads: List[Optional[torch.Tensor]] = [None] * ctx.n_src
-        if any(ctx.needs_input_grad[2:2 + ctx.n_src]):
-            src_grads = [torch.empty(shape, dtype=dtype, device=device) for shape, dtype, device in ctx.src_meta]
-            plan.backward(grads, src_grads, stream)
-        # gradient with respect to the text embeddings: the rows forward replaced carry none
-        text_grads: List[Optional[torch.Tensor]] = [None] * len(grads)
-        if any(ctx.needs_input_grad[2 + ctx.n_src:]):
-            if torch.is_grad_enabled():                     # create_graph: the copy is part of the graph
-                text_grads = [g.clone() for g in grads]
-                plan.zero_image_rows(text_grads, stream)
-            else:
-                text_grads = [torch.empty_like(g) for g in grads]
-                plan.text_grads(grads, text_grads, stream)
-        return (None, None, *src_grads, *text_grads)
+        n = ctx.n_src
+        want = any(ctx.needs_input_grad[2:2 + n]), any(ctx.needs_input_grad[2 + n:])
+        if torch.is_grad_enabled():                         # create_graph: differentiable in turn
+            got = _BoundaryGrads.apply(ctx.plan, ctx.src_meta, want, *grad_dst)
+        else:
+            got = _grads(ctx.plan, ctx.src_meta, want, grad_dst)
+        k = n if want[0] else 0
+        return (None, None, *(got[:k] or (None,) * n), *(got[k:] or (None,) * len(grad_dst)))
+
+
+def _grads(plan: Plan, src_meta, want, grad_dst) -> tuple:
+    """The source gradients and the text gradients, each if they are wanted, in one tuple."""
+    stream = torch.cuda.current_stream()
+    grads = [g.contiguous() for g in grad_dst]
+    src_grads: List[torch.Tensor] = []
+    if want[0]:
+        src_grads = [torch.empty(shape, dtype=dtype, device=device) for shape, dtype, device in src_meta]
+        plan.backward(grads, src_grads, stream)
+    # gradient with respect to the text embeddings: the rows forward replaced carry none
+    text_grads: List[torch.Tensor] = []
+    if want[1]:
+        text_grads = [torch.empty_like(g) for g in grads]
+        plan.text_grads(grads, text_grads, stream)
+    return (*src_grads, *text_grads)
+
+
+class _BoundaryGrads(torch.autograd.Function):
+    """_grads as a function of the destination gradients, in which it is linear: its derivative carries cotangents of the
+    source gradients to the image rows and cotangents of the text gradients to the others, as the transform itself does."""
+
+    @staticmethod
+    def forward(ctx, plan: Plan, src_meta, want, *grad_dst):
+        ctx.plan, ctx.src_meta, ctx.want = plan, src_meta, want
+        return _grads(plan, src_meta, want, [g.detach() for g in grad_dst])
+
+    @staticmethod
+    def backward(ctx, *h):
+        plan, (want_src, want_text) = ctx.plan, ctx.want
+        n = len(ctx.src_meta) if want_src else 0
+        if not want_src:                                    # the image rows get nothing
+            return (None, None, None, *_BoundaryGrads.apply(plan, ctx.src_meta, ctx.want, *h))
+        if want_text:
+            dst = [t.clone() for t in h[n:]]
+        else:
+            dst = [h[0].new_zeros(plan.info.dst_rows_per_buf, plan.hidden) for _ in range(plan.info.n_dst_bufs)]
+        # every copy of a source rank received the same sum: their cotangents add up, in the copy that forward reads
+        src = list(h[:n])
+        i = 0
+        for copies in plan.src_copies():
+            if copies > 1:
+                src[i] = torch.stack(src[i:i + copies]).float().sum(0).to(src[i].dtype)
+                src[i + 1:i + copies] = [t.detach() for t in src[i + 1:i + copies]]
+            i += copies
+        return (None, None, None, *boundary_transform(plan, src, dst))
 
 
 def boundary_transform(plan: Plan, src_bufs: Sequence[torch.Tensor], text_bufs: Sequence[torch.Tensor]):

@@ -260,6 +260,7 @@ class Plan:
     def __init__(self, src, dst: Grid, tmap, host_only: bool = False):
         L = _lib()
         self._h = C.c_void_p(0)
+        self._grids = [src] if isinstance(src, Grid) else list(src)
         if not isinstance(src, Grid):           # several source grids: tmap[e][m] = edge e, microbatch m
             srcs = list(src)
             if len(tmap) != len(srcs) or any(len(row) != len(tmap[0]) for row in tmap) or not tmap[0]:
@@ -321,6 +322,10 @@ class Plan:
     # -- introspection ------------------------------------------------------
     def src_rows(self) -> List[int]:
         return list(self._rows)
+
+    def src_copies(self) -> List[int]:
+        """TP copies of every source rank, in the order of the source buffers."""
+        return [g.tp for g in self._grids for _ in range(self.info.n_maps * g.dp)]
 
     def segments(self) -> List[hp_segment_t]:
         n = self.info.n_segments

@@ -203,6 +203,64 @@ def test_autograd_gives_only_the_gradients_that_are_wanted(src_grad, text_grad, 
     plan.close()
 
 
+@pytest.mark.parametrize("tp_src,src_on,text_on,maps", [(1, True, True, 1), (2, True, True, 1), (3, True, False, 2),
+                                                        (1, False, True, 1)])
+def test_second_derivatives(tp_src, src_on, text_on, maps):
+    """Gradients taken with create_graph, differentiated again, against autograd of the definition in 64 bits: every copy of a
+    source rank has the gradient of its rows, text embeddings that of theirs, and none from under the image rows."""
+    rng = np.random.default_rng(tp_src)
+    src, dst = wl.Grid(tp=tp_src, dp=2), wl.Grid(tp=2, cp=2, cp_split=wl.CP_ZIGZAG, row_order=wl.ROW_SBH)
+    tms = [wl.token_map_from_lens(rng, 2, 24, 9, [[5, 7], [9]]) for _ in range(maps)]
+    for tm in tms:
+        tm.dtype = wl.DT_F32
+    plan = hp.hp_plan_create_batched(src, dst, tms) if maps > 1 else hp.hp_plan_create(src, dst, tms[0])
+    probs = [oracle.Problem(src, dst, tm) for tm in tms]
+    rows, drows, n_dst = plan.src_rows(), plan.info.dst_rows_per_buf, plan.info.n_dst_bufs
+    new = lambda r: torch.from_numpy(rng.standard_normal((r, 9)))                     # noqa: E731
+    x, t, u, v = [new(r) for r in rows], [new(drows) for _ in range(n_dst)], [new(r) for r in rows], [new(drows) for _ in range(n_dst)]
+    per_src, per_dst = len(rows) // maps, n_dst // maps
+
+    # the definition: for each destination buffer the source buffer and row of its image rows
+    where = []
+    for m, prob in enumerate(probs):
+        for j in range(per_dst):
+            sb, sr = (torch.from_numpy(np.asarray(a)).long() for a in prob.forward_map(j))
+            where.append((torch.where(sb >= 0, sb + m * per_src, sb), sr))
+
+    def definition(xs, ts):
+        outs = []
+        for (sb, sr), b in zip(where, ts):
+            o = [xs[int(s)][int(r)] if s >= 0 else b[k] for k, (s, r) in enumerate(zip(sb, sr))]
+            outs.append(torch.stack(o))
+        return outs
+
+    def second(xs, ts, us, vs, transform, ref):
+        xs = [a.clone().requires_grad_(src_on) for a in xs]
+        ts = [a.clone().requires_grad_(text_on) for a in ts]
+        read = [xs[i - i % tp_src] for i in range(len(xs))] if ref else xs             # forward reads copy 0
+        outs = transform(read, [a.clone() for a in ts])
+        loss = sum((o ** 3).sum() * (1 + k) for k, o in enumerate(outs))
+        wanted = xs * src_on + ts * text_on
+        if ref:                                                                        # ... and every copy gets its gradient
+            wanted = [xs[i - i % tp_src] for i in range(len(xs))] * src_on + ts * text_on
+        g = torch.autograd.grad(loss, wanted, create_graph=True)
+        s = sum((a * (b ** 2 + b)).sum() for a, b in zip(us * src_on + vs * text_on, g))
+        leaders = xs[::tp_src] * src_on + ts * text_on
+        return [a.detach() for a in g], torch.autograd.grad(s, leaders)
+
+    x = [x[i - i % tp_src] for i in range(len(x))]          # the copies of a rank hold the same rows
+    want_g, want_s = second(x, t, u, v, definition, True)
+    dev = lambda a: [b.float().cuda() for b in a]                                      # noqa: E731
+    got_g, got_s = second(dev(x), dev(t), dev(u), dev(v), lambda a, b: hp.boundary_transform(plan, a, b), False)
+    # all sums are of a few dozen terms in binary32: 2^-24 each, measured against the largest value
+    for got, want in ((got_g, want_g), (got_s, want_s)):
+        assert len(got) == len(want)
+        for a, b in zip(got, want):
+            scale = float(b.abs().max()) if b.numel() else 1.0
+            assert torch.allclose(a.cpu().double(), b, rtol=0, atol=1e-5 * scale)
+    plan.close()
+
+
 def test_plans_made_while_the_last_ones_still_run():
     """Plans with tables in device memory, each used on one of two busy streams and dropped at once: every launch reads
     its own plan's tables."""
