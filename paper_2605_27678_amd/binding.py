@@ -89,19 +89,32 @@ class _Desc(C.Structure):
 
 
 def _load_marshal():
-    """Loads hp_marshal.so once.  Only called when torch is there (it needs its libraries)."""
+    """Loads hp_marshal.so once.  Only called when torch is there (it needs its libraries).  Without it, or with one that
+    was built for another torch, every call takes the way through Python."""
     global _marshal
     from importlib.machinery import ExtensionFileLoader
     from importlib.util import module_from_spec, spec_from_file_location
     path = os.path.join(_PKG, "hp_marshal.so")
-    if not os.path.exists(path):
-        raise RuntimeError(f"{path} is missing: build it first (python -m paper_2605_27678_amd.build)")
-    loader = ExtensionFileLoader("hp_marshal", path)
-    module = module_from_spec(spec_from_file_location("hp_marshal", path, loader=loader))
-    loader.exec_module(module)
+    try:
+        loader = ExtensionFileLoader("hp_marshal", path)
+        module = module_from_spec(spec_from_file_location("hp_marshal", path, loader=loader))
+        loader.exec_module(module)
+        if module.torch_version != sys.modules["torch"].__version__:
+            raise ImportError(f"it was built for torch {module.torch_version}")
+    except (ImportError, OSError) as e:
+        import warnings
+        warnings.warn(f"{path} is not used, calls take a few microseconds more ({e}); "
+                      "python -m paper_2605_27678_amd.build builds it", RuntimeWarning, stacklevel=4)
+        _marshal = _leave
+        return
     for name in ("hp_forward", "hp_forward_static", "hp_backward", "hp_backward_accumulate", "hp_text_grads"):
         _ADDR[name] = C.cast(getattr(_lib(), name), C.c_void_p).value
     _marshal = module.call
+
+
+def _leave(*args):
+    """In the place of hp_marshal's call(): leaves every call to the way through Python."""
+    return None
 
 
 def _lib():
@@ -340,7 +353,7 @@ class Plan:
             if "torch" not in sys.modules:
                 return False
             _load_marshal()
-        rc = _marshal(_ADDR[name], self._h.value or 0, self._desc_at, kind_a, a, kind_b, b, stream)
+        rc = _marshal(_ADDR.get(name, 0), self._h.value or 0, self._desc_at, kind_a, a, kind_b, b, stream)
         if rc is None:
             return False
         if rc < 0:

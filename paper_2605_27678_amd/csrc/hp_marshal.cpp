@@ -97,4 +97,12 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "hp_marshal", nullptr, -1, methods,
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit_hp_marshal(void) { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit_hp_marshal(void) {
+    PyObject *m = PyModule_Create(&module);
+    // a tensor's layout is that of the torch it was compiled against: the binding compares
+    if (m && PyModule_AddStringConstant(m, "torch_version", HP_TORCH_VERSION) < 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}

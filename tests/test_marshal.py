@@ -1,4 +1,9 @@
 """The marshalling extension: what it takes is what the way through Python takes, and what it leaves is still reported."""
+import os
+import subprocess
+import sys
+import warnings
+
 import numpy as np
 import pytest
 import torch
@@ -31,6 +36,49 @@ def test_host_buffers_and_foreign_objects_take_the_way_through_python():
     plan.close()
     with pytest.raises(ValueError):
         hp.hp_forward(plan, src, dst)
+
+
+def test_the_binding_goes_on_without_the_extension(monkeypatch, tmp_path):
+    monkeypatch.setattr(binding, "_PKG", str(tmp_path))
+    monkeypatch.setattr(binding, "_marshal", None)
+    plan = make(True)
+    src, dst = buffers(plan, "cpu")
+    with pytest.warns(RuntimeWarning, match="hp_marshal.so is not used"):
+        with pytest.raises(ValueError, match="contiguous CUDA tensor"):
+            hp.hp_forward(plan, src, dst)
+    with warnings.catch_warnings():
+        warnings.simplefilter("error")                      # said once
+        assert plan._call("hp_forward", binding.SRC, src, binding.DST, dst, None) is False
+
+
+def test_an_extension_for_another_torch_is_not_used(monkeypatch):
+    monkeypatch.setattr(binding, "_marshal", None)
+    monkeypatch.setattr(torch, "__version__", "0.0")
+    with pytest.warns(RuntimeWarning, match="built for torch"):
+        assert make(True)._call("hp_forward", binding.SRC, [], binding.DST, [], None) is False
+
+
+@pytest.mark.parametrize("gone", ["torch", "g++", "headers"])
+def test_the_library_builds_without_the_extension(monkeypatch, tmp_path, gone):
+    from paper_2605_27678_amd import build
+    lib, ext, ran = tmp_path / "libhp.so", tmp_path / "hp_marshal.so", []
+    ext.write_text("an older one")
+    monkeypatch.setattr(build, "LIB_PATH", str(lib))
+    monkeypatch.setattr(build, "MARSHAL_PATH", str(ext))
+    if gone == "torch":
+        monkeypatch.setitem(sys.modules, "torch", None)
+
+    def run(cmd, **kw):
+        ran.append(os.path.basename(cmd[0]))
+        if cmd[0] == "g++" and gone == "g++":
+            raise FileNotFoundError("g++")
+        if cmd[0] != "g++":
+            lib.write_text("built")
+        return subprocess.CompletedProcess(cmd, int(cmd[0] == "g++"), "", "no headers")
+
+    monkeypatch.setattr(build.subprocess, "run", run)
+    assert build.build_library() == str(lib) and lib.exists() and not ext.exists()
+    assert ran[-1] == "hipcc" and ("g++" in ran) == (gone != "torch")
 
 
 @pytest.mark.gpu
