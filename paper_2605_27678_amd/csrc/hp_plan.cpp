@@ -281,8 +281,7 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
     else if (c == 8 && dense && in(fwd, 40, 450)) set(f, K1, 64, 6);            // 0.99-1.25; [S,B,H] order 0.93-1.02
     else if (c >= 10 && dense && in(fwd, 100, 450)) set(f, K1, 64, 5);          // 0.96-1.28; 9 copies 0.91-1.09, [S,B,H] 0.86-1.05
 
-    // With one and two copies a workgroup moves little for each search, and the depth of the tree (16 segments a level)
-    // decides.
+    // With few copies a workgroup moves little for each search, and the depth of the tree (16 segments a level) decides.
     const double bwd = (double)p->bwd_bytes;
     if (c == 1 && s == 1 && in(bwd, 25, 200)) {
         if (segs <= 16) set(b, K1, 64, 28);                                     // 1.01-1.09; more segments 0.73-0.86
@@ -290,11 +289,11 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
     else if (c == 1 && s == 1 && bwd >= 200 * MB) {
         if (segs <= 256) set(b, K4, 128, 24);                                   // 0.99-1.04; more segments 0.95-1.00
     }
-    else if (c == 2 && s == 1 && in(bwd, 80, 250)) {
-        if (segs <= 16) set(b, K8, 256, 24);                                    // 0.99-1.06; more segments 0.96-1.02, 40 MB 0.97-1.05
+    else if (c == 2 && s == 1 && in(bwd, 80, 290)) {
+        if (segs <= 16) set(b, K8, 256, 24);                                    // 0.99-1.06; more segments 0.95-1.02, 40 MB 0.97-1.05
     }
     else if (c == 2 && s > 1 && bwd >= 40 * MB) set(b, K1, 64, 20);             // 1.05-1.09; 27 MB: 0.95-1.02
-    else if (c == 4 && s == 1 && in(bwd, 35, 260)) set(b, K1, 64, 24);          // 1.01-1.14; 300 MB: 0.97-1.04, 400 MB: 0.96
+    else if (c == 4 && s == 1 && in(bwd, 35, segs <= 16 ? 360 : 220)) set(b, K1, 64, 24);   // 1.02-1.14; more segments from 240 MB 0.95-1.04
     else if (generic && c < 8 && bwd >= (c <= 5 ? 16 : 30) * MB &&              // 3 copies 1.03-1.35, 5 to 7 0.98-1.28
              !(f32 && (s > 1 ? bwd >= 600 * MB : c == 7 && bwd >= 500 * MB)))   // there 0.97-1.02 and 0.95-1.02
         set(b, K1, 64, c <= 5 && s == 1 ? 28 : 24);

@@ -513,12 +513,12 @@ def test_binary32_accumulation_leaves_its_starting_shape_only_where_another_is_f
 @pytest.mark.parametrize("direction,tp,tp_src,mbytes,f32,images,want", [
     # two copies, backward: large workgroups while the root of the search tree is all of it
     (1, 2, 1, 166, True, 24, (1024, 64, 30)), (1, 2, 1, 166, True, 16, (8192, 256, 24)),
-    (1, 2, 1, 166, False, 17, (1024, 64, 30)), (1, 2, 1, 60, False, 1, (1024, 64, 30)), (1, 2, 1, 280, False, 1, (1024, 64, 30)),
+    (1, 2, 1, 166, False, 17, (1024, 64, 30)), (1, 2, 1, 60, False, 1, (1024, 64, 30)), (1, 2, 1, 300, False, 1, (1024, 64, 30)),
     # one copy, backward: small tiles while it is, and larger workgroups with two levels at most
     (1, 1, 1, 100, False, 16, (1024, 64, 28)), (1, 1, 1, 100, False, 17, (2048, 64, 30)), (1, 1, 1, 150, True, 40, (2048, 64, 30)),
     (1, 1, 1, 1000, False, 256, (4096, 128, 24)), (1, 1, 1, 1000, False, 257, (2048, 64, 30)), (1, 1, 1, 20, False, 1, (2048, 64, 30)),
     # few bytes, and what is faster in one element type only
-    (1, 4, 1, 20, True, 1, (1024, 64, 16)), (1, 4, 1, 150, False, 1, (1024, 64, 24)), (1, 4, 1, 300, False, 1, (1024, 64, 16)),
+    (1, 4, 1, 20, True, 1, (1024, 64, 16)), (1, 4, 1, 150, False, 1, (1024, 64, 24)), (1, 4, 1, 300, False, 16, (1024, 64, 24)), (1, 4, 1, 300, False, 17, (1024, 64, 16)),
     (1, 7, 1, 1200, True, 1, (1024, 64, 16)), (1, 7, 1, 1200, False, 1, (1024, 64, 24)), (1, 6, 1, 20, False, 1, (1024, 64, 16)),
     (1, 3, 2, 2500, True, 1, (1024, 64, 16)), (1, 3, 2, 2500, False, 1, (1024, 64, 24)), (1, 12, 1, 150, True, 1, (1024, 64, 16)),
     (1, 12, 1, 150, False, 1, (4096, 128, 24)), (1, 2, 2, 27, False, 1, (1024, 64, 16)), (1, 2, 2, 200, False, 1, (1024, 64, 20)),
