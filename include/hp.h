@@ -301,11 +301,13 @@ int hp_zero_image_rows(const hp_plan_t *plan, void *const *dst_bufs, void *strea
  * embeddings that hp_forward overwrote at the image positions: text_grad_bufs
  * receive a copy of dst_grad_bufs in which the image-token rows are zero.  What
  * hp_zero_image_rows gives on a copy, without reading those rows or writing them
- * twice, and for every buffer in one launch or a few.
+ * twice, and for every buffer in one launch or a few.  Where the runs of text and
+ * image rows are too many and too short for that, it is a copy of the whole
+ * buffers and hp_zero_image_rows.
  *   dst_grad_bufs, text_grad_bufs: HOST arrays of n_dst_bufs DEVICE pointers,
  *             shapes as for hp_forward's dst_bufs; no buffer may overlap another.
  *             Every row of every text_grad_bufs buffer is written.
- * The first call on a plan works out its runs of text and image rows on the host;
+ * The first call on a plan works out on the host which it is, and the runs;
  * nothing is allocated on the device.  Returns after enqueueing. */
 int hp_text_grads(const hp_plan_t *plan, const void *const *dst_grad_bufs,
                   void *const *text_grad_bufs, void *stream);
@@ -412,7 +414,9 @@ int hp_plan_tune_accumulate(hp_plan_t *plan, const void *const *dst_grad_bufs,
  * (-1, their initial value): the plan then picks them from its replica counts - the more buffers a
  * row's traffic spreads over (1 + TP_dst forward, TP_dst + TP_src backward) the
  * lower the cap, so that about 100 KB per compute unit stay in flight; the
- * figures are what hp_plan_tune finds most often per replica count.
+ * figures are what hp_plan_tune finds most often per replica count - and, where
+ * other shapes were measured to be faster, from the bytes that the launch moves,
+ * the element type and the number of segments.
  * Returns HP_EINVAL for an unknown key or an out-of-range value. */
 #define HP_AUTO (-1)
 int hp_set_option(const char *key, int64_t value);

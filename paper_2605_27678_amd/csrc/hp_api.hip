@@ -706,10 +706,14 @@ void launch_tiles(const hp_plan *p, Direction dir, int nontemporal, const Launch
 // Whether a plan's tables travel with its launches: they fit behind the buffer
 // pointers - the descriptors and the level below the root, there are no more for
 // so few segments; the same for every tile size, because every tree has as many
-// keys - and a launch moves less than 1 GiB.  From there on the upload is lost in
-// the launch (170 us and more), and tables in device memory are the faster ones to
-// walk (2.06 GB backward from four copies: 311 us with them in the arguments, 308
-// in device memory; below, 330 MB made, used and dropped: 53 against 79 us).
+// keys - and a launch moves less than 1 GiB.  Such a plan takes 13 us to make and
+// one whose tables are uploaded 32, which a step that makes its plan waits for
+// while its launches are short (made, used once each way and dropped, 165 MB a
+// launch: 54.3 against 56.8 us).  A launch reads them from there 0.2 to 0.5 us
+// later than from device memory (50 MB: 0.95-0.99 of the rate, 150 MB 0.97-1.00);
+// from 300 MB on that is within 0.3 % either way (1, 2, 4 and 8 copies, both
+// element types, 50 MB to 2.4 GB), and the upload is hidden behind the launches,
+// so that where the line lies between 300 MB and 1 GiB matters to neither.
 constexpr int64_t kMaxInlineBytes = (int64_t)1 << 30;
 size_t inline_seg_at(const hp_plan *p) {
     return (offsetof(Args, b) + (size_t)(p->n_src_bufs + p->n_dst_bufs) * sizeof(void *) + 63) / 64 * 64;

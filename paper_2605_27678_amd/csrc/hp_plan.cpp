@@ -351,10 +351,10 @@ void default_launches(hp_plan *p) {
     }
     const int c = p->dst_copies, s = p->src_copies;
     Launch f{1, 64, c <= 1 ? 24 : c <= 4 ? 12 : c <= 7 ? 8 : 5, 2};                          // 2 KiB tiles
-    if (c == 2) f = Launch{2, 256, 28, 2};      // two copies: 4 KiB tiles, 256 lanes (+3.6 % on config 4 over 2 KiB x 64, cap 14)
+    if (c == 2) f = Launch{2, 256, 28, 2};      // two copies: 4 KiB tiles, 256 lanes (sixteen microbatches of hidden 8192 in one launch: +3.6 % over 2 KiB x 64, cap 14)
     Launch b = c + s <= 2 ? Launch{1, 64, 30, 3} : c + s == 3 ? Launch{0, 64, 30, 3} : Launch{0, 64, 16, 3};
     // accumulating backward: the binary32 accumulators are read and written, 2 * 4 / elem_bytes row sizes per copy;
-    // caps as the measured search finds them for 6, 8 and 16 streams (configs 4, 3 and 5)
+    // caps as the measured search finds them for 6, 8 and 16 streams (two, four and eight copies; the last from two source copies)
     const int acc_streams = c + s * 8 / p->elem_bytes;
     Launch a{1, 64, acc_streams <= 4 ? 16 : acc_streams <= 6 ? 13 : acc_streams <= 8 ? 11 : acc_streams <= 12 ? 9 : 7, 3};
     by_size(p, f, b, a);

@@ -80,8 +80,8 @@ def test_long_context_image_counts(k):
 @pytest.mark.parametrize("hidden", [7, 9, 12, 100, 320, 1000, 5120])
 def test_long_context_spans_at_several_hidden_sizes(hidden):
     """The full config-3 grid and spans (34 segments, ragged tails, spans that
-    straddle zigzag chunk borders) with rows of 14 B .. 10 KB: exercises the
-    2/4/8/16-byte lane paths and many tiles per segment."""
+    straddle zigzag chunk borders) with rows of 14 B .. 10 KB: whole-line and
+    ragged rows, rows shorter than a 16-byte chunk and many tiles per segment."""
     w = wl.long_context(n_images=9)
     tm = replace(w.maps[0], hidden=hidden)
     hp.hp_set_option("tile_bytes_fwd", 1024)
@@ -202,7 +202,7 @@ def test_all_ones_returns_replica_count_and_text_rows_untouched():
 
 
 def test_misaligned_pointers_use_narrow_lanes():
-    """Views that start 2 bytes into an allocation: only 2-byte alignment."""
+    """Views that start 2 bytes into an allocation: only 2-byte alignment (16-byte lanes at an address that they do not divide)."""
     rng = np.random.default_rng(8)
     tm = wl.token_map_from_lens(rng, 1, 64, 24, [[10, 20]])
     src, dst = wl.Grid(dp=2), wl.Grid(tp=2, cp=2)
