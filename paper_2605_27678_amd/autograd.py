@@ -80,11 +80,11 @@ class _BoundaryGrads(torch.autograd.Function):
         if not want_src:                                    # the image rows get nothing
             return (None, None, None, *_BoundaryGrads.apply(plan, ctx.src_meta, ctx.want, *h))
         if want_text:
-            dst = [t.clone() for t in h[n:]]
+            dst = [t.clone(memory_format=torch.contiguous_format) for t in h[n:]]
         else:
             dst = [h[0].new_zeros(plan.info.dst_rows_per_buf, plan.hidden) for _ in range(plan.info.n_dst_bufs)]
         # every copy of a source rank received the same sum: their cotangents add up, in the copy that forward reads
-        src = list(h[:n])
+        src = [t.contiguous() for t in h[:n]]
         i = 0
         for copies in plan.src_copies():
             if copies > 1:

@@ -246,7 +246,8 @@ def test_second_derivatives(tp_src, src_on, text_on, maps):
         g = torch.autograd.grad(loss, wanted, create_graph=True)
         s = sum((a * (b ** 2 + b)).sum() for a, b in zip(us * src_on + vs * text_on, g))
         leaders = xs[::tp_src] * src_on + ts * text_on
-        return [a.detach() for a in g], torch.autograd.grad(s, leaders)
+        plain = torch.autograd.grad(sum(b.sum() + b.t().reshape(-1)[::2].sum() for b in g), leaders, retain_graph=True)
+        return [a.detach() for a in g], [*plain, *torch.autograd.grad(s, leaders)]  # cotangents expanded, strided, plain
 
     x = [x[i - i % tp_src] for i in range(len(x))]          # the copies of a rank hold the same rows
     want_g, want_s = second(x, t, u, v, definition, True)
