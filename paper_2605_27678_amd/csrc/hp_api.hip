@@ -19,6 +19,7 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 #include "hp.h"
@@ -29,7 +30,6 @@ namespace {
 
 using hp::KParams;
 using hp::TileView;
-using hp::locate_tile;
 
 thread_local int g_last_hip_error = 0;
 
@@ -72,39 +72,156 @@ template <int N> struct Bytes {
 template <> struct Bytes<4> { typedef uint32_t type; typedef uint32_t mem __attribute__((aligned(2))); };
 template <> struct Bytes<2> { typedef uint16_t type; typedef uint16_t mem; };
 
+// Device memory, said so: addresses that come out of a table would be taken for
+// flat ones.
+#define HP_GLOBAL __attribute__((address_space(1)))
+typedef HP_GLOBAL char gchar;
+
 template <int N, bool NT>
-__device__ __forceinline__ typename Bytes<N>::type ld(const char *p) {
-    typedef typename Bytes<N>::mem M;
-    if constexpr (NT) return __builtin_nontemporal_load((const M *)p);
-    else return *(const M *)p;
+__device__ __forceinline__ typename Bytes<N>::type ld(const gchar *p) {
+    typedef HP_GLOBAL const typename Bytes<N>::mem M;
+    if constexpr (NT) return __builtin_nontemporal_load((M *)p);
+    else return *(M *)p;
 }
 template <int N, bool NT>
-__device__ __forceinline__ void st(char *p, typename Bytes<N>::type v) {
-    typedef typename Bytes<N>::mem M;
-    if constexpr (NT) __builtin_nontemporal_store((M)v, (M *)p);
-    else *(M *)p = (M)v;
+__device__ __forceinline__ void st(gchar *p, typename Bytes<N>::type v) {
+    typedef HP_GLOBAL typename Bytes<N>::mem M;
+    if constexpr (NT) __builtin_nontemporal_store((typename Bytes<N>::mem)v, (M *)p);
+    else *(M *)p = (typename Bytes<N>::mem)v;
 }
 
 // What the tiles of a launch look like.  Three kernels, because the start of a
 // workgroup is what a launch of short-lived ones waits for: testing for ragged
-// rows in the kernel of whole lines cost 3 % there (110 MB forward to two copies:
-// 25.5 -> 26.4 us).
+// rows in the kernel of whole lines cost 3 % there (110 MB forward to two copies,
+// when a lookup still took twice as long: 25.5 -> 26.4 us).
 enum Tiles {
     kLines,     // dense on both sides, and every row is whole 128-byte lines
     kRagged,    // dense on both sides, rows of any length
     kStrided,   // groups of whole row-strided rows ([S,B,H] order with several samples per rank, rows shorter than a tile)
 };
 
+// Workgroups are handed to the chip's 8 accelerator dies (XCDs, each with its
+// own L2) round-robin by workgroup id.
+constexpr uint32_t kXcds = 8;
+
+// The kernel's arguments are one Args and begin with it.
+__device__ __forceinline__ uintptr_t args_base() { return (uintptr_t)__builtin_amdgcn_kernarg_segment_ptr(); }
+
+// Where a workgroup finds its tile are three reads, each at the address that the
+// one before it gave: the root of the tree, a segment, the buffers' addresses.
+// When a launch starts none of that is in a cache.  The first workgroup of each
+// XCD therefore touches all of the arguments at once, a lane a line, and the two
+// later reads of its XCD's workgroups find them in the L2: 0.3 to 0.6 us a launch
+// (42 MB to eight copies 8.2 -> 7.7 us, 45 MB a direction in [S,B,H] order, both
+// 19.4 -> 18.1; eight workgroups of an XCD instead of one: 0.1 us less of it, all
+// of them: 0.3).  What was read is used for nothing; touched() keeps the loads.
+__device__ __forceinline__ uint32_t touch_args() {
+    uint32_t v = 0;
+    if (blockIdx.x < kXcds && threadIdx.x < sizeof(Args) / hp::kLineBytes)
+        v = *(const HP_GLOBAL uint32_t *)(args_base() + threadIdx.x * hp::kLineBytes);
+    return v;
+}
+__device__ __forceinline__ void touched(uint32_t v) {
+    if (blockIdx.x < kXcds) asm volatile("" ::"v"(v));      // only there: it waits for the stores as well
+}
+
+// The addresses of the buffers, in the arguments.
+__device__ __forceinline__ const HP_TABLE uint64_t *buffers() {
+    return (const HP_TABLE uint64_t *)(args_base() + offsetof(Args, b));
+}
+__device__ __forceinline__ gchar *at(uint64_t address) { return (gchar *)address; }
+
+// Keeps a wave busy with scalar additions, n rounds of some eleven instructions,
+// before its first load.  A compute unit's waves share the scalar unit, so that those
+// which start together come out of this one after the other and their loads reach
+// memory in an even stream; where a few copies are read in small tiles, memory is
+// faster for that by more than the time it takes (pace_of).  Sleeping as long does
+// not do it: the waves wake as they went (2.06 GB from four copies: no gain at 64 to
+// 2048 cycles).
+__device__ __forceinline__ void pace(uint32_t n) {
+    uint32_t x = 0, y = 0;
+    for (uint32_t i = 0; i < n; ++i)
+        asm volatile("s_add_u32 %0, %0, 1\n\ts_add_u32 %1, %1, 1\n\ts_add_u32 %0, %0, 1\n\ts_add_u32 %1, %1, 1\n\t"
+                     "s_add_u32 %0, %0, 1\n\ts_add_u32 %1, %1, 1\n\ts_add_u32 %0, %0, 1\n\ts_add_u32 %1, %1, 1"
+                     : "+s"(x), "+s"(y) : : "scc");
+}
+
 // The tile of this workgroup.  Ragged: its ends on lines of the first destination copy.
 template <Tiles TILES>
 __device__ __forceinline__ TileView my_tile(const Args &a) {
-    // the kernel's arguments are one Args and begin with it
-    const uintptr_t args = (uintptr_t)__builtin_amdgcn_kernarg_segment_ptr();
+    const uintptr_t args = args_base();
     const uintptr_t segs = a.k.seg_at ? args + a.k.seg_at : (uintptr_t)a.k.segs;
     const uintptr_t tree = a.k.seg_at ? args + a.k.tree_at : (uintptr_t)a.k.tree;
-    TileView t = locate_tile(a.k, (const HP_TABLE hp::Seg *)segs, (const HP_TABLE uint32_t *)tree, blockIdx.x);
-    if (TILES == kRagged) hp::align_tile(t, (uint64_t)(uintptr_t)a.b.p[a.k.dst_base + t.dst_buf0]);
+    TileView t = hp::locate_tile<TILES == kStrided ? hp::kRowGroups : hp::kWholeTiles>(
+        a.k, (const HP_TABLE hp::Seg *)segs, (const HP_TABLE uint32_t *)tree, blockIdx.x);
+    if (TILES == kRagged) hp::align_tile(t, buffers()[a.k.dst_base + t.dst_buf0]);
     return t;
+}
+
+// How many chunks of UNIT bytes a tile has, and how many are whole; tiles of lines have no others.
+template <uint32_t UNIT, Tiles TILES>
+__device__ __forceinline__ void count_chunks(const KParams &k, const TileView &t, uint32_t &all, uint32_t &whole) {
+    if (TILES == kLines) all = whole = t.nbytes / UNIT;
+    else hp::count_chunks<UNIT, TILES != kStrided>(k, t, all, whole);
+}
+
+// N neighbouring addresses of the table, read with one instruction (N = 1: as is).
+// Left to itself the compiler reads one after the other and waits for each, with
+// nothing in flight yet: the two together, and the search, 45 MB a direction in
+// [S,B,H] order 18.1 -> 17.3 us, 166 MB to and from two copies 53.0 -> 52.2.
+template <int N> struct AddressWords {
+    typedef uint32_t type __attribute__((ext_vector_type(2 * N)));
+    typedef uint32_t mem __attribute__((ext_vector_type(2 * N), aligned(8)));
+    __device__ __forceinline__ static type read(const HP_TABLE uint64_t *b) { return *(const HP_TABLE mem *)b; }
+    __device__ __forceinline__ static uint64_t get(type w, int i) { return (uint64_t)w[2 * i + 1] << 32 | w[2 * i]; }
+};
+
+// Where a tile lies in the first copy of its source buffer and in its NREP
+// destination copies (0: in none of them, the count is known at run time only).
+// All the addresses are read before the first is used.
+template <int NREP>
+struct Places {
+    gchar *src, *dst[NREP > 0 ? NREP : 1];
+    // widen = bytes on the source side for each byte of a tile (accumulators: 2 or 1)
+    __device__ __forceinline__ Places(const KParams &k, const TileView &t, uint32_t widen = 1) {
+        const HP_TABLE uint64_t *b = buffers();
+        uint64_t s = b[t.src_buf];
+        if constexpr (NREP > 0) {
+            typedef AddressWords<NREP> W;
+            typename W::type w = W::read(b + (k.dst_base + t.dst_buf0));
+            asm("" : "+s"(s), "+s"(w));
+#pragma unroll
+            for (int r = 0; r < NREP; ++r) dst[r] = at(W::get(w, r) + t.dst_off);
+        }
+        src = at(s + t.src_off * widen);
+    }
+};
+
+// Calls f(r, addresses of a tile in copies r .. r + N - 1) for groups of N copies
+// that cover all of them: one group of NREP copies, or, where the count is known at
+// run time only, groups of four and a last one of what is left.
+template <int NREP, typename F>
+__device__ __forceinline__ void for_copies(const KParams &k, const TileView &t, const Places<NREP> &places, uint32_t nrep,
+                                           const F &f) {
+    if constexpr (NREP > 0) {
+        f(0u, places.dst);
+    } else {
+        const HP_TABLE uint64_t *b = buffers() + (k.dst_base + t.dst_buf0);
+        auto group = [&](uint32_t r, auto size) {
+            constexpr int N = decltype(size)::value;
+            typedef AddressWords<N> W;
+            const typename W::type w = W::read(b + r);
+            gchar *p[N];
+#pragma unroll
+            for (int i = 0; i < N; ++i) p[i] = at(W::get(w, i) + t.dst_off);
+            f(r, p);
+        };
+        uint32_t r = 0;
+        for (; r + 4 <= nrep; r += 4) group(r, std::integral_constant<int, 4>());
+        if (nrep - r == 3) group(r, std::integral_constant<int, 3>());
+        else if (nrep - r == 2) group(r, std::integral_constant<int, 2>());
+        else if (nrep - r == 1) group(r, std::integral_constant<int, 1>());
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -115,60 +232,74 @@ __device__ __forceinline__ TileView my_tile(const Args &a) {
 // a tile: lanes past the end re-read the tile's last chunk and skip the stores,
 // so there is still no branch around a load.
 template <int NREP, int U, Tiles TILES, bool GUARD, bool NTL, bool NTS>
-__device__ __forceinline__ void forward_group(const BufTable &bufs, const KParams &k, const TileView &t,
-                                              const char *src, uint32_t nrep, uint32_t done, uint32_t n) {
+__device__ __forceinline__ void forward_group(const KParams &k, const TileView &t, const Places<NREP> &places,
+                                              uint32_t nrep, uint32_t done, uint32_t n) {
     u32x4 v[U];
     uint32_t i[U];
     hp::ChunkView c[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        i[u] = done + u * blockDim.x + threadIdx.x;
+        i[u] = done + u * k.block + threadIdx.x;
         c[u] = hp::chunk_at<16, TILES != kStrided, GUARD && TILES == kRagged>(k, t, GUARD ? min(i[u], n - 1) : i[u]);
-        v[u] = ld<16, NTL>(src + c[u].src);
+        v[u] = ld<16, NTL>(places.src + c[u].src);
     }
-#pragma unroll 4
-    for (uint32_t r = 0; r < nrep; ++r) {
-        char *dst = (char *)bufs.p[k.dst_base + t.dst_buf0 + r] + t.dst_off;
+    auto store = [&](gchar *p) {
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            if (!GUARD || i[u] < n) st<16, NTS>(dst + (TILES != kStrided ? c[u].src : c[u].dst), v[u]);
-    }
+            if (!GUARD || i[u] < n) st<16, NTS>(p + (TILES != kStrided ? c[u].src : c[u].dst), v[u]);
+    };
+    for_copies<NREP>(k, t, places, nrep, [&](uint32_t, auto &p) {
+        constexpr int N = sizeof(p) / sizeof(*p);
+#pragma unroll
+        for (int r = 0; r < N; ++r) store(p[r]);
+    });
 }
 
+// Whether a lane takes one chunk at a time through all copies, not two or four.  In
+// the shapes that the launches take, to four copies: 2.06 GB 380 -> 326 us, 1.13 GB
+// 204 -> 182, 205 MB and less no difference; three copies: 800 MB 133 -> 128, 2 GB
+// 328 -> 306; one copy: 2 GB 317 -> 310; sixteen: 2 GB 370 -> 346.  To eight copies
+// two at a time are the faster (2.2 GB 348 against 401 us), and so to the counts
+// that have no kernel of their own (six, 800 MB: 133 against 153).
+template <int NREP> constexpr bool kForwardSingly = NREP == 1 || NREP == 3 || NREP == 4;
+
 template <int NREP, Tiles TILES, bool NTL, bool NTS>
-__device__ __forceinline__ void forward_tile(const BufTable &bufs, const KParams &k, const TileView &t, uint32_t nrep) {
-    const char *src = (const char *)bufs.p[t.src_buf] + t.src_off;
+__device__ __forceinline__ void forward_tile(const KParams &k, const TileView &t, uint32_t nrep) {
+    const Places<NREP> places(k, t);
+    if constexpr (NREP == 0) pace(k.pace);
     uint32_t n, whole;
-    hp::count_chunks<16, TILES != kStrided>(k, t, n, whole);
-    const uint32_t step = blockDim.x;
+    count_chunks<16, TILES>(k, t, n, whole);
+    const uint32_t step = k.block;
     uint32_t done = 0;                                       // uniform
     if (TILES != kLines && __builtin_expect(n == 0, 0)) {                       // shorter than a chunk
         for (uint32_t i = threadIdx.x; i < t.nbytes / 2; i += step) {
             const hp::ChunkView c = hp::element_at<2>(k, t, i);
-            const uint16_t v = ld<2, NTL>(src + c.src);
+            const uint16_t v = ld<2, NTL>(places.src + c.src);
             for (uint32_t r = 0; r < nrep; ++r)
-                st<2, NTS>((char *)bufs.p[k.dst_base + t.dst_buf0 + r] + t.dst_off + c.dst, v);
+                st<2, NTS>(at(buffers()[k.dst_base + t.dst_buf0 + r] + t.dst_off) + c.dst, v);
         }
         return;
     }
-    for (; whole - done >= 4 * step; done += 4 * step)
-        forward_group<NREP, 4, TILES, false, NTL, NTS>(bufs, k, t, src, nrep, done, n);
-    if (whole - done >= 2 * step) {
-        forward_group<NREP, 2, TILES, false, NTL, NTS>(bufs, k, t, src, nrep, done, n);
-        done += 2 * step;
+    if constexpr (!kForwardSingly<NREP>) {
+        for (; whole - done >= 4 * step; done += 4 * step)
+            forward_group<NREP, 4, TILES, false, NTL, NTS>(k, t, places, nrep, done, n);
+        if (whole - done >= 2 * step) {
+            forward_group<NREP, 2, TILES, false, NTL, NTS>(k, t, places, nrep, done, n);
+            done += 2 * step;
+        }
     }
-    if (whole - done >= step) {
-        forward_group<NREP, 1, TILES, false, NTL, NTS>(bufs, k, t, src, nrep, done, n);
-        done += step;
-    }
-    if (n - done > 0) forward_group<NREP, 1, TILES, true, NTL, NTS>(bufs, k, t, src, nrep, done, n);
+    for (; whole - done >= step; done += step)
+        forward_group<NREP, 1, TILES, false, NTL, NTS>(k, t, places, nrep, done, n);
+    if (n - done > 0) forward_group<NREP, 1, TILES, true, NTL, NTS>(k, t, places, nrep, done, n);
 }
 
 template <int NREP, Tiles TILES, bool NTL, bool NTS>
 __global__ void __launch_bounds__(1024)
 hp_forward_kernel(const Args a) {
+    const uint32_t touch = touch_args();
     const TileView t = my_tile<TILES>(a);
-    forward_tile<NREP, TILES, NTL, NTS>(a.b, a.k, t, NREP > 0 ? (uint32_t)NREP : a.k.dst_copies);
+    forward_tile<NREP, TILES, NTL, NTS>(a.k, t, NREP > 0 ? (uint32_t)NREP : a.k.dst_copies);
+    touched(touch);
 }
 
 // ---------------------------------------------------------------------------
@@ -176,16 +307,17 @@ hp_forward_kernel(const Args a) {
 // row of every destination copy is set to zero
 // ---------------------------------------------------------------------------
 template <Tiles TILES, bool NTS>
-__device__ __forceinline__ void zero_tile(const BufTable &bufs, const KParams &k, const TileView &t) {
+__device__ __forceinline__ void zero_tile(const KParams &k, const TileView &t) {
     uint32_t n, whole;
-    hp::count_chunks<16, TILES != kStrided>(k, t, n, whole);
+    count_chunks<16, TILES>(k, t, n, whole);
+    const HP_TABLE uint64_t *b = buffers() + (k.dst_base + t.dst_buf0);
     for (uint32_t r = 0; r < k.dst_copies; ++r) {
-        char *dst = (char *)bufs.p[k.dst_base + t.dst_buf0 + r] + t.dst_off;
+        gchar *dst = at(b[r] + t.dst_off);
         if (TILES != kLines && n == 0) {
-            for (uint32_t i = threadIdx.x; i < t.nbytes / 2; i += blockDim.x)
+            for (uint32_t i = threadIdx.x; i < t.nbytes / 2; i += k.block)
                 st<2, NTS>(dst + hp::element_at<2>(k, t, i).dst, 0);
         } else {
-            for (uint32_t i = threadIdx.x; i < n; i += blockDim.x)
+            for (uint32_t i = threadIdx.x; i < n; i += k.block)
                 st<16, NTS>(dst + hp::chunk_at<16, TILES != kStrided, TILES == kRagged>(k, t, i).dst, (u32x4)0u);
         }
     }
@@ -194,7 +326,9 @@ __device__ __forceinline__ void zero_tile(const BufTable &bufs, const KParams &k
 template <Tiles TILES, bool NTS>
 __global__ void __launch_bounds__(1024)
 hp_zero_rows_kernel(const Args a) {
-    zero_tile<TILES, NTS>(a.b, a.k, my_tile<TILES>(a));
+    const uint32_t touch = touch_args();
+    zero_tile<TILES, NTS>(a.k, my_tile<TILES>(a));
+    touched(touch);
 }
 
 // ---------------------------------------------------------------------------
@@ -211,13 +345,15 @@ template <Tiles TILES, bool NTL>
 __global__ void __launch_bounds__(1024)
 hp_text_grads_kernel(const Args a) {
     const KParams &k = a.k;
+    const uint32_t touch = touch_args();
     const TileView t = my_tile<TILES>(a);
     // a run lies at the same place in both buffers
-    const char *src = (const char *)a.b.p[t.src_buf + blockIdx.y] + t.dst_off;
-    char *dst = (char *)a.b.p[k.dst_base + t.dst_buf0 + blockIdx.y] + t.dst_off;
+    const gchar *src = at(buffers()[t.src_buf + blockIdx.y] + t.dst_off);
+    gchar *dst = at(buffers()[k.dst_base + t.dst_buf0 + blockIdx.y] + t.dst_off);
+    touched(touch);
     uint32_t n, whole;
-    hp::count_chunks<16, TILES != kStrided>(k, t, n, whole);
-    const uint32_t step = blockDim.x;
+    count_chunks<16, TILES>(k, t, n, whole);
+    const uint32_t step = k.block;
     if (TILES != kLines && __builtin_expect(n == 0, 0)) {             // shorter than a chunk
         for (uint32_t i = threadIdx.x; i < t.nbytes / 2; i += step) {
             const uint64_t at = hp::element_at<2>(k, t, i).dst;
@@ -318,6 +454,15 @@ struct Elems {
 template <int DT, bool ACC>
 constexpr int kLaneElems = ACC || DT == HP_F32 ? 4 : 8;
 
+// From this many copies on a lane takes one chunk of each at a time, not two: a wave
+// then has four loads and more in flight as it is, and the waves' loads interleave
+// more finely (the best shape of each: 2.06 GB from four copies 313 -> 304 us, 2.4 GB
+// from eight 373 -> 366, 8.05 GB from eight to two source copies 1268 -> 1227; from
+// two and three copies no difference).  Accumulating, where half of a wave's bytes
+// are accumulators, two at a time are the better: 3.9 GB from two copies 1140 ->
+// 1060 us, 0.55 GB from eight 401 -> 377; four at a time are no better.
+constexpr int kSingly = 4;
+
 // U chunks of E elements per lane starting at chunk `done`, straight-line: the
 // loads of all replicas (groups of four when the replica count is only known at
 // run time) are issued before the first add.  GUARD as in forward_group; ELEMENT:
@@ -329,68 +474,65 @@ constexpr int kLaneElems = ACC || DT == HP_F32 ? 4 : 8;
 // before it computes too: an overwriting store repeats the same values, an
 // accumulating one leaves them out.
 template <int DT, int E, bool ACC, int NREP, int U, Tiles TILES, bool GUARD, bool NTL, bool NTS>
-__device__ __forceinline__ void backward_group(const BufTable &bufs, const KParams &k, const TileView &t,
+__device__ __forceinline__ void backward_group(const KParams &k, const TileView &t, const Places<NREP> &places,
                                                uint32_t nrep, uint32_t done, uint32_t n) {
     typedef Elems<DT, E> In;
     typedef Elems<ACC ? HP_F32 : DT, E> Out;
     typedef typename In::V VI;
     typedef typename Out::V VO;
     constexpr bool ELEMENT = E == 1;
-    constexpr int G = NREP > 0 ? NREP : 4;
     constexpr uint32_t kElemBytes = DT == HP_F32 ? 4 : 2;
     constexpr uint32_t kWiden = ACC ? 4 / kElemBytes : 1;      // accumulator bytes per gradient byte
     uint32_t i[U];
     hp::ChunkView c[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        i[u] = done + u * blockDim.x + threadIdx.x;
+        i[u] = done + u * k.block + threadIdx.x;
         const uint32_t ic = GUARD ? min(i[u], n - 1) : i[u];
         if constexpr (ELEMENT) c[u] = hp::element_at<kElemBytes>(k, t, ic);
         else c[u] = hp::chunk_at<In::kBytes, TILES != kStrided, GUARD && TILES == kRagged>(k, t, ic);
     }
-    // source-side offset of this tile in the output dtype
-    const uint64_t out_off = t.src_off * kWiden;
+    // the accumulators of the first source copy travel with the gradients
+    VO old[U];
+    if constexpr (ACC) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) old[u] = ld<Out::kBytes, NTL>(places.src + c[u].src * kWiden);
+    }
     float acc[U][E];
-    for (uint32_t r0 = 0; r0 < nrep; r0 += G) {
+    for_copies<NREP>(k, t, places, nrep, [&](uint32_t r0, auto &p) {
+        constexpr int G = sizeof(p) / sizeof(*p);
         VI v[G][U];
 #pragma unroll
         for (int g = 0; g < G; ++g) {
-            // past the last replica of a run-time count: re-read the last one, result unused
-            const uint32_t r = NREP > 0 ? r0 + g : min(r0 + g, nrep - 1);
-            const char *gp = (const char *)bufs.p[k.dst_base + t.dst_buf0 + r] + t.dst_off;
 #pragma unroll
-            for (int u = 0; u < U; ++u) v[g][u] = ld<In::kBytes, NTL>(gp + (TILES != kStrided && !ELEMENT ? c[u].src : c[u].dst));
+            for (int u = 0; u < U; ++u) v[g][u] = ld<In::kBytes, NTL>(p[g] + (TILES != kStrided && !ELEMENT ? c[u].src : c[u].dst));
         }
         // ascending tp: copy 0 starts the accumulator, copies 1.. are added in order
 #pragma unroll
         for (int g = 0; g < G; ++g) {
-            if (NREP > 0 || r0 + g < nrep) {
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    float x[E];
-                    In::unpack(v[g][u], x);
+            for (int u = 0; u < U; ++u) {
+                float x[E];
+                In::unpack(v[g][u], x);
 #pragma unroll
-                    for (int e = 0; e < E; ++e) acc[u][e] = (g == 0 && r0 == 0) ? x[e] : acc[u][e] + x[e];
-                }
+                for (int e = 0; e < E; ++e) acc[u][e] = (g == 0 && r0 == 0) ? x[e] : acc[u][e] + x[e];
             }
         }
-    }
+    });
+    gchar *out = places.src;
     if constexpr (!ACC) {
         VO res[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) res[u] = Out::pack(acc[u]);
-        for (uint32_t s = 0; s < t.src_copies; ++s) {
-            char *out = (char *)bufs.p[t.src_buf + s] + out_off;
+        for (uint32_t s = 0;;) {
 #pragma unroll
             for (int u = 0; u < U; ++u)
                 if (!GUARD || i[u] < n) st<Out::kBytes, NTS>(out + c[u].src, res[u]);
+            if (++s >= t.src_copies) break;
+            out = at(buffers()[t.src_buf + s] + t.src_off);
         }
     } else {
-        for (uint32_t s = 0; s < t.src_copies; ++s) {
-            char *out = (char *)bufs.p[t.src_buf + s] + out_off;
-            VO old[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) old[u] = ld<Out::kBytes, NTL>(out + c[u].src * kWiden);
+        for (uint32_t s = 0;;) {
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 float x[E];
@@ -407,37 +549,45 @@ __device__ __forceinline__ void backward_group(const BufTable &bufs, const KPara
                             st<4, NTS>(out + c[u].src * kWiden + e * 4, __float_as_uint(x[e]));
                 }
             }
+            if (++s >= t.src_copies) break;
+            out = at(buffers()[t.src_buf + s] + t.src_off * kWiden);
+#pragma unroll
+            for (int u = 0; u < U; ++u) old[u] = ld<Out::kBytes, NTL>(out + c[u].src * kWiden);
         }
     }
 }
 
 template <int DT, bool ACC, int NREP, Tiles TILES, bool NTL, bool NTS>
-__device__ __forceinline__ void backward_tile(const BufTable &bufs, const KParams &k, const TileView &t, uint32_t nrep) {
+__device__ __forceinline__ void backward_tile(const KParams &k, const TileView &t, uint32_t nrep) {
     constexpr int E = kLaneElems<DT, ACC>;
     constexpr uint32_t kElemBytes = DT == HP_F32 ? 4 : 2;
+    constexpr uint32_t kWiden = ACC ? 4 / kElemBytes : 1;
+    const Places<NREP> places(k, t, kWiden);
+    if constexpr (!ACC && NREP != 1 && NREP != 8) pace(k.pace);
     uint32_t n, whole;
-    hp::count_chunks<Elems<DT, E>::kBytes, TILES != kStrided>(k, t, n, whole);
-    const uint32_t step = blockDim.x;
+    count_chunks<Elems<DT, E>::kBytes, TILES>(k, t, n, whole);
+    const uint32_t step = k.block;
     uint32_t done = 0;                                               // uniform
     if (TILES != kLines && __builtin_expect(n == 0, 0)) {                               // shorter than a chunk
         for (n = t.nbytes / kElemBytes; done < n; done += step)
-            backward_group<DT, 1, ACC, 0, 1, TILES, true, NTL, NTS>(bufs, k, t, nrep, done, n);
+            backward_group<DT, 1, ACC, 0, 1, TILES, true, NTL, NTS>(k, t, Places<0>(k, t, kWiden), nrep, done, n);
         return;
     }
-    for (; whole - done >= 2 * step; done += 2 * step)
-        backward_group<DT, E, ACC, NREP, 2, TILES, false, NTL, NTS>(bufs, k, t, nrep, done, n);
-    if (whole - done >= step) {
-        backward_group<DT, E, ACC, NREP, 1, TILES, false, NTL, NTS>(bufs, k, t, nrep, done, n);
-        done += step;
-    }
-    if (n - done > 0) backward_group<DT, E, ACC, NREP, 1, TILES, true, NTL, NTS>(bufs, k, t, nrep, done, n);
+    if constexpr (ACC || NREP < kSingly)
+        for (; whole - done >= 2 * step; done += 2 * step)
+            backward_group<DT, E, ACC, NREP, 2, TILES, false, NTL, NTS>(k, t, places, nrep, done, n);
+    for (; whole - done >= step; done += step)
+        backward_group<DT, E, ACC, NREP, 1, TILES, false, NTL, NTS>(k, t, places, nrep, done, n);
+    if (n - done > 0) backward_group<DT, E, ACC, NREP, 1, TILES, true, NTL, NTS>(k, t, places, nrep, done, n);
 }
 
 template <int DT, bool ACC, int NREP, Tiles TILES, bool NTL, bool NTS>
 __global__ void __launch_bounds__(1024)
 hp_backward_kernel(const Args a) {
+    const uint32_t touch = touch_args();
     const TileView t = my_tile<TILES>(a);
-    backward_tile<DT, ACC, NREP, TILES, NTL, NTS>(a.b, a.k, t, NREP > 0 ? (uint32_t)NREP : a.k.dst_copies);
+    backward_tile<DT, ACC, NREP, TILES, NTL, NTS>(a.k, t, NREP > 0 ? (uint32_t)NREP : a.k.dst_copies);
+    touched(touch);
 }
 
 // ---------------------------------------------------------------------------
@@ -454,10 +604,6 @@ struct ProbeArgs {
     uint32_t n_tiles;        // ceil(n_chunks / chunks_per_wg)
     uint32_t tiles_per_xcd;  // ceil(n_tiles / kXcds), for the XCD-chunked schedules
 };
-
-// Workgroups are handed to the chip's 8 accelerator dies (XCDs, each with its
-// own L2) round-robin by workgroup id.
-constexpr uint32_t kXcds = 8;
 
 template <int U, bool GUARD, bool NTL, bool NTS>
 __device__ __forceinline__ void probe_group(const ProbeArgs &a, uint64_t base, uint32_t done, uint32_t n) {
@@ -477,7 +623,7 @@ __device__ __forceinline__ void probe_group(const ProbeArgs &a, uint64_t base, u
             if (r0 + g < a.n_read) {
                 const u32x4 *p = a.rd[r0 + g] + base;
 #pragma unroll
-                for (int u = 0; u < U; ++u) v[g][u] = ld<16, NTL>((const char *)(p + (GUARD ? min(i[u], n - 1) : i[u])));
+                for (int u = 0; u < U; ++u) v[g][u] = ld<16, NTL>((const gchar *)(p + (GUARD ? min(i[u], n - 1) : i[u])));
             }
 #pragma unroll
         for (int g = 0; g < 4; ++g)
@@ -489,7 +635,7 @@ __device__ __forceinline__ void probe_group(const ProbeArgs &a, uint64_t base, u
     for (uint32_t w = 0; w < a.n_write; ++w) {
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            if (!GUARD || i[u] < n) st<16, NTS>((char *)(a.wr[w] + base + i[u]), acc[u]);
+            if (!GUARD || i[u] < n) st<16, NTS>((gchar *)(a.wr[w] + base + i[u]), acc[u]);
     }
     if (a.n_write == 0) {
         // read-only pattern: keep the loads alive with a store that the data never triggers
@@ -508,11 +654,11 @@ __device__ __forceinline__ void probe_deep(const ProbeArgs &a, uint64_t base) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         v[u] = (u32x4){1u, 2u, 3u, 4u};
-        if (a.n_read) v[u] = ld<16, NTL>((const char *)(a.rd[0] + base + u * blockDim.x + threadIdx.x));
+        if (a.n_read) v[u] = ld<16, NTL>((const gchar *)(a.rd[0] + base + u * blockDim.x + threadIdx.x));
     }
     for (uint32_t w = 0; w < a.n_write; ++w) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) st<16, NTS>((char *)(a.wr[w] + base + u * blockDim.x + threadIdx.x), v[u]);
+        for (int u = 0; u < U; ++u) st<16, NTS>((gchar *)(a.wr[w] + base + u * blockDim.x + threadIdx.x), v[u]);
     }
 }
 
@@ -655,6 +801,7 @@ void launch_forward(int copies, const LaunchCfg &c, const Args &a) {
     switch (copies) {
         case 1: HP_LAUNCH((hp_forward_kernel<1, TILES, NTL, NTS>), c, a); break;
         case 2: HP_LAUNCH((hp_forward_kernel<2, TILES, NTL, NTS>), c, a); break;
+        case 3: HP_LAUNCH((hp_forward_kernel<3, TILES, NTL, NTS>), c, a); break;
         case 4: HP_LAUNCH((hp_forward_kernel<4, TILES, NTL, NTS>), c, a); break;
         case 8: HP_LAUNCH((hp_forward_kernel<8, TILES, NTL, NTS>), c, a); break;
         default: HP_LAUNCH((hp_forward_kernel<0, TILES, NTL, NTS>), c, a); break;
@@ -666,6 +813,7 @@ void launch_backward_nrep(int copies, const LaunchCfg &c, const Args &a) {
     switch (copies) {
         case 1: HP_LAUNCH((hp_backward_kernel<DT, ACC, 1, TILES, NTL, NTS>), c, a); break;
         case 2: HP_LAUNCH((hp_backward_kernel<DT, ACC, 2, TILES, NTL, NTS>), c, a); break;
+        case 3: HP_LAUNCH((hp_backward_kernel<DT, ACC, 3, TILES, NTL, NTS>), c, a); break;
         case 4: HP_LAUNCH((hp_backward_kernel<DT, ACC, 4, TILES, NTL, NTS>), c, a); break;
         case 8: HP_LAUNCH((hp_backward_kernel<DT, ACC, 8, TILES, NTL, NTS>), c, a); break;
         default: HP_LAUNCH((hp_backward_kernel<DT, ACC, 0, TILES, NTL, NTS>), c, a); break;
@@ -740,6 +888,28 @@ void put_tables(const hp_plan *p, int variant, Args &a) {
     }
 }
 
+// Rounds of pace() for a launch in tiles of 1 KiB, one wave each, where it was
+// measured (the same buffers in turn, 0 to 48 rounds, caps 0.85 to 1.15 of the
+// shape's own; one source copy).  Every level of the tree below the root takes the
+// place of four rounds.  Backward from two copies 1.04-1.13 of the unpaced rate from
+// 450 MB on (2.2 GB 361 -> 320 us), from three 1.03-1.06, from four 1.04-1.09 (2.06
+// GB over 8 CP ranks 320 -> 301), from five to seven 1.03-1.06 from 1 GB on; 150 MB
+// 0.97-1.00, eight and sixteen copies 0.94-1.01, one 1.00-1.02.  Forward: to 13 and
+// more copies, 100 MB to 1.5 GB, 1.03-1.06, else 0.80-1.04, mostly below 1.
+// Accumulating: 0.97-1.01.
+uint32_t pace_of(const hp_plan *p, Direction dir, const hp::Launch &L) {
+    if (L.tile_variant != 0 || L.block != 64 || p->src_copies != 1) return 0;
+    const int c = p->dst_copies, below = 4 * ((int)p->tree_info[0].n_levels - 1);
+    const double bytes = dir == kForward ? (1.0 + c) * (double)p->n_rows * (double)p->row_bytes : (double)p->bwd_bytes;
+    int rounds = 0;
+    if (dir == kForward) rounds = c >= 13 && bytes < 1.5e9 ? 12 : 0;
+    else if (dir != kBackward || bytes < 400e6) rounds = 0;
+    else if (c == 2) rounds = 12;
+    else if (c == 3 || c == 4) rounds = 20;
+    else if (c >= 5 && c <= 7 && bytes >= 800e6) rounds = 28;
+    return rounds > below ? (uint32_t)(rounds - below) : 0u;
+}
+
 // Enqueues one kernel for direction `dir` with launch shape `L`.
 int enqueue_params(const hp_plan *p, Direction dir, const hp::Launch &L, const BufTable &bt, hipStream_t stream,
                    EventPair ev, const KParams &k);
@@ -758,6 +928,8 @@ int enqueue_params(const hp_plan *p, Direction dir, const hp::Launch &L, const B
     a.k = params;
     std::memcpy(a.b.p, bt.p, (size_t)(p->n_src_bufs + p->n_dst_bufs) * sizeof(void *));
     if (dir == kBackwardAcc) hp::set_row_chunks(a.k, 4u * (uint32_t)p->elem_bytes);
+    a.k.block = (uint32_t)L.block;
+    a.k.pace = pace_of(p, dir, L);
     if (!a.k.segs) put_tables(p, L.tile_variant, a);
     const KParams &k = a.k;
     LaunchCfg c;
@@ -853,6 +1025,7 @@ int enqueue_runs(const hp_plan *p, const std::vector<hp::Seg> &runs, const RunGr
         a.b.p[g.bufs + i] = out[g.buf0 + i];
     }
     a.k.dst_base = (uint32_t)g.bufs;
+    a.k.block = (uint32_t)kTextLaunch.block;
     const size_t seg_at = (offsetof(Args, b) + (size_t)g.bufs * 2 * sizeof(void *) + 63) / 64 * 64;
     const size_t tree_at = seg_at + (g.n * sizeof(hp::Seg) + 63) / 64 * 64;
     const size_t nodes = (g.n + hp::kTreeFanout - 1) / hp::kTreeFanout;

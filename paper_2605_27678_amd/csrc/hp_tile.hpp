@@ -24,15 +24,18 @@ struct KParams {
     const uint32_t *tree;       // search trees (64-byte aligned nodes of 16 keys)
     uint32_t seg_at, tree_at;   // if not 0: the tables travel with the arguments, this many bytes from their start
     uint32_t n_levels;          // levels of this launch's tree
-    uint32_t level_off[kMaxTreeLevels];   // start of each level, in keys; level 0 = leaves
     uint32_t tile_bytes;
     uint32_t row_bytes;
-    uint32_t rows_per_tile;     // row-strided segments, rows shorter than a tile: tile_bytes / row_bytes
-    uint32_t parts_per_row;     // row-strided segments, rows of at least a tile: ceil(row_bytes / tile_bytes); else 0
-    uint32_t row_chunks;        // row-strided tiles of whole rows: lane chunks of one row (see set_row_chunks)
-    uint32_t row_magic, row_one;
+    uint32_t block;             // work-items of a workgroup
     uint32_t dst_base;          // index of the first destination pointer in BufTable
     uint32_t dst_copies;        // replicas of each row on the destination side
+    uint32_t parts_per_row;     // row-strided segments, rows of at least a tile: ceil(row_bytes / tile_bytes); else 0
+    uint32_t part_magic, part_shift;      // t / parts_per_row = t * part_magic >> (31 + part_shift)
+    uint32_t rows_per_tile;     // row-strided segments, rows shorter than a tile: tile_bytes / row_bytes
+    uint32_t row_chunks;        // row-strided tiles of whole rows: lane chunks of one row (see set_row_chunks)
+    uint32_t row_magic, row_one;
+    uint32_t pace;              // rounds of pace() before a tile's loads (kernels that have it)
+    uint32_t level_off[kMaxTreeLevels];   // start of each level, in keys; level 0 = leaves
 };
 
 // One workgroup's share of the launch.
@@ -54,42 +57,84 @@ struct TileView {
 #endif
 
 // One node of the search tree: 16 ascending keys (padding = UINT32_MAX), fetched
-// with one 64-byte scalar load.  Returns how many keys are <= tile, and the
-// largest of them.  About a hundred instructions a node, and that is as well:
-// the scalar unit then hands a compute unit's workgroups to memory at an even
-// pace.  The same search in three instructions a key (48 in all) made the
-// memory-bound launches slower at every resident-wave cap (2.06 GB backward
-// from four copies: 304 -> 320 us).
+// with one 64-byte scalar load; the first is <= tile.  Returns the index of the
+// last key that is <= tile, and that key.  Bisected in pairs of keys: four
+// compares and eight selects.  What a wave does before its first load is time in
+// which it has nothing in flight, at the start of a launch and at every replacement
+// of a workgroup.  Against comparing all 16 keys (a hundred instructions), the same
+// buffers in turn: to four copies, 100 MB 16.24 -> 16.18 us, 2.06 GB 334 -> 327; from two
+// copies, 100 MB 17.2 -> 17.0, 900 MB in 561 segments (three levels) 161 -> 138.
 template <typename Node>
-HP_HD void search_node(Node node, uint32_t tile, uint32_t &count, uint32_t &key) {
-    uint32_t c = 0, best = 0;
+HP_HD void search_node(Node node, uint32_t tile, uint32_t &index, uint32_t &key) {
+    uint64_t q[kTreeFanout / 2];
 #pragma unroll
-    for (int j = 0; j < kTreeFanout; ++j) {
-        const uint32_t v = node[j];
-        const bool le = v <= tile;
-        c += le ? 1u : 0u;
-        best = le ? v : best;
-    }
-    count = c;
-    key = best;
+    for (int j = 0; j < 8; ++j) q[j] = (uint64_t)node[2 * j + 1] << 32 | node[2 * j];
+    const bool b3 = tile >= (uint32_t)q[4];
+    index = b3 ? 8u : 0u;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) q[j] = b3 ? q[4 + j] : q[j];
+    const bool b2 = tile >= (uint32_t)q[2];
+    index = b2 ? index + 4u : index;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) q[j] = b2 ? q[2 + j] : q[j];
+    const bool b1 = tile >= (uint32_t)q[1];
+    q[0] = b1 ? q[1] : q[0];
+    index = b1 ? index + 2u : index;
+    const bool b0 = tile >= (uint32_t)(q[0] >> 32);
+    key = b0 ? (uint32_t)(q[0] >> 32) : (uint32_t)q[0];
+    uint32_t next = index + 1u;
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm("" : "+s"(next));       // a select; the sum with a truth value goes through the vector unit
+#endif
+    index = b0 ? next : index;
 }
+
+// A whole descriptor with one scalar load (left to itself the compiler reads it in
+// three, each after a wait for the one before).
+HP_HD Seg load_seg(const HP_TABLE Seg *p) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
+    u32x8 w = *(const HP_TABLE u32x8 *)p;
+    asm("" : "+s"(w));
+    return __builtin_bit_cast(Seg, w);
+#else
+    return *p;
+#endif
+}
+
+// left < tile ? left : tile, without a 64-bit comparison (the scalar unit has none).
+HP_HD uint32_t clip(uint64_t left, uint32_t tile) {
+    const uint32_t lo = (uint32_t)left;
+    uint32_t hi = (uint32_t)(left >> 32);
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm("" : "+s"(hi));
+#endif
+    return hi ? tile : lo < tile ? lo : tile;
+}
+
+// What the segments of a launch may be: a kernel's variants leave out the others.
+enum SegKinds {
+    kAnySegs,
+    kWholeTiles,    // dense, or row-strided with rows of at least a tile
+    kRowGroups,     // row-strided with rows shorter than a tile
+};
 
 // Scalar code: every value here is uniform over the workgroup.  One dependent
 // scalar load per tree level below the root, then the descriptor, then the buffer
 // pointers.  segs and tree point at k's tables (k.segs and k.tree, or behind the
 // arguments).
+template <SegKinds KINDS>
 HP_HD TileView locate_tile(const KParams &k, const HP_TABLE Seg *segs, const HP_TABLE uint32_t *tree, uint32_t tile) {
-    uint32_t lo, first, count;
-    search_node(k.root, tile, count, first);
-    lo = count - 1;
+    uint32_t lo, first, index;
+    search_node(k.root, tile, lo, first);
 #pragma unroll
     for (int l = kMaxTreeLevels - 2; l >= 0; --l) {
-        if ((uint32_t)l + 1 < k.n_levels) {
-            search_node(tree + k.level_off[l] + (size_t)lo * kTreeFanout, tile, count, first);
-            lo = lo * kTreeFanout + count - 1;
+        if (__builtin_expect((uint32_t)l + 1 < k.n_levels, l == 0)) {
+            search_node(tree + k.level_off[l] + (size_t)lo * kTreeFanout, tile, index, first);
+            lo = lo * kTreeFanout + index;
         }
     }
-    const HP_TABLE Seg &s = segs[lo];
+    const Seg s = load_seg(segs + lo);
     const uint32_t t = tile - first;
     TileView v;
     v.pitch_rows = s.pitch_rows;
@@ -97,16 +142,16 @@ HP_HD TileView locate_tile(const KParams &k, const HP_TABLE Seg *segs, const HP_
     v.dst_buf0 = s.dst_buf0;
     v.src_copies = s.src_copies;
     v.first = t == 0;
-    if (s.pitch_rows == 1) {
+    if (KINDS != kRowGroups && s.pitch_rows == 1) {
         const uint64_t off = (uint64_t)t * k.tile_bytes;
         const uint64_t left = (uint64_t)s.n_rows * k.row_bytes - off;
         v.src_off = s.src_off + off;
         v.dst_off = s.dst_off + off;
-        v.nbytes = left < k.tile_bytes ? (uint32_t)left : k.tile_bytes;
+        v.nbytes = clip(left, k.tile_bytes);
         v.left = left;
-    } else if (k.parts_per_row) {
+    } else if (KINDS == kWholeTiles || (KINDS == kAnySegs && k.parts_per_row)) {
         // a piece of one row: dense on both sides, handled like a dense tile
-        const uint32_t row = t / k.parts_per_row;
+        const uint32_t row = (uint32_t)((uint64_t)t * k.part_magic >> 31 >> k.part_shift);
         const uint32_t off = (t - row * k.parts_per_row) * k.tile_bytes;
         const uint32_t left = k.row_bytes - off;
         v.pitch_rows = 1;
@@ -117,8 +162,7 @@ HP_HD TileView locate_tile(const KParams &k, const HP_TABLE Seg *segs, const HP_
         v.left = left;
     } else {
         const uint64_t row0 = (uint64_t)t * k.rows_per_tile;
-        const uint64_t rows_left = s.n_rows - row0;
-        const uint32_t rows = rows_left < k.rows_per_tile ? (uint32_t)rows_left : k.rows_per_tile;
+        const uint32_t rows = clip(s.n_rows - row0, k.rows_per_tile);
         v.src_off = s.src_off + row0 * k.row_bytes;
         v.dst_off = s.dst_off + row0 * s.pitch_rows * k.row_bytes;
         v.nbytes = rows * k.row_bytes;
@@ -128,7 +172,7 @@ HP_HD TileView locate_tile(const KParams &k, const HP_TABLE Seg *segs, const HP_
 }
 
 #if !defined(__HIP_DEVICE_COMPILE__)
-inline TileView locate_tile(const KParams &k, uint32_t tile) { return locate_tile(k, k.segs, k.tree, tile); }
+inline TileView locate_tile(const KParams &k, uint32_t tile) { return locate_tile<kAnySegs>(k, k.segs, k.tree, tile); }
 #endif
 
 // Moves both ends of a dense tile up to the next 128-byte line of its first
@@ -213,6 +257,18 @@ HP_HD ChunkView element_at(const KParams &k, const TileView &t, uint32_t i) {
     return c;
 }
 
+// Multiplication in place of t / parts_per_row, exact for t < 2^31 (a grid has no
+// more tiles): with 2^part_shift >= parts the magic number, rounded up, is off by
+// less than 2^part_shift in 2^(31 + part_shift).  The division itself, some 30
+// instructions of the vector unit and a read back from it, stood before the first
+// load of every piece of a row.
+inline void set_parts(KParams &k) {
+    k.part_magic = k.part_shift = 0;
+    if (!k.parts_per_row) return;
+    while ((1u << k.part_shift) < k.parts_per_row) ++k.part_shift;
+    k.part_magic = (uint32_t)((((uint64_t)1 << (31 + k.part_shift)) + k.parts_per_row - 1) / k.parts_per_row);
+}
+
 // The kernel parameters of a launch with tiles of 1 KiB << variant; segs and
 // tree point at the plan's tables wherever the caller keeps them (device memory
 // for a launch, the plan's host vectors for the host-side walk).
@@ -230,7 +286,9 @@ inline KParams kernel_params(const hp_plan &p, int variant, const Seg *segs, con
     k.row_bytes = (uint32_t)p.row_bytes;
     k.rows_per_tile = std::max<uint32_t>(1u, k.tile_bytes / k.row_bytes);
     k.parts_per_row = k.row_bytes >= k.tile_bytes ? (k.row_bytes + k.tile_bytes - 1) / k.tile_bytes : 0u;
+    set_parts(k);
     set_row_chunks(k, 16u);
+    k.block = k.pace = 0;       // set by the launch
     k.dst_base = (uint32_t)p.n_src_bufs;
     k.dst_copies = (uint32_t)p.dst_copies;
     return k;
