@@ -255,16 +255,21 @@ int make_tables(hp_plan *p) {
 // sequence a program runs (forward, backward, forward, ...; forward, accumulate,
 // ... - a shape that leaves dirty lines behind is paid for by the next launch,
 // and ranks wrongly when it is timed alone), in both element types, with rows of
-// 1 to 24 KiB, images of 16 to 1024 rows, both row orders and launches of 8 MB to
-// 2 GB (accumulating ones to 5 GB); the figures are the direction's gain over that
+// 1 to 24 KiB, images of 16 to 4096 rows, both row orders and launches of 8 MB to
+// 3.5 GB (accumulating ones to 5 GB); the figures are the direction's gain over that
 // range, and after the semicolon what it would be where the line has ended.  Copy
 // counts measured: 1 to 14 and 16 with one source copy; 1 to 8 and 12 with two.
 // Launches of up to about 400 MB find part of
 // their buffers in the 256 MB memory-side cache and want more waves; replica
-// counts without a kernel of their own (all but 1, 2, 4 and 8) wait for their
-// groups of four loads and want more of them in flight.
+// counts without a kernel of their own (all but 1, 2, 3, 4 and 8) wait for their
+// groups of four loads and want more of them in flight; and the more copies there
+// are to write, the fewer waves keep a compute unit's 40 to 50 KB on their way.
+// Since a workgroup finds its tile in half the time, small tiles gain up to more
+// segments and fewer waves do: over 450 random calls of 12 MB to 3.5 GB (1 to 16
+// copies) the lookup and these lines together took the forward's time to 0.93 of
+// what it was (0.71-1.09) and the backward's to 0.93 (0.70-1.06).
 void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
-    constexpr int K1 = 0, K4 = 2, K8 = 3;                    // tiles of 1, 4 and 8 KiB
+    constexpr int K1 = 0, K2 = 1, K4 = 2, K8 = 3;            // tiles of 1, 2, 4 and 8 KiB
     const int c = p->dst_copies, s = p->src_copies;
     const bool generic = c != 1 && c != 2 && c != 4 && c != 8, f32 = p->elem_bytes == 4, dense = p->dst_stride == 1;
     const size_t segs = p->segments.size();
@@ -273,13 +278,34 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
     auto in = [](double bytes, double from, double to) { return bytes >= from * MB && bytes < to * MB; };
 
     const double fwd = (1.0 + c) * (double)p->n_rows * (double)p->row_bytes;
-    if (c == 1 && fwd >= 200 * MB && segs <= 256) set(f, K4, 128, 24);          // 0.99-1.03; more segments 0.98-1.03
+    if (c == 1 && fwd >= 200 * MB && segs <= 256) {
+        if (fwd < 400 * MB) set(f, K4, 128, 24);                                // 0.99-1.03; more segments 0.98-1.03
+        else set(f, K2, 64, 20);                                                // 1.00-1.02
+    }
     else if (c == 2 && in(fwd, 40, 290)) set(f, K8, 256, 16);                   // 0.98-1.13; 300 MB: 0.96-1.00
+    else if (c == 2 && fwd >= 400 * MB) {
+        if (segs <= 256) set(f, K1, 64, 24);                                    // 1.01-1.05; 300 MB 0.98-1.00
+        else if (fwd >= 1000 * MB) set(f, K2, 64, 20);                          // 1.03-1.07
+    }
+    else if (c == 3 && in(fwd, 40, 1000)) {
+        if (segs <= 128) set(f, K1, 64, fwd < 200 * MB ? 10 : 16);              // 1.01-1.09; more segments 0.94-1.0
+    }
+    else if (c == 4 && in(fwd, 8, 180)) {
+        if (segs <= 256) set(f, K1, 64, 8);                                     // 0.99-1.08; more segments 0.96-1.02, 450 MB 0.87-0.91
+    }
     else if (c >= 5 && c <= 7 && in(fwd, 40, 450)) {
         if (c > 5 || segs <= 16) set(f, K1, 64, 10);                            // 0.96-1.20; 20 MB 0.89-1.06, five copies and more segments 0.87-1.03
     }
-    else if (c == 8 && dense && in(fwd, 40, 450)) set(f, K1, 64, 6);            // 0.99-1.25; [S,B,H] order 0.93-1.02
-    else if (c >= 10 && dense && in(fwd, 100, 450)) set(f, K1, 64, 5);          // 0.96-1.28; 9 copies 0.91-1.09, [S,B,H] 0.86-1.05
+    else if (c >= 5 && c <= 7 && fwd >= 450 * MB) {
+        if (segs <= 256) set(f, K1, 64, 14);                                    // 1.02-1.07; more segments 0.97-1.02
+    }
+    else if (c == 8 && dense && in(fwd, 40, 450)) set(f, K1, 64, 5);            // 0.99-1.25; [S,B,H] order 0.93-1.02
+    else if (c >= 13 && dense && in(fwd, 40, 100)) set(f, K4, 64, 8);           // 1.06-1.08
+    else if (c >= 10 && dense && in(fwd, 100, 450)) set(f, K1, 64, c <= 12 ? 5 : 3);    // 0.96-1.28, cap 3 1.05-1.08 on top; 9 copies 0.91-1.09, [S,B,H] 0.86-1.05
+    else if (c >= 10 && dense && in(fwd, 450, c <= 12 ? 1200 : 1500)) {
+        if (c > 12 || segs <= 256) set(f, K1, 64, 3);                           // 1.05-1.21; twelve copies, 1.4 GB, more segments 0.71
+    }
+    else if (c >= 13 && dense && in(fwd, 1500, 2600)) set(f, K2, 64, 3);        // 1.04-1.10; 2.8 GB 0.91
 
     // With few copies a workgroup moves little for each search, and the depth of the tree (16 segments a level) decides.
     const double bwd = (double)p->bwd_bytes;
@@ -292,11 +318,19 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
     else if (c == 2 && s == 1 && in(bwd, 80, 290)) {
         if (segs <= 16) set(b, K8, 256, 24);                                    // 0.99-1.06; more segments 0.95-1.02, 40 MB 0.97-1.05
     }
+    else if (c == 2 && s == 1 && bwd >= 450 * MB) {
+        if (segs > 256) set(b, K1, 64, 28);                                     // 1.00-1.01
+    }
     else if (c == 2 && s > 1 && bwd >= 40 * MB) set(b, K1, 64, 20);             // 1.05-1.09; 27 MB: 0.95-1.02
     else if (c == 4 && s == 1 && in(bwd, 35, segs <= 16 ? 360 : 220)) set(b, K1, 64, 24);   // 1.02-1.14; more segments from 240 MB 0.95-1.04
     else if (generic && c < 8 && bwd >= (c <= 5 ? 16 : 30) * MB &&              // 3 copies 1.03-1.35, 5 to 7 0.98-1.28
              !(f32 && (s > 1 ? bwd >= 600 * MB : c == 7 && bwd >= 500 * MB)))   // there 0.97-1.02 and 0.95-1.02
-        set(b, K1, 64, c <= 5 && s == 1 ? 28 : 24);
+        set(b, K1, 64, (c == 5 || c == 6) && bwd >= 450 * MB ? 16 : c == 3 && s == 1 && bwd >= 450 * MB ? 20 : c <= 5 && s == 1 ? 28 : 24);   // cap 16: 1.01-1.02; cap 20, paced: 1.01-1.06
+    else if (c == 8 && in(bwd, 40, 450)) set(b, K1, 64, 12);                    // 1.00-1.04
+    else if (c == 8 && in(bwd, 450, 1500)) set(b, K1, 64, 11);                  // 1.02-1.05
+    else if (c == 8 && bwd >= 1500 * MB) set(b, K4, 64, 5);                     // 1.03-1.06, to two source copies 1.05-1.11
+    else if (c > 12 && dense && in(bwd, 40, 250)) set(b, K1, 64, 12);           // 1.02-1.07; 350 MB 0.97-1.00, [S,B,H] order 0.85-1.0
+    else if (c > 8 && bwd >= 600 * MB) set(b, K1, 64, 10);                      // 1.02-1.06
     else if (c > 8 && !f32 && in(bwd, 100, 250)) set(b, K4, 128, 24);           // 0.98-1.14; binary32: 0.97-1.00, 300 MB: 0.94-1.01
 
     const double acc = (double)p->bwd_accum_bytes;
@@ -309,15 +343,25 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
                            : c == 8 ? dense && in(acc, 150, 400)                // 1.00-1.05; 670 MB: 0.84-0.89
                                     : acc < 300 * MB;                           // 1.02-1.30; 1.6 GB: 0.87-0.97
         if (s == 1 && gains) set(a, K1, 64, 24);
+        else if (c <= 2 && s == 1 && acc >= 1500 * MB) set(a, K4, 64, 8);       // 1.03-1.06; 450 MB: 0.97-1.01
     } else if (s > 1) {
         if (acc < 200 * MB || generic) set(a, K1, 64, 16);                      // 1.04-1.44
     } else if (acc < 400 * MB) {
-        if (c == 2 ? acc < 280 * MB : c <= 5) set(a, K4, 256, 24);              // 0.97-1.48; two copies, 300 MB: 0.99-1.02
+        if (c == 2 && acc >= 350 * MB) set(a, K1, 64, 16);                      // 1.01-1.03
+        else if ((c == 3 || c == 4) && acc >= 250 * MB) set(a, K1, 64, c == 3 ? 16 : 14);   // 1.01-1.02
+        else if (c == 2 ? acc < 280 * MB : c <= 5) set(a, K4, 256, dense ? 24 : 0);         // 0.97-1.48; two copies, 300 MB: 0.99-1.02
         else if (c >= 5 && c < 8) set(a, K1, 64, 24);                           // 1.10-1.63
         else if (c == 8 && dense && in(acc, 50, 350)) set(a, K4, 256, 16);      // 1.01-1.11; 27 MB 0.96, 400 MB 0.99, [S,B,H] 0.96-1.07
-        else if (c > 8) set(a, K1, 64, 20);                                     // 1.21-1.71
+        else if (c > 8) set(a, K1, 64, c <= 12 || acc < 150 * MB ? 20 : 10);    // 1.21-1.71, cap 10 1.01-1.02 on top; twelve copies 0.95
     } else if (c == 1 || generic) {
-        set(a, K1, 64, c <= 8 ? 20 : 16);                                       // 1.02-1.26, more than 8 copies 1.20-1.37
+        if ((c == 6 || c == 7) && dense && acc >= 900 * MB) set(a, K2, 64, 8);  // 1.05-1.30; five copies 0.96
+        else set(a, K1, 64, c == 1 || c == 5 ? 20 : c <= 8 ? 16 : 10);          // 1.02-1.26, more than 8 copies 1.20-1.37
+    } else if (c == 2) {
+        set(a, K1, 64, 16);                                                     // 1.01-1.03
+    } else if (c == 4) {
+        set(a, K2, 64, 8);                                                      // 1.01-1.02
+    } else if (acc >= 450 * MB) {
+        set(a, K1, 64, 10);                                                     // eight copies: 1.02-1.05
     }
 }
 
