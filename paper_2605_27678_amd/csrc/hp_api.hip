@@ -258,7 +258,7 @@ __device__ __forceinline__ void forward_group(const KParams &k, const TileView &
 // Whether a lane takes one chunk at a time through all copies, not two or four.  In
 // the shapes that the launches take, to four copies: 2.06 GB 380 -> 326 us, 1.13 GB
 // 204 -> 182, 205 MB and less no difference; three copies: 800 MB 133 -> 128, 2 GB
-// 328 -> 306; one copy: 2 GB 317 -> 310; sixteen: 2 GB 370 -> 346.  To eight copies
+// 328 -> 306; one copy: 2 GB 317 -> 310.  To eight copies
 // two at a time are the faster (2.2 GB 348 against 401 us), and so to the counts
 // that have no kernel of their own (six, 800 MB: 133 against 153).
 template <int NREP> constexpr bool kForwardSingly = NREP == 1 || NREP == 3 || NREP == 4;
