@@ -889,25 +889,25 @@ void put_tables(const hp_plan *p, int variant, Args &a) {
 }
 
 // Rounds of pace() for a launch in tiles of 1 KiB, one wave each, where it was
-// measured (the same buffers in turn, 0 to 48 rounds, caps 0.85 to 1.15 of the
-// shape's own; one source copy).  Every level of the tree below the root takes the
-// place of four rounds.  Backward from two copies 1.04-1.13 of the unpaced rate from
-// 450 MB on (2.2 GB 361 -> 320 us), from three 1.03-1.06, from four 1.04-1.09 (2.06
-// GB over 8 CP ranks 320 -> 301), from five to seven 1.03-1.06 from 1 GB on; 150 MB
-// 0.97-1.00, eight and sixteen copies 0.94-1.01, one 1.00-1.02.  Forward: to 13 and
-// more copies, 100 MB to 1.5 GB, 1.03-1.06, else 0.80-1.04, mostly below 1.
-// Accumulating: 0.97-1.01.
+// measured (the same buffers in turn, 0 to 28 rounds; one source copy), by the
+// levels of the search tree, each of which takes the place of three to four.  At
+// these, backward from 450 MB to 4.5 GB: two copies 1.01-1.05 of the unpaced rate
+// (four levels 0.93 with 6), three 1.03-1.06, four 1.04-1.07 (2.06 GB over 8 CP ranks
+// 318 -> 304 us), five to seven 1.03-1.06 from 1 GB on and 0.97-0.99 at 450 MB; 150 MB
+// 0.97-1.00, eight and sixteen copies 0.94-1.01, one 1.00-1.02.  The range is narrow:
+// six rounds more lose what they gain.  Forward: to 13 and more copies, 100 MB to 1.5
+// GB, 1.03-1.06, else 0.80-1.04, mostly below 1.  Accumulating: 0.97-1.01.
 uint32_t pace_of(const hp_plan *p, Direction dir, const hp::Launch &L) {
+    static const uint8_t two[] = {14, 11, 7, 0}, three[] = {18, 14, 11, 9}, four[] = {22, 18, 14, 10},
+                         more[] = {28, 24, 20, 20}, wide[] = {12, 8, 4, 0};
     if (L.tile_variant != 0 || L.block != 64 || p->src_copies != 1) return 0;
-    const int c = p->dst_copies, below = 4 * ((int)p->tree_info[0].n_levels - 1);
-    const double bytes = dir == kForward ? (1.0 + c) * (double)p->n_rows * (double)p->row_bytes : (double)p->bwd_bytes;
-    int rounds = 0;
-    if (dir == kForward) rounds = c >= 13 && bytes < 1.5e9 ? 12 : 0;
-    else if (dir != kBackward || bytes < 400e6) rounds = 0;
-    else if (c == 2) rounds = 12;
-    else if (c == 3 || c == 4) rounds = 20;
-    else if (c >= 5 && c <= 7 && bytes >= 800e6) rounds = 28;
-    return rounds > below ? (uint32_t)(rounds - below) : 0u;
+    const int c = p->dst_copies, level = (int)p->tree_info[0].n_levels - 1;
+    if (level < 0 || level > 3) return 0;
+    if (dir == kForward) return c >= 13 && (1.0 + c) * (double)p->n_rows * (double)p->row_bytes < 1.5e9 ? wide[level] : 0;
+    const double bytes = (double)p->bwd_bytes;
+    if (dir != kBackward || bytes < 400e6) return 0;
+    return c == 2 ? two[level] : c == 4 ? four[level]
+         : c == 3 && bytes >= 450e6 ? three[level] : c >= 5 && c <= 7 && bytes >= 800e6 ? more[level] : 0;
 }
 
 // Enqueues one kernel for direction `dir` with launch shape `L`.
