@@ -463,6 +463,14 @@ constexpr int kLaneElems = ACC || DT == HP_F32 ? 4 : 8;
 // 1060 us, 0.55 GB from eight 401 -> 377; four at a time are no better.
 constexpr int kSingly = 4;
 
+// Whether the accumulators of the first source copy are read before the gradients,
+// to travel with them, or after they are summed up.  Before: one, two and four copies
+// of bf16, 0.3 to 3.5 GB 1.00-1.02 of the rate; binary32, up to 0.3 GB 1.00-1.03, above
+// 0.99-1.00.  Where more bf16 loads are in flight as it is, that is too many: three
+// copies 0.98-1.0, five and more 0.98-0.99 (0.3 to 6.5 GB, to one and two source copies).
+template <int DT, int NREP>
+constexpr bool kAccumulatorsFirst = DT == HP_F32 || NREP == 1 || NREP == 2 || NREP == 4;
+
 // U chunks of E elements per lane starting at chunk `done`, straight-line: the
 // loads of all replicas (groups of four when the replica count is only known at
 // run time) are issued before the first add.  GUARD as in forward_group; ELEMENT:
@@ -492,9 +500,8 @@ __device__ __forceinline__ void backward_group(const KParams &k, const TileView 
         if constexpr (ELEMENT) c[u] = hp::element_at<kElemBytes>(k, t, ic);
         else c[u] = hp::chunk_at<In::kBytes, TILES != kStrided, GUARD && TILES == kRagged>(k, t, ic);
     }
-    // the accumulators of the first source copy travel with the gradients
     VO old[U];
-    if constexpr (ACC) {
+    if constexpr (ACC && kAccumulatorsFirst<DT, NREP>) {
 #pragma unroll
         for (int u = 0; u < U; ++u) old[u] = ld<Out::kBytes, NTL>(places.src + c[u].src * kWiden);
     }
@@ -532,6 +539,10 @@ __device__ __forceinline__ void backward_group(const KParams &k, const TileView 
             out = at(buffers()[t.src_buf + s] + t.src_off);
         }
     } else {
+        if constexpr (!kAccumulatorsFirst<DT, NREP>) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) old[u] = ld<Out::kBytes, NTL>(out + c[u].src * kWiden);
+        }
         for (uint32_t s = 0;;) {
 #pragma unroll
             for (int u = 0; u < U; ++u) {

@@ -272,6 +272,8 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
     constexpr int K1 = 0, K2 = 1, K4 = 2, K8 = 3;            // tiles of 1, 2, 4 and 8 KiB
     const int c = p->dst_copies, s = p->src_copies;
     const bool generic = c != 1 && c != 2 && c != 4 && c != 8, f32 = p->elem_bytes == 4, dense = p->dst_stride == 1;
+    const bool whole = dense || p->row_bytes >= 4096;        // tiles of 1 KiB are nearly all whole
+    const bool even = dense || p->row_bytes % 16 == 0;       // and so are their lanes
     const size_t segs = p->segments.size();
     constexpr double MB = 1e6;
     auto set = [](Launch &L, int tile, int block, int cap) { L = Launch{tile, block, cap, L.nontemporal}; };
@@ -343,23 +345,35 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
                            : c == 8 ? dense && in(acc, 150, 400)                // 1.00-1.05; 670 MB: 0.84-0.89
                                     : acc < 300 * MB;                           // 1.02-1.30; 1.6 GB: 0.87-0.97
         if (s == 1 && gains) set(a, K1, 64, 24);
-        else if (c <= 2 && s == 1 && acc >= 1500 * MB) set(a, K4, 64, 8);       // 1.03-1.06; 450 MB: 0.97-1.01
+        else if (c <= 2 && s == 1 && acc >= 1500 * MB && (dense || p->row_bytes % 4096 == 0))
+            set(a, K4, 64, 8);                                                  // 1.02-1.06; 450 MB: 0.97-1.01, [S,B,H] rows of 6 KiB 0.93
     } else if (s > 1) {
-        if (acc < 200 * MB || generic) set(a, K1, 64, 16);                      // 1.04-1.44
+        // few waves want whole tiles: pieces of row-strided rows under 4 KiB 0.96-1.01 with the smaller caps, 1.02-1.13 with 16
+        if (acc < 200 * MB || (generic && !whole)) set(a, K1, 64, 16);          // 1.04-1.44
+        else if (generic) set(a, K1, 64, c > 8 && acc >= 400 * MB ? 10 : acc < 1000 * MB ? 16 : 13);   // 0.99-1.04; cap 16 to the end 0.98-1.00
+        else if (whole && (c == 4 || c == 8)) set(a, K1, 64, c == 4 ? 13 : 8);  // 0.98-1.09; else 0.98-1.04
     } else if (acc < 400 * MB) {
-        if (c == 2 && acc >= 350 * MB) set(a, K1, 64, 16);                      // 1.01-1.03
-        else if ((c == 3 || c == 4) && acc >= 250 * MB) set(a, K1, 64, c == 3 ? 16 : 14);   // 1.01-1.02
+        if (c == 2 && acc >= 350 * MB && even) set(a, K1, 64, 16);              // 1.02
+        else if (c >= 3 && c <= 7 && acc >= 250 * MB) set(a, K1, 64, c == 3 ? 20 : c == 4 ? 14 : 16);   // 1.01-1.03; 200 MB 0.99-1.01
         else if (c == 2 ? acc < 280 * MB : c <= 5) set(a, K4, 256, dense ? 24 : 0);         // 0.97-1.48; two copies, 300 MB: 0.99-1.02
         else if (c >= 5 && c < 8) set(a, K1, 64, 24);                           // 1.10-1.63
         else if (c == 8 && dense && in(acc, 50, 350)) set(a, K4, 256, 16);      // 1.01-1.11; 27 MB 0.96, 400 MB 0.99, [S,B,H] 0.96-1.07
-        else if (c > 8) set(a, K1, 64, c <= 12 || acc < 150 * MB ? 20 : 10);    // 1.21-1.71, cap 10 1.01-1.02 on top; twelve copies 0.95
-    } else if (c == 1 || generic) {
-        if ((c == 6 || c == 7) && dense && acc >= 900 * MB) set(a, K2, 64, 8);  // 1.05-1.30; five copies 0.96
-        else set(a, K1, 64, c == 1 || c == 5 ? 20 : c <= 8 ? 16 : 10);          // 1.02-1.26, more than 8 copies 1.20-1.37
+        else if (c > 8) set(a, K1, 64, c <= 10 || acc < 150 * MB ? 20 : 12);    // 1.21-1.71, cap 12 1.00-1.02 on top; 9 copies 0.99
+    } else if (c == 1 || (generic && !whole)) {
+        set(a, K1, 64, c < 8 ? 20 : 16);                                        // 1.00-1.02, pieces of short rows 1.02-1.15
     } else if (c == 2) {
-        set(a, K1, 64, 16);                                                     // 1.01-1.03
+        if (even) set(a, K1, 64, 16);                                           // 1.01-1.02, from 2 GB on 1.00; [S,B,H] rows of 6 KiB 1.15, not of whole lanes 0.94-0.98
+    } else if (c == 3) {
+        if (acc < 1500 * MB) set(a, K1, 64, 20);                                // 1.01-1.02
+        else set(a, K2, 64, 11);                                                // 1.01-1.02
     } else if (c == 4) {
         set(a, K2, 64, 8);                                                      // 1.01-1.02
+    } else if (c == 5) {
+        set(a, K1, 64, acc < 1000 * MB ? 16 : 14);                              // 1.02-1.26; cap 20 to the end 0.97-0.99
+    } else if (c < 8) {
+        set(a, K1, 64, acc < 600 * MB ? 16 : 13);                               // 1.02-1.26; cap 16 to the end 0.99-1.02
+    } else if (c > 8) {
+        set(a, K1, 64, c < 13 ? 12 : 11);                                       // 1.20-1.37; cap 10 0.99-1.00
     } else if (acc >= 450 * MB) {
         set(a, K1, 64, 10);                                                     // eight copies: 1.02-1.05
     }

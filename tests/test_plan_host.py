@@ -488,14 +488,15 @@ def test_plans_from_several_threads():
     assert not errors, errors
 
 
-def _shape_of(direction, tp, mbytes, f32=False, tp_src=1, images=1, row_bytes=8192):
+def _shape_of(direction, tp, mbytes, f32=False, tp_src=1, images=1, row_bytes=8192, sbh=False):
     """Tile, workgroup and cap of a plan whose launch of this direction moves about `mbytes` MB."""
     e = 4 if f32 else 2
     per_row = (1 + tp, tp + tp_src, tp + 8 * tp_src / e)[direction] * row_bytes
     n = max(1, round(mbytes * 1e6 / per_row / images))
     start = [i * (n + 1) for i in range(images)]
-    tm = wl.TokenMap(1, images * (n + 1), row_bytes // e, [0] * images, start, [n] * images, None, int(f32))
-    p = hp.hp_plan_create_host(wl.Grid(tp=tp_src), wl.Grid(tp=tp), tm)
+    batch = 2 if sbh else 1                                 # the second sample of [S,B,H] order is text
+    tm = wl.TokenMap(batch, images * (n + 1), row_bytes // e, [0] * images, start, [n] * images, None, int(f32))
+    p = hp.hp_plan_create_host(wl.Grid(tp=tp_src), wl.Grid(tp=tp, row_order=wl.ROW_SBH if sbh else wl.ROW_BSH), tm)
     assert p.info.n_segments == images
     L = p.get_launch(direction)
     p.close()
@@ -527,6 +528,27 @@ def test_binary32_accumulation_leaves_its_starting_shape_only_where_another_is_f
     (2, 2, 1, 300, False, 1, (2048, 64, 13)), (2, 8, 1, 27, False, 1, (2048, 64, 9)), (2, 8, 1, 200, False, 1, (4096, 256, 16))])
 def test_shapes_by_size_hold_where_they_were_measured_to_be_faster(direction, tp, tp_src, mbytes, f32, images, want):
     assert _shape_of(direction, tp, mbytes, f32, tp_src, images) == want
+
+
+# Shapes of launches that a rule made for their neighbours had slowed: each was measured on the same buffers, in the sequence
+# that a program runs, against the shapes around it.
+@pytest.mark.parametrize("direction,tp,tp_src,mbytes,images,want", [
+    # accumulating: three copies, five and more, and two source copies want fewer waves the more they move
+    (2, 3, 1, 300, 30, (1024, 64, 20)), (2, 3, 1, 800, 30, (1024, 64, 20)), (2, 3, 1, 2500, 30, (2048, 64, 11)), (2, 3, 1, 200, 30, (4096, 256, 24)),
+    (2, 5, 1, 300, 30, (1024, 64, 16)), (2, 5, 1, 800, 30, (1024, 64, 16)), (2, 5, 1, 1200, 30, (1024, 64, 14)), (2, 7, 1, 2500, 30, (1024, 64, 13)),
+    (2, 12, 1, 300, 9, (1024, 64, 12)), (2, 16, 1, 500, 9, (1024, 64, 11)), (2, 9, 1, 2500, 9, (1024, 64, 12)),
+    (2, 16, 2, 235, 9, (1024, 64, 16)), (2, 4, 2, 2500, 30, (1024, 64, 13)), (2, 8, 2, 3900, 30, (1024, 64, 8)), (2, 12, 2, 1000, 30, (1024, 64, 10)), (2, 5, 2, 1400, 30, (1024, 64, 13))])
+def test_shapes_by_size_where_a_neighbour_s_shape_lost(direction, tp, tp_src, mbytes, images, want):
+    assert _shape_of(direction, tp, mbytes, False, tp_src, images) == want
+
+
+# [S,B,H] order: short rows and those that begin between lines leave tiles partly empty
+@pytest.mark.parametrize("direction,tp,tp_src,mbytes,f32,row_bytes,want", [
+    (2, 2, 1, 2000, False, 16378, (2048, 64, 13)), (2, 2, 1, 2000, False, 6224, (1024, 64, 16)), (2, 1, 1, 2500, True, 6176, (2048, 64, 16)),
+    (2, 1, 1, 2500, True, 8192, (4096, 64, 8)), (2, 3, 1, 2000, False, 1280, (1024, 64, 20)), (2, 9, 1, 2000, False, 1280, (1024, 64, 16)),
+    (2, 6, 1, 2000, False, 8192, (1024, 64, 13)), (2, 4, 2, 2000, False, 3088, (2048, 64, 9)), (2, 12, 2, 1000, False, 1280, (1024, 64, 16))])
+def test_shapes_by_size_of_row_strided_launches(direction, tp, tp_src, mbytes, f32, row_bytes, want):
+    assert _shape_of(direction, tp, mbytes, f32, tp_src, 30, row_bytes, sbh=True) == want
 
 
 @pytest.mark.parametrize("tp,tp_src,gib,hidden,sbh", [(1, 1, 66, 12288, False), (1, 1, 120, 12288, False), (2, 1, 70, 8192, False),
