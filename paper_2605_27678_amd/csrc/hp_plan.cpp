@@ -273,7 +273,11 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
     const int c = p->dst_copies, s = p->src_copies;
     const bool generic = c != 1 && c != 2 && c != 4 && c != 8, f32 = p->elem_bytes == 4, dense = p->dst_stride == 1;
     const bool whole = dense || p->row_bytes >= 4096;        // tiles of 1 KiB are nearly all whole
-    const bool even = dense || p->row_bytes % 16 == 0;       // and so are their lanes
+    // A row-strided row is cut into tiles from its start: whether it fills what it is cut into, in whole lanes.
+    auto filled = [&](int64_t tile) {
+        const int64_t row = p->row_bytes, cut = (row + tile - 1) / tile * tile;
+        return dense || (row >= tile && row % 16 == 0 && 20 * row >= 17 * cut);
+    };
     const size_t segs = p->segments.size();
     constexpr double MB = 1e6;
     auto set = [](Launch &L, int tile, int block, int cap) { L = Launch{tile, block, cap, L.nontemporal}; };
@@ -285,9 +289,9 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
         else set(f, K2, 64, 20);                                                // 1.00-1.02
     }
     else if (c == 2 && in(fwd, 40, 290)) set(f, K8, 256, 16);                   // 0.98-1.13; 300 MB: 0.96-1.00
-    else if (c == 2 && fwd >= 400 * MB) {
-        if (segs <= 256) set(f, K1, 64, 24);                                    // 1.01-1.05; 300 MB 0.98-1.00
-        else if (fwd >= 1000 * MB) set(f, K2, 64, 20);                          // 1.03-1.07
+    else if (c == 2 && fwd >= 300 * MB && filled(1024)) {
+        if (segs <= 256) set(f, K1, 64, 20);                                    // 1.01-1.04 to 1.2 GB, 1.01-1.02 to 15 GB; else 0.93-1.02
+        else if (segs <= 1024 && fwd >= 1500 * MB) set(f, K1, 64, 24);          // 1.01-1.03; smaller launches and more segments 0.97-1.02
     }
     else if (c == 3 && in(fwd, 40, 1000)) {
         if (segs <= 128) set(f, K1, 64, fwd < 200 * MB ? 10 : 16);              // 1.01-1.09; more segments 0.94-1.0
@@ -353,7 +357,7 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
         else if (generic) set(a, K1, 64, c > 8 && acc >= 400 * MB ? 10 : acc < 1000 * MB ? 16 : 13);   // 0.99-1.04; cap 16 to the end 0.98-1.00
         else if (whole && (c == 4 || c == 8)) set(a, K1, 64, c == 4 ? 13 : 8);  // 0.98-1.09; else 0.98-1.04
     } else if (acc < 400 * MB) {
-        if (c == 2 && acc >= 350 * MB && even) set(a, K1, 64, 16);              // 1.02
+        if (c == 2 && acc >= 350 * MB && filled(1024)) set(a, K1, 64, 16);              // 1.02
         else if (c >= 3 && c <= 7 && acc >= 250 * MB) set(a, K1, 64, c == 3 ? 20 : c == 4 ? 14 : 16);   // 1.01-1.03; 200 MB 0.99-1.01
         else if (c == 2 ? acc < 280 * MB : c <= 5) set(a, K4, 256, dense ? 24 : 0);         // 0.97-1.48; two copies, 300 MB: 0.99-1.02
         else if (c >= 5 && c < 8) set(a, K1, 64, 24);                           // 1.10-1.63
@@ -362,7 +366,7 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
     } else if (c == 1 || (generic && !whole)) {
         set(a, K1, 64, c < 8 ? 20 : 16);                                        // 1.00-1.02, pieces of short rows 1.02-1.15
     } else if (c == 2) {
-        if (even) set(a, K1, 64, 16);                                           // 1.01-1.02, from 2 GB on 1.00; [S,B,H] rows of 6 KiB 1.15, not of whole lanes 0.94-0.98
+        if (filled(1024)) set(a, K1, 64, 16);                                           // 1.01-1.02, from 2 GB on 1.00; [S,B,H] rows of 6 KiB 1.15, not of whole lanes 0.94-0.98
     } else if (c == 3) {
         if (acc < 1500 * MB) set(a, K1, 64, 20);                                // 1.01-1.02
         else set(a, K2, 64, 11);                                                // 1.01-1.02
@@ -409,7 +413,7 @@ void default_launches(hp_plan *p) {
     }
     const int c = p->dst_copies, s = p->src_copies;
     Launch f{1, 64, c <= 1 ? 24 : c <= 4 ? 12 : c <= 7 ? 8 : 5, 2};                          // 2 KiB tiles
-    if (c == 2) f = Launch{2, 256, 28, 2};      // two copies: 4 KiB tiles, 256 lanes (sixteen microbatches of hidden 8192 in one launch: +3.6 % over 2 KiB x 64, cap 14)
+    if (c == 2) f = Launch{2, 256, 28, 2};      // two copies: 4 KiB tiles, 256 lanes, where by_size has no other (from 300 MB on that is many segments and rows that fill small tiles badly)
     Launch b = c + s <= 2 ? Launch{1, 64, 30, 3} : c + s == 3 ? Launch{0, 64, 30, 3} : Launch{0, 64, 16, 3};
     // accumulating backward: the binary32 accumulators are read and written, 2 * 4 / elem_bytes row sizes per copy;
     // caps as the measured search finds them for 6, 8 and 16 streams (two, four and eight copies; the last from two source copies)

@@ -533,6 +533,9 @@ def test_shapes_by_size_hold_where_they_were_measured_to_be_faster(direction, tp
 # Shapes of launches that a rule made for their neighbours had slowed: each was measured on the same buffers, in the sequence
 # that a program runs, against the shapes around it.
 @pytest.mark.parametrize("direction,tp,tp_src,mbytes,images,want", [
+    # two copies, forward: few segments, a few hundred and more
+    (0, 2, 1, 350, 60, (1024, 64, 20)), (0, 2, 1, 5000, 200, (1024, 64, 20)), (0, 2, 1, 2200, 500, (1024, 64, 24)), (0, 2, 1, 1000, 500, (4096, 256, 28)),
+    (0, 2, 1, 3000, 3000, (4096, 256, 28)),
     # accumulating: three copies, five and more, and two source copies want fewer waves the more they move
     (2, 3, 1, 300, 30, (1024, 64, 20)), (2, 3, 1, 800, 30, (1024, 64, 20)), (2, 3, 1, 2500, 30, (2048, 64, 11)), (2, 3, 1, 200, 30, (4096, 256, 24)),
     (2, 5, 1, 300, 30, (1024, 64, 16)), (2, 5, 1, 800, 30, (1024, 64, 16)), (2, 5, 1, 1200, 30, (1024, 64, 14)), (2, 7, 1, 2500, 30, (1024, 64, 13)),
@@ -544,6 +547,7 @@ def test_shapes_by_size_where_a_neighbour_s_shape_lost(direction, tp, tp_src, mb
 
 # [S,B,H] order: short rows and those that begin between lines leave tiles partly empty
 @pytest.mark.parametrize("direction,tp,tp_src,mbytes,f32,row_bytes,want", [
+    (0, 2, 1, 1000, False, 1280, (4096, 256, 28)), (0, 2, 1, 1000, False, 3088, (4096, 256, 28)), (0, 2, 1, 1000, False, 6224, (1024, 64, 20)),
     (2, 2, 1, 2000, False, 16378, (2048, 64, 13)), (2, 2, 1, 2000, False, 6224, (1024, 64, 16)), (2, 1, 1, 2500, True, 6176, (2048, 64, 16)),
     (2, 1, 1, 2500, True, 8192, (4096, 64, 8)), (2, 3, 1, 2000, False, 1280, (1024, 64, 20)), (2, 9, 1, 2000, False, 1280, (1024, 64, 16)),
     (2, 6, 1, 2000, False, 8192, (1024, 64, 13)), (2, 4, 2, 2000, False, 3088, (2048, 64, 9)), (2, 12, 2, 1000, False, 1280, (1024, 64, 16))])
