@@ -906,15 +906,19 @@ void put_tables(const hp_plan *p, int variant, Args &a) {
 // (four levels 0.93 with 6), three 1.03-1.06, four 1.04-1.07 (2.06 GB over 8 CP ranks
 // 318 -> 304 us), five to seven 1.03-1.06 from 1 GB on and 0.97-0.99 at 450 MB; 150 MB
 // 0.97-1.00, eight and sixteen copies 0.94-1.01, one 1.00-1.02.  The range is narrow:
-// six rounds more lose what they gain.  Forward: to 13 and more copies, 100 MB to 1.5
-// GB, 1.03-1.06, else 0.80-1.04, mostly below 1.  Accumulating: 0.97-1.01.
+// six rounds more lose what they gain.  Forward: to sixteen copies, 200 MB to 1.5 GB,
+// in 16 and in 256 segments 1.02-1.04, three rounds either way within 1 % of that; more segments, and
+// 13 to 15 copies, from the first round on less than none.  Accumulating: 0.97-1.01.
 uint32_t pace_of(const hp_plan *p, Direction dir, const hp::Launch &L) {
     static const uint8_t two[] = {14, 11, 7, 0}, three[] = {18, 14, 11, 9}, four[] = {22, 18, 14, 10},
-                         more[] = {28, 24, 20, 20}, wide[] = {12, 8, 4, 0};
+                         more[] = {28, 24, 20, 20}, wide[] = {12, 9, 0, 0};
     if (L.tile_variant != 0 || L.block != 64 || p->src_copies != 1) return 0;
     const int c = p->dst_copies, level = (int)p->tree_info[0].n_levels - 1;
     if (level < 0 || level > 3) return 0;
-    if (dir == kForward) return c >= 13 && (1.0 + c) * (double)p->n_rows * (double)p->row_bytes < 1.5e9 ? wide[level] : 0;
+    if (dir == kForward) {
+        const double moved = (1.0 + c) * (double)p->n_rows * (double)p->row_bytes;
+        return c == 16 && moved >= 200e6 && moved < 1.5e9 && p->dst_stride == 1 ? wide[level] : 0;
+    }
     const double bytes = (double)p->bwd_bytes;
     if (dir != kBackward || bytes < 400e6) return 0;
     return c == 2 ? two[level] : c == 4 ? four[level]

@@ -307,11 +307,13 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
     }
     else if (c == 8 && dense && in(fwd, 40, 450)) set(f, K1, 64, 5);            // 0.99-1.25; [S,B,H] order 0.93-1.02
     else if (c >= 13 && dense && in(fwd, 40, 100)) set(f, K4, 64, 8);           // 1.06-1.08
-    else if (c >= 10 && dense && in(fwd, 100, 450)) set(f, K1, 64, c <= 12 ? 5 : 3);    // 0.96-1.28, cap 3 1.05-1.08 on top; 9 copies 0.91-1.09, [S,B,H] 0.86-1.05
-    else if (c >= 10 && dense && in(fwd, 450, c <= 12 ? 1200 : 1500)) {
-        if (c > 12 || segs <= 256) set(f, K1, 64, 3);                           // 1.05-1.21; twelve copies, 1.4 GB, more segments 0.71
+    else if (c >= 10 && c <= 12 && dense && in(fwd, 100, c == 12 ? 450 : 600)) set(f, K1, 64, 5);   // 0.96-1.28; ten copies, 700 MB 0.98-1.0, 1.1 GB 0.85; [S,B,H] 0.86-1.05
+    else if (c == 12 && dense && in(fwd, 450, 1000)) {
+        if (segs <= 256) set(f, K1, 64, 3);                                     // 1.03-1.09; 1.2 GB 0.93-0.97
     }
-    else if (c >= 13 && dense && in(fwd, 1500, 2600)) set(f, K2, 64, 3);        // 1.04-1.10; 2.8 GB 0.91
+    else if (c >= 13 && c <= 15 && dense && in(fwd, 100, 1200)) set(f, K1, 64, 4);  // 0.98-1.10; 1.4 GB 0.94-1.03
+    else if (c == 16 && dense && in(fwd, 100, 1500)) set(f, K1, 64, 3);         // 1.01-1.11, paced; 1.7 GB 0.91-0.99
+    else if (c >= 13 && dense && fwd >= 1200 * MB) set(f, K2, 64, 3);   // 0.99-1.03 to 4 GB
 
     // With few copies a workgroup moves little for each search, and the depth of the tree (16 segments a level) decides.
     const double bwd = (double)p->bwd_bytes;

@@ -536,6 +536,9 @@ def test_shapes_by_size_hold_where_they_were_measured_to_be_faster(direction, tp
     # two copies, forward: few segments, a few hundred and more
     (0, 2, 1, 350, 60, (1024, 64, 20)), (0, 2, 1, 5000, 200, (1024, 64, 20)), (0, 2, 1, 2200, 500, (1024, 64, 24)), (0, 2, 1, 1000, 500, (4096, 256, 28)),
     (0, 2, 1, 3000, 3000, (4096, 256, 28)),
+    # ten and more copies, forward
+    (0, 10, 1, 500, 60, (1024, 64, 5)), (0, 10, 1, 1200, 60, (2048, 64, 5)), (0, 11, 1, 1200, 9, (2048, 64, 5)), (0, 12, 1, 700, 60, (1024, 64, 3)), (0, 12, 1, 1200, 60, (2048, 64, 5)),
+    (0, 13, 1, 700, 60, (1024, 64, 4)), (0, 15, 1, 1400, 60, (2048, 64, 3)), (0, 16, 1, 700, 60, (1024, 64, 3)), (0, 16, 1, 4000, 60, (2048, 64, 3)),
     # accumulating: three copies, five and more, and two source copies want fewer waves the more they move
     (2, 3, 1, 300, 30, (1024, 64, 20)), (2, 3, 1, 800, 30, (1024, 64, 20)), (2, 3, 1, 2500, 30, (2048, 64, 11)), (2, 3, 1, 200, 30, (4096, 256, 24)),
     (2, 5, 1, 300, 30, (1024, 64, 16)), (2, 5, 1, 800, 30, (1024, 64, 16)), (2, 5, 1, 1200, 30, (1024, 64, 14)), (2, 7, 1, 2500, 30, (1024, 64, 13)),
