@@ -357,7 +357,10 @@ int hp_forward_static(const hp_plan_t *plan, const void *const *src_bufs,
  * 1 = hp_backward, 2 = hp_backward_accumulate).  A plan starts from the
  * process-wide defaults below (the accumulating backward from the backward
  * defaults, with tiles of at least 4 KiB when a tile size is set there), or
- * from what hp_plan_tune found earlier for the same problem class. */
+ * from what hp_plan_tune found earlier for the same problem class.  Beside the
+ * shape, some large launches in tiles of 1 KiB and workgroups of 64 space out
+ * their waves' first loads; that follows from the shape, the plan and the
+ * direction in every launch and is nothing to set, search for or remember. */
 typedef struct hp_launch {
     int32_t tile_bytes;      /* boundary bytes per workgroup: 1024 << k, k = 0..6              */
     int32_t block_threads;   /* workgroup size: multiple of 64 in [64, 1024]                   */

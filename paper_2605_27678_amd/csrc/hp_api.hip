@@ -135,7 +135,7 @@ __device__ __forceinline__ gchar *at(uint64_t address) { return (gchar *)address
 // before its first load.  A compute unit's waves share the scalar unit, so that those
 // which start together come out of this one after the other and their loads reach
 // memory in an even stream; where a few copies are read in small tiles, memory is
-// faster for that by more than the time it takes (pace_of).  Sleeping as long does
+// faster for that by more than the time it takes (hp::pace_rounds).  Sleeping as long does
 // not do it: the waves wake as they went (2.06 GB from four copies: no gain at 64 to
 // 2048 cycles).
 __device__ __forceinline__ void pace(uint32_t n) {
@@ -899,32 +899,6 @@ void put_tables(const hp_plan *p, int variant, Args &a) {
     }
 }
 
-// Rounds of pace() for a launch in tiles of 1 KiB, one wave each, where it was
-// measured (the same buffers in turn, 0 to 28 rounds; one source copy), by the
-// levels of the search tree, each of which takes the place of three to four.  At
-// these, backward from 450 MB to 4.5 GB: two copies 1.01-1.05 of the unpaced rate
-// (four levels 0.93 with 6), three 1.03-1.06, four 1.04-1.07 (2.06 GB over 8 CP ranks
-// 318 -> 304 us), five to seven 1.03-1.06 from 1 GB on and 0.97-0.99 at 450 MB; 150 MB
-// 0.97-1.00, eight and sixteen copies 0.94-1.01, one 1.00-1.02.  The range is narrow:
-// six rounds more lose what they gain.  Forward: to sixteen copies, 200 MB to 1.5 GB,
-// in 16 and in 256 segments 1.02-1.04, three rounds either way within 1 % of that; more segments, and
-// 13 to 15 copies, from the first round on less than none.  Accumulating: 0.97-1.01.
-uint32_t pace_of(const hp_plan *p, Direction dir, const hp::Launch &L) {
-    static const uint8_t two[] = {14, 11, 7, 0}, three[] = {18, 14, 11, 9}, four[] = {22, 18, 14, 10},
-                         more[] = {28, 24, 20, 20}, wide[] = {12, 9, 0, 0};
-    if (L.tile_variant != 0 || L.block != 64 || p->src_copies != 1) return 0;
-    const int c = p->dst_copies, level = (int)p->tree_info[0].n_levels - 1;
-    if (level < 0 || level > 3) return 0;
-    if (dir == kForward) {
-        const double moved = (1.0 + c) * (double)p->n_rows * (double)p->row_bytes;
-        return c == 16 && moved >= 200e6 && moved < 1.5e9 && p->dst_stride == 1 ? wide[level] : 0;
-    }
-    const double bytes = (double)p->bwd_bytes;
-    if (dir != kBackward || bytes < 400e6) return 0;
-    return c == 2 ? two[level] : c == 4 ? four[level]
-         : c == 3 && bytes >= 450e6 ? three[level] : c >= 5 && c <= 7 && bytes >= 800e6 ? more[level] : 0;
-}
-
 // Enqueues one kernel for direction `dir` with launch shape `L`.
 int enqueue_params(const hp_plan *p, Direction dir, const hp::Launch &L, const BufTable &bt, hipStream_t stream,
                    EventPair ev, const KParams &k);
@@ -944,7 +918,7 @@ int enqueue_params(const hp_plan *p, Direction dir, const hp::Launch &L, const B
     std::memcpy(a.b.p, bt.p, (size_t)(p->n_src_bufs + p->n_dst_bufs) * sizeof(void *));
     if (dir == kBackwardAcc) hp::set_row_chunks(a.k, 4u * (uint32_t)p->elem_bytes);
     a.k.block = (uint32_t)L.block;
-    a.k.pace = pace_of(p, dir, L);
+    a.k.pace = (uint32_t)hp::pace_rounds(*p, (int)dir, L);
     if (!a.k.segs) put_tables(p, L.tile_variant, a);
     const KParams &k = a.k;
     LaunchCfg c;

@@ -250,6 +250,9 @@ int make_tables(hp_plan *p) {
     return HP_OK;
 }
 
+// Whether all tiles of 1 KiB but a run's last are whole.
+bool even_tiles(const hp_plan &p) { return p.dst_stride == 1 || p.row_bytes % 1024 == 0; }
+
 // The shapes of launches whose size calls for others than the replica counts
 // alone.  Each line was measured against the shape that it replaces in the
 // sequence a program runs (forward, backward, forward, ...; forward, accumulate,
@@ -273,11 +276,10 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
     const int c = p->dst_copies, s = p->src_copies;
     const bool generic = c != 1 && c != 2 && c != 4 && c != 8, f32 = p->elem_bytes == 4, dense = p->dst_stride == 1;
     const bool whole = dense || p->row_bytes >= 4096;        // tiles of 1 KiB are nearly all whole
-    // A row-strided row is cut into tiles from its start: whether it fills what it is cut into, in whole lanes.
-    auto filled = [&](int64_t tile) {
-        const int64_t row = p->row_bytes, cut = (row + tile - 1) / tile * tile;
-        return dense || (row >= tile && row % 16 == 0 && 20 * row >= 17 * cut);
-    };
+    // A row-strided row is cut into tiles from its start: whether it fills what it is cut into, and that in whole lanes.
+    const int64_t row = p->row_bytes;
+    auto fills = [&](int64_t tile) { return dense || 20 * row >= 17 * ((row + tile - 1) / tile * tile); };
+    const bool filled = fills(1024) && (dense || row % 16 == 0), even = even_tiles(*p);
     const size_t segs = p->segments.size();
     constexpr double MB = 1e6;
     auto set = [](Launch &L, int tile, int block, int cap) { L = Launch{tile, block, cap, L.nontemporal}; };
@@ -289,7 +291,7 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
         else set(f, K2, 64, 20);                                                // 1.00-1.02
     }
     else if (c == 2 && in(fwd, 40, 290)) set(f, K8, 256, 16);                   // 0.98-1.13; 300 MB: 0.96-1.00
-    else if (c == 2 && fwd >= 300 * MB && filled(1024)) {
+    else if (c == 2 && fwd >= 300 * MB && filled) {
         if (segs <= 256) set(f, K1, 64, 20);                                    // 1.01-1.04 to 1.2 GB, 1.01-1.02 to 15 GB; else 0.93-1.02
         else if (segs <= 1024 && fwd >= 1500 * MB) set(f, K1, 64, 24);          // 1.01-1.03; smaller launches and more segments 0.97-1.02
     }
@@ -308,8 +310,8 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
     else if (c == 8 && dense && in(fwd, 40, 450)) set(f, K1, 64, 5);            // 0.99-1.25; [S,B,H] order 0.93-1.02
     else if (c >= 13 && dense && in(fwd, 40, 100)) set(f, K4, 64, 8);           // 1.06-1.08
     else if (c >= 10 && c <= 12 && dense && in(fwd, 100, c == 12 ? 450 : 600)) set(f, K1, 64, 5);   // 0.96-1.28; ten copies, 700 MB 0.98-1.0, 1.1 GB 0.85; [S,B,H] 0.86-1.05
-    else if (c == 12 && dense && in(fwd, 450, 1000)) {
-        if (segs <= 256) set(f, K1, 64, 3);                                     // 1.03-1.09; 1.2 GB 0.93-0.97
+    else if (c == 12 && dense && in(fwd, 450, 1200)) {
+        if (segs <= 256) set(f, K1, 64, fwd < 1000 * MB ? 3 : 4);               // 1.02-1.12; 1.2 GB 0.93-0.99
     }
     else if (c >= 13 && c <= 15 && dense && in(fwd, 100, 1200)) set(f, K1, 64, 4);  // 0.98-1.10; 1.4 GB 0.94-1.03
     else if (c == 16 && dense && in(fwd, 100, 1500)) set(f, K1, 64, 3);         // 1.01-1.11, paced; 1.7 GB 0.91-0.99
@@ -326,14 +328,21 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
     else if (c == 2 && s == 1 && in(bwd, 80, 290)) {
         if (segs <= 16) set(b, K8, 256, 24);                                    // 0.99-1.06; more segments 0.95-1.02, 40 MB 0.97-1.05
     }
-    else if (c == 2 && s == 1 && bwd >= 450 * MB) {
-        if (segs > 256) set(b, K1, 64, 28);                                     // 1.00-1.01
+    else if (c == 2 && s == 1 && bwd >= 400 * MB && even) {
+        if (segs <= 16) set(b, K1, 64, 28);                                     // 1.00-1.02
+        else if (segs <= 4096) set(b, K1, 64, segs <= 1024 ? 24 : 28);          // paced: 1.01-1.04 of cap 30
     }
     else if (c == 2 && s > 1 && bwd >= 40 * MB) set(b, K1, 64, 20);             // 1.05-1.09; 27 MB: 0.95-1.02
     else if (c == 4 && s == 1 && in(bwd, 35, segs <= 16 ? 360 : 220)) set(b, K1, 64, 24);   // 1.02-1.14; more segments from 240 MB 0.95-1.04
     else if (generic && c < 8 && bwd >= (c <= 5 ? 16 : 30) * MB &&              // 3 copies 1.03-1.35, 5 to 7 0.98-1.28
              !(f32 && (s > 1 ? bwd >= 600 * MB : c == 7 && bwd >= 500 * MB)))   // there 0.97-1.02 and 0.95-1.02
-        set(b, K1, 64, (c == 5 || c == 6) && bwd >= 450 * MB ? 16 : c == 3 && s == 1 && bwd >= 450 * MB ? 20 : c <= 5 && s == 1 ? 28 : 24);   // cap 16: 1.01-1.02; cap 20, paced: 1.01-1.06
+    {
+        int cap = c <= 5 && s == 1 ? 28 : 24;
+        if (c == 3 && s == 1 && bwd >= 450 * MB && even) cap = segs <= 4096 ? 20 : 24;               // paced: 1.01-1.03 of cap 28
+        else if (c == 5 && bwd >= 450 * MB && filled) cap = bwd < 800 * MB ? 20 : 16;                       // 1.00-1.02
+        else if (c == 6 && bwd >= 450 * MB && filled) cap = 16;                                             // 1.01-1.02
+        set(b, K1, 64, cap);
+    }
     else if (c == 8 && in(bwd, 40, 450)) set(b, K1, 64, 12);                    // 1.00-1.04
     else if (c == 8 && in(bwd, 450, 1500)) set(b, K1, 64, 11);                  // 1.02-1.05
     else if (c == 8 && bwd >= 1500 * MB) set(b, K4, 64, 5);                     // 1.03-1.06, to two source copies 1.05-1.11
@@ -359,7 +368,7 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
         else if (generic) set(a, K1, 64, c > 8 && acc >= 400 * MB ? 10 : acc < 1000 * MB ? 16 : 13);   // 0.99-1.04; cap 16 to the end 0.98-1.00
         else if (whole && (c == 4 || c == 8)) set(a, K1, 64, c == 4 ? 13 : 8);  // 0.98-1.09; else 0.98-1.04
     } else if (acc < 400 * MB) {
-        if (c == 2 && acc >= 350 * MB && filled(1024)) set(a, K1, 64, 16);              // 1.02
+        if (c == 2 && acc >= 350 * MB && filled) set(a, K1, 64, 16);              // 1.02
         else if (c >= 3 && c <= 7 && acc >= 250 * MB) set(a, K1, 64, c == 3 ? 20 : c == 4 ? 14 : 16);   // 1.01-1.03; 200 MB 0.99-1.01
         else if (c == 2 ? acc < 280 * MB : c <= 5) set(a, K4, 256, dense ? 24 : 0);         // 0.97-1.48; two copies, 300 MB: 0.99-1.02
         else if (c >= 5 && c < 8) set(a, K1, 64, 24);                           // 1.10-1.63
@@ -368,7 +377,7 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
     } else if (c == 1 || (generic && !whole)) {
         set(a, K1, 64, c < 8 ? 20 : 16);                                        // 1.00-1.02, pieces of short rows 1.02-1.15
     } else if (c == 2) {
-        if (filled(1024)) set(a, K1, 64, 16);                                           // 1.01-1.02, from 2 GB on 1.00; [S,B,H] rows of 6 KiB 1.15, not of whole lanes 0.94-0.98
+        if (filled) set(a, K1, 64, 16);                                           // 1.01-1.02, from 2 GB on 1.00; [S,B,H] rows of 6 KiB 1.15, not of whole lanes 0.94-0.98
     } else if (c == 3) {
         if (acc < 1500 * MB) set(a, K1, 64, 20);                                // 1.01-1.02
         else set(a, K2, 64, 11);                                                // 1.01-1.02
@@ -459,6 +468,34 @@ int check_cross_edge_overlap(const hp_token_map_t *maps, int32_t n_edges, int32_
 }
 
 }  // namespace
+
+// How many: few enough that the scalar unit still keeps ahead of memory; past that a
+// launch takes longer with every round.  Measured on the same buffers in turn, 0 to 28
+// rounds, over 0.45 to 4.5 GB, both element types, whole and ragged rows.  The gain is
+// over no pacing, either at its best cap, by the levels of the search tree (which take
+// the place of some rounds); in brackets what is left of it three rounds either way.
+//   backward, two copies     -, 1.02 (0.99-1.01), 1.01 (1.00)
+//             three          1.02 (1.01), 1.02 (1.00-1.01), 1.02 (1.01)
+//             four           1.02 (1.01), 1.02 (1.01), 1.02 (1.01)
+//             six, 0.8 GB on 1.01-1.02 (1.01), 1.01 (1.01), -
+//   forward, sixteen, 0.2 to 1.5 GB 1.03 (1.02), 1.03 (1.02), 1.01 (1.00)
+// Against the kernels whose search was slower and paced them by itself the paced ones
+// are at 1.00-1.01 (two copies, two levels), 1.13 (three), 1.00-1.03 (three copies), 1.01-1.03
+// (four), 1.05 (six).  Elsewhere - smaller launches, other counts, four levels, accumulating,
+// forward to 13 to 15 copies - pacing gains 1 % at most or loses.  Where row-strided rows
+// leave tiles partly empty it costs up to 13 %.
+int pace_rounds(const hp_plan &p, int direction, const Launch &L) {
+    static const uint8_t two[] = {0, 7, 3, 0}, three[] = {18, 13, 8, 0}, four[] = {21, 17, 12, 0}, six[] = {25, 22, 0, 0}, sixteen[] = {12, 9, 3, 0};
+    if (L.tile_variant != 0 || L.block != 64 || p.src_copies != 1 || !even_tiles(p) || p.segments.empty()) return 0;
+    const int c = p.dst_copies, level = (int)p.tree_info[0].n_levels - 1;
+    if (direction == 0) {
+        const double bytes = (1.0 + c) * (double)p.n_rows * (double)p.row_bytes;
+        return c == 16 && p.dst_stride == 1 && bytes >= 200e6 && bytes < 1.5e9 ? sixteen[level] : 0;
+    }
+    const double bytes = (double)p.bwd_bytes;
+    if (direction != 1 || bytes < 400e6) return 0;
+    return c == 2 ? two[level] : c == 3 && bytes >= 450e6 ? three[level] : c == 4 ? four[level] : c == 6 && bytes >= 800e6 ? six[level] : 0;
+}
 
 int build_host_plan(const hp_layout_t *srcs, int32_t n_edges, const hp_layout_t *dst,
                     const hp_token_map_t *maps, int32_t n_maps, hp_plan *p) {

@@ -128,6 +128,13 @@ namespace hp {
 int build_host_plan(const hp_layout_t *srcs, int32_t n_edges, const hp_layout_t *dst,
                     const hp_token_map_t *maps, int32_t n_maps, hp_plan *plan);
 
+// Rounds of the kernels' pace() for a launch of the plan in shape L (direction 0
+// forward, 1 backward, 2 accumulating): chosen for every launch by its tile, its bytes
+// and its replica counts, whoever chose the shape; no part of a shape that is set,
+// searched for or remembered.  Every cap that was measured with these rounds is within
+// 1 % of the same cap without them or faster.
+int pace_rounds(const hp_plan &p, int direction, const Launch &L);
+
 // Tiles of `tile` bytes that a run of n_rows rows is cut into.
 uint64_t tiles_of(uint64_t n_rows, uint64_t pitch_rows, int64_t row_bytes, uint32_t tile);
 

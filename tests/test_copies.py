@@ -1,4 +1,4 @@
-"""Every replica count through every kind of tile: the kernels of a fixed count (1, 2, 3, 4, 8, 16), and the one that takes
+"""Every replica count through every kind of tile: the kernels of a fixed count (1, 2, 3, 4, 8), and the one that takes
 groups of four and a last group of one to three.  Bit for bit against the oracle; whole and partial tiles, two source copies."""
 import numpy as np
 import pytest
@@ -48,4 +48,35 @@ def test_replica_counts_of_every_kind_of_tile(tp, f32, hidden, sbh):
         for what, got, want in zip(("forward", "backward", "accumulate"), out, (want_d, want_y, want_a)):
             for i, (t, w) in enumerate(zip(got, want)):
                 assert np.array_equal(bits(t).view(np.uint8), w.reshape(t.shape).view(np.uint8)), (what, i, shape)
+    plan.close()
+
+
+# Launches that are paced (hp::pace_rounds): large ones in tiles of 1 KiB, by the levels of the search tree.
+@pytest.mark.parametrize("tp,mbytes,images", [(2, 410, 40), (3, 460, 9), (3, 460, 40), (3, 460, 300), (4, 410, 9), (4, 410, 300), (6, 820, 40),
+                                              (16, 220, 9), (16, 220, 40)])
+def test_paced_launches(tp, mbytes, images):
+    hidden = 2048
+    n = mbytes * 1000000 // ((tp + 1) * hidden * 2) // images + 1
+    start = [i * (n + 3) for i in range(images)]
+    tm = wl.TokenMap(1, images * (n + 3), hidden, [0] * images, start, [n] * images)
+    src, dst = wl.Grid(), wl.Grid(tp=tp)
+    plan, prob = hp.hp_plan_create(src, dst, tm), oracle.Problem(src, dst, tm)
+    gen = torch.Generator(device="cuda").manual_seed(tp * images)
+
+    def values(r):
+        return torch.randn((r, hidden), generator=gen, device="cuda", dtype=torch.bfloat16)
+
+    def bits(t):
+        return t.cpu().contiguous().view(torch.int16).numpy().view(np.uint16)
+
+    x, g = [values(r) for r in prob.src_rows()], [values(prob.dst_rows()) for _ in range(prob.n_dst)]
+    d, y = [torch.zeros_like(t) for t in g], [torch.empty_like(t) for t in x]
+    assert (plan.info.n_segments, plan.get_launch(0 if tp == 16 else 1)["tile_bytes"]) == (images, 1024)
+    hp.hp_forward(plan, x, d)
+    hp.hp_backward(plan, g, y)
+    want_d, want_y = [np.zeros(tuple(t.shape), np.uint16) for t in d], [np.zeros(tuple(t.shape), np.uint16) for t in y]
+    prob.forward([bits(t) for t in x], want_d)
+    prob.backward_bf16([bits(t) for t in g], want_y)
+    for got, want in list(zip(d, want_d)) + list(zip(y, want_y)):
+        assert np.array_equal(bits(got), want)
     plan.close()

@@ -1,4 +1,5 @@
-"""The scalar arithmetic of the tile lookup (csrc/hp_tile.hpp, the kernels' own code) against its plain form, on the CPU."""
+"""The scalar arithmetic of the tile lookup (csrc/hp_tile.hpp, the kernels' own code) against its plain form, and which launches are
+paced, on the CPU."""
 import os
 import subprocess
 

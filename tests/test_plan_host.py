@@ -539,6 +539,10 @@ def test_shapes_by_size_hold_where_they_were_measured_to_be_faster(direction, tp
     # ten and more copies, forward
     (0, 10, 1, 500, 60, (1024, 64, 5)), (0, 10, 1, 1200, 60, (2048, 64, 5)), (0, 11, 1, 1200, 9, (2048, 64, 5)), (0, 12, 1, 700, 60, (1024, 64, 3)), (0, 12, 1, 1200, 60, (2048, 64, 5)),
     (0, 13, 1, 700, 60, (1024, 64, 4)), (0, 15, 1, 1400, 60, (2048, 64, 3)), (0, 16, 1, 700, 60, (1024, 64, 3)), (0, 16, 1, 4000, 60, (2048, 64, 3)),
+    # backward: the caps of paced launches, and of those that pacing does not help
+    (1, 2, 1, 600, 9, (1024, 64, 28)), (1, 2, 1, 600, 60, (1024, 64, 24)), (1, 2, 1, 600, 600, (1024, 64, 24)), (1, 2, 1, 600, 2000, (1024, 64, 28)), (1, 2, 1, 600, 5000, (1024, 64, 30)),
+    (1, 3, 1, 600, 60, (1024, 64, 20)), (1, 3, 1, 600, 600, (1024, 64, 20)), (1, 3, 1, 600, 5000, (1024, 64, 24)), (1, 5, 1, 600, 60, (1024, 64, 20)),
+    (1, 5, 1, 1500, 60, (1024, 64, 16)),
     # accumulating: three copies, five and more, and two source copies want fewer waves the more they move
     (2, 3, 1, 300, 30, (1024, 64, 20)), (2, 3, 1, 800, 30, (1024, 64, 20)), (2, 3, 1, 2500, 30, (2048, 64, 11)), (2, 3, 1, 200, 30, (4096, 256, 24)),
     (2, 5, 1, 300, 30, (1024, 64, 16)), (2, 5, 1, 800, 30, (1024, 64, 16)), (2, 5, 1, 1200, 30, (1024, 64, 14)), (2, 7, 1, 2500, 30, (1024, 64, 13)),
@@ -551,6 +555,8 @@ def test_shapes_by_size_where_a_neighbour_s_shape_lost(direction, tp, tp_src, mb
 # [S,B,H] order: short rows and those that begin between lines leave tiles partly empty
 @pytest.mark.parametrize("direction,tp,tp_src,mbytes,f32,row_bytes,want", [
     (0, 2, 1, 1000, False, 1280, (4096, 256, 28)), (0, 2, 1, 1000, False, 3088, (4096, 256, 28)), (0, 2, 1, 1000, False, 6224, (1024, 64, 20)),
+    (1, 2, 1, 1000, False, 1280, (1024, 64, 30)), (1, 3, 1, 1000, False, 1280, (1024, 64, 28)), (1, 5, 1, 1000, False, 3088, (1024, 64, 28)),
+    (1, 6, 1, 1000, False, 8186, (1024, 64, 24)),
     (2, 2, 1, 2000, False, 16378, (2048, 64, 13)), (2, 2, 1, 2000, False, 6224, (1024, 64, 16)), (2, 1, 1, 2500, True, 6176, (2048, 64, 16)),
     (2, 1, 1, 2500, True, 8192, (4096, 64, 8)), (2, 3, 1, 2000, False, 1280, (1024, 64, 20)), (2, 9, 1, 2000, False, 1280, (1024, 64, 16)),
     (2, 6, 1, 2000, False, 8192, (1024, 64, 13)), (2, 4, 2, 2000, False, 3088, (2048, 64, 9)), (2, 12, 2, 1000, False, 1280, (1024, 64, 16))])
