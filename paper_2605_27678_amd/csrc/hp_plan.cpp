@@ -343,11 +343,11 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
         else if (c == 6 && bwd >= 450 * MB && filled) cap = 16;                                             // 1.01-1.02
         set(b, K1, 64, cap);
     }
-    else if (c == 8 && in(bwd, 40, 450)) set(b, K1, 64, 12);                    // 1.00-1.04
-    else if (c == 8 && in(bwd, 450, 1500)) set(b, K1, 64, 11);                  // 1.02-1.05
-    else if (c == 8 && bwd >= 1500 * MB) set(b, K4, 64, 5);                     // 1.03-1.06, to two source copies 1.05-1.11
+    // half a dozen to a dozen waves of eight and more copies have to have whole tiles: [S,B,H] rows that leave them partly empty lose 2-13 % here
+    else if (c == 8 && bwd >= 1500 * MB && (dense || row < 4096 || fills(4096))) set(b, K4, 64, 5);   // 1.01-1.06, to two source copies 1.05-1.11
+    else if (c == 8 && bwd >= 40 * MB && filled) set(b, K1, 64, bwd < 450 * MB ? 12 : 11);   // 1.00-1.03
     else if (c > 12 && dense && in(bwd, 40, 250)) set(b, K1, 64, 12);           // 1.02-1.07; 350 MB 0.97-1.00, [S,B,H] order 0.85-1.0
-    else if (c > 8 && bwd >= 600 * MB) set(b, K1, 64, 10);                      // 1.02-1.06
+    else if (c > 8 && bwd >= 600 * MB && filled) set(b, K1, 64, 10);            // 1.02-1.06
     else if (c > 8 && !f32 && in(bwd, 100, 250)) set(b, K4, 128, 24);           // 0.98-1.14; binary32: 0.97-1.00, 300 MB: 0.94-1.01
 
     const double acc = (double)p->bwd_accum_bytes;

@@ -556,7 +556,8 @@ def test_shapes_by_size_where_a_neighbour_s_shape_lost(direction, tp, tp_src, mb
 @pytest.mark.parametrize("direction,tp,tp_src,mbytes,f32,row_bytes,want", [
     (0, 2, 1, 1000, False, 1280, (4096, 256, 28)), (0, 2, 1, 1000, False, 3088, (4096, 256, 28)), (0, 2, 1, 1000, False, 6224, (1024, 64, 20)),
     (1, 2, 1, 1000, False, 1280, (1024, 64, 30)), (1, 3, 1, 1000, False, 1280, (1024, 64, 28)), (1, 5, 1, 1000, False, 3088, (1024, 64, 28)),
-    (1, 6, 1, 1000, False, 8186, (1024, 64, 24)),
+    (1, 6, 1, 1000, False, 8186, (1024, 64, 24)), (1, 8, 1, 2500, False, 5120, (1024, 64, 11)), (1, 8, 1, 2500, False, 3088, (4096, 64, 5)),
+    (1, 8, 1, 600, False, 3088, (1024, 64, 16)), (1, 12, 1, 1000, False, 1280, (1024, 64, 16)), (1, 12, 1, 1000, False, 514, (1024, 64, 16)), (1, 16, 1, 2900, False, 3072, (1024, 64, 10)),
     (2, 2, 1, 2000, False, 16378, (2048, 64, 13)), (2, 2, 1, 2000, False, 6224, (1024, 64, 16)), (2, 1, 1, 2500, True, 6176, (2048, 64, 16)),
     (2, 1, 1, 2500, True, 8192, (4096, 64, 8)), (2, 3, 1, 2000, False, 1280, (1024, 64, 20)), (2, 9, 1, 2000, False, 1280, (1024, 64, 16)),
     (2, 6, 1, 2000, False, 8192, (1024, 64, 13)), (2, 4, 2, 2000, False, 3088, (2048, 64, 9)), (2, 12, 2, 1000, False, 1280, (1024, 64, 16))])
