@@ -296,16 +296,16 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
         else if (segs <= 1024 && fwd >= 1500 * MB) set(f, K1, 64, 24);          // 1.01-1.03; smaller launches and more segments 0.97-1.02
     }
     else if (c == 3 && in(fwd, 40, 1000)) {
-        if (segs <= 128) set(f, K1, 64, fwd < 200 * MB ? 10 : 16);              // 1.01-1.09; more segments 0.94-1.0
+        if (segs <= 128 && (filled || row < 1024)) set(f, K1, 64, fwd < 200 * MB ? 10 : 16);   // 1.00-1.14; more segments 0.94-1.0, rows of 1280 and 3088 bytes 0.87-0.99
     }
     else if (c == 4 && in(fwd, 8, 180)) {
-        if (segs <= 256) set(f, K1, 64, 8);                                     // 0.99-1.08; more segments 0.96-1.02, 450 MB 0.87-0.91
+        if (segs <= 256 && (filled || row < 1024)) set(f, K1, 64, 8);           // 0.99-1.15; more segments 0.96-1.02, rows of 1280 bytes 0.92, 450 MB 0.87-0.91
     }
     else if (c >= 5 && c <= 7 && in(fwd, 40, 450)) {
         if (c > 5 || segs <= 16) set(f, K1, 64, 10);                            // 0.96-1.20; 20 MB 0.89-1.06, five copies and more segments 0.87-1.03
     }
     else if (c >= 5 && c <= 7 && fwd >= 450 * MB) {
-        if (segs <= 256) set(f, K1, 64, 14);                                    // 1.02-1.07; more segments 0.97-1.02
+        if (segs <= 256 && (filled || row < 2048)) set(f, K1, 64, 14);          // 1.02-1.15; more segments 0.97-1.02, rows of 3088 and 8186 bytes 0.94-0.99
     }
     else if (c == 8 && dense && in(fwd, 40, 450)) set(f, K1, 64, 5);            // 0.99-1.25; [S,B,H] order 0.93-1.02
     else if (c >= 13 && dense && in(fwd, 40, 100)) set(f, K4, 64, 8);           // 1.06-1.08

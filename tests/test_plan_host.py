@@ -554,6 +554,8 @@ def test_shapes_by_size_where_a_neighbour_s_shape_lost(direction, tp, tp_src, mb
 
 # [S,B,H] order: short rows and those that begin between lines leave tiles partly empty
 @pytest.mark.parametrize("direction,tp,tp_src,mbytes,f32,row_bytes,want", [
+    (0, 3, 1, 150, False, 1280, (2048, 64, 12)), (0, 3, 1, 150, False, 5120, (1024, 64, 10)), (0, 4, 1, 100, False, 1280, (2048, 64, 12)),
+    (0, 4, 1, 100, False, 514, (1024, 64, 8)), (0, 5, 1, 600, False, 3088, (2048, 64, 8)), (0, 6, 1, 600, False, 1280, (1024, 64, 14)),
     (0, 2, 1, 1000, False, 1280, (4096, 256, 28)), (0, 2, 1, 1000, False, 3088, (4096, 256, 28)), (0, 2, 1, 1000, False, 6224, (1024, 64, 20)),
     (1, 2, 1, 1000, False, 1280, (1024, 64, 30)), (1, 3, 1, 1000, False, 1280, (1024, 64, 28)), (1, 5, 1, 1000, False, 3088, (1024, 64, 28)),
     (1, 6, 1, 1000, False, 8186, (1024, 64, 24)), (1, 8, 1, 2500, False, 5120, (1024, 64, 11)), (1, 8, 1, 2500, False, 3088, (4096, 64, 5)),
