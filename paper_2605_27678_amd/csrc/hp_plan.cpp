@@ -257,24 +257,23 @@ bool even_tiles(const hp_plan &p) { return p.dst_stride == 1 || p.row_bytes % 10
 // alone.  Each line was measured against the shape that it replaces in the
 // sequence a program runs (forward, backward, forward, ...; forward, accumulate,
 // ... - a shape that leaves dirty lines behind is paid for by the next launch,
-// and ranks wrongly when it is timed alone), in both element types, with rows of
-// 1 to 24 KiB, images of 16 to 4096 rows, both row orders and launches of 8 MB to
-// 3.5 GB (accumulating ones to 5 GB); the figures are the direction's gain over that
-// range, and after the semicolon what it would be where the line has ended.  Copy
-// counts measured: 1 to 14 and 16 with one source copy; 1 to 8 and 12 with two.
+// and ranks wrongly when it is timed alone) and on the same buffers (two sets
+// differ by 2 % and now and then by 10), in both element types, with rows of
+// 0.5 to 24 KiB, images of 16 to 4096 rows, both row orders and launches of 8 MB to
+// 4.5 GB; the figures are the direction's gain over that range, and after the
+// semicolon what it would be where the line has ended.  Copy
+// counts measured: 1 to 16 with one source copy; 1 to 8 and 12 with two.
 // Launches of up to about 400 MB find part of
 // their buffers in the 256 MB memory-side cache and want more waves; replica
 // counts without a kernel of their own (all but 1, 2, 3, 4 and 8) wait for their
-// groups of four loads and want more of them in flight; and the more copies there
-// are to write, the fewer waves keep a compute unit's 40 to 50 KB on their way.
-// Since a workgroup finds its tile in half the time, small tiles gain up to more
-// segments and fewer waves do: over 450 random calls of 12 MB to 3.5 GB (1 to 16
-// copies) the lookup and these lines together took the forward's time to 0.93 of
-// what it was (0.71-1.09) and the backward's to 0.93 (0.70-1.06).
+// groups of four loads and want more of them in flight; the more copies there
+// are to write, the fewer waves keep a compute unit's 40 to 50 KB on their way; and
+// small tiles want segments and rows that fill them.
 void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
     constexpr int K1 = 0, K2 = 1, K4 = 2, K8 = 3;            // tiles of 1, 2, 4 and 8 KiB
     const int c = p->dst_copies, s = p->src_copies;
-    const bool generic = c != 1 && c != 2 && c != 4 && c != 8, f32 = p->elem_bytes == 4, dense = p->dst_stride == 1;
+    const bool between = c != 1 && c != 2 && c != 4 && c != 8;                  // 3, 5 to 7, 9 to 16 copies
+    const bool f32 = p->elem_bytes == 4, dense = p->dst_stride == 1;
     const bool whole = dense || p->row_bytes >= 4096;        // tiles of 1 KiB are nearly all whole
     // A row-strided row is cut into tiles from its start: whether it fills what it is cut into, and that in whole lanes.
     const int64_t row = p->row_bytes;
@@ -286,10 +285,7 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
     auto in = [](double bytes, double from, double to) { return bytes >= from * MB && bytes < to * MB; };
 
     const double fwd = (1.0 + c) * (double)p->n_rows * (double)p->row_bytes;
-    if (c == 1 && fwd >= 200 * MB && segs <= 256) {
-        if (fwd < 400 * MB) set(f, K4, 128, 24);                                // 0.99-1.03; more segments 0.98-1.03
-        else set(f, K2, 64, 20);                                                // 1.00-1.02
-    }
+    if (c == 1 && fwd >= 200 * MB && segs <= 256) set(f, K4, 128, 24);          // 0.99-1.03; more segments 0.98-1.03
     else if (c == 2 && in(fwd, 40, 290)) set(f, K8, 256, 16);                   // 0.98-1.13; 300 MB: 0.96-1.00
     else if (c == 2 && fwd >= 300 * MB && filled) {
         if (segs <= 256) set(f, K1, 64, 20);                                    // 1.01-1.04 to 1.2 GB, 1.01-1.02 to 15 GB; else 0.93-1.02
@@ -308,7 +304,6 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
         if (segs <= 256 && (filled || row < 2048)) set(f, K1, 64, 14);          // 1.02-1.15; more segments 0.97-1.02, rows of 3088 and 8186 bytes 0.94-0.99
     }
     else if (c == 8 && dense && in(fwd, 40, 450)) set(f, K1, 64, 5);            // 0.99-1.25; [S,B,H] order 0.93-1.02
-    else if (c >= 13 && dense && in(fwd, 40, 100)) set(f, K4, 64, 8);           // 1.06-1.08
     else if (c >= 10 && c <= 12 && dense && in(fwd, 100, c == 12 ? 450 : 600)) set(f, K1, 64, 5);   // 0.96-1.28; ten copies, 700 MB 0.98-1.0, 1.1 GB 0.85; [S,B,H] 0.86-1.05
     else if (c == 12 && dense && in(fwd, 450, 1200)) {
         if (segs <= 256) set(f, K1, 64, fwd < 1000 * MB ? 3 : 4);               // 1.02-1.12; 1.2 GB 0.93-0.99
@@ -334,13 +329,13 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
     }
     else if (c == 2 && s > 1 && bwd >= 40 * MB) set(b, K1, 64, 20);             // 1.05-1.09; 27 MB: 0.95-1.02
     else if (c == 4 && s == 1 && in(bwd, 35, segs <= 16 ? 360 : 220)) set(b, K1, 64, 24);   // 1.02-1.14; more segments from 240 MB 0.95-1.04
-    else if (generic && c < 8 && bwd >= (c <= 5 ? 16 : 30) * MB &&              // 3 copies 1.03-1.35, 5 to 7 0.98-1.28
+    else if (between && c < 8 && bwd >= (c <= 5 ? 16 : 30) * MB &&              // 3 copies 1.03-1.35, 5 to 7 0.98-1.28
              !(f32 && (s > 1 ? bwd >= 600 * MB : c == 7 && bwd >= 500 * MB)))   // there 0.97-1.02 and 0.95-1.02
     {
         int cap = c <= 5 && s == 1 ? 28 : 24;
-        if (c == 3 && s == 1 && bwd >= 450 * MB && even) cap = segs <= 4096 ? 20 : 24;               // paced: 1.01-1.03 of cap 28
-        else if (c == 5 && bwd >= 450 * MB && filled) cap = bwd < 800 * MB ? 20 : 16;                       // 1.00-1.02
-        else if (c == 6 && bwd >= 450 * MB && filled) cap = 16;                                             // 1.01-1.02
+        if (c == 3 && s == 1 && bwd >= 450 * MB && even) cap = segs <= 4096 ? 20 : 24;   // paced: 1.01-1.03 of cap 28
+        else if (c == 5 && bwd >= 450 * MB && filled) cap = bwd < 800 * MB ? 20 : 16;   // 1.00-1.02
+        else if (c == 6 && bwd >= 450 * MB && filled) cap = 16;                 // 1.01-1.02
         set(b, K1, 64, cap);
     }
     // half a dozen to a dozen waves of eight and more copies have to have whole tiles: [S,B,H] rows that leave them partly empty lose 2-13 % here
@@ -364,8 +359,8 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
             set(a, K4, 64, 8);                                                  // 1.02-1.06; 450 MB: 0.97-1.01, [S,B,H] rows of 6 KiB 0.93
     } else if (s > 1) {
         // few waves want whole tiles: pieces of row-strided rows under 4 KiB 0.96-1.01 with the smaller caps, 1.02-1.13 with 16
-        if (acc < 200 * MB || (generic && !whole)) set(a, K1, 64, 16);          // 1.04-1.44
-        else if (generic) set(a, K1, 64, c > 8 && acc >= 400 * MB ? 10 : acc < 1000 * MB ? 16 : 13);   // 0.99-1.04; cap 16 to the end 0.98-1.00
+        if (acc < 200 * MB || (between && !whole)) set(a, K1, 64, 16);          // 1.04-1.44
+        else if (between) set(a, K1, 64, c > 8 && acc >= 400 * MB ? 10 : acc < 1000 * MB ? 16 : 13);   // 0.99-1.04; cap 16 to the end 0.98-1.00
         else if (whole && (c == 4 || c == 8)) set(a, K1, 64, c == 4 ? 13 : 8);  // 0.98-1.09; else 0.98-1.04
     } else if (acc < 400 * MB) {
         if (c == 2 && acc >= 350 * MB && filled) set(a, K1, 64, 16);              // 1.02
@@ -374,7 +369,7 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
         else if (c >= 5 && c < 8) set(a, K1, 64, 24);                           // 1.10-1.63
         else if (c == 8 && dense && in(acc, 50, 350)) set(a, K4, 256, 16);      // 1.01-1.11; 27 MB 0.96, 400 MB 0.99, [S,B,H] 0.96-1.07
         else if (c > 8) set(a, K1, 64, c <= 10 || acc < 150 * MB ? 20 : 12);    // 1.21-1.71, cap 12 1.00-1.02 on top; 9 copies 0.99
-    } else if (c == 1 || (generic && !whole)) {
+    } else if (c == 1 || (between && !whole)) {
         set(a, K1, 64, c < 8 ? 20 : 16);                                        // 1.00-1.02, pieces of short rows 1.02-1.15
     } else if (c == 2) {
         if (filled) set(a, K1, 64, 16);                                           // 1.01-1.02, from 2 GB on 1.00; [S,B,H] rows of 6 KiB 1.15, not of whole lanes 0.94-0.98

@@ -536,6 +536,8 @@ def test_shapes_by_size_hold_where_they_were_measured_to_be_faster(direction, tp
     # two copies, forward: few segments, a few hundred and more
     (0, 2, 1, 350, 60, (1024, 64, 20)), (0, 2, 1, 5000, 200, (1024, 64, 20)), (0, 2, 1, 2200, 500, (1024, 64, 24)), (0, 2, 1, 1000, 500, (4096, 256, 28)),
     (0, 2, 1, 3000, 3000, (4096, 256, 28)),
+    # lines that gained less than two sets of buffers differ by, or nothing, are none
+    (0, 1, 1, 900, 60, (4096, 128, 24)), (0, 13, 1, 80, 60, (2048, 64, 5)), (0, 16, 1, 60, 9, (2048, 64, 5)),
     # ten and more copies, forward
     (0, 10, 1, 500, 60, (1024, 64, 5)), (0, 10, 1, 1200, 60, (2048, 64, 5)), (0, 11, 1, 1200, 9, (2048, 64, 5)), (0, 12, 1, 700, 60, (1024, 64, 3)), (0, 12, 1, 1200, 60, (2048, 64, 5)),
     (0, 13, 1, 700, 60, (1024, 64, 4)), (0, 15, 1, 1400, 60, (2048, 64, 3)), (0, 16, 1, 700, 60, (1024, 64, 3)), (0, 16, 1, 4000, 60, (2048, 64, 3)),
