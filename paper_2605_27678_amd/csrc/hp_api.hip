@@ -927,7 +927,7 @@ int enqueue_params(const hp_plan *p, Direction dir, const hp::Launch &L, const B
     c.lds_bytes = lds_for_cap(L.block, L.waves_per_cu);
     c.stream = stream;
     c.ev = ev;
-    if (p->dst_stride != 1 && k.parts_per_row == 0) launch_tiles<kStrided>(p, dir, L.nontemporal, c, a);
+    if (hp::seg_kinds(k, (uint64_t)p->dst_stride) == hp::kRowGroups) launch_tiles<kStrided>(p, dir, L.nontemporal, c, a);
     else if (k.row_bytes % hp::kLineBytes) launch_tiles<kRagged>(p, dir, L.nontemporal, c, a);
     else launch_tiles<kLines>(p, dir, L.nontemporal, c, a);
     if (hip_failed(hipGetLastError())) return HP_EHIP;
@@ -1041,7 +1041,7 @@ int enqueue_runs(const hp_plan *p, const std::vector<hp::Seg> &runs, const RunGr
     c.lds_bytes = lds_for_cap(kTextLaunch.block, kTextLaunch.waves_per_cu);
     c.stream = stream;
     const bool lines = a.k.row_bytes % hp::kLineBytes == 0;
-    if (runs[g.first].pitch_rows != 1 && a.k.parts_per_row == 0) HP_LAUNCH((hp_text_grads_kernel<kStrided, true>), c, a);
+    if (hp::seg_kinds(a.k, runs[g.first].pitch_rows) == hp::kRowGroups) HP_LAUNCH((hp_text_grads_kernel<kStrided, true>), c, a);
     else if (cached && lines) HP_LAUNCH((hp_text_grads_kernel<kLines, false>), c, a);
     else if (cached) HP_LAUNCH((hp_text_grads_kernel<kRagged, false>), c, a);
     else if (lines) HP_LAUNCH((hp_text_grads_kernel<kLines, true>), c, a);

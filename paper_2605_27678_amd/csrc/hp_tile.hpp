@@ -112,12 +112,15 @@ HP_HD uint32_t clip(uint64_t left, uint32_t tile) {
     return hi ? tile : lo < tile ? lo : tile;
 }
 
-// What the segments of a launch may be: a kernel's variants leave out the others.
+// What the segments of a launch are; they all have the same pitch, and a kernel's
+// variants leave out the other kind.
 enum SegKinds {
-    kAnySegs,
     kWholeTiles,    // dense, or row-strided with rows of at least a tile
     kRowGroups,     // row-strided with rows shorter than a tile
 };
+inline SegKinds seg_kinds(const KParams &k, uint64_t pitch_rows) {
+    return pitch_rows != 1 && k.parts_per_row == 0 ? kRowGroups : kWholeTiles;
+}
 
 // Scalar code: every value here is uniform over the workgroup.  One dependent
 // scalar load per tree level below the root, then the descriptor, then the buffer
@@ -142,14 +145,14 @@ HP_HD TileView locate_tile(const KParams &k, const HP_TABLE Seg *segs, const HP_
     v.dst_buf0 = s.dst_buf0;
     v.src_copies = s.src_copies;
     v.first = t == 0;
-    if (KINDS != kRowGroups && s.pitch_rows == 1) {
+    if (KINDS == kWholeTiles && s.pitch_rows == 1) {
         const uint64_t off = (uint64_t)t * k.tile_bytes;
         const uint64_t left = (uint64_t)s.n_rows * k.row_bytes - off;
         v.src_off = s.src_off + off;
         v.dst_off = s.dst_off + off;
         v.nbytes = clip(left, k.tile_bytes);
         v.left = left;
-    } else if (KINDS == kWholeTiles || (KINDS == kAnySegs && k.parts_per_row)) {
+    } else if (KINDS == kWholeTiles) {
         // a piece of one row: dense on both sides, handled like a dense tile
         const uint32_t row = (uint32_t)((uint64_t)t * k.part_magic >> 31 >> k.part_shift);
         const uint32_t off = (t - row * k.parts_per_row) * k.tile_bytes;
@@ -172,7 +175,11 @@ HP_HD TileView locate_tile(const KParams &k, const HP_TABLE Seg *segs, const HP_
 }
 
 #if !defined(__HIP_DEVICE_COMPILE__)
-inline TileView locate_tile(const KParams &k, uint32_t tile) { return locate_tile<kAnySegs>(k, k.segs, k.tree, tile); }
+// The lookup that a launch's kernels have, on the host.
+inline TileView locate_tile(const KParams &k, uint32_t tile) {
+    return seg_kinds(k, k.segs->pitch_rows) == kRowGroups ? locate_tile<kRowGroups>(k, k.segs, k.tree, tile)
+                                                          : locate_tile<kWholeTiles>(k, k.segs, k.tree, tile);
+}
 #endif
 
 // Moves both ends of a dense tile up to the next 128-byte line of its first

@@ -6,7 +6,9 @@
 //     segment's buffers,
 //   - every tile stays inside the source buffer and the destination buffers
 //     (dense tiles: one byte range; row-strided tiles: whole rows at the pitch),
-//   - no tile is empty or larger than the tile size, and lane chunks divide it.
+//   - no tile is empty or larger than the tile size, and lane chunks divide it,
+//   - all segments of a plan have one pitch, by which a launch's kernels are
+//     chosen; the walk takes their variant of the lookup, and both occur.
 // usage: walk_tiles <seed> <plans>
 #include <algorithm>
 #include <cstdio>
@@ -25,7 +27,7 @@ int main(int argc, char **argv) {
     std::mt19937_64 rng(argc > 1 ? std::atoll(argv[1]) : 1);
     const int plans = argc > 2 ? std::atoi(argv[2]) : 300;
     auto R = [&](int lo, int hi) { return (int)(lo + rng() % (uint64_t)(hi - lo + 1)); };
-    long tiles_walked = 0;
+    long tiles_walked = 0, by_kind[2] = {0, 0};
     int done = 0;
     for (int it = 0; done < plans && it < 100 * plans; ++it) {
         const int cps[] = {1, 2, 4, 8};
@@ -65,6 +67,7 @@ int main(int argc, char **argv) {
                 t = (uint32_t)i;
                 CHECK((int64_t)p.dsegs[i].n_rows == p.segments[i].n_rows);
                 CHECK((int64_t)p.dsegs[i].pitch_rows == p.segments[i].dst_row_stride);
+                CHECK((int64_t)p.dsegs[i].pitch_rows == p.dst_stride);
                 CHECK((int32_t)p.dsegs[i].src_buf == p.segments[i].src_buf);
                 CHECK((int32_t)p.dsegs[i].dst_buf0 == p.segments[i].dst_buf0);
                 CHECK(p.dsegs[i].src_off == (uint64_t)p.segments[i].src_row0 * (uint64_t)p.row_bytes);
@@ -84,6 +87,7 @@ int main(int argc, char **argv) {
             for (uint32_t t = 0; t < n_tiles; ++t) {
                 const hp::TileView tv = hp::locate_tile(k, t);
                 ++tiles_walked;
+                ++by_kind[hp::seg_kinds(k, (uint64_t)p.dst_stride)];
                 while (seg < p.dsegs.size() && covered == (uint64_t)p.dsegs[seg].n_rows * row) { ++seg; covered = 0; }
                 CHECK(seg < p.dsegs.size());
                 const hp::Seg &s = p.dsegs[seg];
@@ -117,5 +121,6 @@ int main(int argc, char **argv) {
         std::free(tree);
     }
     std::printf("plans %d tiles %ld\n", done, tiles_walked);
+    if (plans >= 100 && (by_kind[hp::kWholeTiles] < 1000 || by_kind[hp::kRowGroups] < 1000)) return 3;
     return done == plans ? 0 : 2;
 }
