@@ -165,7 +165,7 @@ __device__ __forceinline__ void count_chunks(const KParams &k, const TileView &t
     else hp::count_chunks<UNIT, TILES != kStrided>(k, t, all, whole);
 }
 
-// N neighbouring addresses of the table, read with one instruction (N = 1: as is).
+// N neighbouring addresses of the table, read at once: with one instruction, three with two.
 // Left to itself the compiler reads one after the other and waits for each, with
 // nothing in flight yet: the two together, and the search, 45 MB a direction in
 // [S,B,H] order 18.1 -> 17.3 us, 166 MB to and from two copies 53.0 -> 52.2.

@@ -63,7 +63,11 @@ struct TileView {
 // which it has nothing in flight, at the start of a launch and at every replacement
 // of a workgroup.  Against comparing all 16 keys (a hundred instructions), the same
 // buffers in turn: to four copies, 100 MB 16.24 -> 16.18 us, 2.06 GB 334 -> 327; from two
-// copies, 100 MB 17.2 -> 17.0, 900 MB in 561 segments (three levels) 161 -> 138.
+// copies, 100 MB 17.2 -> 17.0, 900 MB in 561 segments (three levels) 161 -> 138.  Not
+// all gain: the long search spaced out a compute unit's waves, and large launches of
+// small tiles with one or two levels lose 1-2 % without it - backward from two and three
+// copies 0.98-0.99, where hp::pace_rounds does the same on purpose, forward to two copies
+// of 2.5 GB and more 0.99.
 template <typename Node>
 HP_HD void search_node(Node node, uint32_t tile, uint32_t &index, uint32_t &key) {
     uint64_t q[kTreeFanout / 2];
