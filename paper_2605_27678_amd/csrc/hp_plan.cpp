@@ -285,7 +285,10 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
     auto in = [](double bytes, double from, double to) { return bytes >= from * MB && bytes < to * MB; };
 
     const double fwd = (1.0 + c) * (double)p->n_rows * (double)p->row_bytes;
-    if (c == 1 && fwd >= 200 * MB && segs <= 256) set(f, K4, 128, 24);          // 0.99-1.03; more segments 0.98-1.03
+    if (c == 1 && fwd >= 200 * MB && segs <= 256) {
+        if (fwd < 400 * MB || !dense) set(f, K4, 128, 24);                      // 0.99-1.03; more segments 0.98-1.03
+        else set(f, K2, 64, 20);                                                // 1.003-1.006 of 4 KiB x 128; [S,B,H] 0.92-0.98
+    }
     else if (c == 2 && in(fwd, 40, 290)) set(f, K8, 256, 16);                   // 0.98-1.13; 300 MB: 0.96-1.00
     else if (c == 2 && fwd >= 300 * MB && filled) {
         if (segs <= 256) set(f, K1, 64, 20);                                    // 1.01-1.04 to 1.2 GB, 1.01-1.02 to 15 GB; else 0.93-1.02

@@ -536,8 +536,7 @@ def test_shapes_by_size_hold_where_they_were_measured_to_be_faster(direction, tp
     # two copies, forward: few segments, a few hundred and more
     (0, 2, 1, 350, 60, (1024, 64, 20)), (0, 2, 1, 5000, 200, (1024, 64, 20)), (0, 2, 1, 2200, 500, (1024, 64, 24)), (0, 2, 1, 1000, 500, (4096, 256, 28)),
     (0, 2, 1, 3000, 3000, (4096, 256, 28)),
-    # lines that gained less than two sets of buffers differ by, or nothing, are none
-    (0, 1, 1, 900, 60, (4096, 128, 24)), (0, 13, 1, 80, 60, (2048, 64, 5)), (0, 16, 1, 60, 9, (2048, 64, 5)),
+    (0, 1, 1, 900, 60, (2048, 64, 20)), (0, 13, 1, 80, 60, (2048, 64, 5)), (0, 16, 1, 60, 9, (2048, 64, 5)),
     # ten and more copies, forward
     (0, 10, 1, 500, 60, (1024, 64, 5)), (0, 10, 1, 1200, 60, (2048, 64, 5)), (0, 11, 1, 1200, 9, (2048, 64, 5)), (0, 12, 1, 700, 60, (1024, 64, 3)), (0, 12, 1, 1200, 60, (2048, 64, 5)),
     (0, 13, 1, 700, 60, (1024, 64, 4)), (0, 15, 1, 1400, 60, (2048, 64, 3)), (0, 16, 1, 700, 60, (1024, 64, 3)), (0, 16, 1, 4000, 60, (2048, 64, 3)),
@@ -556,7 +555,7 @@ def test_shapes_by_size_where_a_neighbour_s_shape_lost(direction, tp, tp_src, mb
 
 # [S,B,H] order: short rows and those that begin between lines leave tiles partly empty
 @pytest.mark.parametrize("direction,tp,tp_src,mbytes,f32,row_bytes,want", [
-    (0, 3, 1, 150, False, 1280, (2048, 64, 12)), (0, 3, 1, 150, False, 5120, (1024, 64, 10)), (0, 4, 1, 100, False, 1280, (2048, 64, 12)),
+    (0, 1, 1, 900, False, 3088, (4096, 128, 24)), (0, 3, 1, 150, False, 1280, (2048, 64, 12)), (0, 3, 1, 150, False, 5120, (1024, 64, 10)), (0, 4, 1, 100, False, 1280, (2048, 64, 12)),
     (0, 4, 1, 100, False, 514, (1024, 64, 8)), (0, 5, 1, 600, False, 3088, (2048, 64, 8)), (0, 6, 1, 600, False, 1280, (1024, 64, 14)),
     (0, 2, 1, 1000, False, 1280, (4096, 256, 28)), (0, 2, 1, 1000, False, 3088, (4096, 256, 28)), (0, 2, 1, 1000, False, 6224, (1024, 64, 20)),
     (1, 2, 1, 1000, False, 1280, (1024, 64, 30)), (1, 3, 1, 1000, False, 1280, (1024, 64, 28)), (1, 5, 1, 1000, False, 3088, (1024, 64, 28)),
