@@ -304,9 +304,12 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
         if (c > 5 || segs <= 16) set(f, K1, 64, 10);                            // 0.96-1.20; 20 MB 0.89-1.06, five copies and more segments 0.87-1.03
     }
     else if (c >= 5 && c <= 7 && fwd >= 450 * MB) {
-        if (segs <= 256 && (filled || row < 2048)) set(f, K1, 64, 14);          // 1.02-1.15; more segments 0.97-1.02, rows of 3088 and 8186 bytes 0.94-0.99
+        if (segs <= (c == 5 ? 256 : 1024) && (filled || row < 2048)) set(f, K1, 64, 14);   // 1.00-1.15; more segments 0.97-1.02, rows of 3088 and 8186 bytes 0.94-0.99
     }
     else if (c == 8 && dense && in(fwd, 40, 450)) set(f, K1, 64, 5);            // 0.99-1.25; [S,B,H] order 0.93-1.02
+    else if (c == 8 && dense && in(fwd, 450, 5000)) {
+        if (segs <= 256) set(f, K1, 64, fwd < 700 * MB ? 5 : 8);                // 1.00-1.06; more segments 0.98-1.02, 7.2 GB 0.99
+    }
     else if (c >= 10 && c <= 12 && dense && in(fwd, 100, c == 12 ? 450 : 600)) set(f, K1, 64, 5);   // 0.96-1.28; ten copies, 700 MB 0.98-1.0, 1.1 GB 0.85; [S,B,H] 0.86-1.05
     else if (c == 12 && dense && in(fwd, 450, 1200)) {
         if (segs <= 256) set(f, K1, 64, fwd < 1000 * MB ? 3 : 4);               // 1.02-1.12; 1.2 GB 0.93-0.99

@@ -537,6 +537,9 @@ def test_shapes_by_size_hold_where_they_were_measured_to_be_faster(direction, tp
     (0, 2, 1, 350, 60, (1024, 64, 20)), (0, 2, 1, 5000, 200, (1024, 64, 20)), (0, 2, 1, 2200, 500, (1024, 64, 24)), (0, 2, 1, 1000, 500, (4096, 256, 28)),
     (0, 2, 1, 3000, 3000, (4096, 256, 28)),
     (0, 1, 1, 900, 60, (2048, 64, 20)), (0, 13, 1, 80, 60, (2048, 64, 5)), (0, 16, 1, 60, 9, (2048, 64, 5)),
+    # eight copies, forward, past what lies in the memory-side cache; six and seven in a few hundred segments
+    (0, 8, 1, 440, 60, (1024, 64, 5)), (0, 8, 1, 600, 60, (1024, 64, 5)), (0, 8, 1, 2000, 60, (1024, 64, 8)), (0, 8, 1, 2000, 600, (2048, 64, 5)),
+    (0, 8, 2, 7200, 60, (2048, 64, 5)), (0, 7, 1, 1000, 500, (1024, 64, 14)), (0, 5, 1, 1000, 500, (2048, 64, 8)),
     # ten and more copies, forward
     (0, 10, 1, 500, 60, (1024, 64, 5)), (0, 10, 1, 1200, 60, (2048, 64, 5)), (0, 11, 1, 1200, 9, (2048, 64, 5)), (0, 12, 1, 700, 60, (1024, 64, 3)), (0, 12, 1, 1200, 60, (2048, 64, 5)),
     (0, 13, 1, 700, 60, (1024, 64, 4)), (0, 15, 1, 1400, 60, (2048, 64, 3)), (0, 16, 1, 700, 60, (1024, 64, 3)), (0, 16, 1, 4000, 60, (2048, 64, 3)),
