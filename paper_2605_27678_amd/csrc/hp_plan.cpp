@@ -94,6 +94,44 @@ std::vector<Seg> dst_runs(const hp_plan &p, bool whole) {
     return runs;
 }
 
+std::vector<Seg> band_runs(const hp_plan &p) {
+    struct Turn { int64_t buf, pos; uint32_t sample; };    // where a sample (a bit) goes from text to image or back
+    const int64_t samples = p.dst_stride, positions = p.dst_rows_per_buf / samples;
+    std::vector<Turn> turns;
+    turns.reserve(2 * p.segments.size());
+    for (const hp_segment_t &s : p.segments) {
+        const uint32_t bit = 1u << (s.dst_row0 % samples);
+        turns.push_back(Turn{s.dst_buf0, s.dst_row0 / samples, bit});
+        turns.push_back(Turn{s.dst_buf0, s.dst_row0 / samples + s.n_rows, bit});
+    }
+    std::sort(turns.begin(), turns.end(), [](const Turn &a, const Turn &b) {
+        return a.buf != b.buf ? a.buf < b.buf : a.pos < b.pos;
+    });
+    std::vector<Seg> runs;
+    size_t at = 0;
+    for (int64_t buf = 0; buf < p.n_dst_bufs; buf += p.dst_copies) {
+        int64_t done = 0;                                  // positions that have a run
+        uint32_t images = 0;
+        auto add = [&](int64_t end) {
+            while (done < end) {                           // a band's rows stay below 2^31, as the kernels' division wants them
+                const int64_t n = std::min<int64_t>(end - done, INT32_MAX / samples);
+                const uint64_t off = (uint64_t)(done * samples) * (uint64_t)p.row_bytes;
+                runs.push_back(Seg{off, off, (uint32_t)(n * samples), 1, (uint16_t)buf, (uint16_t)buf, images});
+                done += n;
+            }
+        };
+        while (at < turns.size() && turns[at].buf == buf) {
+            const int64_t pos = turns[at].pos;
+            uint32_t next = images;
+            for (; at < turns.size() && turns[at].buf == buf && turns[at].pos == pos; ++at) next ^= turns[at].sample;
+            if (next != images) add(pos);                  // else one image ends where the next begins
+            images = next;
+        }
+        add(positions);
+    }
+    return runs;
+}
+
 namespace {
 
 // Position of one fused-sequence token on the destination side.

@@ -144,4 +144,11 @@ uint64_t tiles_of(uint64_t n_rows, uint64_t pitch_rows, int64_t row_bytes, uint3
 // (among the destination buffers).  whole: one dense run of text a buffer,
 // whatever lies there and in whichever row order.
 std::vector<Seg> dst_runs(const hp_plan &p, bool whole);
+
+// The same rows in [S,B,H] order as bands: dense runs of whole positions, all their
+// samples side by side, in which every sample is text or image throughout.  src_copies
+// holds a bit for each sample, set where it is image; pitch_rows = 1, and the rest as
+// above.  For plans of 2 to kMaxBandSamples samples a buffer.
+constexpr int kMaxBandSamples = 32;
+std::vector<Seg> band_runs(const hp_plan &p);
 }  // namespace hp

@@ -35,6 +35,7 @@ struct KParams {
     uint32_t row_chunks;        // row-strided tiles of whole rows: lane chunks of one row (see set_row_chunks)
     uint32_t row_magic, row_one;
     uint32_t pace;              // rounds of pace() before a tile's loads (kernels that have it)
+    uint32_t band_samples, band_magic, band_shift;     // text gradients in bands (band_runs): samples of a position, and their division as above
     uint32_t level_off[kMaxTreeLevels];   // start of each level, in keys; level 0 = leaves
 };
 
@@ -43,6 +44,7 @@ struct TileView {
     uint64_t src_off, dst_off;  // bytes from the buffer bases
     uint32_t nbytes;
     uint32_t pitch_rows;        // 1 = dense destination
+    uint32_t row;               // row-strided segments and bands: the tile's (first) row
     uint32_t src_buf, dst_buf0;
     uint32_t src_copies;        // identical TP copies of the source rank
     uint32_t first;             // dense: 1 = the tile starts its run (the segment, or one row of a row-strided one)
@@ -126,11 +128,15 @@ inline SegKinds seg_kinds(const KParams &k, uint64_t pitch_rows) {
     return pitch_rows != 1 && k.parts_per_row == 0 ? kRowGroups : kWholeTiles;
 }
 
+// x / n for x < 2^31, n's magic number and shift made by set_division.
+HP_HD uint32_t divide(uint32_t x, uint32_t magic, uint32_t shift) { return (uint32_t)((uint64_t)x * magic >> 31 >> shift); }
+
 // Scalar code: every value here is uniform over the workgroup.  One dependent
 // scalar load per tree level below the root, then the descriptor, then the buffer
 // pointers.  segs and tree point at k's tables (k.segs and k.tree, or behind the
 // arguments).
-template <SegKinds KINDS>
+// BANDS: dense runs that are cut row by row, as row-strided ones are.
+template <SegKinds KINDS, bool BANDS = false>
 HP_HD TileView locate_tile(const KParams &k, const HP_TABLE Seg *segs, const HP_TABLE uint32_t *tree, uint32_t tile) {
     uint32_t lo, first, index;
     search_node(k.root, tile, lo, first);
@@ -149,7 +155,7 @@ HP_HD TileView locate_tile(const KParams &k, const HP_TABLE Seg *segs, const HP_
     v.dst_buf0 = s.dst_buf0;
     v.src_copies = s.src_copies;
     v.first = t == 0;
-    if (KINDS == kWholeTiles && s.pitch_rows == 1) {
+    if (KINDS == kWholeTiles && !BANDS && s.pitch_rows == 1) {
         const uint64_t off = (uint64_t)t * k.tile_bytes;
         const uint64_t left = (uint64_t)s.n_rows * k.row_bytes - off;
         v.src_off = s.src_off + off;
@@ -158,7 +164,7 @@ HP_HD TileView locate_tile(const KParams &k, const HP_TABLE Seg *segs, const HP_
         v.left = left;
     } else if (KINDS == kWholeTiles) {
         // a piece of one row: dense on both sides, handled like a dense tile
-        const uint32_t row = (uint32_t)((uint64_t)t * k.part_magic >> 31 >> k.part_shift);
+        const uint32_t row = divide(t, k.part_magic, k.part_shift);
         const uint32_t off = (t - row * k.parts_per_row) * k.tile_bytes;
         const uint32_t left = k.row_bytes - off;
         v.pitch_rows = 1;
@@ -167,6 +173,7 @@ HP_HD TileView locate_tile(const KParams &k, const HP_TABLE Seg *segs, const HP_
         v.nbytes = left < k.tile_bytes ? left : k.tile_bytes;
         v.first = off == 0;
         v.left = left;
+        v.row = row;
     } else {
         const uint64_t row0 = (uint64_t)t * k.rows_per_tile;
         const uint32_t rows = clip(s.n_rows - row0, k.rows_per_tile);
@@ -174,6 +181,7 @@ HP_HD TileView locate_tile(const KParams &k, const HP_TABLE Seg *segs, const HP_
         v.dst_off = s.dst_off + row0 * s.pitch_rows * k.row_bytes;
         v.nbytes = rows * k.row_bytes;
         v.left = v.nbytes;
+        v.row = (uint32_t)row0;
     }
     return v;
 }
@@ -221,6 +229,10 @@ struct ChunkView {
     uint64_t dst;
     uint32_t src, over;
 };
+// The row of chunk i of a row-strided tile of whole rows.
+HP_HD uint32_t row_of_chunk(const KParams &k, uint32_t i) {
+    return (uint32_t)(((uint64_t)i * k.row_magic) >> 32) + (i & k.row_one);
+}
 template <uint32_t UNIT, bool DENSE, bool GUARD>
 HP_HD ChunkView chunk_at(const KParams &k, const TileView &t, uint32_t i) {
     ChunkView c;
@@ -230,7 +242,7 @@ HP_HD ChunkView chunk_at(const KParams &k, const TileView &t, uint32_t i) {
         c.over = at - c.src;
         c.dst = c.src;
     } else {
-        const uint32_t row = (uint32_t)(((uint64_t)i * k.row_magic) >> 32) + (i & k.row_one);
+        const uint32_t row = row_of_chunk(k, i);
         const uint32_t at = (i - row * k.row_chunks) * UNIT, last = k.row_bytes - UNIT;
         const uint32_t col = at > last ? last : at;
         c.src = row * k.row_bytes + col;
@@ -268,16 +280,22 @@ HP_HD ChunkView element_at(const KParams &k, const TileView &t, uint32_t i) {
     return c;
 }
 
-// Multiplication in place of t / parts_per_row, exact for t < 2^31 (a grid has no
-// more tiles): with 2^part_shift >= parts the magic number, rounded up, is off by
-// less than 2^part_shift in 2^(31 + part_shift).  The division itself, some 30
+// Multiplication in place of x / n, exact for x < 2^31 (a grid has no
+// more tiles): with 2^shift >= n the magic number, rounded up, is off by
+// less than 2^shift in 2^(31 + shift).  The division itself, some 30
 // instructions of the vector unit and a read back from it, stood before the first
 // load of every piece of a row.
-inline void set_parts(KParams &k) {
-    k.part_magic = k.part_shift = 0;
-    if (!k.parts_per_row) return;
-    while ((1u << k.part_shift) < k.parts_per_row) ++k.part_shift;
-    k.part_magic = (uint32_t)((((uint64_t)1 << (31 + k.part_shift)) + k.parts_per_row - 1) / k.parts_per_row);
+inline void set_division(uint32_t n, uint32_t &magic, uint32_t &shift) {
+    magic = shift = 0;
+    if (!n) return;
+    while ((1u << shift) < n) ++shift;
+    magic = (uint32_t)((((uint64_t)1 << (31 + shift)) + n - 1) / n);
+}
+inline void set_parts(KParams &k) { set_division(k.parts_per_row, k.part_magic, k.part_shift); }
+
+// Text gradients in bands: the sample (0 .. band_samples - 1) of a run's row, less than 2^31.
+HP_HD uint32_t band_sample(const KParams &k, uint32_t row) {
+    return row - divide(row, k.band_magic, k.band_shift) * k.band_samples;
 }
 
 // The kernel parameters of a launch with tiles of 1 KiB << variant; segs and
@@ -300,6 +318,7 @@ inline KParams kernel_params(const hp_plan &p, int variant, const Seg *segs, con
     set_parts(k);
     set_row_chunks(k, 16u);
     k.block = k.pace = 0;       // set by the launch
+    k.band_samples = k.band_magic = k.band_shift = 0;      // by that of text gradients in bands
     k.dst_base = (uint32_t)p.n_src_bufs;
     k.dst_copies = (uint32_t)p.dst_copies;
     return k;
