@@ -98,7 +98,10 @@ enum Tiles {
     kLines,     // dense on both sides, and every row is whole 128-byte lines
     kRagged,    // dense on both sides, rows of any length
     kStrided,   // groups of whole row-strided rows ([S,B,H] order with several samples per rank, rows shorter than a tile)
+    kCut,       // row-strided rows of whole lines, cut by bytes of the source across their ends (hp::cuts_launch)
 };
+// Whether a tile lies on the destination side as it does on the source's.
+template <Tiles TILES> constexpr bool kDense = TILES == kLines || TILES == kRagged;
 
 // Workgroups are handed to the chip's 8 accelerator dies (XCDs, each with its
 // own L2) round-robin by workgroup id.
@@ -152,7 +155,7 @@ __device__ __forceinline__ TileView my_tile(const Args &a) {
     const uintptr_t args = args_base();
     const uintptr_t segs = a.k.seg_at ? args + a.k.seg_at : (uintptr_t)a.k.segs;
     const uintptr_t tree = a.k.seg_at ? args + a.k.tree_at : (uintptr_t)a.k.tree;
-    TileView t = hp::locate_tile<TILES == kStrided ? hp::kRowGroups : hp::kWholeTiles, BANDS>(
+    TileView t = hp::locate_tile<TILES == kStrided ? hp::kRowGroups : TILES == kCut ? hp::kCutRows : hp::kWholeTiles, BANDS>(
         a.k, (const HP_TABLE hp::Seg *)segs, (const HP_TABLE uint32_t *)tree, blockIdx.x);
     if (TILES == kRagged) hp::align_tile(t, buffers()[a.k.dst_base + t.dst_buf0]);
     return t;
@@ -161,8 +164,15 @@ __device__ __forceinline__ TileView my_tile(const Args &a) {
 // How many chunks of UNIT bytes a tile has, and how many are whole; tiles of lines have no others.
 template <uint32_t UNIT, Tiles TILES>
 __device__ __forceinline__ void count_chunks(const KParams &k, const TileView &t, uint32_t &all, uint32_t &whole) {
-    if (TILES == kLines) all = whole = t.nbytes / UNIT;
+    if (TILES == kLines || TILES == kCut) all = whole = t.nbytes / UNIT;
     else hp::count_chunks<UNIT, TILES != kStrided>(k, t, all, whole);
+}
+
+// Chunk i of a tile; END: it may be the one that was moved back to end with its run.
+template <uint32_t UNIT, Tiles TILES, bool END>
+__device__ __forceinline__ hp::ChunkView chunk(const KParams &k, const TileView &t, uint32_t i) {
+    if constexpr (TILES == kCut) return hp::cut_chunk<UNIT>(k, t, i);
+    else return hp::chunk_at<UNIT, TILES != kStrided, END && TILES == kRagged>(k, t, i);
 }
 
 // N neighbouring addresses of the table, read at once: with one instruction, three with two.
@@ -240,13 +250,13 @@ __device__ __forceinline__ void forward_group(const KParams &k, const TileView &
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         i[u] = done + u * k.block + threadIdx.x;
-        c[u] = hp::chunk_at<16, TILES != kStrided, GUARD && TILES == kRagged>(k, t, GUARD ? min(i[u], n - 1) : i[u]);
+        c[u] = chunk<16, TILES, GUARD>(k, t, GUARD ? min(i[u], n - 1) : i[u]);
         v[u] = ld<16, NTL>(places.src + c[u].src);
     }
     auto store = [&](gchar *p) {
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            if (!GUARD || i[u] < n) st<16, NTS>(p + (TILES != kStrided ? c[u].src : c[u].dst), v[u]);
+            if (!GUARD || i[u] < n) st<16, NTS>(p + (kDense<TILES> ? c[u].src : c[u].dst), v[u]);
     };
     for_copies<NREP>(k, t, places, nrep, [&](uint32_t, auto &p) {
         constexpr int N = sizeof(p) / sizeof(*p);
@@ -271,7 +281,7 @@ __device__ __forceinline__ void forward_tile(const KParams &k, const TileView &t
     count_chunks<16, TILES>(k, t, n, whole);
     const uint32_t step = k.block;
     uint32_t done = 0;                                       // uniform
-    if (TILES != kLines && __builtin_expect(n == 0, 0)) {                       // shorter than a chunk
+    if (TILES != kLines && TILES != kCut && __builtin_expect(n == 0, 0)) {                       // shorter than a chunk
         for (uint32_t i = threadIdx.x; i < t.nbytes / 2; i += step) {
             const hp::ChunkView c = hp::element_at<2>(k, t, i);
             const uint16_t v = ld<2, NTL>(places.src + c.src);
@@ -313,12 +323,12 @@ __device__ __forceinline__ void zero_tile(const KParams &k, const TileView &t) {
     const HP_TABLE uint64_t *b = buffers() + (k.dst_base + t.dst_buf0);
     for (uint32_t r = 0; r < k.dst_copies; ++r) {
         gchar *dst = at(b[r] + t.dst_off);
-        if (TILES != kLines && n == 0) {
+        if (TILES != kLines && TILES != kCut && n == 0) {
             for (uint32_t i = threadIdx.x; i < t.nbytes / 2; i += k.block)
                 st<2, NTS>(dst + hp::element_at<2>(k, t, i).dst, 0);
         } else {
             for (uint32_t i = threadIdx.x; i < n; i += k.block)
-                st<16, NTS>(dst + hp::chunk_at<16, TILES != kStrided, TILES == kRagged>(k, t, i).dst, (u32x4)0u);
+                st<16, NTS>(dst + chunk<16, TILES, true>(k, t, i).dst, (u32x4)0u);
         }
     }
 }
@@ -366,7 +376,7 @@ hp_text_grads_kernel(const Args a) {
     uint32_t n, whole;
     count_chunks<16, TILES>(k, t, n, whole);
     const uint32_t step = k.block;
-    if (TILES != kLines && __builtin_expect(n == 0, 0)) {             // shorter than a chunk
+    if (TILES != kLines && TILES != kCut && __builtin_expect(n == 0, 0)) {             // shorter than a chunk
         for (uint32_t i = threadIdx.x; i < t.nbytes / 2; i += step) {
             const uint64_t at = hp::element_at<2>(k, t, i).dst;
             uint16_t v = 0;
@@ -383,7 +393,7 @@ hp_text_grads_kernel(const Args a) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const uint32_t i = done + u * step + threadIdx.x;
-            at[u] = hp::chunk_at<16, TILES != kStrided, TILES == kRagged>(k, t, min(i, n - 1)).dst;
+            at[u] = chunk<16, TILES, true>(k, t, min(i, n - 1)).dst;
             v[u] = (u32x4)0u;
             if constexpr (BANDS && TILES == kStrided) text[u] = !image(hp::row_of_chunk(k, min(i, n - 1)));
         }
@@ -516,7 +526,7 @@ __device__ __forceinline__ void backward_group(const KParams &k, const TileView 
         i[u] = done + u * k.block + threadIdx.x;
         const uint32_t ic = GUARD ? min(i[u], n - 1) : i[u];
         if constexpr (ELEMENT) c[u] = hp::element_at<kElemBytes>(k, t, ic);
-        else c[u] = hp::chunk_at<In::kBytes, TILES != kStrided, GUARD && TILES == kRagged>(k, t, ic);
+        else c[u] = chunk<In::kBytes, TILES, GUARD>(k, t, ic);
     }
     VO old[U];
     if constexpr (ACC && kAccumulatorsFirst<DT, NREP>) {
@@ -530,7 +540,7 @@ __device__ __forceinline__ void backward_group(const KParams &k, const TileView 
 #pragma unroll
         for (int g = 0; g < G; ++g) {
 #pragma unroll
-            for (int u = 0; u < U; ++u) v[g][u] = ld<In::kBytes, NTL>(p[g] + (TILES != kStrided && !ELEMENT ? c[u].src : c[u].dst));
+            for (int u = 0; u < U; ++u) v[g][u] = ld<In::kBytes, NTL>(p[g] + (kDense<TILES> && !ELEMENT ? c[u].src : c[u].dst));
         }
         // ascending tp: copy 0 starts the accumulator, copies 1.. are added in order
 #pragma unroll
@@ -569,7 +579,7 @@ __device__ __forceinline__ void backward_group(const KParams &k, const TileView 
 #pragma unroll
                 for (int e = 0; e < E; ++e) x[e] = x[e] + acc[u][e];
                 if (GUARD && i[u] >= n) continue;
-                if (ELEMENT || TILES == kLines || (TILES == kRagged && !GUARD) || c[u].over == 0) {
+                if (ELEMENT || TILES == kLines || TILES == kCut || (TILES == kRagged && !GUARD) || c[u].over == 0) {
                     st<Out::kBytes, NTS>(out + c[u].src * kWiden, Out::pack(x));
                 } else {
 #pragma unroll
@@ -597,7 +607,7 @@ __device__ __forceinline__ void backward_tile(const KParams &k, const TileView &
     count_chunks<Elems<DT, E>::kBytes, TILES>(k, t, n, whole);
     const uint32_t step = k.block;
     uint32_t done = 0;                                               // uniform
-    if (TILES != kLines && __builtin_expect(n == 0, 0)) {                               // shorter than a chunk
+    if (TILES != kLines && TILES != kCut && __builtin_expect(n == 0, 0)) {                               // shorter than a chunk
         for (n = t.nbytes / kElemBytes; done < n; done += step)
             backward_group<DT, 1, ACC, 0, 1, TILES, true, NTL, NTS>(k, t, Places<0>(k, t, kWiden), nrep, done, n);
         return;
@@ -917,6 +927,15 @@ void put_tables(const hp_plan *p, int variant, Args &a) {
     }
 }
 
+bool cuts(const hp_plan *p, Direction dir, const hp::Launch &L) {
+    return hp::cuts_launch(*p, dir == kZeroRows ? kForward : dir, L.tile_variant);
+}
+
+// What a launch with shape `L` tells its kernel, its tables wherever they lie.
+KParams launch_params(const hp_plan *p, Direction dir, const hp::Launch &L, const hp::Seg *segs, const uint32_t *tree) {
+    return hp::kernel_params(*p, L.tile_variant, segs, tree, cuts(p, dir, L));
+}
+
 // Enqueues one kernel for direction `dir` with launch shape `L`.
 int enqueue_params(const hp_plan *p, Direction dir, const hp::Launch &L, const BufTable &bt, hipStream_t stream,
                    EventPair ev, const KParams &k);
@@ -924,7 +943,7 @@ int enqueue_params(const hp_plan *p, Direction dir, const hp::Launch &L, const B
 int enqueue(const hp_plan *p, Direction dir, const hp::Launch &L, const BufTable &bt, hipStream_t stream,
             EventPair ev) {
     const int rc = enqueue_params(p, dir, L, bt, stream, ev,
-                                  hp::kernel_params(*p, L.tile_variant, p->d_segs, p->d_tree));
+                                  launch_params(p, dir, L, p->d_segs, p->d_tree));
     if (rc == HP_OK && p->d_segs) p->note_stream((void *)stream);
     return rc;
 }
@@ -940,12 +959,14 @@ int enqueue_params(const hp_plan *p, Direction dir, const hp::Launch &L, const B
     if (!a.k.segs) put_tables(p, L.tile_variant, a);
     const KParams &k = a.k;
     LaunchCfg c;
-    c.grid = dim3(p->n_tiles(L.tile_variant));
+    c.grid = dim3(k.rows_per_tile == 0 ? p->cut_tiles[L.tile_variant] : p->n_tiles(L.tile_variant));
     c.block = dim3((unsigned)L.block);
     c.lds_bytes = lds_for_cap(L.block, L.waves_per_cu);
     c.stream = stream;
     c.ev = ev;
-    if (hp::seg_kinds(k, (uint64_t)p->dst_stride) == hp::kRowGroups) launch_tiles<kStrided>(p, dir, L.nontemporal, c, a);
+    const hp::SegKinds kind = hp::seg_kinds(k, (uint64_t)p->dst_stride);
+    if (kind == hp::kCutRows) launch_tiles<kCut>(p, dir, L.nontemporal, c, a);
+    else if (kind == hp::kRowGroups) launch_tiles<kStrided>(p, dir, L.nontemporal, c, a);
     else if (k.row_bytes % hp::kLineBytes) launch_tiles<kRagged>(p, dir, L.nontemporal, c, a);
     else launch_tiles<kLines>(p, dir, L.nontemporal, c, a);
     if (hip_failed(hipGetLastError())) return HP_EHIP;
@@ -1625,7 +1646,7 @@ int hp_plan_query(const hp_plan_t *p, hp_plan_info_t *info) {
     o.fwd_bytes = (1 + (int64_t)p->dst_copies) * o.boundary_bytes;
     o.bwd_bytes = p->bwd_bytes;
     o.n_segments = (int32_t)p->segments.size();
-    o.n_tiles = (int32_t)p->n_tiles(p->fwd.tile_variant);
+    o.n_tiles = (int32_t)(cuts(p, kForward, p->fwd) ? p->cut_tiles[p->fwd.tile_variant] : p->n_tiles(p->fwd.tile_variant));
     o.on_device = p->device >= 0 ? 1 : 0;
     o.device = p->device;
     o.n_maps = p->n_maps;
@@ -1735,14 +1756,11 @@ int hp_forward_static(const hp_plan_t *p, const void *const *src_bufs, void *con
     if (rc != HP_OK || p->segments.empty()) return rc;
     const hp::Launch &L = p->fwd;
     if (inline_tables(p))
-        return enqueue_params(p, kForward, L, bt, (hipStream_t)stream, EventPair{},
-                              hp::kernel_params(*p, L.tile_variant, nullptr, nullptr));
-    // what this launch reads: the segment descriptors and the search tree of its tile size only
-    const hp::TreeInfo &ti = p->tree_info[L.tile_variant];
+        return enqueue_params(p, kForward, L, bt, (hipStream_t)stream, EventPair{}, launch_params(p, kForward, L, nullptr, nullptr));
+    // what this launch reads: the segment descriptors and its own search tree only
     const size_t seg_bytes = (p->dsegs.size() * sizeof(hp::Seg) + 63) / 64 * 64;          // tree nodes stay 64-byte aligned
-    const uint32_t tree_begin = ti.level_off[0];
-    const uint32_t tree_end = L.tile_variant + 1 < hp::kTileVariants ? p->tree_info[L.tile_variant + 1].level_off[0]
-                                                                      : (uint32_t)p->tree.size();
+    const hp::TreeInfo &ti = cuts(p, kForward, L) ? p->cut_info[L.tile_variant] : p->tree_info[L.tile_variant];
+    const uint32_t tree_begin = ti.level_off[0], tree_end = ti.level_off[ti.n_levels - 1] + hp::kTreeFanout;   // up to its root
     const size_t tree_bytes = (size_t)(tree_end - tree_begin) * sizeof(uint32_t);
     if (seg_bytes + tree_bytes > (size_t)HP_STATIC_MAX_TABLE_BYTES) return HP_ELAYOUT;
     unsigned char *tables = static_tables(&rc);
@@ -1751,7 +1769,7 @@ int hp_forward_static(const hp_plan_t *p, const void *const *src_bufs, void *con
     rc = upload_words(tables, (const uint32_t *)p->dsegs.data(), p->dsegs.size() * sizeof(hp::Seg) / 4, st);
     if (rc == HP_OK) rc = upload_words(tables + seg_bytes, p->tree.data() + tree_begin, tree_end - tree_begin, st);
     if (rc != HP_OK) return rc;
-    KParams k = hp::kernel_params(*p, L.tile_variant, (const hp::Seg *)tables, (const uint32_t *)(tables + seg_bytes));
+    KParams k = launch_params(p, kForward, L, (const hp::Seg *)tables, (const uint32_t *)(tables + seg_bytes));
     for (uint32_t l = 0; l < k.n_levels; ++l) k.level_off[l] -= tree_begin;               // offsets inside the copied tree
     return enqueue_params(p, kForward, L, bt, st, EventPair{}, k);
 }

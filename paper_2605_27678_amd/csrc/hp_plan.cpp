@@ -45,6 +45,14 @@ uint64_t tiles_of(uint64_t n_rows, uint64_t pitch_rows, int64_t row_bytes, uint3
     return (n_rows + rows_per - 1) / rows_per;
 }
 
+bool cut_by_bytes(const hp_plan &p, uint32_t tile) {
+    if (p.dst_stride == 1 || p.row_bytes % 128 || p.row_bytes > kMaxCutRow) return false;
+    if (p.row_bytes % tile == 0 || tile % p.row_bytes == 0) return false;
+    for (const hp_segment_t &s : p.segments)
+        if (s.n_rows * (p.row_bytes / 128) > INT32_MAX) return false;      // the kernels divide lines in 31 bits
+    return true;
+}
+
 std::vector<Seg> dst_runs(const hp_plan &p, bool whole) {
     std::vector<Seg> runs;
     if (whole) {                                           // dense, whatever the row order
@@ -265,8 +273,7 @@ int make_tables(hp_plan *p) {
     }
     // 16-ary search trees over the keys of each variant
     p->tree.clear();
-    for (int v = 0; v < kTileVariants && n > 0; ++v) {
-        const uint32_t *keys = p->first_tile.data() + (size_t)v * (n + 1);
+    auto add_tree = [&](const uint32_t *keys, TreeInfo &ti) -> int {
         std::vector<std::vector<uint32_t>> levels;
         levels.emplace_back(keys, keys + n);
         while (levels.back().size() > (size_t)kTreeFanout) {
@@ -276,7 +283,6 @@ int make_tables(hp_plan *p) {
             levels.push_back(std::move(up));
         }
         if (levels.size() > (size_t)kMaxTreeLevels) return HP_ELAYOUT;
-        TreeInfo &ti = p->tree_info[v];
         ti.n_levels = (uint32_t)levels.size();
         for (size_t l = 0; l < levels.size(); ++l) {
             std::vector<uint32_t> &lv = levels[l];
@@ -284,12 +290,37 @@ int make_tables(hp_plan *p) {
             ti.level_off[l] = (uint32_t)p->tree.size();
             p->tree.insert(p->tree.end(), lv.begin(), lv.end());
         }
+        return HP_OK;
+    };
+    int rc = HP_OK;
+    for (int v = 0; v < kTileVariants && n > 0 && rc == HP_OK; ++v)
+        rc = add_tree(p->first_tile.data() + (size_t)v * (n + 1), p->tree_info[v]);
+    std::vector<uint32_t> keys(n);
+    for (int v = 0; v < kTileVariants; ++v) {
+        p->cut_tiles[v] = 0;
+        if (rc != HP_OK || n == 0 || !cut_by_bytes(*p, tile_bytes_of(v))) continue;
+        uint64_t acc = 0;                                      // no more than there are rows or pieces of them: fits
+        for (size_t i = 0; i < n; ++i) {
+            keys[i] = (uint32_t)acc;
+            acc += tiles_of((uint64_t)p->segments[i].n_rows, 1, p->row_bytes, tile_bytes_of(v));
+        }
+        p->cut_tiles[v] = (uint32_t)acc;
+        rc = add_tree(keys.data(), p->cut_info[v]);
     }
-    return HP_OK;
+    return rc;
+}
+
+// Row-strided rows that launches in small tiles can cut by bytes; those of 2 KiB and more want what dense launches want.
+bool cut_rows(const hp_plan &p) { return cut_by_bytes(p, 1024) || cut_by_bytes(p, 2048); }
+bool like_dense(const hp_plan &p) { return p.row_bytes >= 2048 && cut_by_bytes(p, 1024); }
+
+// Forward to eight copies in short rows, between what tiles of 1 KiB and cutting suit: 0.93-0.97 with either.
+bool eight_short(const hp_plan &p, double fwd_bytes) {
+    return p.dst_stride > 1 && p.dst_copies == 8 && p.row_bytes < 1536 && fwd_bytes >= 450e6 && fwd_bytes < 1500e6;
 }
 
 // Whether all tiles of 1 KiB but a run's last are whole.
-bool even_tiles(const hp_plan &p) { return p.dst_stride == 1 || p.row_bytes % 1024 == 0; }
+bool even_tiles(const hp_plan &p) { return p.dst_stride == 1 || p.row_bytes % 1024 == 0 || like_dense(p); }
 
 // The shapes of launches whose size calls for others than the replica counts
 // alone.  Each line was measured against the shape that it replaces in the
@@ -311,10 +342,11 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
     constexpr int K1 = 0, K2 = 1, K4 = 2, K8 = 3;            // tiles of 1, 2, 4 and 8 KiB
     const int c = p->dst_copies, s = p->src_copies;
     const bool between = c != 1 && c != 2 && c != 4 && c != 8;                  // 3, 5 to 7, 9 to 16 copies
-    const bool f32 = p->elem_bytes == 4, dense = p->dst_stride == 1;
+    const bool f32 = p->elem_bytes == 4, dense = p->dst_stride == 1 || like_dense(*p);
     const bool whole = dense || p->row_bytes >= 4096;        // tiles of 1 KiB are nearly all whole
     // A row-strided row is cut into tiles from its start: whether it fills what it is cut into, and that in whole lanes.
     const int64_t row = p->row_bytes;
+    const bool full = dense || cut_rows(*p);                 // tiles are whole where the launch wants them to be
     auto fills = [&](int64_t tile) { return dense || 20 * row >= 17 * ((row + tile - 1) / tile * tile); };
     const bool filled = fills(1024) && (dense || row % 16 == 0), even = even_tiles(*p);
     const size_t segs = p->segments.size();
@@ -344,17 +376,17 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
     else if (c >= 5 && c <= 7 && fwd >= 450 * MB) {
         if (segs <= (c == 5 ? 256 : 1024) && (filled || row < 2048)) set(f, K1, 64, 14);   // 1.00-1.15; more segments 0.97-1.02, rows of 3088 and 8186 bytes 0.94-0.99
     }
-    else if (c == 8 && dense && in(fwd, 40, 450)) set(f, K1, 64, 5);            // 0.99-1.25; [S,B,H] order 0.93-1.02
-    else if (c == 8 && dense && in(fwd, 450, 5000)) {
+    else if (c == 8 && full && in(fwd, 40, 450)) set(f, K1, 64, 5);            // 0.99-1.25; [S,B,H] order 0.93-1.02
+    else if (c == 8 && full && in(fwd, 450, 5000) && !eight_short(*p, fwd)) {
         if (segs <= 256) set(f, K1, 64, fwd < 700 * MB ? 5 : 8);                // 1.00-1.06; more segments 0.98-1.02, 7.2 GB 0.99
     }
-    else if (c >= 10 && c <= 12 && dense && in(fwd, 100, c == 12 ? 450 : 600)) set(f, K1, 64, 5);   // 0.96-1.28; ten copies, 700 MB 0.98-1.0, 1.1 GB 0.85; [S,B,H] 0.86-1.05
-    else if (c == 12 && dense && in(fwd, 450, 1200)) {
+    else if (c >= 10 && c <= 12 && full && in(fwd, 100, c == 12 ? 450 : 600)) set(f, K1, 64, 5);   // 0.96-1.28; ten copies, 700 MB 0.98-1.0, 1.1 GB 0.85; [S,B,H] 0.86-1.05
+    else if (c == 12 && full && in(fwd, 450, 1200)) {
         if (segs <= 256) set(f, K1, 64, fwd < 1000 * MB ? 3 : 4);               // 1.02-1.12; 1.2 GB 0.93-0.99
     }
-    else if (c >= 13 && c <= 15 && dense && in(fwd, 100, 1200)) set(f, K1, 64, 4);  // 0.98-1.10; 1.4 GB 0.94-1.03
-    else if (c == 16 && dense && in(fwd, 100, 1500)) set(f, K1, 64, 3);         // 1.01-1.11, paced; 1.7 GB 0.91-0.99
-    else if (c >= 13 && dense && fwd >= 1200 * MB) set(f, K2, 64, 3);   // 0.99-1.03 to 4 GB
+    else if (c >= 13 && c <= 15 && full && in(fwd, 100, 1200)) set(f, K1, 64, 4);  // 0.98-1.10; 1.4 GB 0.94-1.03
+    else if (c == 16 && full && in(fwd, 100, 1500)) set(f, K1, 64, 3);         // 1.01-1.11, paced; 1.7 GB 0.91-0.99
+    else if (c >= 13 && full && fwd >= 1200 * MB) set(f, K2, 64, 3);   // 0.99-1.03 to 4 GB
 
     // With few copies a workgroup moves little for each search, and the depth of the tree (16 segments a level) decides.
     const double bwd = (double)p->bwd_bytes;
@@ -385,7 +417,7 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
     // half a dozen to a dozen waves of eight and more copies have to have whole tiles: [S,B,H] rows that leave them partly empty lose 2-13 % here
     else if (c == 8 && bwd >= 1500 * MB && (dense || row < 4096 || fills(4096))) set(b, K4, 64, 5);   // 1.01-1.06, to two source copies 1.05-1.11
     else if (c == 8 && bwd >= 40 * MB && filled) set(b, K1, 64, bwd < 450 * MB ? 12 : 11);   // 1.00-1.03
-    else if (c > 12 && dense && in(bwd, 40, 250)) set(b, K1, 64, 12);           // 1.02-1.07; 350 MB 0.97-1.00, [S,B,H] order 0.85-1.0
+    else if (c > 12 && p->dst_stride == 1 && in(bwd, 40, 250)) set(b, K1, 64, 12);           // 1.02-1.07; 350 MB 0.97-1.00, [S,B,H] order 0.85-1.0
     else if (c > 8 && bwd >= 600 * MB && filled) set(b, K1, 64, 10);            // 1.02-1.06
     else if (c > 8 && !f32 && in(bwd, 100, 250)) set(b, K4, 128, 24);           // 0.98-1.14; binary32: 0.97-1.00, 300 MB: 0.94-1.01
 
@@ -534,6 +566,31 @@ int pace_rounds(const hp_plan &p, int direction, const Launch &L) {
     const double bytes = (double)p.bwd_bytes;
     if (direction != 1 || bytes < 400e6) return 0;
     return c == 2 ? two[level] : c == 3 && bytes >= 450e6 ? three[level] : c == 4 ? four[level] : c == 6 && bytes >= 800e6 ? six[level] : 0;
+}
+
+// Against a tile for a row's rest, or for the whole rows that fit, by the share of a
+// tile that those fill; the same buffers in turn, two and four samples a position,
+// rows of 384 to 12416 bytes, 1 to 16 copies, 40 MB to 2 GB, the direction's gain:
+//   forward      share under 0.87: 1.0-1.3 to 450 MB, above 1.0-1.8 (3.5 TB/s at 0.53: to four
+//                copies in rows of 2176 bytes, 1.2 GB 327 -> 213 us); more: 0.95-1.0 to 400 MB, 1.0-1.1
+//   backward     rows of 1 KiB and more 0.98-1.4; shorter ones 0.96-1.05; share over 0.82, 150 MB 0.96-1.0
+//   accumulating 0.98-1.4
+// The lines that are left out forward lost 3 to 10 %: launches in which partly empty
+// tiles happen to leave as much on its way as suits them.
+bool cuts_launch(const hp_plan &p, int direction, int variant) {
+    if (!p.cut_tiles[variant]) return false;
+    const int64_t row = p.row_bytes, tile = tile_bytes_of(variant), c = p.dst_copies;
+    const double share = row >= tile ? (double)row / (double)((row + tile - 1) / tile * tile) : (double)(tile / row * row) / (double)tile;
+    if (direction == 1) {
+        const double bytes = (double)p.bwd_bytes;
+        return row >= 1024 && (bytes < 400e6 ? share < 0.82 : share < 0.87 || like_dense(p));
+    }
+    const double bytes = direction == 2 ? (double)p.bwd_accum_bytes : (1.0 + (double)c) * (double)p.n_rows * (double)row;
+    if (share >= 0.87 && bytes < 400e6) return false;
+    if (direction == 2) return true;
+    if ((c == 3 || c == 4) && row >= 1024 && row < 2048 && bytes < 450e6) return false;
+    if ((c == 6 || c == 7) && share >= 0.7 && row < 3072 && bytes < 450e6) return false;
+    return !eight_short(p, bytes);
 }
 
 int build_host_plan(const hp_layout_t *srcs, int32_t n_edges, const hp_layout_t *dst,

@@ -88,6 +88,10 @@ struct hp_plan {
     std::vector<uint32_t> first_tile;     // kTileVariants x (n_segments + 1), row-major
     std::vector<uint32_t> tree;           // the search trees of all variants, 64-byte aligned nodes
     hp::TreeInfo tree_info[hp::kTileVariants] = {};
+    // Launches that cut row-strided segments by bytes (hp::cut_by_bytes): their tiles, 0 where a launch does not, and
+    // their trees, behind the others.
+    uint32_t cut_tiles[hp::kTileVariants] = {};
+    hp::TreeInfo cut_info[hp::kTileVariants] = {};
     hp::Launch fwd{}, bwd{}, acc{};       // hp_forward, hp_backward, hp_backward_accumulate
     // device side
     hp::Seg *d_segs = nullptr;
@@ -134,6 +138,17 @@ int build_host_plan(const hp_layout_t *srcs, int32_t n_edges, const hp_layout_t 
 // searched for or remembered.  Every cap that was measured with these rounds is within
 // 1 % of the same cap without them or faster.
 int pace_rounds(const hp_plan &p, int direction, const Launch &L);
+
+// Whether a launch with tiles of `tile` bytes cuts the plan's row-strided segments by
+// bytes of their source, across the ends of rows: where a tile holds neither whole
+// rows nor a row whole tiles, and rows are whole lines.  (Other rows are cut one by
+// one, at lines of the destination.)
+constexpr int64_t kMaxCutRow = 128 << 10;      // row_of_chunk is exact
+bool cut_by_bytes(const hp_plan &p, uint32_t tile);
+
+// Whether a launch of the plan in this direction (0 forward, 1 backward, 2 accumulating)
+// is cut by bytes, if its tiles can be.
+bool cuts_launch(const hp_plan &p, int direction, int variant);
 
 // Tiles of `tile` bytes that a run of n_rows rows is cut into.
 uint64_t tiles_of(uint64_t n_rows, uint64_t pitch_rows, int64_t row_bytes, uint32_t tile);

@@ -31,7 +31,8 @@ struct KParams {
     uint32_t dst_copies;        // replicas of each row on the destination side
     uint32_t parts_per_row;     // row-strided segments, rows of at least a tile: ceil(row_bytes / tile_bytes); else 0
     uint32_t part_magic, part_shift;      // t / parts_per_row = t * part_magic >> (31 + part_shift)
-    uint32_t rows_per_tile;     // row-strided segments, rows shorter than a tile: tile_bytes / row_bytes
+    uint32_t rows_per_tile;     // row-strided segments, rows shorter than a tile: tile_bytes / row_bytes; 0 = cut by bytes, with the
+                                // magic number of parts_per_row for a row's lines
     uint32_t row_chunks;        // row-strided tiles of whole rows: lane chunks of one row (see set_row_chunks)
     uint32_t row_magic, row_one;
     uint32_t pace;              // rounds of pace() before a tile's loads (kernels that have it)
@@ -45,6 +46,7 @@ struct TileView {
     uint32_t nbytes;
     uint32_t pitch_rows;        // 1 = dense destination
     uint32_t row;               // row-strided segments and bands: the tile's (first) row
+    uint32_t col;               // cut by bytes: where the tile begins in that row
     uint32_t src_buf, dst_buf0;
     uint32_t src_copies;        // identical TP copies of the source rank
     uint32_t first;             // dense: 1 = the tile starts its run (the segment, or one row of a row-strided one)
@@ -123,9 +125,11 @@ HP_HD uint32_t clip(uint64_t left, uint32_t tile) {
 enum SegKinds {
     kWholeTiles,    // dense, or row-strided with rows of at least a tile
     kRowGroups,     // row-strided with rows shorter than a tile
+    kCutRows,       // row-strided, cut by bytes
 };
+constexpr uint32_t kLineBytes = 128;
 inline SegKinds seg_kinds(const KParams &k, uint64_t pitch_rows) {
-    return pitch_rows != 1 && k.parts_per_row == 0 ? kRowGroups : kWholeTiles;
+    return k.rows_per_tile == 0 ? kCutRows : pitch_rows != 1 && k.parts_per_row == 0 ? kRowGroups : kWholeTiles;
 }
 
 // x / n for x < 2^31, n's magic number and shift made by set_division.
@@ -174,6 +178,15 @@ HP_HD TileView locate_tile(const KParams &k, const HP_TABLE Seg *segs, const HP_
         v.first = off == 0;
         v.left = left;
         v.row = row;
+    } else if (KINDS == kCutRows) {
+        const uint64_t off = (uint64_t)t * k.tile_bytes;
+        const uint32_t row0 = divide(t * (k.tile_bytes / kLineBytes), k.part_magic, k.part_shift);
+        v.col = (uint32_t)off - row0 * k.row_bytes;
+        v.src_off = s.src_off + off;
+        v.dst_off = s.dst_off + (uint64_t)row0 * s.pitch_rows * k.row_bytes + v.col;
+        v.left = (uint64_t)s.n_rows * k.row_bytes - off;
+        v.nbytes = clip(v.left, k.tile_bytes);
+        v.row = row0;
     } else {
         const uint64_t row0 = (uint64_t)t * k.rows_per_tile;
         const uint32_t rows = clip(s.n_rows - row0, k.rows_per_tile);
@@ -189,8 +202,11 @@ HP_HD TileView locate_tile(const KParams &k, const HP_TABLE Seg *segs, const HP_
 #if !defined(__HIP_DEVICE_COMPILE__)
 // The lookup that a launch's kernels have, on the host.
 inline TileView locate_tile(const KParams &k, uint32_t tile) {
-    return seg_kinds(k, k.segs->pitch_rows) == kRowGroups ? locate_tile<kRowGroups>(k, k.segs, k.tree, tile)
-                                                          : locate_tile<kWholeTiles>(k, k.segs, k.tree, tile);
+    switch (seg_kinds(k, k.segs->pitch_rows)) {
+        case kRowGroups: return locate_tile<kRowGroups>(k, k.segs, k.tree, tile);
+        case kCutRows: return locate_tile<kCutRows>(k, k.segs, k.tree, tile);
+        default: return locate_tile<kWholeTiles>(k, k.segs, k.tree, tile);
+    }
 }
 #endif
 
@@ -199,7 +215,6 @@ inline TileView locate_tile(const KParams &k, uint32_t tile) {
 // begins and ends: the tiles of a run still partition it, but where rows are no
 // multiple of a line, two tiles - two workgroups, on two XCDs with an L2 each -
 // no longer share one.  A tile of fewer than 128 bytes may become empty.
-constexpr uint32_t kLineBytes = 128;
 HP_HD void align_tile(TileView &v, uint64_t dst_base) {
     if (v.pitch_rows != 1) return;
     const uint32_t up = (uint32_t)(0 - (dst_base + v.dst_off)) & (kLineBytes - 1);
@@ -252,6 +267,20 @@ HP_HD ChunkView chunk_at(const KParams &k, const TileView &t, uint32_t i) {
     return c;
 }
 
+// Chunk i of a tile that was cut by bytes: on the source side it lies as in a dense
+// tile, on the destination's it has the rest of the positions between its row and the tile's
+// first before it.  Rows of a tile and more: their end is passed once at most.
+template <uint32_t UNIT>
+HP_HD ChunkView cut_chunk(const KParams &k, const TileView &t, uint32_t i) {
+    ChunkView c;
+    c.src = i * UNIT;
+    c.over = 0;
+    const uint64_t gap = (uint64_t)(t.pitch_rows - 1) * k.row_bytes;
+    if (k.row_bytes >= k.tile_bytes) c.dst = c.src + (t.col + c.src >= k.row_bytes ? gap : 0);
+    else c.dst = c.src + row_of_chunk(k, i + t.col / UNIT) * gap;
+    return c;
+}
+
 // How many chunks of UNIT bytes a tile has, and how many of them lie in their
 // run as they are (those before the moved one).  0 chunks: the run is shorter
 // than a chunk and is walked element by element.
@@ -301,9 +330,10 @@ HP_HD uint32_t band_sample(const KParams &k, uint32_t row) {
 // The kernel parameters of a launch with tiles of 1 KiB << variant; segs and
 // tree point at the plan's tables wherever the caller keeps them (device memory
 // for a launch, the plan's host vectors for the host-side walk).
-inline KParams kernel_params(const hp_plan &p, int variant, const Seg *segs, const uint32_t *tree) {
+// cut: for the launch that cuts row-strided segments by bytes, where the plan has one.
+inline KParams kernel_params(const hp_plan &p, int variant, const Seg *segs, const uint32_t *tree, bool cut = false) {
     KParams k;
-    const TreeInfo &ti = p.tree_info[variant];
+    const TreeInfo &ti = cut ? p.cut_info[variant] : p.tree_info[variant];
     for (int j = 0; j < kTreeFanout; ++j)
         k.root[j] = ti.n_levels ? p.tree[ti.level_off[ti.n_levels - 1] + j] : UINT32_MAX;
     k.segs = segs;
@@ -316,6 +346,10 @@ inline KParams kernel_params(const hp_plan &p, int variant, const Seg *segs, con
     k.rows_per_tile = std::max<uint32_t>(1u, k.tile_bytes / k.row_bytes);
     k.parts_per_row = k.row_bytes >= k.tile_bytes ? (k.row_bytes + k.tile_bytes - 1) / k.tile_bytes : 0u;
     set_parts(k);
+    if (cut) {
+        k.parts_per_row = k.rows_per_tile = 0;
+        set_division(k.row_bytes / kLineBytes, k.part_magic, k.part_shift);
+    }
     set_row_chunks(k, 16u);
     k.block = k.pace = 0;       // set by the launch
     k.band_samples = k.band_magic = k.band_shift = 0;      // by that of text gradients in bands
