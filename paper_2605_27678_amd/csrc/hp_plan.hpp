@@ -144,6 +144,7 @@ int pace_rounds(const hp_plan &p, int direction, const Launch &L);
 // rows nor a row whole tiles, and rows are whole lines.  (Other rows are cut one by
 // one, at lines of the destination.)
 constexpr int64_t kMaxCutRow = 128 << 10;      // row_of_chunk is exact
+constexpr int kCutVariants = 4;                // tiles of up to 8 KiB, which launches start from
 bool cut_by_bytes(const hp_plan &p, uint32_t tile);
 
 // Whether a launch of the plan in this direction (0 forward, 1 backward, 2 accumulating)

@@ -71,7 +71,7 @@ int main(int argc, char **argv) {
         for (v = 0; v < hp::kTileVariants; ++v) {
             tile = 0;
             const int64_t bytes = hp::tile_bytes_of(v);
-            CHECK((p.cut_tiles[v] > 0) == (p.row_bytes % bytes != 0 && bytes % p.row_bytes != 0));
+            CHECK((p.cut_tiles[v] > 0) == (v < hp::kCutVariants && p.row_bytes % bytes != 0 && bytes % p.row_bytes != 0));
             CHECK(p.cut_tiles[v] <= p.n_tiles(v));
             if (!p.cut_tiles[v]) continue;
             if (walk<16>(p, tree, &tiles) || (!f32 && walk<8>(p, tree, &tiles))) return 1;
