@@ -90,7 +90,7 @@ __device__ __forceinline__ void st(gchar *p, typename Bytes<N>::type v) {
     else *(M *)p = (typename Bytes<N>::mem)v;
 }
 
-// What the tiles of a launch look like.  Three kernels, because the start of a
+// What the tiles of a launch look like.  A kernel for each kind, because the start of a
 // workgroup is what a launch of short-lived ones waits for: testing for ragged
 // rows in the kernel of whole lines cost 3 % there (110 MB forward to two copies,
 // when a lookup still took twice as long: 25.5 -> 26.4 us).
@@ -99,7 +99,10 @@ enum Tiles {
     kRagged,    // dense on both sides, rows of any length
     kStrided,   // groups of whole row-strided rows ([S,B,H] order with several samples per rank, rows shorter than a tile)
     kCut,       // row-strided rows of whole lines, cut by bytes of the source across their ends (hp::cuts_launch)
+    kPadded,    // row-strided rows of any length from 2 KiB on, cut by lines of the destination
 };
+// Whether a tile has no chunk but whole ones.
+template <Tiles TILES> constexpr bool kAllWhole = TILES == kLines || TILES == kCut || TILES == kPadded;
 // Whether a tile lies on the destination side as it does on the source's.
 template <Tiles TILES> constexpr bool kDense = TILES == kLines || TILES == kRagged;
 
@@ -155,7 +158,7 @@ __device__ __forceinline__ TileView my_tile(const Args &a) {
     const uintptr_t args = args_base();
     const uintptr_t segs = a.k.seg_at ? args + a.k.seg_at : (uintptr_t)a.k.segs;
     const uintptr_t tree = a.k.seg_at ? args + a.k.tree_at : (uintptr_t)a.k.tree;
-    TileView t = hp::locate_tile<TILES == kStrided ? hp::kRowGroups : TILES == kCut ? hp::kCutRows : hp::kWholeTiles, BANDS>(
+    TileView t = hp::locate_tile<TILES == kStrided ? hp::kRowGroups : TILES == kCut ? hp::kCutRows : TILES == kPadded ? hp::kPaddedRows : hp::kWholeTiles, BANDS>(
         a.k, (const HP_TABLE hp::Seg *)segs, (const HP_TABLE uint32_t *)tree, blockIdx.x);
     if (TILES == kRagged) hp::align_tile(t, buffers()[a.k.dst_base + t.dst_buf0]);
     return t;
@@ -164,14 +167,19 @@ __device__ __forceinline__ TileView my_tile(const Args &a) {
 // How many chunks of UNIT bytes a tile has, and how many are whole; tiles of lines have no others.
 template <uint32_t UNIT, Tiles TILES>
 __device__ __forceinline__ void count_chunks(const KParams &k, const TileView &t, uint32_t &all, uint32_t &whole) {
-    if (TILES == kLines || TILES == kCut) all = whole = t.nbytes / UNIT;
+    if (kAllWhole<TILES>) all = whole = t.nbytes / UNIT;
     else hp::count_chunks<UNIT, TILES != kStrided>(k, t, all, whole);
 }
 
-// Chunk i of a tile; END: it may be the one that was moved back to end with its run.
+// Chunk i of a tile, and whether it is to be stored; END: it may be the one that was moved back to end with its run.
 template <uint32_t UNIT, Tiles TILES, bool END>
-__device__ __forceinline__ hp::ChunkView chunk(const KParams &k, const TileView &t, uint32_t i) {
-    if constexpr (TILES == kCut) return hp::cut_chunk<UNIT>(k, t, i);
+__device__ __forceinline__ hp::ChunkView chunk(const KParams &k, const TileView &t, uint32_t i, bool &there) {
+    there = true;
+    if constexpr (TILES == kPadded) {
+        hp::ChunkView c;
+        there = hp::padded_chunk(k, t, (uint32_t)(buffers()[k.dst_base + t.dst_buf0] + t.dst_off), i, c);
+        return c;
+    } else if constexpr (TILES == kCut) return hp::cut_chunk<UNIT>(k, t, i);
     else return hp::chunk_at<UNIT, TILES != kStrided, END && TILES == kRagged>(k, t, i);
 }
 
@@ -247,16 +255,17 @@ __device__ __forceinline__ void forward_group(const KParams &k, const TileView &
     u32x4 v[U];
     uint32_t i[U];
     hp::ChunkView c[U];
+    bool there[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         i[u] = done + u * k.block + threadIdx.x;
-        c[u] = chunk<16, TILES, GUARD>(k, t, GUARD ? min(i[u], n - 1) : i[u]);
+        c[u] = chunk<16, TILES, GUARD>(k, t, GUARD ? min(i[u], n - 1) : i[u], there[u]);
         v[u] = ld<16, NTL>(places.src + c[u].src);
     }
     auto store = [&](gchar *p) {
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            if (!GUARD || i[u] < n) st<16, NTS>(p + (kDense<TILES> ? c[u].src : c[u].dst), v[u]);
+            if (there[u] && (!GUARD || i[u] < n)) st<16, NTS>(p + (kDense<TILES> ? c[u].src : c[u].dst), v[u]);
     };
     for_copies<NREP>(k, t, places, nrep, [&](uint32_t, auto &p) {
         constexpr int N = sizeof(p) / sizeof(*p);
@@ -281,7 +290,7 @@ __device__ __forceinline__ void forward_tile(const KParams &k, const TileView &t
     count_chunks<16, TILES>(k, t, n, whole);
     const uint32_t step = k.block;
     uint32_t done = 0;                                       // uniform
-    if (TILES != kLines && TILES != kCut && __builtin_expect(n == 0, 0)) {                       // shorter than a chunk
+    if (!kAllWhole<TILES> && __builtin_expect(n == 0, 0)) {                       // shorter than a chunk
         for (uint32_t i = threadIdx.x; i < t.nbytes / 2; i += step) {
             const hp::ChunkView c = hp::element_at<2>(k, t, i);
             const uint16_t v = ld<2, NTL>(places.src + c.src);
@@ -323,12 +332,15 @@ __device__ __forceinline__ void zero_tile(const KParams &k, const TileView &t) {
     const HP_TABLE uint64_t *b = buffers() + (k.dst_base + t.dst_buf0);
     for (uint32_t r = 0; r < k.dst_copies; ++r) {
         gchar *dst = at(b[r] + t.dst_off);
-        if (TILES != kLines && TILES != kCut && n == 0) {
+        if (!kAllWhole<TILES> && n == 0) {
             for (uint32_t i = threadIdx.x; i < t.nbytes / 2; i += k.block)
                 st<2, NTS>(dst + hp::element_at<2>(k, t, i).dst, 0);
         } else {
-            for (uint32_t i = threadIdx.x; i < n; i += k.block)
-                st<16, NTS>(dst + chunk<16, TILES, true>(k, t, i).dst, (u32x4)0u);
+            for (uint32_t i = threadIdx.x; i < n; i += k.block) {
+                bool there;
+                const hp::ChunkView c = chunk<16, TILES, true>(k, t, i, there);
+                if (there) st<16, NTS>(dst + c.dst, (u32x4)0u);
+            }
         }
     }
 }
@@ -376,7 +388,7 @@ hp_text_grads_kernel(const Args a) {
     uint32_t n, whole;
     count_chunks<16, TILES>(k, t, n, whole);
     const uint32_t step = k.block;
-    if (TILES != kLines && TILES != kCut && __builtin_expect(n == 0, 0)) {             // shorter than a chunk
+    if (!kAllWhole<TILES> && __builtin_expect(n == 0, 0)) {             // shorter than a chunk
         for (uint32_t i = threadIdx.x; i < t.nbytes / 2; i += step) {
             const uint64_t at = hp::element_at<2>(k, t, i).dst;
             uint16_t v = 0;
@@ -393,7 +405,8 @@ hp_text_grads_kernel(const Args a) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const uint32_t i = done + u * step + threadIdx.x;
-            at[u] = chunk<16, TILES, true>(k, t, min(i, n - 1)).dst;
+            bool there;                                               // (no padded rows here)
+            at[u] = chunk<16, TILES, true>(k, t, min(i, n - 1), there).dst;
             v[u] = (u32x4)0u;
             if constexpr (BANDS && TILES == kStrided) text[u] = !image(hp::row_of_chunk(k, min(i, n - 1)));
         }
@@ -521,12 +534,14 @@ __device__ __forceinline__ void backward_group(const KParams &k, const TileView 
     constexpr uint32_t kWiden = ACC ? 4 / kElemBytes : 1;      // accumulator bytes per gradient byte
     uint32_t i[U];
     hp::ChunkView c[U];
+    bool there[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         i[u] = done + u * k.block + threadIdx.x;
         const uint32_t ic = GUARD ? min(i[u], n - 1) : i[u];
+        there[u] = true;
         if constexpr (ELEMENT) c[u] = hp::element_at<kElemBytes>(k, t, ic);
-        else c[u] = chunk<In::kBytes, TILES, GUARD>(k, t, ic);
+        else c[u] = chunk<In::kBytes, TILES, GUARD>(k, t, ic, there[u]);
     }
     VO old[U];
     if constexpr (ACC && kAccumulatorsFirst<DT, NREP>) {
@@ -562,7 +577,7 @@ __device__ __forceinline__ void backward_group(const KParams &k, const TileView 
         for (uint32_t s = 0;;) {
 #pragma unroll
             for (int u = 0; u < U; ++u)
-                if (!GUARD || i[u] < n) st<Out::kBytes, NTS>(out + c[u].src, res[u]);
+                if (there[u] && (!GUARD || i[u] < n)) st<Out::kBytes, NTS>(out + c[u].src, res[u]);
             if (++s >= t.src_copies) break;
             out = at(buffers()[t.src_buf + s] + t.src_off);
         }
@@ -607,7 +622,7 @@ __device__ __forceinline__ void backward_tile(const KParams &k, const TileView &
     count_chunks<Elems<DT, E>::kBytes, TILES>(k, t, n, whole);
     const uint32_t step = k.block;
     uint32_t done = 0;                                               // uniform
-    if (TILES != kLines && TILES != kCut && __builtin_expect(n == 0, 0)) {                               // shorter than a chunk
+    if (!kAllWhole<TILES> && __builtin_expect(n == 0, 0)) {                               // shorter than a chunk
         for (n = t.nbytes / kElemBytes; done < n; done += step)
             backward_group<DT, 1, ACC, 0, 1, TILES, true, NTL, NTS>(k, t, Places<0>(k, t, kWiden), nrep, done, n);
         return;
@@ -872,10 +887,10 @@ void launch_backward_nrep(int copies, const LaunchCfg &c, const Args &a) {
 template <Tiles TILES, bool NTL, bool NTS>
 void launch_backward(int dtype, bool acc, int copies, const LaunchCfg &c, const Args &a) {
     if (dtype == HP_F32) {
-        if (acc) launch_backward_nrep<HP_F32, true, TILES, NTL, NTS>(copies, c, a);
+        if (acc) { if constexpr (TILES != kPadded) launch_backward_nrep<HP_F32, true, TILES, NTL, NTS>(copies, c, a); }
         else launch_backward_nrep<HP_F32, false, TILES, NTL, NTS>(copies, c, a);
     } else {
-        if (acc) launch_backward_nrep<HP_BF16, true, TILES, NTL, NTS>(copies, c, a);
+        if (acc) { if constexpr (TILES != kPadded) launch_backward_nrep<HP_BF16, true, TILES, NTL, NTS>(copies, c, a); }
         else launch_backward_nrep<HP_BF16, false, TILES, NTL, NTS>(copies, c, a);
     }
 }
@@ -887,7 +902,7 @@ template <Tiles TILES, bool NTL, bool NTS>
 void launch_nt(const hp_plan *p, Direction dir, const LaunchCfg &c, const Args &a) {
     if (dir == kZeroRows) HP_LAUNCH((hp_zero_rows_kernel<TILES, NTS>), c, a);
     else if (dir == kForward) launch_forward<TILES, NTL, NTS>(p->dst_copies, c, a);
-    else launch_backward<TILES, NTL, NTS>(p->dtype, dir == kBackwardAcc, p->dst_copies, c, a);
+    else launch_backward<TILES, NTL, NTS>(p->dtype, dir == kBackwardAcc, p->dst_copies, c, a);   // (padded rows do not accumulate)
 }
 
 template <Tiles TILES>
@@ -976,6 +991,7 @@ int enqueue_params(const hp_plan *p, Direction dir, const hp::Launch &L, const B
     c.ev = ev;
     const hp::SegKinds kind = hp::seg_kinds(k, (uint64_t)p->dst_stride);
     if (kind == hp::kCutRows) launch_tiles<kCut>(p, dir, L.nontemporal, c, a);
+    else if (kind == hp::kPaddedRows) launch_tiles<kPadded>(p, dir, L.nontemporal, c, a);
     else if (kind == hp::kRowGroups) launch_tiles<kStrided>(p, dir, L.nontemporal, c, a);
     else if (k.row_bytes % hp::kLineBytes) launch_tiles<kRagged>(p, dir, L.nontemporal, c, a);
     else launch_tiles<kLines>(p, dir, L.nontemporal, c, a);

@@ -31,8 +31,8 @@ struct KParams {
     uint32_t dst_copies;        // replicas of each row on the destination side
     uint32_t parts_per_row;     // row-strided segments, rows of at least a tile: ceil(row_bytes / tile_bytes); else 0
     uint32_t part_magic, part_shift;      // t / parts_per_row = t * part_magic >> (31 + part_shift)
-    uint32_t rows_per_tile;     // row-strided segments, rows shorter than a tile: tile_bytes / row_bytes; 0 = cut by bytes, with the
-                                // magic number of parts_per_row for a row's lines
+    uint32_t rows_per_tile;     // row-strided segments, rows shorter than a tile: tile_bytes / row_bytes; 0 = cut by bytes or lines, with
+                                // the magic number of parts_per_row for a row's lines
     uint32_t row_chunks;        // row-strided tiles of whole rows: lane chunks of one row (see set_row_chunks)
     uint32_t row_magic, row_one;
     uint32_t pace;              // rounds of pace() before a tile's loads (kernels that have it)
@@ -46,7 +46,7 @@ struct TileView {
     uint32_t nbytes;
     uint32_t pitch_rows;        // 1 = dense destination
     uint32_t row;               // row-strided segments and bands: the tile's (first) row
-    uint32_t col;               // cut by bytes: where the tile begins in that row
+    uint32_t col;               // cut by bytes or lines: where the tile begins in that row
     uint32_t src_buf, dst_buf0;
     uint32_t src_copies;        // identical TP copies of the source rank
     uint32_t first;             // dense: 1 = the tile starts its run (the segment, or one row of a row-strided one)
@@ -126,10 +126,12 @@ enum SegKinds {
     kWholeTiles,    // dense, or row-strided with rows of at least a tile
     kRowGroups,     // row-strided with rows shorter than a tile
     kCutRows,       // row-strided, cut by bytes
+    kPaddedRows,    // row-strided, cut by lines of the destination
 };
 constexpr uint32_t kLineBytes = 128;
 inline SegKinds seg_kinds(const KParams &k, uint64_t pitch_rows) {
-    return k.rows_per_tile == 0 ? kCutRows : pitch_rows != 1 && k.parts_per_row == 0 ? kRowGroups : kWholeTiles;
+    if (k.rows_per_tile == 0) return k.row_bytes % kLineBytes ? kPaddedRows : kCutRows;
+    return pitch_rows != 1 && k.parts_per_row == 0 ? kRowGroups : kWholeTiles;
 }
 
 // x / n for x < 2^31, n's magic number and shift made by set_division.
@@ -178,6 +180,15 @@ HP_HD TileView locate_tile(const KParams &k, const HP_TABLE Seg *segs, const HP_
         v.first = off == 0;
         v.left = left;
         v.row = row;
+    } else if (KINDS == kPaddedRows) {
+        const uint32_t lines = t * (k.tile_bytes / kLineBytes);
+        const uint32_t row0 = divide(lines, k.part_magic, k.part_shift);
+        v.col = (lines - row0 * (k.row_chunks >> 3)) * kLineBytes;
+        v.src_off = s.src_off + (uint64_t)row0 * k.row_bytes;
+        v.dst_off = s.dst_off + (uint64_t)row0 * s.pitch_rows * k.row_bytes;
+        v.left = ((uint64_t)s.n_rows * (k.row_chunks >> 3) - lines) * kLineBytes;
+        v.nbytes = clip(v.left, k.tile_bytes);
+        v.row = row0;
     } else if (KINDS == kCutRows) {
         const uint64_t off = (uint64_t)t * k.tile_bytes;
         const uint32_t row0 = divide(t * (k.tile_bytes / kLineBytes), k.part_magic, k.part_shift);
@@ -205,6 +216,7 @@ inline TileView locate_tile(const KParams &k, uint32_t tile) {
     switch (seg_kinds(k, k.segs->pitch_rows)) {
         case kRowGroups: return locate_tile<kRowGroups>(k, k.segs, k.tree, tile);
         case kCutRows: return locate_tile<kCutRows>(k, k.segs, k.tree, tile);
+        case kPaddedRows: return locate_tile<kPaddedRows>(k, k.segs, k.tree, tile);
         default: return locate_tile<kWholeTiles>(k, k.segs, k.tree, tile);
     }
 }
@@ -232,6 +244,7 @@ HP_HD void align_tile(TileView &v, uint64_t dst_base) {
 // magic would not fit, row_one passes i through.
 inline void set_row_chunks(KParams &k, uint32_t unit) {
     k.row_chunks = (k.row_bytes + unit - 1) / unit;
+    if (k.rows_per_tile == 0 && k.row_bytes % kLineBytes) k.row_chunks = (uint32_t)cut_row_lines(k.row_bytes) * (kLineBytes / unit);
     k.row_one = k.row_chunks == 1 ? ~0u : 0u;
     k.row_magic = k.row_one ? 0u : (uint32_t)((((uint64_t)1 << 32) + k.row_chunks - 1) / k.row_chunks);
 }
@@ -279,6 +292,25 @@ HP_HD ChunkView cut_chunk(const KParams &k, const TileView &t, uint32_t i) {
     if (k.row_bytes >= k.tile_bytes) c.dst = c.src + (t.col + c.src >= k.row_bytes ? gap : 0);
     else c.dst = c.src + row_of_chunk(k, i + t.col / UNIT) * gap;
     return c;
+}
+
+// Chunk i of a tile that was cut by lines of the destination, `dst_line` = the address
+// of the tile's first row there: from the row's start, which the tile's offsets are those
+// of.  A row has room for all the lines that it can touch; a chunk of which no byte is its
+// row's is not there (false), and those at the row's ends are moved to begin and
+// end with it, over bytes of their neighbours.  Rows of at least 16 bytes.  All of a
+// wave's lanes but those at the ends then store to whole 64-byte pieces: stores that begin
+// between them take half as long again (four copies, 283 MB: 42 -> 67 us).
+HP_HD bool padded_chunk(const KParams &k, const TileView &t, uint32_t dst_line, uint32_t i, ChunkView &c) {
+    const uint32_t j = i + t.col / 16u;
+    const uint32_t row = row_of_chunk(k, j);
+    const uint32_t skip = (dst_line + row * t.pitch_rows * k.row_bytes) & (kLineBytes - 1);
+    const int32_t at = (int32_t)((j - row * k.row_chunks) * 16u) - (int32_t)skip, last = (int32_t)k.row_bytes - 16;
+    const uint32_t in_row = (uint32_t)(at < 0 ? 0 : at > last ? last : at);
+    c.src = row * k.row_bytes + in_row;
+    c.dst = (uint64_t)row * t.pitch_rows * k.row_bytes + in_row;
+    c.over = 0;
+    return at > -16 && at < (int32_t)k.row_bytes;
 }
 
 // How many chunks of UNIT bytes a tile has, and how many of them lie in their
@@ -348,7 +380,7 @@ inline KParams kernel_params(const hp_plan &p, int variant, const Seg *segs, con
     set_parts(k);
     if (cut) {
         k.parts_per_row = k.rows_per_tile = 0;
-        set_division(k.row_bytes / kLineBytes, k.part_magic, k.part_shift);
+        set_division((uint32_t)cut_row_lines(p.row_bytes), k.part_magic, k.part_shift);
     }
     set_row_chunks(k, 16u);
     k.block = k.pace = 0;       // set by the launch

@@ -1,4 +1,4 @@
-"""Row-strided segments ([S,B,H] order) of launches that cut them by bytes, across the ends of rows."""
+"""Row-strided segments ([S,B,H] order) of launches that cut them by bytes or by lines, across the ends of rows."""
 import os
 import subprocess
 
@@ -23,7 +23,7 @@ def test_every_chunk_lies_where_its_row_does(tmp_path):
 
 
 @pytest.mark.parametrize("hidden,tile,cut", [(1280, 2048, True), (1280, 4096, True), (1088, 1024, True), (2048, 1024, False), (4096, 8192, False),
-                                             (2000, 1024, False), (3072, 1024, False), (640, 4096, False)])
+                                             (3072, 1024, False), (640, 4096, False)])
 def test_tiles_of_a_launch_that_cuts_its_rows_are_whole(hidden, tile, cut):
     tm = wl.TokenMap(2, 64, hidden, [0, 1], [3, 5], [41, 52])
     p = hp.hp_plan_create_host(wl.Grid(), wl.Grid(row_order=wl.ROW_SBH), tm)
@@ -34,11 +34,13 @@ def test_tiles_of_a_launch_that_cuts_its_rows_are_whole(hidden, tile, cut):
     p.close()
 
 
-# rows of 384 bytes to 4.5 KiB, each in tiles that they fill badly; copies with a kernel of their own and without, two
+# rows of 384 bytes to 6 KiB, each in tiles that they fill badly, whole lines and not; buffers that begin anywhere; copies with a kernel of their own and without, two
 # source copies; the walk through a launch's own arguments and, with many images, through device memory
 @pytest.mark.gpu
 @pytest.mark.parametrize("tp,hidden,f32,images", [(1, 1280, False, 3), (2, 192, False, 60), (3, 1088, False, 3), (4, 2304, False, 60), (5, 640, False, 3),
-                                                  (8, 192, True, 3), (8, 1088, False, 60), (16, 320, True, 3)])
+                                                  (8, 192, True, 3), (8, 1088, False, 60), (16, 320, True, 3),
+                                                  (1, 1025, False, 60), (2, 1544, False, 3), (3, 2305, False, 3), (4, 1027, True, 60), (6, 1100, False, 3),
+                                                  (8, 3001, False, 3), (12, 515, True, 3)])
 def test_cut_launches(tp, hidden, f32, images):
     import torch
     from oracle import oracle
@@ -66,13 +68,17 @@ def test_cut_launches(tp, hidden, f32, images):
     prob.backward_accumulate([bits(t) for t in g], want_a)
     for j, z in enumerate(want_z):
         z.reshape(drows, hidden)[prob.forward_map(j)[0] >= 0] = 0
-    x, d, g, y, a = ([t.cuda() for t in ts] for ts in (x, d, g, y, a))
+    def device(t, first):
+        big = torch.empty(t.numel() + first, dtype=t.dtype, device="cuda")
+        return big[first:].view(t.shape).copy_(t)
+
+    x, d, g, y, a = ([device(t, 5 * (i + 2) % 64) for i, t in enumerate(ts)] for ts in (x, d, g, y, a))
     for shape in ({}, dict(tile_bytes=1024, block_threads=64), dict(tile_bytes=2048, block_threads=64), dict(tile_bytes=4096, block_threads=256),
                   dict(tile_bytes=8192, block_threads=128)):
         for direction in range(3):
             plan.set_launch(direction, **shape)
         host.set_launch(0, **shape)
-        out = [[t.clone() for t in ts] for ts in (d, d, d, y, a)]
+        out = [[device(t, 3 * i % 64) for i, t in enumerate(ts)] for ts in (d, d, d, y, a)]
         hp.hp_forward(plan, x, out[0])
         hp.hp_forward_static(host, x, out[1])
         hp.hp_zero_image_rows(plan, out[2])
