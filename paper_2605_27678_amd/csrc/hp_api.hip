@@ -99,7 +99,7 @@ enum Tiles {
     kRagged,    // dense on both sides, rows of any length
     kStrided,   // groups of whole row-strided rows ([S,B,H] order with several samples per rank, rows shorter than a tile)
     kCut,       // row-strided rows of whole lines, cut by bytes of the source across their ends (hp::cuts_launch)
-    kPadded,    // row-strided rows of any length from 2 KiB on, cut by lines of the destination
+    kPadded,    // row-strided rows of any length from 256 bytes on, cut by lines of the destination (hp::cuts_launch)
 };
 // Whether a tile has no chunk but whole ones.
 template <Tiles TILES> constexpr bool kAllWhole = TILES == kLines || TILES == kCut || TILES == kPadded;
@@ -177,7 +177,7 @@ __device__ __forceinline__ hp::ChunkView chunk(const KParams &k, const TileView 
     there = true;
     if constexpr (TILES == kPadded) {
         hp::ChunkView c;
-        there = hp::padded_chunk(k, t, (uint32_t)(buffers()[k.dst_base + t.dst_buf0] + t.dst_off), i, c);
+        there = hp::padded_chunk<UNIT>(k, t, (uint32_t)(buffers()[k.dst_base + t.dst_buf0] + t.dst_off), i, c);
         return c;
     } else if constexpr (TILES == kCut) return hp::cut_chunk<UNIT>(k, t, i);
     else return hp::chunk_at<UNIT, TILES != kStrided, END && TILES == kRagged>(k, t, i);
@@ -593,13 +593,14 @@ __device__ __forceinline__ void backward_group(const KParams &k, const TileView 
                 Out::unpack(old[u], x);
 #pragma unroll
                 for (int e = 0; e < E; ++e) x[e] = x[e] + acc[u][e];
-                if (GUARD && i[u] >= n) continue;
-                if (ELEMENT || TILES == kLines || TILES == kCut || (TILES == kRagged && !GUARD) || c[u].over == 0) {
+                if (!there[u] || (GUARD && i[u] >= n)) continue;
+                const bool all = TILES != kPadded || c[u].end == In::kBytes;
+                if (ELEMENT || TILES == kLines || TILES == kCut || (TILES == kRagged && !GUARD) || (c[u].over == 0 && all)) {
                     st<Out::kBytes, NTS>(out + c[u].src * kWiden, Out::pack(x));
                 } else {
 #pragma unroll
                     for (int e = 0; e < E; ++e)
-                        if (e * kElemBytes >= c[u].over)
+                        if (e * kElemBytes >= c[u].over && (all || e * kElemBytes < c[u].end))
                             st<4, NTS>(out + c[u].src * kWiden + e * 4, __float_as_uint(x[e]));
                 }
             }
@@ -887,10 +888,10 @@ void launch_backward_nrep(int copies, const LaunchCfg &c, const Args &a) {
 template <Tiles TILES, bool NTL, bool NTS>
 void launch_backward(int dtype, bool acc, int copies, const LaunchCfg &c, const Args &a) {
     if (dtype == HP_F32) {
-        if (acc) { if constexpr (TILES != kPadded) launch_backward_nrep<HP_F32, true, TILES, NTL, NTS>(copies, c, a); }
+        if (acc) launch_backward_nrep<HP_F32, true, TILES, NTL, NTS>(copies, c, a);
         else launch_backward_nrep<HP_F32, false, TILES, NTL, NTS>(copies, c, a);
     } else {
-        if (acc) { if constexpr (TILES != kPadded) launch_backward_nrep<HP_BF16, true, TILES, NTL, NTS>(copies, c, a); }
+        if (acc) launch_backward_nrep<HP_BF16, true, TILES, NTL, NTS>(copies, c, a);
         else launch_backward_nrep<HP_BF16, false, TILES, NTL, NTS>(copies, c, a);
     }
 }
@@ -902,7 +903,7 @@ template <Tiles TILES, bool NTL, bool NTS>
 void launch_nt(const hp_plan *p, Direction dir, const LaunchCfg &c, const Args &a) {
     if (dir == kZeroRows) HP_LAUNCH((hp_zero_rows_kernel<TILES, NTS>), c, a);
     else if (dir == kForward) launch_forward<TILES, NTL, NTS>(p->dst_copies, c, a);
-    else launch_backward<TILES, NTL, NTS>(p->dtype, dir == kBackwardAcc, p->dst_copies, c, a);   // (padded rows do not accumulate)
+    else launch_backward<TILES, NTL, NTS>(p->dtype, dir == kBackwardAcc, p->dst_copies, c, a);
 }
 
 template <Tiles TILES>

@@ -45,8 +45,6 @@ uint64_t tiles_of(uint64_t n_rows, uint64_t pitch_rows, int64_t row_bytes, uint3
     return (n_rows + rows_per - 1) / rows_per;
 }
 
-int64_t cut_row_lines(int64_t row_bytes) { return row_bytes % 128 ? row_bytes / 128 + 2 : row_bytes / 128; }
-
 bool cut_by_bytes(const hp_plan &p, uint32_t tile) {
     if (p.dst_stride == 1 || p.row_bytes > kMaxCutRow) return false;
     if (p.row_bytes % 128 ? p.row_bytes < kMinPaddedRow : p.row_bytes % tile == 0 || tile % p.row_bytes == 0) return false;
@@ -320,9 +318,11 @@ double row_share(int64_t row, int64_t tile) {
     return row >= tile ? (double)row / (double)((row + tile - 1) / tile * tile) : (double)(tile / row * row) / (double)tile;
 }
 // Whether rows that are not whole lines fill tiles of lines enough better: see cuts_launch.
-bool padding_pays(const hp_plan &p, uint32_t tile) {
+// Groups of shorter rows store between 64-byte pieces, padded ones do not, and may fill less.
+bool padding_pays(const hp_plan &p, uint32_t tile, int direction) {
+    const double more = p.row_bytes >= tile ? 0.03 : direction == 0 ? -0.25 : -0.12;
     return p.row_bytes % 128 && cut_by_bytes(p, tile) &&
-           (double)p.row_bytes / (double)(128 * cut_row_lines(p.row_bytes)) >= row_share(p.row_bytes, tile) + 0.03;
+           (double)p.row_bytes / (double)(128 * cut_row_lines(p.row_bytes)) >= row_share(p.row_bytes, tile) + more;
 }
 // Row-strided rows that launches in small tiles can cut by bytes; those of 2 KiB and more want what dense launches want.
 bool cut_rows(const hp_plan &p) { return p.row_bytes % 128 == 0 && (cut_by_bytes(p, 1024) || cut_by_bytes(p, 2048)); }
@@ -360,7 +360,7 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
     const bool whole = dense || p->row_bytes >= 4096;        // tiles of 1 KiB are nearly all whole
     // A row-strided row is cut into tiles from its start: whether it fills what it is cut into, and that in whole lanes.
     const int64_t row = p->row_bytes;
-    const bool full = dense || cut_rows(*p) || padding_pays(*p, 1024);                 // tiles are whole where the launch wants them to be
+    const bool full = dense || cut_rows(*p) || (row >= 2048 && padding_pays(*p, 1024, 0));                 // tiles are whole where the launch wants them to be
     auto fills = [&](int64_t tile) { return dense || 20 * row >= 17 * ((row + tile - 1) / tile * tile); };
     const bool filled = fills(1024) && (dense || row % 16 == 0), even = even_tiles(*p);
     const size_t segs = p->segments.size();
@@ -592,28 +592,28 @@ int pace_rounds(const hp_plan &p, int direction, const Launch &L) {
 //                copies in rows of 2176 bytes, 1.2 GB 327 -> 213 us); more: 0.95-1.0 to 400 MB, 1.0-1.1
 //   backward     rows of 1 KiB and more 0.98-1.4; shorter ones 0.96-1.05; share over 0.82, 150 MB 0.96-1.0
 //   accumulating 0.98-1.4
-// Rows that are not whole lines, against tiles that each row cuts for itself at lines (4 to 21 KB
-// a row, 1 to 16 copies, 30 MB to 1.5 GB), where lines for all that a row can touch fill 3 % more of a tile
-// or more:
-//   forward      1.0-1.75 (rows of 4610 bytes to two copies, 0.7 GB 1.61; 2320 bytes to four, 1.5 GB 1.44)
-//   backward     0.97-1.55 (5400 bytes, one copy, 0.7 GB 1.28)
-// For less than those 3 % it is 0.8-1.05; accumulating, where a byte may be added to once only, rows are cut one by one.
+// Rows that are not whole lines, in as many lines as they can touch, against tiles that each row cuts
+// for itself at lines, or groups of whole rows (0.4 to 21 KB a row, 1 to 16 copies, 30 MB to 1.5 GB), where
+// they pay (padding_pays):
+//   forward      1.0-1.75 (rows of 4610 bytes to two copies, 0.7 GB 1.61; 2320 bytes to four, 1.5 GB 1.46)
+//   backward     0.97-1.7 (1390 bytes from eight copies, 0.5 GB 1.45)
+//   accumulating 0.97-1.45
+// Rows of a tile and more that fill tiles as well without: 0.8-1.05; groups of rows backward that fill a
+// tile to 12 % more: 0.92-1.02, forward to 25 % more still 1.0-1.2.
 // The lines that are left out forward lost 3 to 10 %: launches in which partly empty
 // tiles happen to leave as much on its way as suits them; backward from one copy 0.91-1.07.
 bool cuts_launch(const hp_plan &p, int direction, int variant) {
     if (!p.cut_tiles[variant]) return false;
     const int64_t row = p.row_bytes, tile = tile_bytes_of(variant), c = p.dst_copies;
     const double share = row_share(row, tile);
+    const double bytes = direction == 1 ? (double)p.bwd_bytes : direction == 2 ? (double)p.bwd_accum_bytes
+                                                                              : (1.0 + (double)c) * (double)p.n_rows * (double)row;
     if (row % 128) {
-        if (direction == 2 || !padding_pays(p, (uint32_t)tile)) return false;
+        if (!padding_pays(p, (uint32_t)tile, direction) || (row < 2048 && bytes < 1e6)) return false;      // (a few tiles: no matter)
         if (direction == 1) return c != 1 || tile != 2048 || share < 0.75;
-        return c != 8 || tile != 2048 || (1.0 + (double)c) * (double)p.n_rows * (double)row < 1000e6;
+        return direction == 2 || c != 8 || tile != 2048 || bytes < 1000e6;
     }
-    if (direction == 1) {
-        const double bytes = (double)p.bwd_bytes;
-        return row >= 1024 && (bytes < 400e6 ? share < 0.82 : share < 0.87 || like_dense(p));
-    }
-    const double bytes = direction == 2 ? (double)p.bwd_accum_bytes : (1.0 + (double)c) * (double)p.n_rows * (double)row;
+    if (direction == 1) return row >= 1024 && (bytes < 400e6 ? share < 0.82 : share < 0.87 || like_dense(p));
     if (share >= 0.87 && bytes < 400e6) return false;
     if (direction == 2) return true;
     if ((c == 3 || c == 4) && row >= 1024 && row < 2048 && bytes < 450e6) return false;

@@ -145,8 +145,8 @@ int pace_rounds(const hp_plan &p, int direction, const Launch &L);
 // one, at lines of the destination.)
 constexpr int64_t kMaxCutRow = 128 << 10;      // row_of_chunk is exact
 // Other rows: by lines of the destination, of which each row gets as many as it can touch.
-constexpr int64_t kMinPaddedRow = 2048;
-int64_t cut_row_lines(int64_t row_bytes);
+constexpr int64_t kMinPaddedRow = 256;
+inline int64_t cut_row_lines(int64_t row_bytes) { return row_bytes % 128 ? row_bytes / 128 + 2 : row_bytes / 128; }
 constexpr int kCutVariants = 4;                // tiles of up to 8 KiB, which launches start from
 bool cut_by_bytes(const hp_plan &p, uint32_t tile);
 

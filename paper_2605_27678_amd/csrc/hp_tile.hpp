@@ -181,12 +181,12 @@ HP_HD TileView locate_tile(const KParams &k, const HP_TABLE Seg *segs, const HP_
         v.left = left;
         v.row = row;
     } else if (KINDS == kPaddedRows) {
-        const uint32_t lines = t * (k.tile_bytes / kLineBytes);
+        const uint32_t row_lines = k.row_bytes / kLineBytes + 2, lines = t * (k.tile_bytes / kLineBytes);
         const uint32_t row0 = divide(lines, k.part_magic, k.part_shift);
-        v.col = (lines - row0 * (k.row_chunks >> 3)) * kLineBytes;
+        v.col = (lines - row0 * row_lines) * kLineBytes;
         v.src_off = s.src_off + (uint64_t)row0 * k.row_bytes;
         v.dst_off = s.dst_off + (uint64_t)row0 * s.pitch_rows * k.row_bytes;
-        v.left = ((uint64_t)s.n_rows * (k.row_chunks >> 3) - lines) * kLineBytes;
+        v.left = ((uint64_t)s.n_rows * row_lines - lines) * kLineBytes;
         v.nbytes = clip(v.left, k.tile_bytes);
         v.row = row0;
     } else if (KINDS == kCutRows) {
@@ -256,6 +256,7 @@ inline void set_row_chunks(KParams &k, uint32_t unit) {
 struct ChunkView {
     uint64_t dst;
     uint32_t src, over;
+    uint32_t end;       // padded rows: bytes before those that the next chunk covers too, else not set
 };
 // The row of chunk i of a row-strided tile of whole rows.
 HP_HD uint32_t row_of_chunk(const KParams &k, uint32_t i) {
@@ -301,16 +302,18 @@ HP_HD ChunkView cut_chunk(const KParams &k, const TileView &t, uint32_t i) {
 // end with it, over bytes of their neighbours.  Rows of at least 16 bytes.  All of a
 // wave's lanes but those at the ends then store to whole 64-byte pieces: stores that begin
 // between them take half as long again (four copies, 283 MB: 42 -> 67 us).
+template <uint32_t UNIT>
 HP_HD bool padded_chunk(const KParams &k, const TileView &t, uint32_t dst_line, uint32_t i, ChunkView &c) {
-    const uint32_t j = i + t.col / 16u;
+    const uint32_t j = i + t.col / UNIT;
     const uint32_t row = row_of_chunk(k, j);
     const uint32_t skip = (dst_line + row * t.pitch_rows * k.row_bytes) & (kLineBytes - 1);
-    const int32_t at = (int32_t)((j - row * k.row_chunks) * 16u) - (int32_t)skip, last = (int32_t)k.row_bytes - 16;
+    const int32_t at = (int32_t)((j - row * k.row_chunks) * UNIT) - (int32_t)skip, last = (int32_t)k.row_bytes - (int32_t)UNIT;
     const uint32_t in_row = (uint32_t)(at < 0 ? 0 : at > last ? last : at);
     c.src = row * k.row_bytes + in_row;
     c.dst = (uint64_t)row * t.pitch_rows * k.row_bytes + in_row;
-    c.over = 0;
-    return at > -16 && at < (int32_t)k.row_bytes;
+    c.over = at > last ? (uint32_t)(at - last) : 0u;
+    c.end = at < 0 ? UNIT - (uint32_t)-at : UNIT;
+    return at > -(int32_t)UNIT && at < (int32_t)k.row_bytes;
 }
 
 // How many chunks of UNIT bytes a tile has, and how many of them lie in their

@@ -40,14 +40,14 @@ def test_tiles_of_a_launch_that_cuts_its_rows_are_whole(hidden, tile, cut):
 @pytest.mark.parametrize("tp,hidden,f32,images", [(1, 1280, False, 3), (2, 192, False, 60), (3, 1088, False, 3), (4, 2304, False, 60), (5, 640, False, 3),
                                                   (8, 192, True, 3), (8, 1088, False, 60), (16, 320, True, 3),
                                                   (1, 1025, False, 60), (2, 1544, False, 3), (3, 2305, False, 3), (4, 1027, True, 60), (6, 1100, False, 3),
-                                                  (8, 3001, False, 3), (12, 515, True, 3)])
+                                                  (8, 3001, False, 3), (12, 515, True, 3), (1, 695, False, 300), (3, 301, False, 300), (8, 195, True, 300)])
 def test_cut_launches(tp, hidden, f32, images):
     import torch
     from oracle import oracle
     rng = np.random.default_rng(100 * tp + hidden)
     src, dst = wl.Grid(tp=2, dp=2), wl.Grid(tp=tp, cp=2, row_order=wl.ROW_SBH)
     lens = [[1, 40, 17], [30, 29], [77]] if images == 3 else [list(rng.integers(1, 4, images)) for _ in range(3)]
-    tm = wl.token_map_from_lens(rng, 3, 80 if images == 3 else 400, hidden, lens)
+    tm = wl.token_map_from_lens(rng, 3, 80 if images == 3 else 400 if images == 60 else 1500, hidden, lens)     # 300: more than 1 MB
     tm.dtype = wl.DT_F32 if f32 else wl.DT_BF16
     plan, host, prob = hp.hp_plan_create(src, dst, tm), hp.hp_plan_create_host(src, dst, tm), oracle.Problem(src, dst, tm)
     rows, drows = prob.src_rows(), prob.dst_rows()

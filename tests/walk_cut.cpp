@@ -45,8 +45,11 @@ static int walk(const hp_plan &p, const uint32_t *tree, long *tiles) {
 
 // Rows that are not whole lines: chunks that are there cover every byte of every row, and none of another; they lie on
 // 16-byte pieces of the destination but where they were moved to an end of their row.
+// What counts of each, between over and end, is every byte once.
+template <uint32_t UNIT>
 static int walk_padded(const hp_plan &p, const uint32_t *tree, uint64_t dst_base, long *tiles) {
-    const hp::KParams k = hp::kernel_params(p, v, p.dsegs.data(), tree, true);
+    hp::KParams k = hp::kernel_params(p, v, p.dsegs.data(), tree, true);
+    hp::set_row_chunks(k, UNIT);
     CHECK(hp::seg_kinds(k, (uint64_t)p.dst_stride) == hp::kPaddedRows);
     std::vector<std::vector<uint8_t>> seen(p.dsegs.size());
     for (size_t i = 0; i < seen.size(); ++i) seen[i].assign((size_t)p.dsegs[i].n_rows * k.row_bytes, 0);
@@ -61,15 +64,16 @@ static int walk_padded(const hp_plan &p, const uint32_t *tree, uint64_t dst_base
         CHECK(t.src_off == s.src_off + row0 * k.row_bytes && t.dst_off == s.dst_off + row0 * s.pitch_rows * k.row_bytes);
         CHECK(t.src_buf == s.src_buf && t.dst_buf0 == s.dst_buf0 && t.col == (done - row0 * lines) * 128);
         CHECK(t.nbytes == std::min<uint64_t>(k.tile_bytes, (s.n_rows * lines - done) * 128));
-        for (uint32_t i = 0; i < t.nbytes / 16; ++i) {
+        for (uint32_t i = 0; i < t.nbytes / UNIT; ++i) {
             hp::ChunkView c;
-            const bool there = hp::padded_chunk(k, t, (uint32_t)(dst_base + t.dst_off), i, c);
+            const bool there = hp::padded_chunk<UNIT>(k, t, (uint32_t)(dst_base + t.dst_off), i, c);
             const uint64_t at = row0 * k.row_bytes + c.src, row = at / k.row_bytes, in_row = at % k.row_bytes;
-            CHECK(row < s.n_rows && in_row + 16 <= k.row_bytes);        // whether there or not: it is read
+            CHECK(row < s.n_rows && in_row + UNIT <= k.row_bytes);      // whether there or not: it is read
             CHECK(t.dst_off + c.dst == s.dst_off + row * s.pitch_rows * k.row_bytes + in_row);
             if (!there) continue;
-            CHECK((dst_base + t.dst_off + c.dst) % 16 == 0 || in_row == 0 || in_row + 16 == k.row_bytes);
-            for (uint32_t b = 0; b < 16; ++b) seen[seg][at + b] = 1;
+            CHECK((dst_base + t.dst_off + c.dst) % UNIT == 0 || in_row == 0 || in_row + UNIT == k.row_bytes);
+            CHECK(c.over < c.end && c.end <= UNIT && c.over % p.elem_bytes == 0 && c.end % p.elem_bytes == 0);
+            for (uint32_t b = c.over; b < c.end; ++b) CHECK(!seen[seg][at + b]++);
         }
         done += t.nbytes / 128;
     }
@@ -88,7 +92,7 @@ int main(int argc, char **argv) {
     for (it = 0; done < plans && it < 100 * plans; ++it) {
         const hp_layout_t src{R(1, 2), 1, R(1, 3), 1, 0, 0, 0, 0};
         const hp_layout_t dst{R(1, 9), R(1, 2), 1, 1, 0, R(0, 1), R(0, 1), HP_ROW_SBH};
-        const int hiddens[] = {64, 192, 320, 448, 640, 1088, 1280, 2304, 65344}, ragged[] = {1025, 1030, 1048, 1544, 2305, 65535};
+        const int hiddens[] = {64, 192, 320, 448, 640, 1088, 1280, 2304, 65344}, ragged[] = {1025, 130, 695, 1544, 2305, 65535};
         const int batch = R(2, 5), seq = 2 * dst.cp * dst.tp * R(1, 12), f32 = R(0, 1);
         std::vector<int32_t> smp, st, ln;
         for (int b = 0; b < batch; ++b)
@@ -112,7 +116,7 @@ int main(int argc, char **argv) {
                 CHECK((p.cut_tiles[v] > 0) == (v < hp::kCutVariants));
                 const uint64_t e = (uint64_t)p.elem_bytes, bases[] = {0, e, 64, 126 / e * e};
                 if (p.cut_tiles[v])
-                    if (walk_padded(p, tree, bases[it % 4], &tiles)) return 1;
+                    if (walk_padded<16>(p, tree, bases[it % 4], &tiles) || (!f32 && walk_padded<8>(p, tree, bases[it % 4], &tiles))) return 1;
                 continue;
             }
             CHECK((p.cut_tiles[v] > 0) == (v < hp::kCutVariants && p.row_bytes % bytes != 0 && bytes % p.row_bytes != 0));
