@@ -332,11 +332,12 @@ int hp_backward_accumulate(const hp_plan_t *plan, const void *const *dst_grad_bu
  * device block that hp_plan_create allocated; this call instead takes ANY plan
  * (normally a host-only one from hp_plan_create_host or the host_only variants,
  * whose creation makes no HIP call) and launches the same kernel.  Small plans
- * carry their tables in the launch's arguments anyway (see hp_plan_create); of a
- * larger one this call writes what the launch needs - the segment descriptors and
- * the search tree of the plan's forward tile size - into a fixed array that the
+ * carry their tables in the launch's arguments anyway (see hp_plan_create), larger
+ * ones take several launches of a part of the segments each.  Where those would be
+ * too many (plans of hundreds of buffers) this call writes what the launch needs - the segment
+ * descriptors and the search tree of the plan's forward tile size - into a fixed array that the
  * library holds in each GPU's memory from load to process end
- * (HP_STATIC_MAX_TABLE_BYTES, 64 KiB: about 1700 segments).  The table bytes then
+ * (HP_STATIC_MAX_TABLE_BYTES, 64 KiB: about 1700 segments, which no plan may exceed).  The table bytes then
  * travel as arguments of small copy kernels on `stream` ahead of the transform
  * kernel, so no host buffer has to outlive the call.  It calls no hipMalloc / hipFree / hipMemcpy
  * and no other allocating routine.  The first call on a device looks up the
