@@ -601,7 +601,8 @@ int pace_rounds(const hp_plan &p, int direction, const Launch &L) {
 // Rows of a tile and more that fill tiles as well without: 0.8-1.05; groups of rows backward that fill a
 // tile to 12 % more: 0.92-1.02, forward to 25 % more still 1.0-1.2.
 // The lines that are left out forward lost 3 to 10 %: launches in which partly empty
-// tiles happen to leave as much on its way as suits them; backward from one copy 0.91-1.07.
+// tiles happen to leave as much on its way as suits them; backward from one copy, rows that
+// are not whole chunks and fill three quarters of 2 KiB tiles, 0.91-1.07.
 bool cuts_launch(const hp_plan &p, int direction, int variant) {
     if (!p.cut_tiles[variant]) return false;
     const int64_t row = p.row_bytes, tile = tile_bytes_of(variant), c = p.dst_copies;
@@ -610,7 +611,7 @@ bool cuts_launch(const hp_plan &p, int direction, int variant) {
                                                                               : (1.0 + (double)c) * (double)p.n_rows * (double)row;
     if (row % 128) {
         if (!padding_pays(p, (uint32_t)tile, direction) || (row < 2048 && bytes < 1e6)) return false;      // (a few tiles: no matter)
-        if (direction == 1) return c != 1 || tile != 2048 || share < 0.75;
+        if (direction == 1) return c != 1 || tile != 2048 || share < 0.75 || row % 16 == 0;
         return direction == 2 || c != 8 || tile != 2048 || bytes < 1000e6;
     }
     if (direction == 1) return row >= 1024 && (bytes < 400e6 ? share < 0.82 : share < 0.87 || like_dense(p));

@@ -36,8 +36,8 @@ struct KParams {
     uint32_t row_chunks;        // row-strided tiles of whole rows: lane chunks of one row (see set_row_chunks)
     uint32_t row_magic, row_one;
     uint32_t pace;              // rounds of pace() before a tile's loads (kernels that have it)
-    uint32_t band_samples, band_magic, band_shift;     // text gradients in bands (band_runs): samples of a position, and their division as above
     uint32_t level_off[kMaxTreeLevels];   // start of each level, in keys; level 0 = leaves
+    uint32_t band_samples, band_magic, band_shift;     // text gradients in bands (band_runs): samples of a position, and their division as above
 };
 
 // One workgroup's share of the launch.
