@@ -25,11 +25,17 @@ import torch
 from .binding import Plan
 
 
+def _current_stream() -> int:
+    """The handle of torch's current stream.  torch.cuda.current_stream() makes an object around it first, 2.7 us of a
+    pass that is bound by the host (123 MB in 16 buffers: 112 us)."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+
+
 class _BoundaryTransform(torch.autograd.Function):
     @staticmethod
     def forward(ctx, plan: Plan, n_src: int, *bufs):
         src, dst = list(bufs[:n_src]), list(bufs[n_src:])
-        stream = torch.cuda.current_stream()
+        stream = _current_stream()
         plan.forward([t.detach() if t is not None else None for t in src], [t.detach() for t in dst], stream)
         ctx.plan, ctx.n_src = plan, n_src
         ctx.src_meta = [(tuple(t.shape), t.dtype, t.device) for t in src]
@@ -50,7 +56,7 @@ class _BoundaryTransform(torch.autograd.Function):
 
 def _grads(plan: Plan, src_meta, want, grad_dst) -> tuple:
     """The source gradients and the text gradients, each if they are wanted, in one tuple."""
-    stream = torch.cuda.current_stream()
+    stream = _current_stream()
     grads = [g.contiguous() for g in grad_dst]
     src_grads: List[torch.Tensor] = []
     if want[0]:
