@@ -605,6 +605,7 @@ int pace_rounds(const hp_plan &p, int direction, const Launch &L) {
 // are not whole chunks and fill three quarters of 2 KiB tiles, 0.91-1.07.
 bool cuts_launch(const hp_plan &p, int direction, int variant) {
     if (!p.cut_tiles[variant]) return false;
+    if (p.cut_tiles[variant] > p.n_tiles(variant) && p.cut_tiles[variant] >= 1u << 22) return false;   // keep_grid counted the others
     const int64_t row = p.row_bytes, tile = tile_bytes_of(variant), c = p.dst_copies;
     const double share = row_share(row, tile);
     const double bytes = direction == 1 ? (double)p.bwd_bytes : direction == 2 ? (double)p.bwd_accum_bytes

@@ -34,6 +34,14 @@ def test_tiles_of_a_launch_that_cuts_its_rows_are_whole(hidden, tile, cut):
     p.close()
 
 
+def test_grids_of_the_largest_padded_launches_stay_below_2_to_the_32_work_items():
+    hidden, rows = 200, (62 << 30) // 400                   # two rows of 400 bytes in a tile, or five lines for each
+    tm = wl.TokenMap(2, rows // 2, hidden, [0, 1], [0, 0], [rows // 2] * 2)
+    p = hp.hp_plan_create_host(wl.Grid(), wl.Grid(row_order=wl.ROW_SBH), tm)
+    assert p.info.n_tiles * p.get_launch(0)["block_threads"] < 2 ** 32
+    p.close()
+
+
 # rows of 384 bytes to 6 KiB, each in tiles that they fill badly, whole lines and not; buffers that begin anywhere; copies with a kernel of their own and without, two
 # source copies; the walk through a launch's own arguments and, with many images, through device memory
 @pytest.mark.gpu
