@@ -152,15 +152,19 @@ __device__ __forceinline__ void pace(uint32_t n) {
                      : "+s"(x), "+s"(y) : : "scc");
 }
 
-// The tile of this workgroup.  Ragged: its ends on lines of the first destination copy.
-template <Tiles TILES, bool BANDS = false>
+// The tile of this workgroup.  Ragged: its ends on lines of the first destination copy, or of the source.
+template <Tiles TILES, bool BANDS = false, bool MAY_ALIGN_SRC = false>
 __device__ __forceinline__ TileView my_tile(const Args &a) {
     const uintptr_t args = args_base();
     const uintptr_t segs = a.k.seg_at ? args + a.k.seg_at : (uintptr_t)a.k.segs;
     const uintptr_t tree = a.k.seg_at ? args + a.k.tree_at : (uintptr_t)a.k.tree;
     TileView t = hp::locate_tile<TILES == kStrided ? hp::kRowGroups : TILES == kCut ? hp::kCutRows : TILES == kPadded ? hp::kPaddedRows : hp::kWholeTiles, BANDS>(
         a.k, (const HP_TABLE hp::Seg *)segs, (const HP_TABLE uint32_t *)tree, blockIdx.x);
-    if (TILES == kRagged) hp::align_tile(t, buffers()[a.k.dst_base + t.dst_buf0]);
+    if (TILES == kRagged) {
+        const bool src = MAY_ALIGN_SRC && a.k.align_src;
+        const uint64_t base = buffers()[src ? t.src_buf : a.k.dst_base + t.dst_buf0];
+        hp::align_tile(t, src ? base + t.src_off - t.dst_off : base);
+    }
     return t;
 }
 
@@ -640,7 +644,7 @@ template <int DT, bool ACC, int NREP, Tiles TILES, bool NTL, bool NTS>
 __global__ void __launch_bounds__(1024)
 hp_backward_kernel(const Args a) {
     const uint32_t touch = touch_args();
-    const TileView t = my_tile<TILES>(a);
+    const TileView t = my_tile<TILES, false, !ACC>(a);
     backward_tile<DT, ACC, NREP, TILES, NTL, NTS>(a.k, t, NREP > 0 ? (uint32_t)NREP : a.k.dst_copies);
     touched(touch);
 }
@@ -1000,6 +1004,7 @@ int enqueue_params(const hp_plan *p, Direction dir, const hp::Launch &L, const B
     if (dir == kBackwardAcc) hp::set_row_chunks(a.k, 4u * (uint32_t)p->elem_bytes);
     a.k.block = (uint32_t)L.block;
     a.k.pace = (uint32_t)hp::pace_rounds(*p, (int)dir, L);
+    a.k.align_src = dir == kBackward && hp::aligns_source(*p);
     const KParams &k = a.k;
     uint32_t tiles = k.rows_per_tile == 0 ? p->cut_tiles[L.tile_variant] : p->n_tiles(L.tile_variant);
     if (!k.segs) tiles = put_tables(p, some.n ? some : SegRange{0, p->dsegs.size()}, tiles, a);

@@ -585,6 +585,17 @@ int pace_rounds(const hp_plan &p, int direction, const Launch &L) {
     return c == 2 ? two[level] : c == 3 && bytes >= 450e6 ? three[level] : c == 4 ? four[level] : c == 6 && bytes >= 800e6 ? six[level] : 0;
 }
 
+// Where rows are not whole lines, a tile's ends lie on lines of one side only, and on the
+// other two tiles share the lines at their ends.  Stores lose more by that than loads: backward, tiles on lines of
+// the source that is written instead of the copies that are read (rows of 2008 to 16816 bytes, 0.1 to 2 GB,
+// the same buffers in turn) one copy 1.02-1.09 (two 0.99, four 0.93-0.95); to two source copies from one 1.08-1.28,
+// from two 1.04-1.14, from three 1.02-1.13, from four 1.00-1.06; to three and four from twice as many 1.02-1.07;
+// from four and more in 40 MB 0.94-1.0.  Accumulating, where the source is read as well: 0.98.
+bool aligns_source(const hp_plan &p) {
+    if (p.dst_copies >= 4 && p.bwd_bytes < 100000000) return false;
+    return p.src_copies == 1 ? p.dst_copies == 1 : p.dst_copies <= 2 * p.src_copies;
+}
+
 // Against a tile for a row's rest, or for the whole rows that fit, by the share of a
 // tile that those fill; the same buffers in turn, two and four samples a position,
 // rows of 384 to 12416 bytes, 1 to 16 copies, 40 MB to 2 GB, the direction's gain:

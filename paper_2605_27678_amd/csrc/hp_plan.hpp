@@ -154,6 +154,9 @@ bool cut_by_bytes(const hp_plan &p, uint32_t tile);
 // is cut by bytes, if its tiles can be.
 bool cuts_launch(const hp_plan &p, int direction, int variant);
 
+// Whether hp_backward's tiles of ragged rows end on lines of the source: see there.
+bool aligns_source(const hp_plan &p);
+
 // Tiles of `tile` bytes that a run of n_rows rows is cut into.
 uint64_t tiles_of(uint64_t n_rows, uint64_t pitch_rows, int64_t row_bytes, uint32_t tile);
 
