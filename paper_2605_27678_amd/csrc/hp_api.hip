@@ -97,14 +97,16 @@ __device__ __forceinline__ void st(gchar *p, typename Bytes<N>::type v) {
 enum Tiles {
     kLines,     // dense on both sides, and every row is whole 128-byte lines
     kRagged,    // dense on both sides, rows of any length
+    kRaggedSrc, // the same, tiles on lines of the source instead of the destination (hp::aligns_source)
     kStrided,   // groups of whole row-strided rows ([S,B,H] order with several samples per rank, rows shorter than a tile)
     kCut,       // row-strided rows of whole lines, cut by bytes of the source across their ends (hp::cuts_launch)
     kPadded,    // row-strided rows of any length from 256 bytes on, cut by lines of the destination (hp::cuts_launch)
 };
 // Whether a tile has no chunk but whole ones.
 template <Tiles TILES> constexpr bool kAllWhole = TILES == kLines || TILES == kCut || TILES == kPadded;
+template <Tiles TILES> constexpr bool kRaggedRows = TILES == kRagged || TILES == kRaggedSrc;
 // Whether a tile lies on the destination side as it does on the source's.
-template <Tiles TILES> constexpr bool kDense = TILES == kLines || TILES == kRagged;
+template <Tiles TILES> constexpr bool kDense = TILES == kLines || kRaggedRows<TILES>;
 
 // Workgroups are handed to the chip's 8 accelerator dies (XCDs, each with its
 // own L2) round-robin by workgroup id.
@@ -153,18 +155,15 @@ __device__ __forceinline__ void pace(uint32_t n) {
 }
 
 // The tile of this workgroup.  Ragged: its ends on lines of the first destination copy, or of the source.
-template <Tiles TILES, bool BANDS = false, bool MAY_ALIGN_SRC = false>
+template <Tiles TILES, bool BANDS = false>
 __device__ __forceinline__ TileView my_tile(const Args &a) {
     const uintptr_t args = args_base();
     const uintptr_t segs = a.k.seg_at ? args + a.k.seg_at : (uintptr_t)a.k.segs;
     const uintptr_t tree = a.k.seg_at ? args + a.k.tree_at : (uintptr_t)a.k.tree;
     TileView t = hp::locate_tile<TILES == kStrided ? hp::kRowGroups : TILES == kCut ? hp::kCutRows : TILES == kPadded ? hp::kPaddedRows : hp::kWholeTiles, BANDS>(
         a.k, (const HP_TABLE hp::Seg *)segs, (const HP_TABLE uint32_t *)tree, blockIdx.x);
-    if (TILES == kRagged) {
-        const bool src = MAY_ALIGN_SRC && a.k.align_src;
-        const uint64_t base = buffers()[src ? t.src_buf : a.k.dst_base + t.dst_buf0];
-        hp::align_tile(t, src ? base + t.src_off - t.dst_off : base);
-    }
+    if (TILES == kRagged) hp::align_tile(t, buffers()[a.k.dst_base + t.dst_buf0]);
+    if (TILES == kRaggedSrc) hp::align_tile(t, buffers()[t.src_buf] + t.src_off - t.dst_off);
     return t;
 }
 
@@ -184,7 +183,7 @@ __device__ __forceinline__ hp::ChunkView chunk(const KParams &k, const TileView 
         there = hp::padded_chunk<UNIT>(k, t, (uint32_t)(buffers()[k.dst_base + t.dst_buf0] + t.dst_off), i, c);
         return c;
     } else if constexpr (TILES == kCut) return hp::cut_chunk<UNIT>(k, t, i);
-    else return hp::chunk_at<UNIT, TILES != kStrided, END && TILES == kRagged>(k, t, i);
+    else return hp::chunk_at<UNIT, TILES != kStrided, END && kRaggedRows<TILES>>(k, t, i);
 }
 
 // N neighbouring addresses of the table, read at once: with one instruction, three with two.
@@ -599,7 +598,7 @@ __device__ __forceinline__ void backward_group(const KParams &k, const TileView 
                 for (int e = 0; e < E; ++e) x[e] = x[e] + acc[u][e];
                 if (!there[u] || (GUARD && i[u] >= n)) continue;
                 const bool all = TILES != kPadded || c[u].end == In::kBytes;
-                if (ELEMENT || TILES == kLines || TILES == kCut || (TILES == kRagged && !GUARD) || (c[u].over == 0 && all)) {
+                if (ELEMENT || TILES == kLines || TILES == kCut || (kRaggedRows<TILES> && !GUARD) || (c[u].over == 0 && all)) {
                     st<Out::kBytes, NTS>(out + c[u].src * kWiden, Out::pack(x));
                 } else {
 #pragma unroll
@@ -644,7 +643,7 @@ template <int DT, bool ACC, int NREP, Tiles TILES, bool NTL, bool NTS>
 __global__ void __launch_bounds__(1024)
 hp_backward_kernel(const Args a) {
     const uint32_t touch = touch_args();
-    const TileView t = my_tile<TILES, false, !ACC>(a);
+    const TileView t = my_tile<TILES>(a);
     backward_tile<DT, ACC, NREP, TILES, NTL, NTS>(a.k, t, NREP > 0 ? (uint32_t)NREP : a.k.dst_copies);
     touched(touch);
 }
@@ -905,7 +904,11 @@ enum Direction { kForward = 0, kBackward = 1, kBackwardAcc = 2, kZeroRows = 3 };
 // The kernel of one tile kind, in the shape's cache policy.
 template <Tiles TILES, bool NTL, bool NTS>
 void launch_nt(const hp_plan *p, Direction dir, const LaunchCfg &c, const Args &a) {
-    if (dir == kZeroRows) HP_LAUNCH((hp_zero_rows_kernel<TILES, NTS>), c, a);
+    if constexpr (TILES == kRaggedSrc) {                     // only the overwriting backward's
+        if (p->dtype == HP_F32) launch_backward_nrep<HP_F32, false, TILES, NTL, NTS>(p->dst_copies, c, a);
+        else launch_backward_nrep<HP_BF16, false, TILES, NTL, NTS>(p->dst_copies, c, a);
+    }
+    else if (dir == kZeroRows) HP_LAUNCH((hp_zero_rows_kernel<TILES, NTS>), c, a);
     else if (dir == kForward) launch_forward<TILES, NTL, NTS>(p->dst_copies, c, a);
     else launch_backward<TILES, NTL, NTS>(p->dtype, dir == kBackwardAcc, p->dst_copies, c, a);
 }
@@ -1004,7 +1007,6 @@ int enqueue_params(const hp_plan *p, Direction dir, const hp::Launch &L, const B
     if (dir == kBackwardAcc) hp::set_row_chunks(a.k, 4u * (uint32_t)p->elem_bytes);
     a.k.block = (uint32_t)L.block;
     a.k.pace = (uint32_t)hp::pace_rounds(*p, (int)dir, L);
-    a.k.align_src = dir == kBackward && hp::aligns_source(*p);
     const KParams &k = a.k;
     uint32_t tiles = k.rows_per_tile == 0 ? p->cut_tiles[L.tile_variant] : p->n_tiles(L.tile_variant);
     if (!k.segs) tiles = put_tables(p, some.n ? some : SegRange{0, p->dsegs.size()}, tiles, a);
@@ -1018,6 +1020,7 @@ int enqueue_params(const hp_plan *p, Direction dir, const hp::Launch &L, const B
     if (kind == hp::kCutRows) launch_tiles<kCut>(p, dir, L.nontemporal, c, a);
     else if (kind == hp::kPaddedRows) launch_tiles<kPadded>(p, dir, L.nontemporal, c, a);
     else if (kind == hp::kRowGroups) launch_tiles<kStrided>(p, dir, L.nontemporal, c, a);
+    else if (k.row_bytes % hp::kLineBytes && dir == kBackward && hp::aligns_source(*p)) launch_tiles<kRaggedSrc>(p, dir, L.nontemporal, c, a);
     else if (k.row_bytes % hp::kLineBytes) launch_tiles<kRagged>(p, dir, L.nontemporal, c, a);
     else launch_tiles<kLines>(p, dir, L.nontemporal, c, a);
     if (hip_failed(hipGetLastError())) return HP_EHIP;

@@ -37,7 +37,6 @@ struct KParams {
     uint32_t row_magic, row_one;
     uint32_t pace;              // rounds of pace() before a tile's loads (kernels that have it)
     uint32_t level_off[kMaxTreeLevels];   // start of each level, in keys; level 0 = leaves
-    uint32_t align_src;         // 1: dense tiles of ragged rows end on lines of the source, 0: of the first destination copy
     uint32_t band_samples, band_magic, band_shift;     // text gradients in bands (band_runs): samples of a position, and their division as above
 };
 
@@ -388,7 +387,6 @@ inline KParams kernel_params(const hp_plan &p, int variant, const Seg *segs, con
     }
     set_row_chunks(k, 16u);
     k.block = k.pace = 0;       // set by the launch
-    k.align_src = 0;
     k.band_samples = k.band_magic = k.band_shift = 0;      // by that of text gradients in bands
     k.dst_base = (uint32_t)p.n_src_bufs;
     k.dst_copies = (uint32_t)p.dst_copies;
