@@ -97,10 +97,10 @@ __device__ __forceinline__ void st(gchar *p, typename Bytes<N>::type v) {
 enum Tiles {
     kLines,     // dense on both sides, and every row is whole 128-byte lines
     kRagged,    // dense on both sides, rows of any length
-    kRaggedSrc, // the same, tiles on lines of the source instead of the destination (hp::aligns_source)
     kStrided,   // groups of whole row-strided rows ([S,B,H] order with several samples per rank, rows shorter than a tile)
     kCut,       // row-strided rows of whole lines, cut by bytes of the source across their ends (hp::cuts_launch)
     kPadded,    // row-strided rows of any length from 256 bytes on, cut by lines of the destination (hp::cuts_launch)
+    kRaggedSrc, // kRagged with tiles on lines of the source instead of the destination (hp::aligns_source)
 };
 // Whether a tile has no chunk but whole ones.
 template <Tiles TILES> constexpr bool kAllWhole = TILES == kLines || TILES == kCut || TILES == kPadded;

@@ -127,3 +127,21 @@ def test_every_cache_policy_has_its_kernel_for_every_kind_of_row():
                     for dtype in (0, 1):
                         for acc in ("false", "true"):
                             assert f"hp_backward_kernel<{dtype}, {acc}, {copies}, (Tiles){tiles}, {ntl}, {nts}>" in names
+
+
+def test_every_cache_policy_has_its_kernel_for_rows_that_are_cut_and_tiles_on_lines_of_the_source():
+    """The same for row-strided rows cut by bytes and by lines, and for the overwriting backward's tiles on lines of the source."""
+    from paper_2605_27678_amd import binding
+    r = subprocess.run(["nm", "-C", binding.LIB_PATH], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stderr
+    names = set(re.findall(r"(hp_\w+_kernel<[^>]*>)", r.stdout.replace("(anonymous namespace)::", "")))
+    for nts in ("false", "true"):
+        for ntl in ("false", "true"):
+            for copies in (0, 1, 2, 4, 8):
+                for dtype in (0, 1):
+                    assert f"hp_backward_kernel<{dtype}, false, {copies}, (Tiles)5, {ntl}, {nts}>" in names
+                    for tiles in ("3", "4"):
+                        assert f"hp_zero_rows_kernel<(Tiles){tiles}, {nts}>" in names
+                        assert f"hp_forward_kernel<{copies}, (Tiles){tiles}, {ntl}, {nts}>" in names
+                        for acc in ("false", "true"):
+                            assert f"hp_backward_kernel<{dtype}, {acc}, {copies}, (Tiles){tiles}, {ntl}, {nts}>" in names
