@@ -45,15 +45,6 @@ uint64_t tiles_of(uint64_t n_rows, uint64_t pitch_rows, int64_t row_bytes, uint3
     return (n_rows + rows_per - 1) / rows_per;
 }
 
-bool cut_by_bytes(const hp_plan &p, uint32_t tile) {
-    if (p.dst_stride == 1 || p.row_bytes > kMaxCutRow) return false;
-    if (p.row_bytes % 128 ? p.row_bytes < kMinPaddedRow : p.row_bytes % tile == 0 || tile % p.row_bytes == 0) return false;
-    const int64_t lines = cut_row_lines(p.row_bytes);
-    for (const hp_segment_t &s : p.segments)
-        if (s.n_rows * lines > INT32_MAX) return false;                    // the kernels divide lines in 31 bits
-    return true;
-}
-
 std::vector<Seg> dst_runs(const hp_plan &p, bool whole) {
     std::vector<Seg> runs;
     if (whole) {                                           // dense, whatever the row order
@@ -296,10 +287,14 @@ int make_tables(hp_plan *p) {
     int rc = HP_OK;
     for (int v = 0; v < kTileVariants && n > 0 && rc == HP_OK; ++v)
         rc = add_tree(p->first_tile.data() + (size_t)v * (n + 1), p->tree_info[v]);
-    std::vector<uint32_t> keys(n);
+    const int64_t row_bytes = p->row_bytes;
+    bool cut = n > 0 && p->dst_stride > 1 && row_bytes <= kMaxCutRow && (row_bytes % 128 == 0 || row_bytes >= kMinPaddedRow);
+    for (size_t i = 0; i < n && cut; ++i) cut = p->segments[i].n_rows * cut_row_lines(row_bytes) <= INT32_MAX;    // the kernels divide lines in 31 bits
+    std::vector<uint32_t> keys(cut ? n : 0);
     for (int v = 0; v < kTileVariants; ++v) {
         p->cut_tiles[v] = 0;
-        if (rc != HP_OK || n == 0 || v >= kCutVariants || !cut_by_bytes(*p, tile_bytes_of(v))) continue;
+        const int64_t tile = tile_bytes_of(v);
+        if (rc != HP_OK || !cut || v >= kCutVariants || (row_bytes % 128 == 0 && (row_bytes % tile == 0 || tile % row_bytes == 0))) continue;
         uint64_t acc = 0;
         for (size_t i = 0; i < n; ++i) {
             keys[i] = (uint32_t)acc;
@@ -319,14 +314,14 @@ double row_share(int64_t row, int64_t tile) {
 }
 // Whether rows that are not whole lines fill tiles of lines enough better: see cuts_launch.
 // Groups of shorter rows store between 64-byte pieces, padded ones do not, and may fill less.
-bool padding_pays(const hp_plan &p, uint32_t tile, int direction) {
-    const double more = p.row_bytes >= tile ? 0.03 : direction == 0 ? -0.25 : -0.12;
-    return p.row_bytes % 128 && cut_by_bytes(p, tile) &&
-           (double)p.row_bytes / (double)(128 * cut_row_lines(p.row_bytes)) >= row_share(p.row_bytes, tile) + more;
+bool padding_pays(const hp_plan &p, int variant, int direction) {
+    const int64_t row = p.row_bytes, tile = tile_bytes_of(variant);
+    const double more = row >= tile ? 0.03 : direction == 0 ? -0.25 : -0.12;
+    return row % 128 && p.cut_tiles[variant] && (double)row / (double)(128 * cut_row_lines(row)) >= row_share(row, tile) + more;
 }
 // Row-strided rows that launches in small tiles can cut by bytes; those of 2 KiB and more want what dense launches want.
-bool cut_rows(const hp_plan &p) { return p.row_bytes % 128 == 0 && (cut_by_bytes(p, 1024) || cut_by_bytes(p, 2048)); }
-bool like_dense(const hp_plan &p) { return p.row_bytes >= 2048 && p.row_bytes % 128 == 0 && cut_by_bytes(p, 1024); }
+bool cut_rows(const hp_plan &p) { return p.row_bytes % 128 == 0 && (p.cut_tiles[0] || p.cut_tiles[1]); }
+bool like_dense(const hp_plan &p) { return p.row_bytes >= 2048 && p.row_bytes % 128 == 0 && p.cut_tiles[0]; }
 
 // Forward to eight copies in short rows, between what tiles of 1 KiB and cutting suit: 0.93-0.97 with either.
 bool eight_short(const hp_plan &p, double fwd_bytes) {
@@ -360,7 +355,7 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
     const bool whole = dense || p->row_bytes >= 4096;        // tiles of 1 KiB are nearly all whole
     // A row-strided row is cut into tiles from its start: whether it fills what it is cut into, and that in whole lanes.
     const int64_t row = p->row_bytes;
-    const bool full = dense || cut_rows(*p) || (row >= 2048 && padding_pays(*p, 1024, 0));                 // tiles are whole where the launch wants them to be
+    const bool full = dense || cut_rows(*p) || (row >= 2048 && padding_pays(*p, 0, 0));                 // tiles are whole where the launch wants them to be
     auto fills = [&](int64_t tile) { return dense || 20 * row >= 17 * ((row + tile - 1) / tile * tile); };
     const bool filled = fills(1024) && (dense || row % 16 == 0), even = even_tiles(*p);
     const size_t segs = p->segments.size();
@@ -622,7 +617,7 @@ bool cuts_launch(const hp_plan &p, int direction, int variant) {
     const double bytes = direction == 1 ? (double)p.bwd_bytes : direction == 2 ? (double)p.bwd_accum_bytes
                                                                               : (1.0 + (double)c) * (double)p.n_rows * (double)row;
     if (row % 128) {
-        if (!padding_pays(p, (uint32_t)tile, direction) || (row < 2048 && bytes < 1e6)) return false;      // (a few tiles: no matter)
+        if (!padding_pays(p, variant, direction) || (row < 2048 && bytes < 1e6)) return false;      // (a few tiles: no matter)
         if (direction == 1) return c != 1 || tile != 2048 || share < 0.75 || row % 16 == 0;
         return direction == 2 || c != 8 || tile != 2048 || bytes < 1000e6;
     }
@@ -754,8 +749,10 @@ int build_host_plan(const hp_layout_t *srcs, int32_t n_edges, const hp_layout_t 
     }
     p->n_src_bufs = edge_base;
 
-    default_launches(p);
-    return make_tables(p);
+    // the launches' shapes ask what can be cut
+    const int rc = make_tables(p);
+    if (rc == HP_OK) default_launches(p);
+    return rc;
 }
 
 }  // namespace hp

@@ -88,8 +88,8 @@ struct hp_plan {
     std::vector<uint32_t> first_tile;     // kTileVariants x (n_segments + 1), row-major
     std::vector<uint32_t> tree;           // the search trees of all variants, 64-byte aligned nodes
     hp::TreeInfo tree_info[hp::kTileVariants] = {};
-    // Launches that cut row-strided segments by bytes (hp::cut_by_bytes): their tiles, 0 where a launch does not, and
-    // their trees, behind the others.
+    // Launches that cut row-strided segments by bytes or lines: their tiles, 0 where a launch cannot, and their trees,
+    // behind the others.  Rules that are asked by every launch read cut_tiles and not the segments.
     uint32_t cut_tiles[hp::kTileVariants] = {};
     hp::TreeInfo cut_info[hp::kTileVariants] = {};
     hp::Launch fwd{}, bwd{}, acc{};       // hp_forward, hp_backward, hp_backward_accumulate
@@ -139,16 +139,14 @@ int build_host_plan(const hp_layout_t *srcs, int32_t n_edges, const hp_layout_t 
 // 1 % of the same cap without them or faster.
 int pace_rounds(const hp_plan &p, int direction, const Launch &L);
 
-// Whether a launch with tiles of `tile` bytes cuts the plan's row-strided segments by
-// bytes of their source, across the ends of rows: where a tile holds neither whole
-// rows nor a row whole tiles, and rows are whole lines.  (Other rows are cut one by
-// one, at lines of the destination.)
+// Launches in tiles of up to 8 KiB can cut the plan's row-strided segments across the ends
+// of rows; hp_plan::cut_tiles says which tile sizes, once and for all when the plan is made.  Rows of whole lines are cut
+// by bytes of their source, where a tile holds neither whole rows nor a row whole tiles; other rows of
+// 256 bytes and more by lines of the destination, of which each row gets as many as it can touch.
 constexpr int64_t kMaxCutRow = 128 << 10;      // row_of_chunk is exact
-// Other rows: by lines of the destination, of which each row gets as many as it can touch.
 constexpr int64_t kMinPaddedRow = 256;
 inline int64_t cut_row_lines(int64_t row_bytes) { return row_bytes % 128 ? row_bytes / 128 + 2 : row_bytes / 128; }
 constexpr int kCutVariants = 4;                // tiles of up to 8 KiB, which launches start from
-bool cut_by_bytes(const hp_plan &p, uint32_t tile);
 
 // Whether a launch of the plan in this direction (0 forward, 1 backward, 2 accumulating)
 // is cut by bytes, if its tiles can be.

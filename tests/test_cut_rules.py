@@ -1,0 +1,26 @@
+"""The rules by which launches of row-strided plans ([S,B,H] order) are cut and shaped, on the host."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def walk(tmp_path_factory):
+    exe, csrc = tmp_path_factory.mktemp("rules") / "walk_rules", os.path.join(ROOT, "paper_2605_27678_amd", "csrc")
+    r = subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-fsanitize=undefined", "-fno-sanitize-recover=all", "-Wall",
+                        "-Wno-unknown-pragmas", "-I", os.path.join(ROOT, "include"), "-I", csrc,
+                        os.path.join(ROOT, "tests", "walk_rules.cpp"), os.path.join(csrc, "hp_plan.cpp"), "-o", str(exe)],
+                       capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr
+
+    def run(check, seed=11, plans=60):
+        r = subprocess.run([str(exe), check, str(seed), str(plans)], capture_output=True, text=True, timeout=600)
+        assert r.returncode == 0 and r.stdout.strip() == f"plans {plans}", r.stdout + r.stderr
+    return run
+
+
+def test_rules_of_a_launch_do_not_read_the_segments(walk):
+    walk("once")

@@ -1,0 +1,67 @@
+// Host-side checks of the rules by which launches of row-strided plans are cut and
+// shaped: built by tests/test_cut_rules.py with UBSan.
+// usage: walk_rules <check> <seed> <plans>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <random>
+#include <vector>
+
+#include "hp_tile.hpp"
+
+static int it;
+#define CHECK(c) do { if (!(c)) { std::printf("plan %d: %s\n", it, #c); return 1; } } while (0)
+
+// A plan of `samples` samples a position, `rows` rows in `images` images in each.
+static int make(hp_plan &p, int tp_src, int tp, int samples, int hidden, int f32, int64_t rows, int images, int order = HP_ROW_SBH) {
+    const hp_layout_t src{tp_src, 1, 1, 1, 0, 0, 0, 0}, dst{tp, 1, 1, 1, 0, 0, 0, order};
+    std::vector<int32_t> smp, st, ln;
+    int64_t seq = 1;
+    for (int b = 0; b < samples; ++b) {
+        int64_t at = 0;
+        for (int k = 0; k < images; ++k) {
+            const int64_t n = (k + 1) * rows / images - k * rows / images;
+            smp.push_back(b); st.push_back((int32_t)at); ln.push_back((int32_t)n);
+            at += n + 1;
+        }
+        seq = at;
+    }
+    const hp_token_map_t m{samples, (int32_t)seq, hidden, f32, (int32_t)smp.size(), smp.data(), st.data(), ln.data(), nullptr};
+    return hp::build_host_plan(&src, 1, &dst, &m, 1, &p);
+}
+
+// What a launch asks is answered from what the plan was made with: no rule reads the segments again, which would
+// cost every launch of a plan of many images a walk.
+static int once(std::mt19937_64 &rng, int plans) {
+    auto R = [&](int lo, int hi) { return (int)(lo + rng() % (uint64_t)(hi - lo + 1)); };
+    long cut = 0;
+    for (it = 0; it < plans; ++it) {
+        const int hiddens[] = {192, 1025, 1088, 1280, 2305, 1544, 2304, 695};
+        hp_plan p;
+        CHECK(make(p, R(1, 2), R(1, 9), R(2, 4), hiddens[R(0, 7)], R(0, 1), 400 << R(0, 7), R(1, 40)) == HP_OK);
+        bool was[3][hp::kTileVariants];
+        int pace[3];
+        const hp::Launch one{0, 64, 16, 3};
+        for (int d = 0; d < 3; ++d) {
+            pace[d] = hp::pace_rounds(p, d, one);
+            for (int v = 0; v < hp::kTileVariants; ++v) cut += was[d][v] = hp::cuts_launch(p, d, v);
+        }
+        for (hp_segment_t &s : p.segments) s.n_rows = INT32_MAX;
+        for (int d = 0; d < 3; ++d) {
+            CHECK(pace[d] == hp::pace_rounds(p, d, one));
+            for (int v = 0; v < hp::kTileVariants; ++v) CHECK(was[d][v] == hp::cuts_launch(p, d, v));
+        }
+    }
+    CHECK(cut > plans);
+    return 0;
+}
+
+int main(int argc, char **argv) {
+    if (argc < 4) return 2;
+    std::mt19937_64 rng(std::atoll(argv[2]));
+    const int plans = std::atoi(argv[3]);
+    int rc = 2;
+    if (!std::strcmp(argv[1], "once")) rc = once(rng, plans);
+    if (rc == 0) std::printf("plans %d\n", plans);
+    return rc;
+}
