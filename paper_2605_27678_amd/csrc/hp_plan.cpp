@@ -38,11 +38,27 @@ int tile_variant_of(int64_t tile_bytes) {
 // Dense runs are cut by bytes.  Row-strided ones are cut row by row: a row at
 // least one tile long is cut into ceil(row / tile) dense pieces, shorter rows are
 // grouped tile / row to a tile.  The kernels use the same formulas.
+namespace {
+struct TileCount {
+    uint64_t row_bytes;
+    uint32_t tile_shift, parts, rows_per;           // parts: of a row of at least a tile; rows_per: rows in a tile; both 0 = dense
+    TileCount(bool dense, int64_t row, uint32_t tile) : row_bytes((uint64_t)row), tile_shift(10), parts(0), rows_per(0) {
+        while ((1u << tile_shift) < tile) ++tile_shift;
+        if (dense) return;
+        if (row_bytes >= tile) parts = (uint32_t)((row_bytes + tile - 1) >> tile_shift);
+        else rows_per = tile / (uint32_t)row_bytes;
+    }
+    uint64_t operator()(uint64_t n_rows) const {
+        if (parts) return n_rows * parts;
+        if (!rows_per) return (n_rows * row_bytes + ((1u << tile_shift) - 1)) >> tile_shift;
+        if (n_rows <= UINT32_MAX - rows_per) return ((uint32_t)n_rows + rows_per - 1) / rows_per;    // half the time of a division in 64 bits
+        return (n_rows + rows_per - 1) / rows_per;
+    }
+};
+}  // namespace
+
 uint64_t tiles_of(uint64_t n_rows, uint64_t pitch_rows, int64_t row_bytes, uint32_t tile) {
-    if (pitch_rows == 1) return (n_rows * row_bytes + tile - 1) / tile;
-    if ((uint64_t)row_bytes >= tile) return n_rows * (((uint64_t)row_bytes + tile - 1) / tile);
-    const uint64_t rows_per = tile / (uint64_t)row_bytes;
-    return (n_rows + rows_per - 1) / rows_per;
+    return TileCount(pitch_rows == 1, row_bytes, tile)(n_rows);
 }
 
 std::vector<Seg> dst_runs(const hp_plan &p, bool whole) {
@@ -252,57 +268,54 @@ int make_tables(hp_plan *p) {
         d.src_buf = (uint16_t)s.src_buf;
         d.dst_buf0 = (uint16_t)s.dst_buf0;
     }
-    p->first_tile.assign((size_t)kTileVariants * (n + 1), 0u);
-    for (int v = 0; v < kTileVariants; ++v) {
+    p->first_tile.resize((size_t)kTileVariants * (n + 1));
+    // The first tile of every segment; false if there are more than a grid may have.
+    auto count = [&](const TileCount &tiles, uint32_t *keys, uint32_t &all) {
         uint64_t acc = 0;
-        uint32_t *row = p->first_tile.data() + (size_t)v * (n + 1);
         for (size_t i = 0; i < n; ++i) {
-            row[i] = (uint32_t)acc;
-            acc += tiles_of((uint64_t)p->segments[i].n_rows, (uint64_t)p->segments[i].dst_row_stride, p->row_bytes, tile_bytes_of(v));
-            if (acc > 0x7fffffffull) return HP_ELAYOUT;        // grid size limit
+            keys[i] = (uint32_t)acc;
+            acc += tiles((uint64_t)p->segments[i].n_rows);
+            if (acc > 0x7fffffffull) return false;
         }
-        row[n] = (uint32_t)acc;
+        all = (uint32_t)acc;
+        return true;
+    };
+    for (int v = 0; v < kTileVariants; ++v) {
+        uint32_t *row = p->first_tile.data() + (size_t)v * (n + 1);
+        if (!count(TileCount(p->dst_stride == 1, p->row_bytes, tile_bytes_of(v)), row, row[n])) return HP_ELAYOUT;
     }
-    // 16-ary search trees over the keys of each variant
+    // Which tile sizes can be cut across the ends of rows.
+    const int64_t row_bytes = p->row_bytes;
+    bool cut = n > 0 && p->dst_stride > 1 && row_bytes <= kMaxCutRow && (row_bytes % 128 == 0 || row_bytes >= kMinPaddedRow);
+    for (size_t i = 0; i < n && cut; ++i) cut = p->segments[i].n_rows * cut_row_lines(row_bytes) <= INT32_MAX;    // the kernels divide lines in 31 bits
+    // 16-ary search trees over the keys of each variant.  Plans are made at step rate, and this and the counts are most
+    // of it: each level is written where it stays.
+    const size_t padded = (n + kTreeFanout - 1) / kTreeFanout * kTreeFanout;
     p->tree.clear();
+    p->tree.reserve((kTileVariants + (cut ? kCutVariants : 0)) * (padded + padded / (kTreeFanout - 1) + kMaxTreeLevels * kTreeFanout));
     auto add_tree = [&](const uint32_t *keys, TreeInfo &ti) -> int {
-        std::vector<std::vector<uint32_t>> levels;
-        levels.emplace_back(keys, keys + n);
-        while (levels.back().size() > (size_t)kTreeFanout) {
-            const std::vector<uint32_t> &below = levels.back();
-            std::vector<uint32_t> up;
-            for (size_t j = 0; j < below.size(); j += kTreeFanout) up.push_back(below[j]);
-            levels.push_back(std::move(up));
+        ti.n_levels = 0;
+        size_t below = n;                                   // keys of the level
+        for (;; below = (below + kTreeFanout - 1) / kTreeFanout) {
+            if (ti.n_levels == (uint32_t)kMaxTreeLevels) return HP_ELAYOUT;
+            const size_t at = p->tree.size(), under = ti.n_levels ? ti.level_off[ti.n_levels - 1] : 0;
+            p->tree.resize(at + (below + kTreeFanout - 1) / kTreeFanout * kTreeFanout, 0xffffffffu);
+            uint32_t *level = p->tree.data() + at;
+            if (ti.n_levels == 0) std::memcpy(level, keys, n * sizeof(uint32_t));
+            else for (size_t j = 0; j < below; ++j) level[j] = p->tree[under + j * kTreeFanout];
+            ti.level_off[ti.n_levels++] = (uint32_t)at;
+            if (below <= (size_t)kTreeFanout) return HP_OK;
         }
-        if (levels.size() > (size_t)kMaxTreeLevels) return HP_ELAYOUT;
-        ti.n_levels = (uint32_t)levels.size();
-        for (size_t l = 0; l < levels.size(); ++l) {
-            std::vector<uint32_t> &lv = levels[l];
-            lv.resize((lv.size() + kTreeFanout - 1) / kTreeFanout * kTreeFanout, 0xffffffffu);
-            ti.level_off[l] = (uint32_t)p->tree.size();
-            p->tree.insert(p->tree.end(), lv.begin(), lv.end());
-        }
-        return HP_OK;
     };
     int rc = HP_OK;
     for (int v = 0; v < kTileVariants && n > 0 && rc == HP_OK; ++v)
         rc = add_tree(p->first_tile.data() + (size_t)v * (n + 1), p->tree_info[v]);
-    const int64_t row_bytes = p->row_bytes;
-    bool cut = n > 0 && p->dst_stride > 1 && row_bytes <= kMaxCutRow && (row_bytes % 128 == 0 || row_bytes >= kMinPaddedRow);
-    for (size_t i = 0; i < n && cut; ++i) cut = p->segments[i].n_rows * cut_row_lines(row_bytes) <= INT32_MAX;    // the kernels divide lines in 31 bits
     std::vector<uint32_t> keys(cut ? n : 0);
     for (int v = 0; v < kTileVariants; ++v) {
         p->cut_tiles[v] = 0;
         const int64_t tile = tile_bytes_of(v);
         if (rc != HP_OK || !cut || v >= kCutVariants || (row_bytes % 128 == 0 && (row_bytes % tile == 0 || tile % row_bytes == 0))) continue;
-        uint64_t acc = 0;
-        for (size_t i = 0; i < n; ++i) {
-            keys[i] = (uint32_t)acc;
-            acc += tiles_of((uint64_t)p->segments[i].n_rows, 1, 128 * cut_row_lines(p->row_bytes), tile_bytes_of(v));
-            if (acc > 0x7fffffffull) break;
-        }
-        if (acc > 0x7fffffffull) continue;
-        p->cut_tiles[v] = (uint32_t)acc;
+        if (!count(TileCount(true, 128 * cut_row_lines(row_bytes), (uint32_t)tile), keys.data(), p->cut_tiles[v])) continue;
         rc = add_tree(keys.data(), p->cut_info[v]);
     }
     return rc;

@@ -24,3 +24,7 @@ def walk(tmp_path_factory):
 
 def test_rules_of_a_launch_do_not_read_the_segments(walk):
     walk("once")
+
+
+def test_tables_of_cut_rows_are_made_in_place(walk):
+    walk("made_in_place")
