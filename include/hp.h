@@ -334,8 +334,11 @@ int hp_backward_accumulate(const hp_plan_t *plan, const void *const *dst_grad_bu
  * whose creation makes no HIP call) and launches the same kernel.  Small plans
  * carry their tables in the launch's arguments anyway (see hp_plan_create), larger
  * ones take several launches of a part of the segments each.  Where those would be
- * too many (plans of hundreds of buffers) this call writes what the launch needs - the segment
- * descriptors and the search tree of the plan's forward tile size - into a fixed array that the
+ * more than it takes to write the tables - which depends on the segments and on the
+ * buffers, whose addresses take the same room: from about 1570 segments on with 19
+ * buffers, 660 with 60, 320 with 150, 90 with 300 - this call writes what the launch
+ * needs, the segment
+ * descriptors and the search tree of the plan's forward tile size, into a fixed array that the
  * library holds in each GPU's memory from load to process end
  * (HP_STATIC_MAX_TABLE_BYTES, 64 KiB: about 1700 segments, which no plan may exceed).  The table bytes then
  * travel as arguments of small copy kernels on `stream` ahead of the transform
@@ -346,8 +349,9 @@ int hp_backward_accumulate(const hp_plan_t *plan, const void *const *dst_grad_bu
  * Returns HP_ELAYOUT when the tables exceed HP_STATIC_MAX_TABLE_BYTES (use
  * hp_forward with a device plan then), otherwise hp_forward's codes; HP_ESTATE
  * is not returned for host-only plans here.
- * All calls of larger plans on one GPU share that GPU's array and it keeps the
- * last call's tables: calls on the SAME stream are ordered by the stream, calls that overlap
+ * All calls of plans of more than about a hundred segments (or fewer, with many buffers:
+ * whatever does not fit one launch's arguments) are to be taken to share that GPU's array,
+ * which keeps the last call's tables: calls on the SAME stream are ordered by the stream, calls that overlap
  * on different streams (or threads using different streams) of one GPU race on
  * it and must be serialised by the caller.  No timing events are attached. */
 #define HP_STATIC_MAX_TABLE_BYTES 65536

@@ -28,6 +28,8 @@
 
 namespace {
 
+using hp::Args;
+using hp::BufTable;
 using hp::KParams;
 using hp::TileView;
 
@@ -38,23 +40,6 @@ inline bool hip_failed(hipError_t e) {
     g_last_hip_error = (int)e;
     return true;
 }
-
-// Device pointers of every buffer of a call, passed by value in the kernel
-// argument segment: sources first, destinations from index n_src on.  Lookups
-// use wave-uniform indices and become scalar loads.
-struct BufTable {
-    void *p[HP_MAX_BUFFERS];
-};
-
-// The arguments of a transform kernel.  The tables of a plan that leaves the
-// room travel behind its buffer pointers (inline_tables), so that an ordinary plan
-// of up to about a hundred segments needs no device memory, no upload and, in the
-// kernel, no load from memory that the launch itself has not just written.
-struct Args {
-    KParams k;
-    BufTable b;
-};
-static_assert(sizeof(Args) <= 4096, "kernel arguments");
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
@@ -781,7 +766,7 @@ static __device__ __align__(256) unsigned char scratch[HP_STATIC_MAX_TABLE_BYTES
 // Table bytes travel in the kernel-argument segment (which a HIP graph node
 // keeps by value), a chunk per launch: no host buffer has to outlive the call
 // and nothing is allocated or copied by the runtime.
-constexpr uint32_t kChunkWords = 896;                       // 3584 bytes, under the 4 KiB argument limit
+using hp::kChunkWords;
 struct TableChunk { uint32_t w[kChunkWords]; };
 
 __global__ void __launch_bounds__(256)
@@ -935,22 +920,8 @@ void launch_tiles(const hp_plan *p, Direction dir, int nontemporal, const Launch
 // element types, 50 MB to 2.4 GB), and the upload is hidden behind the launches,
 // so that where the line lies between 300 MB and 1 GiB matters to neither.
 constexpr int64_t kMaxInlineBytes = (int64_t)1 << 30;
-size_t inline_seg_at(const hp_plan *p) {
-    return (offsetof(Args, b) + (size_t)(p->n_src_bufs + p->n_dst_bufs) * sizeof(void *) + 63) / 64 * 64;
-}
-bool inline_fits(const hp_plan *p, size_t n) {
-    const size_t leaves = n > (size_t)hp::kTreeFanout ? (n + hp::kTreeFanout - 1) / hp::kTreeFanout * 64 : 0;
-    return inline_seg_at(p) + (n * sizeof(hp::Seg) + 63) / 64 * 64 + leaves <= sizeof(Args);
-}
 bool inline_tables(const hp_plan *p) {
-    return inline_fits(p, p->segments.size()) && (1 + (int64_t)p->dst_copies) * p->n_rows * p->row_bytes < kMaxInlineBytes;
-}
-// As many launches as it takes to bring the segments of a plan with their arguments; 0: that cannot be.
-size_t inline_launches(const hp_plan *p) {
-    const size_t n = p->segments.size();
-    for (size_t launches = 1; launches <= n; ++launches)
-        if (inline_fits(p, (n + launches - 1) / launches)) return launches;
-    return 0;
+    return hp::inline_fits(*p, p->segments.size()) && (1 + (int64_t)p->dst_copies) * p->n_rows * p->row_bytes < kMaxInlineBytes;
 }
 
 // The segments of a launch; all of them, but where a plan takes several.
@@ -960,7 +931,7 @@ struct SegRange { size_t first, n; };
 // pointers.  Its tree is the last level of the plan's and, if that has more than a node,
 // the root above it: there is no room for more.  Returns its tiles, of `all`.
 uint32_t put_tables(const hp_plan *p, SegRange r, uint32_t all, Args &a) {
-    const size_t seg_at = inline_seg_at(p), tree_at = seg_at + (r.n * sizeof(hp::Seg) + 63) / 64 * 64;
+    const size_t seg_at = hp::inline_seg_at(*p), tree_at = seg_at + (r.n * sizeof(hp::Seg) + 63) / 64 * 64;
     const size_t nodes = (r.n + hp::kTreeFanout - 1) / hp::kTreeFanout;
     const uint32_t *keys = p->tree.data() + a.k.level_off[0] + r.first;
     const uint32_t tiles = (r.first + r.n < p->dsegs.size() ? keys[r.n] : all) - keys[0];
@@ -1817,11 +1788,8 @@ int hp_forward_static(const hp_plan_t *p, const void *const *src_bufs, void *con
     const uint32_t tree_begin = ti.level_off[0], tree_end = ti.level_off[ti.n_levels - 1] + hp::kTreeFanout;   // up to its root
     const size_t tree_bytes = (size_t)(tree_end - tree_begin) * sizeof(uint32_t);
     if (seg_bytes + tree_bytes > (size_t)HP_STATIC_MAX_TABLE_BYTES) return HP_ELAYOUT;
-    // Several launches that each bring their segments, where they are no more than the kernels that would write the
-    // tables and the one that reads them: 120 segments, 2.8 MB, 19.6 -> 11.0 us; 400 segments, 192 MB 40.4 -> 35.3;
-    // 1000 segments, 46 MB 52.8 -> 46.7.  With hundreds of buffers there is room for few segments beside them: 0.99.
-    const size_t chunk = kChunkWords * sizeof(uint32_t), n = p->dsegs.size(), launches = inline_launches(p);
-    if (launches && launches <= (p->dsegs.size() * sizeof(hp::Seg) + chunk - 1) / chunk + (tree_bytes + chunk - 1) / chunk + 1) {
+    if (const size_t launches = hp::static_launches(*p, tree_bytes)) {
+        const size_t n = p->dsegs.size();
         const KParams k = launch_params(p, kForward, L, nullptr, nullptr);
         for (size_t i = 0; i < launches && rc == HP_OK; ++i)
             rc = enqueue_params(p, kForward, L, bt, (hipStream_t)stream, EventPair{}, k,

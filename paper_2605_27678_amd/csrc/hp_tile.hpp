@@ -40,6 +40,23 @@ struct KParams {
     uint32_t band_samples, band_magic, band_shift;     // text gradients in bands (band_runs): samples of a position, and their division as above
 };
 
+// Device pointers of every buffer of a call, passed by value in the kernel
+// argument segment: sources first, destinations from index n_src on.  Lookups
+// use wave-uniform indices and become scalar loads.
+struct BufTable {
+    void *p[HP_MAX_BUFFERS];
+};
+
+// The arguments of a transform kernel.  The tables of a plan that leaves the
+// room travel behind its buffer pointers (inline_tables), so that an ordinary plan
+// of up to about a hundred segments needs no device memory, no upload and, in the
+// kernel, no load from memory that the launch itself has not just written.
+struct Args {
+    KParams k;
+    BufTable b;
+};
+static_assert(sizeof(Args) <= 4096, "kernel arguments");
+
 // One workgroup's share of the launch.
 struct TileView {
     uint64_t src_off, dst_off;  // bytes from the buffer bases
@@ -391,6 +408,35 @@ inline KParams kernel_params(const hp_plan &p, int variant, const Seg *segs, con
     k.dst_base = (uint32_t)p.n_src_bufs;
     k.dst_copies = (uint32_t)p.dst_copies;
     return k;
+}
+
+// Where the tables begin behind a plan's buffer pointers in a launch's arguments, and whether those of n of its
+// segments fit there.
+inline size_t inline_seg_at(const hp_plan &p) {
+    return (offsetof(Args, b) + (size_t)(p.n_src_bufs + p.n_dst_bufs) * sizeof(void *) + 63) / 64 * 64;
+}
+inline bool inline_fits(const hp_plan &p, size_t n) {
+    const size_t leaves = n > (size_t)kTreeFanout ? (n + kTreeFanout - 1) / kTreeFanout * 64 : 0;
+    return inline_seg_at(p) + (n * sizeof(Seg) + 63) / 64 * 64 + leaves <= sizeof(Args);
+}
+
+// A launch of hp_forward_static that writes tables into the device's array first takes a kernel for each of these.
+constexpr uint32_t kChunkWords = 896;                       // 3584 bytes, under the 4 KiB argument limit
+
+// How many launches hp_forward_static takes for a plan of several, each of which brings a part of the segments; 0: the
+// tables are written into the device's array instead, `tree_bytes` of them the search tree.  Several launches are
+// taken where they are no more than the kernels that would write the tables and the one that reads them: 120
+// segments, 2.8 MB, 19.6 -> 11.0 us; 400 segments, 192 MB 40.4 -> 35.3; 1000 segments, 46 MB 52.8 -> 46.7.  A launch
+// has room for about (3584 - 8 buffers) / 36 segments and a kernel writes 98 to 112, so that it depends on both: plans of up to 18
+// buffers always take several launches, others write the tables from about 1570 segments on with 19 buffers, 1440
+// with 28, 660 with 60, 450 with 100, 320 with 150 and 90 with 300 (and a few hundred more alternate with the
+// rounding up of either).  At hundreds of buffers the two are within 1 %.
+inline size_t static_launches(const hp_plan &p, size_t tree_bytes) {
+    const size_t chunk = kChunkWords * sizeof(uint32_t), n = p.dsegs.size();
+    const size_t most = (n * sizeof(Seg) + chunk - 1) / chunk + (tree_bytes + chunk - 1) / chunk + 1;
+    for (size_t launches = 1; launches <= std::min(n, most); ++launches)
+        if (inline_fits(p, (n + launches - 1) / launches)) return launches;
+    return 0;
 }
 
 }  // namespace hp
