@@ -365,10 +365,9 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
     const int c = p->dst_copies, s = p->src_copies;
     const bool between = c != 1 && c != 2 && c != 4 && c != 8;                  // 3, 5 to 7, 9 to 16 copies
     const bool f32 = p->elem_bytes == 4, dense = p->dst_stride == 1 || like_dense(*p);
-    const bool whole = dense || p->row_bytes >= 4096;        // tiles of 1 KiB are nearly all whole
     // A row-strided row is cut into tiles from its start: whether it fills what it is cut into, and that in whole lanes.
     const int64_t row = p->row_bytes;
-    const bool full = dense || cut_rows(*p) || (row >= 2048 && padding_pays(*p, 0, 0));                 // tiles are whole where the launch wants them to be
+    const bool full = dense || cut_rows(*p) || (row >= 2048 && padding_pays(*p, 0, 0));       // tiles of 1 KiB are whole, or as full as larger ones at least
     auto fills = [&](int64_t tile) { return dense || 20 * row >= 17 * ((row + tile - 1) / tile * tile); };
     const bool filled = fills(1024) && (dense || row % 16 == 0), even = even_tiles(*p);
     const size_t segs = p->segments.size();
@@ -377,6 +376,11 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
     auto in = [](double bytes, double from, double to) { return bytes >= from * MB && bytes < to * MB; };
 
     const double fwd = (1.0 + c) * (double)p->n_rows * (double)p->row_bytes;
+    // Rows of three and a half KiB and a little more leave as much of tiles of 1 KiB empty as of 2 KiB.  Forward in the smaller
+    // ones, where they are not cut: 0.87-0.97 to four copies, 0.94-0.98 to twelve and more, 0.93-0.99 to eight and ten up to
+    // 200 MB (1.02-1.09 above).
+    const bool halves = p->dst_stride > 1 && row > 2048 && row < 4096 && row_share(row, 1024) < 0.95 && row_share(row, 1024) <= row_share(row, 2048) &&
+                        !cuts_launch(*p, 0, K1) && (c < 8 || c >= 12 || fwd < 200 * MB);
     if (c == 1 && fwd >= 200 * MB && segs <= 256) {
         if (fwd < 400 * MB || !dense) set(f, K4, 128, 24);                      // 0.99-1.03; more segments 0.98-1.03
         else set(f, K2, 64, 20);                                                // 1.003-1.006 of 4 KiB x 128; [S,B,H] 0.92-0.98
@@ -393,7 +397,7 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
         if (segs <= 256 && (filled || row < 1024)) set(f, K1, 64, 8);           // 0.99-1.15; more segments 0.96-1.02, rows of 1280 bytes 0.92, 450 MB 0.87-0.91
     }
     else if (c == 4 && in(fwd, 205, 1000)) {
-        if (segs <= (fwd < 900 * MB ? 512 : 256) && row > 2048) set(f, K1, 64, fwd < 450 * MB ? 12 : 14);   // 1.00-1.10; 1 to 4 GB 0.99-1.03, rows of 1 and 2 KiB 0.98-1.03, two thousand segments 0.91-1.0
+        if (segs <= (fwd < 900 * MB ? 512 : 256) && row > 2048 && !halves) set(f, K1, 64, fwd < 450 * MB ? 12 : 14);   // 1.00-1.10; 1 to 4 GB 0.99-1.03, rows of 1 and 2 KiB 0.98-1.03, two thousand segments 0.91-1.0
     }
     else if (c >= 5 && c <= 7 && in(fwd, 40, 450)) {
         if (c > 5 || segs <= 16) set(f, K1, 64, 10);                            // 0.96-1.20; 20 MB 0.89-1.06, five copies and more segments 0.87-1.03
@@ -401,16 +405,16 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
     else if (c >= 5 && c <= 7 && fwd >= 450 * MB) {
         if (segs <= (c == 5 ? 256 : 1024) && (filled || row < 2048)) set(f, K1, 64, 14);   // 1.00-1.15; more segments 0.97-1.02, rows of 3088 and 8186 bytes 0.94-0.99
     }
-    else if (c == 8 && full && in(fwd, 40, 450)) set(f, K1, 64, 5);            // 0.99-1.25; [S,B,H] order 0.93-1.02
+    else if (c == 8 && full && !halves && in(fwd, 40, 450)) set(f, K1, 64, 5);            // 0.99-1.25; [S,B,H] order, four and two samples, cut or not, 0.96-1.25
     else if (c == 8 && full && in(fwd, 450, 5000) && !eight_short(*p, fwd)) {
-        if (segs <= 256) set(f, K1, 64, fwd < 700 * MB ? 5 : 8);                // 1.00-1.06; more segments 0.98-1.02, 7.2 GB 0.99
+        if (segs <= 256) set(f, K1, 64, fwd < 700 * MB ? 5 : 8);                // 1.00-1.06; more segments 0.98-1.02, 7.2 GB 0.99; [S,B,H] 0.94-1.24
     }
-    else if (c >= 10 && c <= 12 && full && in(fwd, 100, c == 12 ? 450 : 600)) set(f, K1, 64, 5);   // 0.96-1.28; ten copies, 700 MB 0.98-1.0, 1.1 GB 0.85; [S,B,H] 0.86-1.05
+    else if (c >= 10 && c <= 12 && full && !halves && in(fwd, 100, c == 12 ? 450 : 600)) set(f, K1, 64, 5);   // 0.96-1.28; ten copies, 700 MB 0.98-1.0, 1.1 GB 0.85; [S,B,H] 0.95-1.20
     else if (c == 12 && full && in(fwd, 450, 1200)) {
         if (segs <= 256) set(f, K1, 64, fwd < 1000 * MB ? 3 : 4);               // 1.02-1.12; 1.2 GB 0.93-0.99
     }
-    else if (c >= 13 && c <= 15 && full && in(fwd, 100, 1200)) set(f, K1, 64, 4);  // 0.98-1.10; 1.4 GB 0.94-1.03
-    else if (c == 16 && full && in(fwd, 100, 1500)) set(f, K1, 64, 3);         // 1.01-1.11, paced; 1.7 GB 0.91-0.99
+    else if (c >= 13 && c <= 15 && full && !halves && in(fwd, 100, 1200)) set(f, K1, 64, 4);  // 0.98-1.10; 1.4 GB 0.94-1.03
+    else if (c == 16 && full && !halves && in(fwd, 100, 1500)) set(f, K1, 64, 3);         // 1.01-1.11, paced; 1.7 GB 0.91-0.99; [S,B,H], not paced, 0.97-1.12
     else if (c >= 13 && full && fwd >= 1200 * MB) set(f, K2, 64, 3);   // 0.99-1.03 to 4 GB
 
     // With few copies a workgroup moves little for each search, and the depth of the tree (16 segments a level) decides.
@@ -439,7 +443,7 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
         else if (c == 6 && bwd >= 450 * MB && filled) cap = 16;                 // 1.01-1.02
         set(b, K1, 64, cap);
     }
-    // half a dozen to a dozen waves of eight and more copies have to have whole tiles: [S,B,H] rows that leave them partly empty lose 2-13 % here
+    // half a dozen to a dozen waves of eight and more copies have to have whole tiles: [S,B,H] rows that leave them partly empty lose 2-13 % here (2560 bytes, cut from 400 MB on, 0.96-1.04)
     else if (c == 8 && bwd >= 1500 * MB && (dense || row < 4096 || fills(4096))) set(b, K4, 64, 5);   // 1.01-1.06, to two source copies 1.05-1.11
     else if (c == 8 && bwd >= 40 * MB && filled) set(b, K1, 64, bwd < 450 * MB ? 12 : 11);   // 1.00-1.03
     else if (c > 12 && p->dst_stride == 1 && in(bwd, 40, 250)) set(b, K1, 64, 12);           // 1.02-1.07; 350 MB 0.97-1.00, [S,B,H] order 0.85-1.0
@@ -448,6 +452,10 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
 
     const double acc = (double)p->bwd_accum_bytes;
     if (acc < 1 * MB) return;                                                   // a few tiles: nothing to choose
+    const bool whole = dense || row >= 4096;                 // tiles of 1 KiB are nearly all whole
+    // In 4 KiB row-strided rows want what dense ones want where they are cut there: rows of 3712, 3968 and 7552 bytes, which
+    // are not, 0.87-0.95 with the wave cap of dense launches (one to three copies, and eight).
+    const bool dense4 = p->dst_stride == 1 || (dense && cuts_launch(*p, 2, K4));
     if (f32) {
         // More waves make these launches faster and the forward after them slower by as much: only the middle sizes gain,
         // and none with several source copies (0.77-1.05).
@@ -456,7 +464,7 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
                            : c == 8 ? dense && in(acc, 150, 400)                // 1.00-1.05; 670 MB: 0.84-0.89
                                     : acc < 300 * MB;                           // 1.02-1.30; 1.6 GB: 0.87-0.97
         if (s == 1 && gains) set(a, K1, 64, 24);
-        else if (c <= 2 && s == 1 && acc >= 1500 * MB && (dense || p->row_bytes % 4096 == 0))
+        else if (c <= 2 && s == 1 && acc >= 1500 * MB && (dense || row % 4096 == 0))
             set(a, K4, 64, 8);                                                  // 1.02-1.06; 450 MB: 0.97-1.01, [S,B,H] rows of 6 KiB 0.93
     } else if (s > 1) {
         // few waves want whole tiles: pieces of row-strided rows under 4 KiB 0.96-1.01 with the smaller caps, 1.02-1.13 with 16
@@ -466,9 +474,9 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
     } else if (acc < 400 * MB) {
         if (c == 2 && acc >= 350 * MB && filled) set(a, K1, 64, 16);              // 1.02
         else if (c >= 3 && c <= 7 && acc >= 250 * MB) set(a, K1, 64, c == 3 ? 20 : c == 4 ? 14 : 16);   // 1.01-1.03; 200 MB 0.99-1.01
-        else if (c == 2 ? acc < 280 * MB : c <= 5) set(a, K4, 256, dense ? 24 : 0);         // 0.97-1.48; two copies, 300 MB: 0.99-1.02
+        else if (c == 2 ? acc < 280 * MB : c <= 5) set(a, K4, 256, dense4 ? 24 : 0);         // 0.97-1.48; two copies, 300 MB: 0.99-1.02
         else if (c >= 5 && c < 8) set(a, K1, 64, 24);                           // 1.10-1.63
-        else if (c == 8 && dense && in(acc, 50, 350)) set(a, K4, 256, 16);      // 1.01-1.11; 27 MB 0.96, 400 MB 0.99, [S,B,H] 0.96-1.07
+        else if (c == 8 && dense4 && in(acc, 50, 350)) set(a, K4, 256, 16);      // 1.01-1.11; 27 MB 0.96, 400 MB 0.99, [S,B,H] 0.96-1.07
         else if (c > 8) set(a, K1, 64, c <= 10 || acc < 150 * MB ? 20 : 12);    // 1.21-1.71, cap 12 1.00-1.02 on top; 9 copies 0.99
     } else if (c == 1 || (between && !whole)) {
         set(a, K1, 64, c < 8 ? 20 : 16);                                        // 1.00-1.02, pieces of short rows 1.02-1.15

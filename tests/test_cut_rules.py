@@ -28,3 +28,7 @@ def test_rules_of_a_launch_do_not_read_the_segments(walk):
 
 def test_tables_of_cut_rows_are_made_in_place(walk):
     walk("made_in_place")
+
+
+def test_shapes_follow_what_is_launched(walk):
+    walk("shapes", plans=1)

@@ -84,6 +84,33 @@ static int made_in_place(std::mt19937_64 &rng, int plans) {
     return 0;
 }
 
+// A plan whose forward moves about `mb` megabytes, in [S,B,H] order with four samples a position.
+static int sized(hp_plan &p, int tp, int row, double mb, int f32 = 0) {
+    return make(p, 1, tp, 4, row / (f32 ? 4 : 2), f32, (int64_t)(mb * 1e6 / (1 + tp) / row / 4), 8);
+}
+
+// Shapes that suit whole tiles are for launches that have them: rows that leave tiles partly empty and are not cut there
+// keep the shape that they had.
+static int shapes() {
+    struct Case { int tp, row; double mb; bool small; };
+    for (const Case &c : {Case{4, 3712, 300, false}, Case{4, 3584, 220, false}, Case{4, 3712, 700, true}, Case{4, 3968, 300, true},
+                          Case{12, 3584, 300, false}, Case{16, 3712, 200, false}, Case{16, 3712, 700, true}, Case{14, 4608, 300, true},
+                          Case{8, 3712, 120, false}, Case{8, 3712, 300, true}, Case{8, 2560, 120, true}, Case{4, 8192, 300, true}}) {
+        hp_plan p;
+        ++it;
+        CHECK(sized(p, c.tp, c.row, c.mb) == HP_OK);
+        CHECK((p.fwd.tile_variant == 0) == c.small);
+    }
+    for (const Case &c : {Case{1, 3712, 60, false}, Case{1, 7552, 60, false}, Case{3, 3968, 60, false}, Case{8, 3712, 100, false},
+                          Case{1, 2304, 60, true}, Case{1, 4608, 60, true}, Case{8, 2304, 100, true}}) {      // accumulating, in 4 KiB
+        hp_plan p;
+        ++it;
+        CHECK(sized(p, c.tp, c.row, c.mb) == HP_OK);
+        CHECK((p.acc.tile_variant == 2 && p.acc.waves_per_cu > 0) == c.small);
+    }
+    return 0;
+}
+
 int main(int argc, char **argv) {
     if (argc < 4) return 2;
     std::mt19937_64 rng(std::atoll(argv[2]));
@@ -91,6 +118,7 @@ int main(int argc, char **argv) {
     int rc = 2;
     if (!std::strcmp(argv[1], "once")) rc = once(rng, plans);
     if (!std::strcmp(argv[1], "made_in_place")) rc = made_in_place(rng, plans);
+    if (!std::strcmp(argv[1], "shapes")) rc = shapes();
     if (rc == 0) std::printf("plans %d\n", plans);
     return rc;
 }
