@@ -396,8 +396,8 @@ void by_size(const hp_plan *p, Launch &f, Launch &b, Launch &a) {
     else if (c == 4 && in(fwd, 8, 180)) {
         if (segs <= 256 && (filled || row < 1024)) set(f, K1, 64, 8);           // 0.99-1.15; more segments 0.96-1.02, rows of 1280 bytes 0.92, 450 MB 0.87-0.91
     }
-    else if (c == 4 && in(fwd, 205, 1000)) {
-        if (segs <= (fwd < 900 * MB ? 512 : 256) && row > 2048 && !halves) set(f, K1, 64, fwd < 450 * MB ? 12 : 14);   // 1.00-1.10; 1 to 4 GB 0.99-1.03, rows of 1 and 2 KiB 0.98-1.03, two thousand segments 0.91-1.0
+    else if (c == 4 && in(fwd, 180, 1000)) {
+        if (segs <= (fwd < 900 * MB ? 512 : 256) && row > 2048 && !halves) set(f, K1, 64, fwd < 450 * MB ? 12 : 14);   // 1.00-1.13; 1 to 4 GB 0.99-1.03, rows of 1 and 2 KiB 0.98-1.03, two thousand segments 0.91-1.0
     }
     else if (c >= 5 && c <= 7 && in(fwd, 40, 450)) {
         if (c > 5 || segs <= 16) set(f, K1, 64, 10);                            // 0.96-1.20; 20 MB 0.89-1.06, five copies and more segments 0.87-1.03

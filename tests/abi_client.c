@@ -48,6 +48,14 @@ int main(void)
         total += segs[i].n_rows;
     }
     CHECK(total == info.n_rows);
+    /* which shape a plan starts from is the library's choice; that it is one that can be set, the interface's promise */
+    for (i = 0; i < 3; ++i) {
+        CHECK(hp_plan_get_launch(plan, i, &shape) == HP_OK && hp_plan_set_launch(plan, i, &shape) == HP_OK);
+        CHECK(shape.tile_bytes >= 1024 && shape.tile_bytes <= 65536 && (shape.tile_bytes & (shape.tile_bytes - 1)) == 0);
+        CHECK(shape.block_threads >= 64 && shape.block_threads <= 1024 && shape.block_threads % 64 == 0);
+    }
+    shape.tile_bytes = 2048; shape.block_threads = 64;
+    CHECK(hp_plan_set_launch(plan, 0, &shape) == HP_OK);
     CHECK(hp_plan_get_launch(plan, 0, &shape) == HP_OK && shape.tile_bytes == 2048 && shape.block_threads == 64);
     shape.tile_bytes = 3000;
     CHECK(hp_plan_set_launch(plan, 0, &shape) == HP_EINVAL);

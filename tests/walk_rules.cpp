@@ -93,7 +93,7 @@ static int sized(hp_plan &p, int tp, int row, double mb, int f32 = 0) {
 // keep the shape that they had.
 static int shapes() {
     struct Case { int tp, row; double mb; bool small; };
-    for (const Case &c : {Case{4, 3712, 300, false}, Case{4, 3584, 220, false}, Case{4, 3712, 700, true}, Case{4, 3968, 300, true},
+    for (const Case &c : {Case{4, 10240, 160, true}, Case{4, 10240, 190, true}, Case{4, 10240, 210, true}, Case{4, 3712, 300, false}, Case{4, 3584, 220, false}, Case{4, 3712, 700, true}, Case{4, 3968, 300, true},
                           Case{12, 3584, 300, false}, Case{16, 3712, 200, false}, Case{16, 3712, 700, true}, Case{14, 4608, 300, true},
                           Case{8, 3712, 120, false}, Case{8, 3712, 300, true}, Case{8, 2560, 120, true}, Case{4, 8192, 300, true}}) {
         hp_plan p;
