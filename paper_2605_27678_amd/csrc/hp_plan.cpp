@@ -326,10 +326,13 @@ double row_share(int64_t row, int64_t tile) {
     return row >= tile ? (double)row / (double)((row + tile - 1) / tile * tile) : (double)(tile / row * row) / (double)tile;
 }
 // Whether rows that are not whole lines fill tiles of lines enough better: see cuts_launch.
-// Groups of shorter rows store between 64-byte pieces, padded ones do not, and may fill less.
+// Groups of shorter rows store between 64-byte pieces, padded ones do not, and may fill less; but not in tiles of 1 KiB, whose
+// few chunks hide that: forward 0.91-1.08 at 60 MB to 2.5 GB, 0.98 in the middle (rows of 600 bytes to three and four
+// copies, 120 MB, 0.88-0.97).
 bool padding_pays(const hp_plan &p, int variant, int direction) {
     const int64_t row = p.row_bytes, tile = tile_bytes_of(variant);
-    const double more = row >= tile ? 0.03 : direction == 0 ? -0.25 : -0.12;
+    if (direction == 0 && tile == 1024 && row < tile) return false;
+    const double more = row >= tile ? 0.03 : direction != 0 ? -0.12 : tile == 8192 ? -0.25 : -0.15;
     return row % 128 && p.cut_tiles[variant] && (double)row / (double)(128 * cut_row_lines(row)) >= row_share(row, tile) + more;
 }
 // Row-strided rows that launches in small tiles can cut by bytes; those of 2 KiB and more want what dense launches want.
@@ -626,10 +629,14 @@ bool aligns_source(const hp_plan &p) {
 //   backward     0.97-1.7 (1390 bytes from eight copies, 0.5 GB 1.45)
 //   accumulating 0.97-1.45
 // Rows of a tile and more that fill tiles as well without: 0.8-1.05; groups of rows backward that fill a
-// tile to 12 % more: 0.92-1.02, forward to 25 % more still 1.0-1.2.
+// tile to 12 % more: 0.92-1.02, forward to 15 % more still 1.0-1.2, to 15 to 25 % more 0.93-1.02 (rows of 500 bytes, 60 MB to
+// 2.5 GB) but in 8 KiB tiles 1.0-1.1.
 // The lines that are left out forward lost 3 to 10 %: launches in which partly empty
-// tiles happen to leave as much on its way as suits them; backward from one copy, rows that
+// tiles happen to leave as much on its way as suits them (two copies, one row in an 8 KiB tile: rows of 4224 to 5120 bytes
+// 0.94-0.99 from 150 MB on, 5376 to 7040 0.98-1.0); backward from one copy, rows that
 // are not whole chunks and fill three quarters of 2 KiB tiles, 0.91-1.07.
+// What is left of such scatter: forward to two to seven copies in rows of 3200, 3456 and 10496 bytes, 0.2 to 1.2 GB, 0.90-0.99,
+// and launches of 5 to 25 MB in either direction 0.80-1.2, 1.00 in the middle.
 bool cuts_launch(const hp_plan &p, int direction, int variant) {
     if (!p.cut_tiles[variant]) return false;
     if (p.cut_tiles[variant] > p.n_tiles(variant) && p.cut_tiles[variant] >= 1u << 22) return false;   // keep_grid counted the others
@@ -645,6 +652,7 @@ bool cuts_launch(const hp_plan &p, int direction, int variant) {
     if (direction == 1) return row >= 1024 && (bytes < 400e6 ? share < 0.82 : share < 0.87 || like_dense(p));
     if (share >= 0.87 && bytes < 400e6) return false;
     if (direction == 2) return true;
+    if (c == 2 && tile == 8192 && row < tile && 2 * row > tile && bytes >= 100e6) return false;     // one row a tile, which is as much as suits it
     if ((c == 3 || c == 4) && row >= 1024 && row < 2048 && bytes < 450e6) return false;
     if ((c == 6 || c == 7) && share >= 0.7 && row < 3072 && bytes < 450e6) return false;
     return !eight_short(p, bytes);

@@ -32,3 +32,7 @@ def test_tables_of_cut_rows_are_made_in_place(walk):
 
 def test_shapes_follow_what_is_launched(walk):
     walk("shapes", plans=1)
+
+
+def test_launches_that_lose_by_it_are_not_cut(walk):
+    walk("cuts", plans=1)

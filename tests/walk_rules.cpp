@@ -111,6 +111,21 @@ static int shapes() {
     return 0;
 }
 
+// Launches that were slower when they were cut: groups of rows forward in 1 KiB tiles, groups that leave much less of a
+// tile empty, one row in an 8 KiB tile to two copies.
+static int cuts() {
+    struct Case { int tp, row; double mb; int direction, variant; bool cut; };
+    for (const Case &c : {Case{4, 600, 120, 0, 0, false}, Case{3, 700, 170, 0, 0, false}, Case{4, 600, 300, 0, 1, true}, Case{4, 600, 120, 1, 0, true},
+                          Case{8, 500, 120, 0, 1, false}, Case{2, 600, 120, 0, 3, true}, Case{2, 4608, 150, 0, 3, false}, Case{2, 4608, 60, 0, 3, true},
+                          Case{2, 9216, 150, 0, 3, true}, Case{2, 2304, 150, 0, 3, true}, Case{3, 4608, 150, 0, 3, true}, Case{4, 2050, 120, 0, 0, true}}) {
+        hp_plan p;
+        ++it;
+        CHECK(sized(p, c.tp, c.row, c.mb) == HP_OK);
+        CHECK(hp::cuts_launch(p, c.direction, c.variant) == c.cut);
+    }
+    return 0;
+}
+
 int main(int argc, char **argv) {
     if (argc < 4) return 2;
     std::mt19937_64 rng(std::atoll(argv[2]));
@@ -119,6 +134,7 @@ int main(int argc, char **argv) {
     if (!std::strcmp(argv[1], "once")) rc = once(rng, plans);
     if (!std::strcmp(argv[1], "made_in_place")) rc = made_in_place(rng, plans);
     if (!std::strcmp(argv[1], "shapes")) rc = shapes();
+    if (!std::strcmp(argv[1], "cuts")) rc = cuts();
     if (rc == 0) std::printf("plans %d\n", plans);
     return rc;
 }
