@@ -35,7 +35,8 @@ def test_tiles_of_a_launch_that_cuts_its_rows_are_whole(hidden, tile, cut):
 
 
 def test_grids_of_the_largest_padded_launches_stay_below_2_to_the_32_work_items():
-    hidden, rows = 200, (62 << 30) // 400                   # two rows of 400 bytes in a tile, or five lines for each
+    # the shape that such a plan starts from, in tiles of 4 KiB; where lines would be too many: test_cut_rules.py
+    hidden, rows = 200, (62 << 30) // 400
     tm = wl.TokenMap(2, rows // 2, hidden, [0, 1], [0, 0], [rows // 2] * 2)
     p = hp.hp_plan_create_host(wl.Grid(), wl.Grid(row_order=wl.ROW_SBH), tm)
     assert p.info.n_tiles * p.get_launch(0)["block_threads"] < 2 ** 32

@@ -36,3 +36,7 @@ def test_shapes_follow_what_is_launched(walk):
 
 def test_launches_that_lose_by_it_are_not_cut(walk):
     walk("cuts", plans=1)
+
+
+def test_grids_of_the_largest_launches_of_lines_stay_below_2_to_the_32_work_items(walk):
+    walk("grids", plans=1)

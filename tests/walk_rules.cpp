@@ -126,6 +126,25 @@ static int cuts() {
     return 0;
 }
 
+// A grid of 2^32 work-items is refused.  Where tiles of lines are more of them than the row by row launch has, which the
+// starting shapes were checked with, the largest launches go row by row: backward from two copies in rows of 900 bytes,
+// 9 lines of 8 a tile against one row a tile.
+static int grids() {
+    long near = 0;
+    for (int64_t rows : {1000, 900000, 1000000, 15000000, 15700000, 16700000}) {
+        hp_plan p;
+        ++it;
+        CHECK(make(p, 2, 2, 4, 450, 0, rows, 1) == HP_OK);
+        CHECK(p.bwd.tile_variant == 0 && p.bwd.block == 64);
+        const uint64_t cut = (uint64_t)p.cut_tiles[0] * 64, plain = (uint64_t)p.n_tiles(0) * 64;
+        near += cut >= 1ull << 32 && plain < 1ull << 32;
+        CHECK((hp::cuts_launch(p, 1, 0) ? cut : plain) < 1ull << 32);
+        CHECK(hp::cuts_launch(p, 1, 0) == (rows < 1000000));
+    }
+    CHECK(near == 3);
+    return 0;
+}
+
 int main(int argc, char **argv) {
     if (argc < 4) return 2;
     std::mt19937_64 rng(std::atoll(argv[2]));
@@ -135,6 +154,7 @@ int main(int argc, char **argv) {
     if (!std::strcmp(argv[1], "made_in_place")) rc = made_in_place(rng, plans);
     if (!std::strcmp(argv[1], "shapes")) rc = shapes();
     if (!std::strcmp(argv[1], "cuts")) rc = cuts();
+    if (!std::strcmp(argv[1], "grids")) rc = grids();
     if (rc == 0) std::printf("plans %d\n", plans);
     return rc;
 }
