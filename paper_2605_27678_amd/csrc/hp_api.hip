@@ -998,69 +998,6 @@ int enqueue_params(const hp_plan *p, Direction dir, const hp::Launch &L, const B
     return HP_OK;
 }
 
-// One launch of the text-gradient kernel: `n` of the runs from `runs` on, whose
-// buffers are the `bufs` from `buf0` on; its tables always travel with the
-// arguments.
-struct RunGroup {
-    size_t first, n;
-    int32_t buf0, bufs;
-};
-size_t run_bytes(size_t n, int32_t bufs) {
-    const size_t ptrs = (offsetof(Args, b) + (size_t)bufs * 2 * sizeof(void *) + 63) / 64 * 64;
-    const size_t leaves = n > (size_t)hp::kTreeFanout ? (n + hp::kTreeFanout - 1) / hp::kTreeFanout * 64 : 0;
-    return ptrs + (n * sizeof(hp::Seg) + 63) / 64 * 64 + leaves;
-}
-// As many runs a launch as the arguments hold.
-std::vector<RunGroup> group_runs(const std::vector<hp::Seg> &runs, int32_t copies) {
-    std::vector<RunGroup> groups;
-    for (size_t i = 0; i < runs.size(); ++i) {
-        const int32_t buf0 = runs[i].dst_buf0;
-        if (!groups.empty()) {
-            RunGroup &g = groups.back();
-            const int32_t bufs = buf0 + copies - g.buf0;
-            if (run_bytes(g.n + 1, bufs) <= sizeof(Args)) {
-                ++g.n;
-                g.bufs = bufs;
-                continue;
-            }
-        }
-        groups.push_back(RunGroup{i, 1, buf0, copies});
-    }
-    return groups;
-}
-
-// Whether the runs of text and image rows are bands: in [S,B,H] order, for as many samples as a band has bits.
-bool text_bands(const hp_plan *p) { return p->dst_stride > 1 && p->dst_stride <= hp::kMaxBandSamples; }
-
-// The runs that hp_text_grads launches for a plan: of text and of image rows, or
-// (*whole) whole buffers to copy, whose image rows are then zeroed.  Runs save the
-// image rows one reading and one writing, about 1 us for 6 MB, and take a launch
-// for every hundred or so, about 4 us each after the first; a copy is two launches.
-// Two buffers of 67 MB, half of them image rows: 512 runs 56 us, 800 runs 67, copied
-// 53; 1000 images in two buffers of 34 MB: 99 against 30; two of 524 MB: 4096 runs
-// 441 us, 5120 row-strided ones 589, copied 476 and 481.
-std::vector<hp::Seg> text_runs(const hp_plan *p, bool *whole) {
-    const double saved = 2.0 * (double)p->n_rows * (double)p->row_bytes * p->dst_copies;
-    const double most = 1.75 + saved / 25e6;                             // launches
-    // About as many runs as there will be at least (segments in another order than their rows count as apart): where
-    // they are too many they are not even made.
-    int64_t images = 0;
-    for (size_t i = 0; i < p->segments.size(); ++i) {
-        const hp_segment_t &b = p->segments[i], &a = p->segments[i ? i - 1 : 0];
-        images += !i || a.dst_buf0 != b.dst_buf0 || a.dst_row0 + a.n_rows * a.dst_row_stride != b.dst_row0;
-    }
-    const int64_t columns = p->n_dst_bufs / p->dst_copies * p->dst_stride;
-    int64_t runs = std::max(columns, std::max(images, 2 * images - columns));
-    if (text_bands(p)) runs = std::min(runs, columns / p->dst_stride * (p->dst_rows_per_buf / p->dst_stride));
-    *whole = images == 0 || (double)runs * sizeof(hp::Seg) > most * sizeof(Args);
-    if (!*whole) {
-        std::vector<hp::Seg> r = text_bands(p) ? hp::band_runs(*p) : hp::dst_runs(*p, false);
-        *whole = (double)group_runs(r, p->dst_copies).size() > most;
-        if (!*whole) return r;
-    }
-    return hp::dst_runs(*p, true);
-}
-
 // 4 KiB tiles, four chunks a lane, 16 waves a compute unit: over tiles of 1 to 16 KiB,
 // 64 to 256 lanes and caps of 4 to 32, the best or within 3 % of it for dense,
 // row-strided and ragged rows (1.6 GB in [B,S,H] order: 254 us, 6.35 TB/s; the
@@ -1073,7 +1010,7 @@ const hp::Launch kTextLaunch{2, 64, 16, 3};
 constexpr int64_t kCachedCopyBytes = (int64_t)1 << 28;
 
 template <bool BANDS>
-int enqueue_runs(const hp_plan *p, const std::vector<hp::Seg> &runs, const RunGroup &g, bool cached,
+int enqueue_runs(const hp_plan *p, const std::vector<hp::Seg> &runs, const hp::RunGroup &g, bool cached,
                  const void *const *grad, void *const *out, hipStream_t stream) {
     const int variant = kTextLaunch.tile_variant;
     Args a;
@@ -1742,11 +1679,11 @@ int hp_text_grads(const hp_plan_t *p, const void *const *dst_grad_bufs, void *co
     }
     if (bits & (uint64_t)(p->elem_bytes - 1)) return HP_EALIGN;
     try {
-        std::call_once(p->runs_once, [&] { p->runs = text_runs(p, &p->runs_whole); });
+        std::call_once(p->runs_once, [&] { p->runs = hp::text_runs(*p, &p->runs_whole); });
         const bool cached =
             p->runs_whole && p->dst_rows_per_buf * p->row_bytes * (int64_t)p->n_dst_bufs < kCachedCopyBytes;
-        for (const RunGroup &g : group_runs(p->runs, p->dst_copies)) {
-            const int rc = !p->runs_whole && text_bands(p)
+        for (const hp::RunGroup &g : hp::group_runs(p->runs, p->dst_copies)) {
+            const int rc = !p->runs_whole && hp::text_bands(*p)
                                ? enqueue_runs<true>(p, p->runs, g, false, dst_grad_bufs, text_grad_bufs, (hipStream_t)stream)
                                : enqueue_runs<false>(p, p->runs, g, cached, dst_grad_bufs, text_grad_bufs, (hipStream_t)stream);
             if (rc != HP_OK) return rc;

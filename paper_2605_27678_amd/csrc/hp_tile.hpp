@@ -6,6 +6,7 @@
 #include <algorithm>
 #include <cstddef>
 #include <cstdint>
+#include <vector>
 
 #include "hp_plan.hpp"
 
@@ -437,6 +438,82 @@ inline size_t static_launches(const hp_plan &p, size_t tree_bytes) {
     for (size_t launches = 1; launches <= std::min(n, most); ++launches)
         if (inline_fits(p, (n + launches - 1) / launches)) return launches;
     return 0;
+}
+
+// One launch of the text-gradient kernel: `n` of the runs from `runs` on, whose
+// buffers are the `bufs` from `buf0` on; its tables always travel with the
+// arguments.
+struct RunGroup {
+    size_t first, n;
+    int32_t buf0, bufs;
+};
+inline size_t run_bytes(size_t n, int32_t bufs) {
+    const size_t ptrs = (offsetof(Args, b) + (size_t)bufs * 2 * sizeof(void *) + 63) / 64 * 64;
+    const size_t leaves = n > (size_t)kTreeFanout ? (n + kTreeFanout - 1) / kTreeFanout * 64 : 0;
+    return ptrs + (n * sizeof(Seg) + 63) / 64 * 64 + leaves;
+}
+// As many runs a launch as the arguments hold.
+inline std::vector<RunGroup> group_runs(const std::vector<Seg> &runs, int32_t copies) {
+    std::vector<RunGroup> groups;
+    for (size_t i = 0; i < runs.size(); ++i) {
+        const int32_t buf0 = runs[i].dst_buf0;
+        if (!groups.empty()) {
+            RunGroup &g = groups.back();
+            const int32_t bufs = buf0 + copies - g.buf0;
+            if (run_bytes(g.n + 1, bufs) <= sizeof(Args)) {
+                ++g.n;
+                g.bufs = bufs;
+                continue;
+            }
+        }
+        groups.push_back(RunGroup{i, 1, buf0, copies});
+    }
+    return groups;
+}
+
+// Whether the runs of text and image rows are bands: in [S,B,H] order, for as many samples as a band has bits.
+inline bool text_bands(const hp_plan &p) { return p.dst_stride > 1 && p.dst_stride <= kMaxBandSamples; }
+
+// The runs that hp_text_grads launches for a plan: of text and of image rows, or
+// (*whole) whole buffers to copy, whose image rows are then zeroed.  Runs save the
+// image rows one reading and one writing, about 1 us for 6 MB, and take a launch
+// for every hundred or so, about 4 us each after the first; a copy is two launches.
+// Two buffers of 67 MB, half of them image rows: 512 runs 56 us, 800 runs 67, copied
+// 53; 1000 images in two buffers of 34 MB: 99 against 30; two of 524 MB: 4096 runs
+// 441 us, 5120 row-strided ones 589, copied 476 and 481.
+inline std::vector<Seg> text_runs(const hp_plan &p, bool *whole) {
+    const double saved = 2.0 * (double)p.n_rows * (double)p.row_bytes * p.dst_copies;
+    const double most = 1.75 + saved / 25e6;                             // launches
+    // About as many runs as there will be at least (segments in another order than their rows count as apart): where
+    // they are too many they are not even made.  Samples share the bands of images that lie where those of the sample
+    // before them do, as under one template for all; others, scattered, hardly any.
+    const int64_t samples = p.dst_stride;
+    int64_t images = 0;
+    bool alike = text_bands(p);
+    size_t before = 0, first = 0;                                        // where the segments of the sample before and of this one begin
+    for (size_t i = 0; i < p.segments.size(); ++i) {
+        const hp_segment_t &b = p.segments[i], &a = p.segments[i ? i - 1 : 0];
+        images += !i || a.dst_buf0 != b.dst_buf0 || a.dst_row0 + a.n_rows * a.dst_row_stride != b.dst_row0;
+        if (!alike) continue;
+        const int64_t sample = b.dst_row0 % samples;
+        if (sample != a.dst_row0 % samples) before = first, first = i;
+        if (sample == 0) continue;
+        const hp_segment_t &o = p.segments[before + (i - first)];
+        alike = before + (i - first) < first && o.dst_buf0 == b.dst_buf0 && o.n_rows == b.n_rows && o.dst_row0 / samples == b.dst_row0 / samples;
+    }
+    const int64_t columns = p.n_dst_bufs / p.dst_copies * p.dst_stride;
+    int64_t runs = std::max(columns, std::max(images, 2 * images - columns));
+    // 4 samples of 120 images in two buffers of 39 MB 32.8 -> 25.8 us, 16 of 64 in 67 MB 57 -> 34, 4 of 400 in 262 MB 211 ->
+    // 153; where that saves less than 30 MB the copy is as fast or faster (two of 11 MB, rows of 2304 bytes, 12.2 -> 14.2).
+    if (alike && saved >= 30e6) runs = (runs + samples - 1) / samples;
+    if (text_bands(p)) runs = std::min(runs, columns / p.dst_stride * (p.dst_rows_per_buf / p.dst_stride));
+    *whole = images == 0 || (double)runs * sizeof(Seg) > most * sizeof(Args);
+    if (!*whole) {
+        std::vector<Seg> r = text_bands(p) ? band_runs(p) : dst_runs(p, false);
+        *whole = (double)group_runs(r, p.dst_copies).size() > most;
+        if (!*whole) return r;
+    }
+    return dst_runs(p, true);
 }
 
 }  // namespace hp

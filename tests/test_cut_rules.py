@@ -40,3 +40,7 @@ def test_launches_that_lose_by_it_are_not_cut(walk):
 
 def test_grids_of_the_largest_launches_of_lines_stay_below_2_to_the_32_work_items(walk):
     walk("grids", plans=1)
+
+
+def test_text_gradients_of_images_that_lie_alike_take_bands(walk):
+    walk("alike", plans=1)

@@ -145,6 +145,33 @@ static int grids() {
     return 0;
 }
 
+// hp_text_grads of samples whose images lie alike takes their bands, which are as many as one sample has runs, where a copy
+// of everything was taken for as many as all samples have; scattered images change nothing.
+static int alike(std::mt19937_64 &rng) {
+    for (it = 0; it < 8; ++it) {
+        const bool scattered = it & 1, last_differs = it & 2;
+        const int samples = 4, images = 60, copies = 2, dp = it & 4 ? 2 : 1;
+        const hp_layout_t src{1, 1, 1, 1, 0, 0, 0, 0}, dst{copies, 1, dp, 1, 0, 0, 0, HP_ROW_SBH};
+        std::vector<int32_t> smp, st, ln;
+        for (int b = 0; b < samples * dp; ++b)
+            for (int k = 0; k < images; ++k) {
+                smp.push_back(b);
+                st.push_back(20 * k + (scattered ? (int)(rng() % 8) : 0));
+                ln.push_back(10 + (last_differs && k == images - 1 && b == samples * dp - 1));
+            }
+        // saves some 40 MB of traffic: worth three launches
+        const hp_token_map_t m{samples * dp, 20 * images + 20, 2048, 0, (int32_t)smp.size(), smp.data(), st.data(), ln.data(), nullptr};
+        hp_plan p;
+        CHECK(hp::build_host_plan(&src, 1, &dst, &m, 1, &p) == HP_OK);
+        bool whole;
+        const std::vector<hp::Seg> runs = hp::text_runs(p, &whole);
+        if (scattered) CHECK(whole && runs.size() == (size_t)dp);
+        else if (!last_differs) CHECK(!whole && runs.size() == (size_t)(2 * images) * dp);
+        else CHECK(whole);                                   // one that differs: as before
+    }
+    return 0;
+}
+
 int main(int argc, char **argv) {
     if (argc < 4) return 2;
     std::mt19937_64 rng(std::atoll(argv[2]));
@@ -155,6 +182,7 @@ int main(int argc, char **argv) {
     if (!std::strcmp(argv[1], "shapes")) rc = shapes();
     if (!std::strcmp(argv[1], "cuts")) rc = cuts();
     if (!std::strcmp(argv[1], "grids")) rc = grids();
+    if (!std::strcmp(argv[1], "alike")) rc = alike(rng);
     if (rc == 0) std::printf("plans %d\n", plans);
     return rc;
 }
