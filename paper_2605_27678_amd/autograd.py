@@ -25,10 +25,18 @@ import torch
 from .binding import Plan
 
 
+# torch's own names for the current device and its current stream's handle; not part of its interface, so that
+# another torch may be without them
+_get_device = getattr(torch._C, "_cuda_getDevice", None)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _current_stream() -> int:
     """The handle of torch's current stream.  torch.cuda.current_stream() makes an object around it first, 2.7 us of a
     pass that is bound by the host (123 MB in 16 buffers: 112 us)."""
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    if _raw_stream is None or _get_device is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_get_device())
 
 
 class _BoundaryTransform(torch.autograd.Function):

@@ -81,6 +81,23 @@ def test_the_library_builds_without_the_extension(monkeypatch, tmp_path, gone):
     assert ran[-1] == "hipcc" and ("g++" in ran) == (gone != "torch")
 
 
+@pytest.mark.parametrize("name", ["_raw_stream", "_get_device"])
+def test_the_current_stream_without_torchs_own_names(monkeypatch, name):
+    from types import SimpleNamespace
+    from paper_2605_27678_amd import autograd
+    monkeypatch.setattr(autograd, name, None)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: SimpleNamespace(cuda_stream=77))
+    assert autograd._current_stream() == 77
+
+
+@pytest.mark.gpu
+def test_the_current_stream_is_torchs():
+    from paper_2605_27678_amd import autograd
+    for stream in (torch.cuda.Stream(), torch.cuda.default_stream()):
+        with torch.cuda.stream(stream):
+            assert autograd._current_stream() == stream.cuda_stream == torch.cuda.current_stream().cuda_stream
+
+
 @pytest.mark.gpu
 def test_device_buffers():
     plan, host = make(False), make(True)
