@@ -814,9 +814,10 @@ struct LaunchCfg {
 };
 
 // hipLaunchKernelGGL without its way over the call configuration, which is pushed,
-// popped and copied in between: a small launch is bound by this call, 2.68 -> 2.44 us
-// with arguments of 4 KiB (with 8 bytes 2.39 -> 2.11).  What it returns is the last
-// error too, where the callers look.
+// popped and copied in between: a small launch is bound by this call, 2.38 -> 2.21 us
+// with arguments of 3760 bytes, four launches in a row (with 64 bytes 1.97 -> 1.81; two hundred
+// in a row 2.57 -> 2.42 and 2.34 -> 2.17).  What it returns is the last error too, where
+// the callers look.
 template <typename T>
 void launch_plain(const void *kernel, const LaunchCfg &c, const T &args) {
     void *p[] = {const_cast<T *>(&args)};

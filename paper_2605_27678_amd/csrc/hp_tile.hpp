@@ -317,7 +317,7 @@ HP_HD ChunkView cut_chunk(const KParams &k, const TileView &t, uint32_t i) {
 // of the tile's first row there: from the row's start, which the tile's offsets are those
 // of.  A row has room for all the lines that it can touch; a chunk of which no byte is its
 // row's is not there (false), and those at the row's ends are moved to begin and
-// end with it, over bytes of their neighbours.  Rows of at least 16 bytes.  All of a
+// end with it, over bytes of their neighbours.  Rows of kMinPaddedRow bytes and more.  All of a
 // wave's lanes but those at the ends then store to whole 64-byte pieces: stores that begin
 // between them take half as long again (four copies, 283 MB: 42 -> 67 us).
 template <uint32_t UNIT>
