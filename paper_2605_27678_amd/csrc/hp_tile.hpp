@@ -486,26 +486,27 @@ inline std::vector<Seg> text_runs(const hp_plan &p, bool *whole) {
     const double most = 1.75 + saved / 25e6;                             // launches
     // About as many runs as there will be at least (segments in another order than their rows count as apart): where
     // they are too many they are not even made.  Samples share the bands of images that lie where those of the sample
-    // before them do, as under one template for all; others, scattered, hardly any.
+    // before them do, as under one template for all; others, scattered, hardly any.  4 samples of 120 images in two buffers
+    // of 39 MB 32.8 -> 25.8 us, 16 of 64 in 67 MB 57 -> 34, 4 of 400 in 262 MB 211 -> 153; where bands save less than
+    // 30 MB the copy is as fast or faster (two of 11 MB, rows of 2304 bytes, 12.2 -> 14.2).
     const int64_t samples = p.dst_stride;
     int64_t images = 0;
-    bool alike = text_bands(p);
-    size_t before = 0, first = 0;                                        // where the segments of the sample before and of this one begin
+    bool alike = text_bands(p) && saved >= 30e6;
+    size_t before = 0, first = 0;                                        // where the segments of the sample before and of this one begin,
+    int64_t earlier = 0, sample = 0;                                     // and which samples these are
     for (size_t i = 0; i < p.segments.size(); ++i) {
         const hp_segment_t &b = p.segments[i], &a = p.segments[i ? i - 1 : 0];
         images += !i || a.dst_buf0 != b.dst_buf0 || a.dst_row0 + a.n_rows * a.dst_row_stride != b.dst_row0;
         if (!alike) continue;
-        const int64_t sample = b.dst_row0 % samples;
-        if (sample != a.dst_row0 % samples) before = first, first = i;
+        const int64_t now = b.dst_row0 % samples;
+        if (now != sample) before = first, first = i, earlier = sample, sample = now;
         if (sample == 0) continue;
         const hp_segment_t &o = p.segments[before + (i - first)];
-        alike = before + (i - first) < first && o.dst_buf0 == b.dst_buf0 && o.n_rows == b.n_rows && o.dst_row0 / samples == b.dst_row0 / samples;
+        alike = before + (i - first) < first && o.dst_buf0 == b.dst_buf0 && o.n_rows == b.n_rows && b.dst_row0 - o.dst_row0 == sample - earlier;
     }
     const int64_t columns = p.n_dst_bufs / p.dst_copies * p.dst_stride;
     int64_t runs = std::max(columns, std::max(images, 2 * images - columns));
-    // 4 samples of 120 images in two buffers of 39 MB 32.8 -> 25.8 us, 16 of 64 in 67 MB 57 -> 34, 4 of 400 in 262 MB 211 ->
-    // 153; where that saves less than 30 MB the copy is as fast or faster (two of 11 MB, rows of 2304 bytes, 12.2 -> 14.2).
-    if (alike && saved >= 30e6) runs = (runs + samples - 1) / samples;
+    if (alike) runs = (runs + samples - 1) / samples;
     if (text_bands(p)) runs = std::min(runs, columns / p.dst_stride * (p.dst_rows_per_buf / p.dst_stride));
     *whole = images == 0 || (double)runs * sizeof(Seg) > most * sizeof(Args);
     if (!*whole) {
